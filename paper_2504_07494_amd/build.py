@@ -1,32 +1,41 @@
-"""Build libapt_hybrid.so (gfx950) in-tree with hipcc."""
+"""Build libapt_hybrid.so (gfx950) in-tree with hipcc: every source is compiled by itself, side by side, then linked."""
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libapt_hybrid.so")
-SOURCES = ["apt_plan.cpp", "apt_pool.cpp", "apt_sched.cpp", "apt_kernels.hip"]
+SOURCES = ["apt_mfma_f16.hip", "apt_mfma_bf16.hip", "apt_kernels.hip", "apt_plan.cpp", "apt_pool.cpp", "apt_sched.cpp"]
 
 
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-           # packed-fp32 instruction forms are kept out of the device code
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-Wno-inline-asm", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-x", "hip"]
-    cmd += [os.path.join(CSRC, s) for s in SOURCES]
-    cmd += ["-o", LIB]
+    flags = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
+             # packed-fp32 instruction forms are kept out of the device code
+             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+             "-Wno-inline-asm", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
     if verbose:
-        cmd += ["-Rpass-analysis=kernel-resource-usage"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    out = "\n".join(l for l in (r.stdout + r.stderr).splitlines() if "packed-fp32-ops" not in l)
-    if r.returncode != 0:
-        sys.stderr.write("\n".join(l for l in out.splitlines() if "error" in l) [:4000] + "\n")
-        raise RuntimeError("hipcc failed")
+        flags += ["-Rpass-analysis=kernel-resource-usage"]
+
+    def run(cmd):
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        out = "\n".join(l for l in (r.stdout + r.stderr).splitlines() if "packed-fp32-ops" not in l)
+        if r.returncode != 0:
+            sys.stderr.write("\n".join(l for l in out.splitlines() if "error" in l)[:4000] + "\n")
+            raise RuntimeError("hipcc failed")
+        return out
+
+    with tempfile.TemporaryDirectory() as tmp, ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+        objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
+        cmds = [[hipcc, *flags, "-x", "hip", "-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objs)]
+        outs = list(ex.map(run, cmds))
+        outs.append(run([hipcc, "--offload-arch=gfx950", "-fPIC", "-shared", *objs, "-o", LIB]))
     if verbose:
-        print(out)
+        print("\n".join(outs))
     return LIB
 
 

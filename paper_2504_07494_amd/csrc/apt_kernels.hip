@@ -12,265 +12,17 @@
 //   cache append / cache write, weight packing, calibration kernels
 //
 // Scores are kept in base-2 units: s2 = softmax_scale*log2(e)*<q,k>, weights 2^(s2 - m).
-#include <hip/hip_runtime.h>
-#include <stdint.h>
 #include <stdlib.h>
 #include <mutex>
-#include "apt_internal.h"
+#include "apt_device.h"
 #include "apt_hybrid_bench.h"
+#include "apt_launch.h"
 
 // Workspace of apt_hybrid_decode_attn_static: one copy per device, held until the process ends.  In host code this
 // name is only a handle for hipGetSymbolAddress; the device address is looked up once per device (device_setup).
 static __device__ __align__(256) unsigned char scratch[APT_STATIC_WORKSPACE_BYTES];
 
 namespace {
-
-constexpr float kSentinel = -1.0e30f;   // "no score yet": finite, so differences never give NaN
-constexpr int kThreads = 256;
-
-typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
-typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
-// 16-byte load of data that is read once (streamed past the caches)
-__device__ inline uint4 load16_stream(const char* p) {
-    const u32x4_t v = __builtin_nontemporal_load((const u32x4_t*)p);
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
-struct ItemParams {
-    const int32_t* plan;          // device blob
-    int32_t* kv_ticket;           // device blob word APT_PW_KV_TICKET: next KV-kind item of the persistent launch
-    const char* q;
-    const char* k_pages;
-    const char* v_pages;
-    const char* hidden_pages;
-    const char* W_K;
-    const char* W_V;
-    const char* W_packed;
-    const char* b_K;
-    const char* b_V;
-    const int32_t* block_tables;
-    float* ws_acc;                // [n_slots][HD]
-    float2* ws_ml;                // [n_slots]
-    int32_t B, H, d, bs, log2_bs, max_blocks;
-    int32_t n_items, n_hidden_items, hidden_chunk, kv_chunk, items_off;
-    float scale_log2e;
-    int32_t item_base;            // one-workgroup-per-item launch: first item of the grid
-    // absorbed-weight hidden path: workspace sections (fp32)
-    float* ab_qt;                 // [n_hid_req][H][d]
-    float* ab_cb;                 // [n_hid_req][H]
-    float* ab_s;                  // [KS][H][ab_tokens] partial scores over d_model slices; slice 0 ends as the scores
-    float2* ab_ml;                // [n_hid_req][H]
-    float* ab_yp;                 // [n_hidden_items][H][d]
-    float* ab_op;                 // [KS][n_hid_req][H][HD]
-    void* ab_pp;                  // 16-bit inputs: softmax weights as 16-bit parts, [16 n_hidden_items][parts * 64][32]
-    int64_t ab_tokens;            // cached tokens of all hidden-kind requests
-    int32_t n_hid_req;
-};
-
-// ---------------------------------------------------------------------------------
-// element helpers.  DT: 0 = fp32, 1 = fp16, 2 = bf16
-// ---------------------------------------------------------------------------------
-template <int DT> struct Elt { static constexpr int bytes = DT == 0 ? 4 : 2; static constexpr int per16 = 16 / bytes; };
-
-__device__ inline float bf16_to_f32(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
-
-template <int DT> __device__ inline float load_elem(const char* base, int64_t idx) {
-    if constexpr (DT == 0) return ((const float*)base)[idx];
-    else if constexpr (DT == 1) return (float)((const _Float16*)base)[idx];
-    else return bf16_to_f32(((const uint16_t*)base)[idx]);
-}
-
-// 16 bytes -> Elt<DT>::per16 floats
-template <int DT> __device__ inline void cvt16(const uint4& v, float* out) {
-    if constexpr (DT == 0) {
-        out[0] = __uint_as_float(v.x); out[1] = __uint_as_float(v.y);
-        out[2] = __uint_as_float(v.z); out[3] = __uint_as_float(v.w);
-    } else if constexpr (DT == 1) {
-        h8_t h = __builtin_bit_cast(h8_t, v);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) out[i] = (float)h[i];
-    } else {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            out[2 * i] = __uint_as_float(w[i] << 16);
-            out[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-        }
-    }
-}
-
-__device__ inline uint16_t f32_to_bf16_rne(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
-// ---------------------------------------------------------------------------------
-// cross-lane helpers
-// ---------------------------------------------------------------------------------
-template <int CTRL> __device__ inline float dpp_mov(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-// Sum over the aligned group of LANES lanes a lane belongs to; every lane gets the sum.
-template <int LANES> __device__ inline float group_sum(float x) {
-    x += dpp_mov<0xB1>(x);                          // quad_perm [1,0,3,2]
-    x += dpp_mov<0x4E>(x);                          // quad_perm [2,3,0,1]
-    if constexpr (LANES >= 8) x += dpp_mov<0x141>(x);   // row_half_mirror
-    if constexpr (LANES >= 16) x += dpp_mov<0x140>(x);  // row_mirror
-    if constexpr (LANES >= 32) x += __shfl_xor(x, 16);
-    if constexpr (LANES >= 64) x += __shfl_xor(x, 32);
-    return x;
-}
-template <int LANES> __device__ inline float group_max(float x) {
-    x = fmaxf(x, dpp_mov<0xB1>(x));
-    x = fmaxf(x, dpp_mov<0x4E>(x));
-    if constexpr (LANES >= 8) x = fmaxf(x, dpp_mov<0x141>(x));
-    if constexpr (LANES >= 16) x = fmaxf(x, dpp_mov<0x140>(x));
-    if constexpr (LANES >= 32) x = fmaxf(x, __shfl_xor(x, 16));
-    if constexpr (LANES >= 64) x = fmaxf(x, __shfl_xor(x, 32));
-    return x;
-}
-
-__device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// ---------------------------------------------------------------------------------
-// KV-kind item
-// ---------------------------------------------------------------------------------
-// K/V block layout [head][slot][HD]: the rows of one (block, head) are one contiguous run
-// of bs*HD elements, read as 1 KB wave loads (64 lanes x 16 B).  LPR lanes share a row,
-// 64/LPR rows per load.  A lane group keeps its own online-softmax state for the rows it
-// sees; the groups are combined through LDS at the end.
-constexpr int kKvUnits = 4;   // 1 KB loads of K (and of V) per pipeline stage
-
-template <int DT, int HD>
-__device__ __forceinline__ void kv_item(const ItemParams& p, int r, int h, int t0, int t1, char* lds) {
-    constexpr int EB = Elt<DT>::bytes;
-    constexpr int EPL = Elt<DT>::per16;          // elements per lane per load
-    constexpr int LPR = HD * EB / 16;            // lanes per row
-    constexpr int RPL = 64 / LPR;                // rows per 1 KB load
-    constexpr int G = 4 * RPL;                   // lane groups in the workgroup
-
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int bs = p.bs;
-    const int log2_nl = p.log2_bs - __builtin_ctz(RPL);     // loads per page per matrix = bs/RPL
-    const int nl_mask = (1 << log2_nl) - 1;
-    const int64_t blk_bytes = (int64_t)bs * p.d * EB;
-    const int64_t head_off = (int64_t)h * bs * HD * EB;
-
-    const int p0 = t0 >> p.log2_bs;
-    const int p1 = (t1 + bs - 1) >> p.log2_bs;
-    // pages of this wave: p0 + w, p0 + w + 4, ...
-    const int npg = (p1 - p0 - w + 3) >> 2;
-    const int nunits = npg > 0 ? (npg << log2_nl) : 0;
-
-    // lane i holds the block ids of the wave's i-th page
-    int32_t kid = 0, vid = 0;
-    if (lane < npg) {
-        const int64_t e = (int64_t)r * 2 * p.max_blocks + p0 + w + 4 * lane;
-        kid = p.block_tables[e];
-        vid = p.block_tables[e + p.max_blocks];
-    }
-
-    // q for the lane's channels, pre-scaled
-    const int c0 = (lane % LPR) * EPL;
-    float qf[EPL];
-#pragma unroll
-    for (int i = 0; i < EPL; ++i)
-        qf[i] = load_elem<DT>(p.q, ((int64_t)r * p.H + h) * HD + c0 + i) * p.scale_log2e;
-
-    float m = kSentinel, l = 0.f, acc[EPL];
-#pragma unroll
-    for (int i = 0; i < EPL; ++i) acc[i] = 0.f;
-
-    uint4 kb[2][kKvUnits], vb[2][kKvUnits];
-    auto issue = [&](int g, uint4* kbuf, uint4* vbuf) {
-#pragma unroll
-        for (int i = 0; i < kKvUnits; ++i) {
-            const int u = g * kKvUnits + i;
-            if (u < nunits) {
-                const int pg = u >> log2_nl;
-                const int64_t kblk = __builtin_amdgcn_readlane(kid, pg);
-                const int64_t vblk = __builtin_amdgcn_readlane(vid, pg);
-                const int64_t off = head_off + (int64_t)(u & nl_mask) * 1024 + lane * 16;
-                kbuf[i] = load16_stream(p.k_pages + kblk * blk_bytes + off);
-                vbuf[i] = load16_stream(p.v_pages + vblk * blk_bytes + off);
-            }
-        }
-    };
-    auto consume = [&](int g, const uint4* kbuf, const uint4* vbuf) {
-        float s[kKvUnits];
-        bool ok[kKvUnits];
-        float mn = m;
-#pragma unroll
-        for (int i = 0; i < kKvUnits; ++i) {
-            const int u = g * kKvUnits + i;
-            const int pg = u >> log2_nl;
-            const int tok = ((p0 + w + 4 * pg) << p.log2_bs) + (u & nl_mask) * RPL + lane / LPR;
-            ok[i] = (u < nunits) && (tok < t1);
-            float kf[EPL];
-            cvt16<DT>(kbuf[i], kf);
-            float part = 0.f;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) part = fmaf(kf[e], qf[e], part);
-            part = group_sum<LPR>(part);
-            s[i] = ok[i] ? part : kSentinel;
-            mn = fmaxf(mn, s[i]);
-        }
-        const float alpha = fast_exp2(m - mn);
-        l *= alpha;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] *= alpha;
-#pragma unroll
-        for (int i = 0; i < kKvUnits; ++i) {
-            const float pw = ok[i] ? fast_exp2(s[i] - mn) : 0.f;
-            l += pw;
-            float vf[EPL];
-            cvt16<DT>(vbuf[i], vf);
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[e] = fmaf(pw, ok[i] ? vf[e] : 0.f, acc[e]);
-        }
-        m = mn;
-    };
-
-    const int ngroups = (nunits + kKvUnits - 1) / kKvUnits;
-    if (ngroups > 0) issue(0, kb[0], vb[0]);
-    for (int g = 0; g < ngroups; g += 2) {
-        if (g + 1 < ngroups) issue(g + 1, kb[1], vb[1]);
-        consume(g, kb[0], vb[0]);
-        if (g + 2 < ngroups) issue(g + 2, kb[0], vb[0]);
-        if (g + 1 < ngroups) consume(g + 1, kb[1], vb[1]);
-    }
-
-    // combine the lane groups: LDS [G] m, [G] l, [G][HD] acc
-    float* gm = (float*)lds;
-    float* gl = gm + G;
-    float* ga = gl + G;
-    const int grp = w * RPL + lane / LPR;
-    if (lane % LPR == 0) { gm[grp] = m; gl[grp] = l; }
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) ga[grp * HD + c0 + e] = acc[e];
-    __syncthreads();
-    if (tid < HD) {
-        float M = kSentinel;
-        for (int g = 0; g < G; ++g) M = fmaxf(M, gm[g]);
-        float L = 0.f, A = 0.f;
-        for (int g = 0; g < G; ++g) {
-            const float wgt = fast_exp2(gm[g] - M);
-            L = fmaf(gl[g], wgt, L);
-            A = fmaf(ga[g * HD + tid], wgt, A);
-        }
-        const int32_t* split_count = p.plan + APT_PW_HEADER;
-        const int32_t* ws_offset = split_count + p.B;
-        const int64_t slot = ((int64_t)ws_offset[r] + t0 / p.kv_chunk) * p.H + h;
-        p.ws_acc[slot * HD + tid] = A;
-        if (tid == 0) p.ws_ml[slot] = make_float2(M, L);
-    }
-}
 
 // ---------------------------------------------------------------------------------
 // hidden-kind item, plain-ALU version (fp32 configs and shapes the MFMA kernel
@@ -345,480 +97,6 @@ __device__ __forceinline__ void hidden_item_valu(const ItemParams& p, int r, int
         const int64_t slot = ((int64_t)ws_offset[r] + t0 / p.hidden_chunk) * p.H + h;
         p.ws_acc[slot * HD + tid] = a;
         if (tid == 0) p.ws_ml[slot] = make_float2(red[0], red[1]);
-    }
-}
-
-// ---------------------------------------------------------------------------------
-// hidden-kind items, MFMA version (fp16 / bf16, head_dim 128): persistent workgroups
-// ---------------------------------------------------------------------------------
-// Per item: K_h and V_h of a tile of up to 320 tokens (TF = 10; described here) or 256 tokens (TF = 8),
-// [256 channels] x [320 tokens] with k = d_model, on v_mfma_f32_16x16x32.  The four waves are (mat, th): mat 0 = K_h channels, mat 1 =
-// V_h channels; th picks the token blocks 2b + th (b = 0..4, 32 tokens each), so a short tile leaves
-// both halves the same number of blocks.  A wave owns a 128 x 160 accumulator tile as 8 x 10 MFMA
-// tiles of 16 x 16: 320 registers, more than the 256 AGPRs, so part of it lives in ordinary VGPRs.
-// The tile is as large as the register file allows because the kernel is bound by the L2 -> LDS
-// copies as much as by the matrix pipes: per k-tile a workgroup copies (256 + 320) rows of 64 B for
-// 256 x 320 x 32 multiply-adds, 10 % fewer bytes per flop than a 256 x 256 tile, and a k-tile lasts
-// 25 % longer, which is that much more latency the four stages can cover.
-// K waves multiply W (rows = channels) by X^T and get D[channel][token]: a lane owns one token per
-// tile column and sums over channels in registers for the score.  V waves multiply X (rows =
-// tokens) by W^T and get D[token][channel]: a lane owns one channel and sums over tokens in
-// registers for the weighted value sum.  Both read the same LDS images; only which image feeds
-// which MFMA operand differs.
-//
-// k runs in tiles of 32 (one MFMA k-step) through four LDS stages, each 16 KB of packed weights
-// (already in LDS order in memory) and 20 KB of X rows, filled by global->LDS copies that bypass
-// registers; up to four k-tiles are in flight or waiting while one is multiplied.  Rows are 64 B;
-// the 16-byte unit c of a row sits at c ^ swz16(row), which keeps the row-wise copies and the
-// column-wise operand reads spread over all banks.  The operands of k-tile kt+1 are read into a
-// second register set while k-tile kt is multiplied.
-//
-// A workgroup walks a queue of items (queue = blockIdx % 8, the XCD the workgroup runs
-// on, so that the workgroups sharing an L2 work on few heads and few token tiles at a
-// time), then a share of the KV-kind items.  While one item's epilogue runs, the first
-// k-tiles of the next item are already on their way into LDS.
-constexpr int kBK = 32;
-constexpr int kRowBytes = kBK * 2;                     // 64 B
-constexpr int kWTileBytes = 256 * kRowBytes;           // 16 KB
-constexpr int kStages = 4;
-constexpr int kXImage = kStages * kWTileBytes;         // LDS offset of the X stages
-constexpr int kMfmaScratch = 5120;                     // epilogue scratch behind the stages
-constexpr int kFragBytes = 16 * kRowBytes;             // the 16 rows of one MFMA operand fragment
-// TF = X fragments (16 tokens) per wave: 10 (tile of 320 tokens) or 8 (256 tokens)
-template <int TF> struct MfmaTile {
-    static constexpr int kTokTile = 32 * TF;                   // token rows of a tile
-    static constexpr int kXChunks = kTokTile / 64;             // 1 KB copies of X rows per wave and k-tile
-    static constexpr int kXTileBytes = kTokTile * kRowBytes;   // 20 KB / 16 KB
-    static constexpr int kLds = kStages * (kWTileBytes + kXTileBytes) + kMfmaScratch;
-    static constexpr int kStageLoads = 4 + kXChunks;           // copies per wave and k-tile: 4 of W, then those of X
-    static_assert(kTokTile % 64 == 0 && kLds <= 160 * 1024 && (TF == 8 || TF == 10), "tile does not fit");
-};
-
-// Position swizzles of the 16-byte units of 64-byte LDS rows, measured free of bank conflicts (SQ_LDS_BANK_CONFLICT = 0,
-// 4 cycles per ds_read_b128) for the operand reads of the two MFMA forms: swz for 32x32x16 (a read covers 32 consecutive
-// rows, two units; used by the absorbed-weight kernels), swz16 for 16x16x32 (16 consecutive rows, all four units; with
-// swz it takes 8 cycles).
-__host__ __device__ inline int swz(int row) { return (row >> 2) & 3; }
-__host__ __device__ inline int swz16(int row) { return (row >> 1) & 3; }
-
-template <int DT> __device__ inline f32x16_t mfma32(const uint4& a, const uint4& b, f32x16_t c) {
-    if constexpr (DT == 1)
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8_t, a), __builtin_bit_cast(h8_t, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8_t, a), __builtin_bit_cast(bf8_t, b), c, 0, 0, 0);
-}
-// A: lane l holds row l % 16, k = 8 (l / 16) .. +7; B: column l % 16, the same k; D: column l % 16, rows 4 (l / 16) + e
-template <int DT> __device__ inline f32x4_t mfma16(const uint4& a, const uint4& b, f32x4_t c) {
-    if constexpr (DT == 1)
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8_t, a), __builtin_bit_cast(h8_t, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8_t, a), __builtin_bit_cast(bf8_t, b), c, 0, 0, 0);
-}
-
-// The same MFMA with its accumulator in ordinary VGPRs.  The compiler keeps every accumulator of a kernel in one
-// register class (here the 256 AGPRs); the tiles beyond those are accumulated through this form.  Its operands are
-// tracked like any other instruction's (wait counts for the LDS reads that feed it); successive uses of one
-// accumulator are a whole k-tile apart.
-template <int DT> __device__ inline void mfma16_vgpr(const uint4& a, const uint4& b, f32x4_t& c) {
-    const u32x4_t av = __builtin_bit_cast(u32x4_t, a), bv = __builtin_bit_cast(u32x4_t, b);
-    if constexpr (DT == 1) asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(c) : "v"(av), "v"(bv));
-    else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(av), "v"(bv));
-}
-
-// 16-byte global -> LDS copy without a register stage: lane i's 16 bytes land at
-// lds_addr + 16 i.  The LDS address goes through M0 and must be wave-uniform.
-__device__ inline void gload_lds16(const void* g, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(g) : "memory", "m0");
-}
-// The same with a wave-uniform 64-bit base and a 32-bit byte offset per lane.
-__device__ inline void gload_lds16_base(const void* base, uint32_t lane_off, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(lane_off), "s"(base)
-                 : "memory", "m0");
-}
-typedef __attribute__((address_space(3))) u32x4_t lds_u32x4_t;
-// 16-byte LDS read at an absolute LDS address (the dynamic LDS base is folded into the operand addresses once)
-__device__ inline uint4 lds_read16(uint32_t addr) {
-    const u32x4_t v = *(const lds_u32x4_t*)(uintptr_t)addr;
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-template <int N> __device__ inline void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-
-// byte offset of operand fragment f inside an LDS image: the W image holds the channels of a wave in order
-// (fragment f = rows 16 f ..), the X image holds the token blocks of a wave interleaved with the other wave's
-// (fragment f = the half f % 2 of the 32-token block f / 2, which sits 64 rows after the previous block)
-__device__ constexpr int w_frag_off(int f) { return f * kFragBytes; }
-__device__ constexpr int x_frag_off(int f) { return (64 * (f >> 1) + 16 * (f & 1)) * kRowBytes; }
-// token row (within the tile) of the first token of X fragment f of the wave with token half th
-__device__ inline int x_frag_row(int th, int f) { return th * 32 + 64 * (f >> 1) + 16 * (f & 1); }
-
-template <int DT, int TF>
-__global__ __launch_bounds__(kThreads) void apt_items_mfma_kernel(ItemParams p) {
-    constexpr int HD = 128;
-    constexpr int kTokFrags = TF, kTokTile = MfmaTile<TF>::kTokTile, kXChunks = MfmaTile<TF>::kXChunks;
-    constexpr int kXTileBytes = MfmaTile<TF>::kXTileBytes, kStageLoads = MfmaTile<TF>::kStageLoads;
-    extern __shared__ __align__(16) char lds[];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int mat = w >> 1, th = w & 1;
-    const int d = p.d;
-    const int nkt = d / kBK;                 // a multiple of 4: d is a multiple of 128
-    const int64_t blk_bytes = (int64_t)p.bs * d * 2;
-    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-    const uint32_t lds_w = lds_base + w * 1024;
-    const int4* items = (const int4*)(p.plan + p.items_off);
-    const int32_t* split_count = p.plan + APT_PW_HEADER;
-    const int32_t* ws_offset = split_count + p.B;
-
-    // ---- LDS layout: W stages 0..3 (16 KB each), X stages 0..3 (20 KB each), then the epilogue scratch
-    float* scr = (float*)(lds + kStages * (kWTileBytes + kXTileBytes));
-    float* p_lds = scr;                     // [kTokTile] softmax weights of the tile (per half, relative to its maximum)
-    float* qs_lds = scr + kTokTile;         // [128] q * scale * log2(e)
-    float* bk_lds = qs_lds + 128;           // [128]
-    float* bv_lds = bk_lds + 128;           // [128]
-    float* o_lds = bv_lds + 128;            // [2][128] per-half un-normalised output
-    float* ml_lds = o_lds + 256;            // [2][2] per-half (m, l); [4], [5] = halves of q . b_K
-    static_assert((kTokTile + 3 * 128 + 256 + 8) * 4 <= kMfmaScratch, "epilogue scratch too small");
-
-    // This lane's 16 bytes of fragment 0, stage 0, in the W image (the channels of this wave) and in the X image
-    // (the token blocks of this wave): row lane % 16 of the fragment, unit (lane / 16) ^ swz16(row); swz does not
-    // change from fragment to fragment (their first rows are multiples of 16), so every other fragment and stage
-    // is a constant offset away.
-    // (computed per item, right before its k loop: kept across the epilogue they would sit in scratch)
-    uint32_t w_base, x_base;
-#define APT_OPERAND_ADDRESSES()                                                                             \
-    {                                                                                                       \
-        int ln_ = lane;                                                                                     \
-        asm volatile("" : "+v"(ln_));                                                                       \
-        const int l16_ = ln_ & 15, qd_ = ln_ >> 4;                                                          \
-        const uint32_t off_ = l16_ * kRowBytes + ((qd_ ^ swz16(l16_)) * 16);                                  \
-        w_base = lds_base + mat * 128 * kRowBytes + off_;                                                   \
-        x_base = lds_base + kXImage + th * 32 * kRowBytes + off_;                                           \
-    }
-
-    // ---- this workgroup's share of the hidden-kind items
-    const int G = gridDim.x, g = blockIdx.x;
-    const int wpx = G >> 3;                                   // workgroups per queue (G is a multiple of 8)
-    const int q_end = p.plan[APT_PW_QUEUE0 + (g & 7) + 1];
-    int qi = p.plan[APT_PW_QUEUE0 + (g & 7)] + (g >> 3);
-
-    // per-lane state of an item: kXChunks X row sources.  An X chunk of 1 KB is 16 rows; wave w
-    // copies chunks w + 4 i: row 16 w + lane/4 + 64 i, LDS unit lane%4 = global unit (lane%4) ^ swz16(row)
-    const int pu = lane & 3, r0 = 16 * w + (lane >> 2);
-    int4 it = make_int4(0, 0, 0, 1);
-    int32_t ids[kXChunks];
-    auto lookup = [&](const int4& item, int32_t* out) {       // block ids of this lane's rows
-#pragma unroll
-        for (int i = 0; i < kXChunks; ++i) {
-            int tok = item.z + r0 + 64 * i;
-            tok = tok < item.w ? tok : item.w - 1;            // rows past the range repeat the last token (masked later)
-            out[i] = p.block_tables[(int64_t)item.x * 2 * p.max_blocks + (tok >> p.log2_bs)];
-        }
-    };
-    uint32_t xsrc[kXChunks];                                  // offsets from hidden_pages in 16-byte units
-    const char* wsrc = nullptr;
-#define APT_MAKE_SOURCES(XS, WS, ITEM, BLK)                                                                 \
-    {                                                                                                       \
-        _Pragma("unroll") for (int i_ = 0; i_ < kXChunks; ++i_) {                                           \
-            const int row_ = r0 + 64 * i_;                                                                  \
-            int tok_ = (ITEM).z + row_;                                                                     \
-            tok_ = tok_ < (ITEM).w ? tok_ : (ITEM).w - 1;                                                   \
-            XS[i_] = (uint32_t)(((int64_t)BLK[i_] * blk_bytes + ((int64_t)(tok_ & (p.bs - 1)) * d) * 2) >> 4) + \
-                     (pu ^ swz16(row_));                                                                      \
-        }                                                                                                   \
-        WS = p.W_packed + (int64_t)(ITEM).y * nkt * kWTileBytes + w * 1024 + lane * 16;                     \
-    }
-    // copies chunk j (0..3: weights, 4..: X rows) of this wave's share of k-tile kt into stage st
-    auto stage_chunk = [&](int kt, int st, int j) {
-        if (j < 4)
-            gload_lds16(wsrc + (int64_t)kt * kWTileBytes + j * 4096, lds_w + st * kWTileBytes + j * 4096);
-        else
-            gload_lds16(p.hidden_pages + (uint64_t)xsrc[j - 4] * 16 + kt * kRowBytes,
-                        lds_w + kXImage + st * kXTileBytes + (j - 4) * 4096);
-    };
-#define APT_STAGE_FIRST(T0, T1)                                                                             \
-    _Pragma("unroll") for (int t_ = (T0); t_ < (T1); ++t_) {                                                \
-        _Pragma("unroll") for (int j_ = 0; j_ < kStageLoads; ++j_) stage_chunk(t_, t_, j_);                 \
-    }
-
-    bool have = qi < q_end;
-    if (have) {
-        it = items[qi];
-        lookup(it, ids);
-        APT_MAKE_SOURCES(xsrc, wsrc, it, ids)
-        APT_STAGE_FIRST(0, 4)
-    }
-
-    // Accumulator tile (i, j): A-side fragment i (rows) x B-side fragment j (columns).  MAT 0 (K wave): A = W
-    // fragments (NI = 8), B = X fragments (NJ = 2 per valid token block); MAT 1 (V wave): A = X, B = W.  The 64
-    // tiles of the first 8 X fragments live in AGPRs (acc_a), the 16 tiles of X fragments 8 and 9 (the fifth
-    // token block of the wave) in VGPRs (acc_v).
-    constexpr int kAccV = kTokFrags > 8 ? 8 * (kTokFrags - 8) : 1;     // tiles accumulated in VGPRs (none for TF = 8)
-    f32x4_t acc_a[64], acc_v[kAccV];
-    // fr[set][..]: the NI A-side fragments, then the NJ B-side fragments of one k-tile.
-    uint4 fr[2][8 + kTokFrags];
-    // X fragment and W fragment of tile (I, J)
-#define APT_XF(MAT, I, J) ((MAT) == 0 ? (J) : (I))
-#define APT_WF(MAT, I, J) ((MAT) == 0 ? (I) : (J))
-    // (indices are clamped so that the branch not taken never names an element outside its array)
-#define APT_ACC_A_SAFE(MAT, I, J) acc_a[APT_XF(MAT, I, J) < 8 ? (I) * 8 + (J) : 0]
-#define APT_ACC_V_SAFE(MAT, I, J) acc_v[APT_XF(MAT, I, J) < 8 ? 0 : (APT_XF(MAT, I, J) - 8) * 8 + APT_WF(MAT, I, J)]
-#define APT_ACC_GET(MAT, I, J) (APT_XF(MAT, I, J) < 8 ? APT_ACC_A_SAFE(MAT, I, J) : APT_ACC_V_SAFE(MAT, I, J))
-    // LDS address of operand slot R (0 .. NI + NJ - 1) in stage ST
-#define APT_SLOT_ADDR(MAT, NI, R, ST)                                                                       \
-    ((MAT) == 0 ? ((R) < (NI) ? w_base + w_frag_off(R) + (ST) * kWTileBytes                                 \
-                              : x_base + x_frag_off((R) - (NI)) + (ST) * kXTileBytes)                       \
-                : ((R) < (NI) ? x_base + x_frag_off(R) + (ST) * kXTileBytes                                 \
-                              : w_base + w_frag_off((R) - (NI)) + (ST) * kWTileBytes))
-    // MFMA index of a k-tile (after the operand reads of the next one) in front of which refill copy C is issued
-#define APT_COPY_AT(C, NI, NJ) ((NI) + (NJ) + (C) * ((NI) * (NJ) - (NI) - (NJ)) / kStageLoads)
-    // One k-tile, in stage ST, its operands already in register set ST % 2.  If another k-tile follows: all
-    // waves meet (this wave's copies of the next k-tile have landed: at most WAITN younger copies may still be in
-    // flight; every wave has all operands of THIS k-tile in registers, so its stage is no longer read), then the
-    // next k-tile's operands are read into the other register set, one read per MFMA; after them, spread over the
-    // remaining MFMAs, this stage is refilled with k-tile kt + 4.
-#define APT_K_TILE(ST, STAGE, WAITN, NEXT, MAT, NI, NJ)                                                     \
-    {                                                                                                       \
-        if (NEXT) {                                                                                         \
-            wait_vmcnt<WAITN>();                                                                            \
-            __syncthreads();                                                                                \
-        }                                                                                                   \
-        __builtin_amdgcn_sched_barrier(0);                                                                  \
-        _Pragma("unroll") for (int m_ = 0; m_ < (NI) * (NJ); ++m_) {                                        \
-            if (NEXT && m_ < (NI) + (NJ))                                                                   \
-                fr[((ST) + 1) & 1][m_] = lds_read16(APT_SLOT_ADDR(MAT, NI, m_, ((ST) + 1) & 3));            \
-            if (STAGE) {                                                                                    \
-                _Pragma("unroll") for (int c_ = 0; c_ < kStageLoads; ++c_)                                  \
-                    if (APT_COPY_AT(c_, NI, NJ) == m_) stage_chunk(kt + 4, ST, c_);                         \
-            }                                                                                               \
-            if (APT_XF(MAT, m_ / (NJ), m_ % (NJ)) < 8)                                                      \
-                APT_ACC_A_SAFE(MAT, m_ / (NJ), m_ % (NJ)) =                                                 \
-                    mfma16<DT>(fr[(ST) & 1][m_ / (NJ)], fr[(ST) & 1][(NI) + m_ % (NJ)],                     \
-                               APT_ACC_A_SAFE(MAT, m_ / (NJ), m_ % (NJ)));                                  \
-            else                                                                                            \
-                mfma16_vgpr<DT>(fr[(ST) & 1][m_ / (NJ)], fr[(ST) & 1][(NI) + m_ % (NJ)],                    \
-                                APT_ACC_V_SAFE(MAT, m_ / (NJ), m_ % (NJ)));                                 \
-            __builtin_amdgcn_sched_barrier(0);                                                              \
-        }                                                                                                   \
-    }
-    // The addresses used inside the k loop must be in registers with nothing pending behind them
-    // when the loop starts: a reload the compiler still waits for inside the loop would also wait
-    // for the staging copies.
-#define APT_K_LOOP(MAT, NI, NJ)                                                                             \
-    {                                                                                                       \
-        asm volatile("" : "+v"(w_base), "+v"(x_base));                                                      \
-        _Pragma("unroll") for (int i_ = 0; i_ < kXChunks; ++i_) asm volatile("" : "+v"(xsrc[i_]));          \
-        asm volatile("" : "+v"(wsrc));                                                                      \
-        _Pragma("unroll") for (int r_ = 0; r_ < (NI) + (NJ); ++r_) fr[0][r_] = lds_read16(APT_SLOT_ADDR(MAT, NI, r_, 0)); \
-        int kt = 0;                                                                                         \
-        for (; kt + 8 <= nkt; kt += 4) {                                                                    \
-            APT_K_TILE(0, true, 2 * kStageLoads, true, MAT, NI, NJ)                                         \
-            ++kt;                                                                                           \
-            APT_K_TILE(1, true, 2 * kStageLoads, true, MAT, NI, NJ)                                         \
-            ++kt;                                                                                           \
-            APT_K_TILE(2, true, 2 * kStageLoads, true, MAT, NI, NJ)                                         \
-            ++kt;                                                                                           \
-            APT_K_TILE(3, true, 2 * kStageLoads, true, MAT, NI, NJ)                                         \
-            kt -= 3;                                                                                        \
-        }                                                                                                   \
-        APT_K_TILE(0, false, 2 * kStageLoads, true, MAT, NI, NJ)   /* the last four k-tiles refill nothing */ \
-        APT_K_TILE(1, false, kStageLoads, true, MAT, NI, NJ)                                                \
-        APT_K_TILE(2, false, 0, true, MAT, NI, NJ)                                                          \
-        APT_K_TILE(3, false, 0, false, MAT, NI, NJ)                                                         \
-    }
-
-    while (have) {
-        const int r = it.x, h = it.y, t0 = it.z, nvalid = it.w - it.z;
-        // block ids of the next item: on their way while this item's first copies land
-        const int nqi = qi + wpx;
-        const bool have_next = nqi < q_end;
-        int4 itn = it;
-        int32_t idsn[kXChunks];
-#pragma unroll
-        for (int i = 0; i < kXChunks; ++i) idsn[i] = 0;
-        if (have_next) {
-            itn = items[nqi];
-            lookup(itn, idsn);
-        }
-        // per-item constants of the epilogue
-        if (tid < HD) {
-            const float qv = load_elem<DT>(p.q, ((int64_t)r * p.H + h) * HD + tid) * p.scale_log2e;
-            const float bk = load_elem<DT>(p.b_K, (int64_t)h * HD + tid);
-            qs_lds[tid] = qv;
-            bk_lds[tid] = bk;
-            bv_lds[tid] = load_elem<DT>(p.b_V, (int64_t)h * HD + tid);
-            const float part = group_sum<64>(qv * bk);
-            if (lane == 0) ml_lds[4 + w] = part;      // waves 0 and 1: halves of q . b_K
-        }
-        // valid token blocks of this wave: blocks 2 b + th below ceil(nvalid / 32)
-        const int nvb = (nvalid + 31) >> 5;
-        const int nb = (nvb - th + 1) >> 1;
-
-#pragma unroll
-        for (int i = 0; i < 64; ++i)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc_a[i][e] = 0.f;
-        if constexpr (kTokFrags > 8) {
-#pragma unroll
-            for (int i = 0; i < kAccV; ++i)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc_v[i][e] = 0.f;
-        }
-
-        APT_OPERAND_ADDRESSES()
-        // everything issued so far has to land here: the loads the compiler keeps track of (or the
-        // wait counts it would place inside the k loop for them would also wait for the staging
-        // copies) and with them the first four k-tiles
-        wait_vmcnt<0>();
-#pragma unroll
-        for (int i = 0; i < kXChunks; ++i) asm volatile("" ::"v"(idsn[i]));
-        asm volatile("" ::"v"(itn.x), "v"(itn.y), "v"(itn.z), "v"(itn.w));
-        __syncthreads();
-        // a short tile multiplies only the token blocks that hold valid tokens (at least one, so
-        // that every wave runs the same barriers)
-        bool full = false;
-        if constexpr (kTokFrags == 10) {
-            if (nb == 5) {
-                full = true;
-                if (mat == 0) APT_K_LOOP(0, 8, 10)
-                else APT_K_LOOP(1, 10, 8)
-            }
-        }
-        if (!full) {
-            if (mat == 0) {
-                if (nb == 4) APT_K_LOOP(0, 8, 8)
-                else if (nb == 3) APT_K_LOOP(0, 8, 6)
-                else if (nb == 2) APT_K_LOOP(0, 8, 4)
-                else APT_K_LOOP(0, 8, 2)
-            } else {
-                if (nb == 4) APT_K_LOOP(1, 8, 8)
-                else if (nb == 3) APT_K_LOOP(1, 6, 8)
-                else if (nb == 2) APT_K_LOOP(1, 4, 8)
-                else APT_K_LOOP(1, 2, 8)
-            }
-        }
-
-        // stages 0..2 are free now (every wave has passed the last barrier of the k loop; stage 3
-        // holds the last k-tile, which slower waves may still read): start the next item's first
-        // three k-tiles, then finish this item
-        if (have_next) {
-            APT_MAKE_SOURCES(xsrc, wsrc, itn, idsn)
-            APT_STAGE_FIRST(0, 3)
-        }
-
-        // ---- epilogue.  Register e of tile (i, j): row 4 (lane / 16) + e of the A-side fragment i,
-        // column lane % 16 of the B-side fragment j.
-        // lane-dependent LDS addresses of the epilogue are rebuilt here from values the compiler cannot see
-        // through: hoisted out of the item loop they would stay live across the k loops and end up in scratch
-        int ln = lane, td = tid;
-        asm volatile("" : "+v"(ln), "+v"(td));
-        const int l16 = ln & 15, qd = ln >> 4;
-        if (mat == 0) {
-            // K wave: rows = channels 16 i + 4 qd + e, columns = tokens of X fragment j
-            const float qb = ml_lds[4] + ml_lds[5];
-            float sp[kTokFrags];
-#pragma unroll
-            for (int j = 0; j < kTokFrags; ++j) sp[j] = 0.f;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float4 q4 = *(const float4*)(qs_lds + 16 * i + 4 * qd);
-#pragma unroll
-                for (int j = 0; j < kTokFrags; ++j) {
-                    const f32x4_t t = APT_ACC_GET(0, i, j);
-                    sp[j] = fmaf(t[0], q4.x, sp[j]);
-                    sp[j] = fmaf(t[1], q4.y, sp[j]);
-                    sp[j] = fmaf(t[2], q4.z, sp[j]);
-                    sp[j] = fmaf(t[3], q4.w, sp[j]);
-                }
-                // the accumulators are read out in small groups: read all at once they push every
-                // long-lived value into scratch, and a scratch reload waits for the copies of the
-                // next item's k-tiles that are in flight here
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            float m = kSentinel;
-            bool ok[kTokFrags];
-#pragma unroll
-            for (int j = 0; j < kTokFrags; ++j) {
-                sp[j] += __shfl_xor(sp[j], 16);
-                sp[j] += __shfl_xor(sp[j], 32);
-                ok[j] = x_frag_row(th, j) + l16 < nvalid;
-                sp[j] = ok[j] ? sp[j] + qb : kSentinel;
-                m = fmaxf(m, sp[j]);
-            }
-            m = group_max<16>(m);                     // the four lane groups hold the same scores
-            float l = 0.f;
-#pragma unroll
-            for (int j = 0; j < kTokFrags; ++j) {
-                const float pw = ok[j] ? fast_exp2(sp[j] - m) : 0.f;
-                l += pw;
-                if (qd == 0) p_lds[x_frag_row(th, j) + l16] = pw;
-            }
-            l = group_sum<16>(l);
-            if (ln == 0) { ml_lds[th * 2] = m; ml_lds[th * 2 + 1] = l; }
-        }
-        __syncthreads();
-        if (have_next) APT_STAGE_FIRST(3, 4)      // every wave has left the k loop: stage 3 is free too
-        if (mat == 1) {
-            // V wave: rows = tokens 4 qd + e of X fragment i, columns = channels 16 j + lane % 16
-            float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < kTokFrags; ++i) {
-                const float4 p4 = *(const float4*)(p_lds + x_frag_row(th, i) + 4 * qd);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const f32x4_t t = APT_ACC_GET(1, i, j);
-                    o[j] = fmaf(t[0], p4.x, o[j]);
-                    o[j] = fmaf(t[1], p4.y, o[j]);
-                    o[j] = fmaf(t[2], p4.z, o[j]);
-                    o[j] = fmaf(t[3], p4.w, o[j]);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            const float l = ml_lds[th * 2 + 1];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                o[j] += __shfl_xor(o[j], 16);
-                o[j] += __shfl_xor(o[j], 32);
-                if (qd == 0) o_lds[th * 128 + 16 * j + l16] = fmaf(l, bv_lds[16 * j + l16], o[j]);
-            }
-        }
-        __syncthreads();
-        if (td < HD) {
-            const float m0 = ml_lds[0], l0 = ml_lds[1], m1 = ml_lds[2], l1 = ml_lds[3];
-            const float M = fmaxf(m0, m1);
-            const float w0 = fast_exp2(m0 - M), w1 = fast_exp2(m1 - M);
-            const int64_t slot = ((int64_t)ws_offset[r] + t0 / p.hidden_chunk) * p.H + h;
-            p.ws_acc[slot * HD + td] = o_lds[td] * w0 + o_lds[128 + td] * w1;
-            if (td == 0) p.ws_ml[slot] = make_float2(M, l0 * w0 + l1 * w1);
-        }
-        have = have_next;
-        qi = nqi;
-        it = itn;
-    }
-#undef APT_K_LOOP
-#undef APT_K_TILE
-#undef APT_COPY_AT
-#undef APT_SLOT_ADDR
-#undef APT_ACC_GET
-#undef APT_ACC_V_SAFE
-#undef APT_ACC_A_SAFE
-#undef APT_WF
-#undef APT_XF
-#undef APT_STAGE_FIRST
-#undef APT_OPERAND_ADDRESSES
-#undef APT_MAKE_SOURCES
-
-    // ---- then a share of the KV-kind items, longest first
-    __syncthreads();
-    // handed out one by one, so that workgroups that finish their hidden-kind share early take more
-    int* ticket_lds = (int*)(lds + kStages * (kWTileBytes + kXTileBytes));
-    for (;;) {
-        if (tid == 0) *ticket_lds = atomicAdd(p.kv_ticket, 1);
-        __syncthreads();
-        const int i = p.n_hidden_items + *ticket_lds;
-        if (i >= p.n_items) break;
-        const int4 kv = items[i];
-        kv_item<DT, HD>(p, kv.x, kv.y, kv.z, kv.w, lds);
-        __syncthreads();
     }
 }
 
@@ -1057,18 +335,6 @@ int launch_items(const ItemParams& p, size_t lds_bytes, hipStream_t st) {
 
 #include "apt_absorbed.inc"
 
-// persistent launch: one workgroup per compute unit, a multiple of 8
-template <int DT>
-int launch_mfma(const ItemParams& p, int n_wg, hipStream_t st) {
-    if (p.hidden_chunk == MfmaTile<10>::kTokTile)
-        hipLaunchKernelGGL((apt_items_mfma_kernel<DT, 10>), dim3(n_wg), dim3(kThreads), MfmaTile<10>::kLds, st, p);
-    else if (p.hidden_chunk == MfmaTile<8>::kTokTile)
-        hipLaunchKernelGGL((apt_items_mfma_kernel<DT, 8>), dim3(n_wg), dim3(kThreads), MfmaTile<8>::kLds, st, p);
-    else
-        return APT_ESHAPE;
-    return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
-}
-
 template <int DT, int HD>
 int launch_items_impl(const ItemParams& p_in, int himpl, char* out, int out_dtype, int n_wg, hipStream_t st) {
     constexpr int EB = Elt<DT>::bytes;
@@ -1088,7 +354,7 @@ int launch_items_impl(const ItemParams& p_in, int himpl, char* out, int out_dtyp
         return launch_items<DT, HD, 1>(p, v > kv_lds ? v : kv_lds, st);
     }
     if constexpr (DT != 0 && HD == 128) {
-        return launch_mfma<DT>(p, n_wg, st);
+        return apt_launch_mfma<DT>(p, n_wg, st);
     }
     return APT_ESHAPE;
 }
@@ -1105,10 +371,6 @@ constexpr int kMaxDevices = 64;
 std::mutex g_setup_mutex;
 DeviceState g_devices[kMaxDevices];
 
-template <typename K> bool raise_lds_limit(K kern) {
-    return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
-}
-
 int device_setup(const DeviceState** out) {
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return APT_EHIP;
@@ -1119,14 +381,13 @@ int device_setup(const DeviceState** out) {
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return APT_EHIP;
         ds.n_wg = cus >= 8 ? (cus / 8) * 8 : 8;
         // every kernel that can be launched with more than 64 KB of dynamic LDS
-        const bool ok = raise_lds_limit(apt_items_mfma_kernel<1, 8>) && raise_lds_limit(apt_items_mfma_kernel<2, 8>) &&
-                        raise_lds_limit(apt_items_mfma_kernel<1, 10>) && raise_lds_limit(apt_items_mfma_kernel<2, 10>) &&
-                        raise_lds_limit(apt_items_kernel<0, 64, 1>) && raise_lds_limit(apt_items_kernel<0, 128, 1>) &&
-                        raise_lds_limit(apt_items_kernel<1, 64, 1>) && raise_lds_limit(apt_items_kernel<1, 128, 1>) &&
-                        raise_lds_limit(apt_items_kernel<2, 64, 1>) && raise_lds_limit(apt_items_kernel<2, 128, 1>) &&
-                        raise_lds_limit(apt_absorb_score_kernel<0>) && raise_lds_limit(apt_absorb_pv_kernel<0>) &&
-                        raise_lds_limit(apt_absorb_score_mfma_kernel<1>) && raise_lds_limit(apt_absorb_score_mfma_kernel<2>) &&
-                        raise_lds_limit(apt_absorb_pv_mfma_kernel<1>) && raise_lds_limit(apt_absorb_pv_mfma_kernel<2>);
+        const bool ok = apt_setup_mfma<1>() && apt_setup_mfma<2>() &&
+                        apt_raise_lds_limit(apt_items_kernel<0, 64, 1>) && apt_raise_lds_limit(apt_items_kernel<0, 128, 1>) &&
+                        apt_raise_lds_limit(apt_items_kernel<1, 64, 1>) && apt_raise_lds_limit(apt_items_kernel<1, 128, 1>) &&
+                        apt_raise_lds_limit(apt_items_kernel<2, 64, 1>) && apt_raise_lds_limit(apt_items_kernel<2, 128, 1>) &&
+                        apt_raise_lds_limit(apt_absorb_score_kernel<0>) && apt_raise_lds_limit(apt_absorb_pv_kernel<0>) &&
+                        apt_raise_lds_limit(apt_absorb_score_mfma_kernel<1>) && apt_raise_lds_limit(apt_absorb_score_mfma_kernel<2>) &&
+                        apt_raise_lds_limit(apt_absorb_pv_mfma_kernel<1>) && apt_raise_lds_limit(apt_absorb_pv_mfma_kernel<2>);
         if (!ok) return APT_EHIP;
         void* ptr = nullptr;
         if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return APT_EHIP;

@@ -1,0 +1,16 @@
+// Launchers that live in translation units of their own.
+#pragma once
+#include "apt_device.h"
+
+// dynamic LDS beyond 64 KB has to be allowed per kernel (per-device set-up)
+template <typename K> static inline bool apt_raise_lds_limit(K kern) {
+    return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
+}
+
+// apt_mfma.inc: hidden-kind items on packed weights (then the KV-kind items, in the same launch).  DT: 1 = fp16, 2 = bf16
+template <int DT> int apt_launch_mfma(const ItemParams& p, int n_wg, hipStream_t st);
+template <int DT> bool apt_setup_mfma();
+template <> int apt_launch_mfma<1>(const ItemParams& p, int n_wg, hipStream_t st);
+template <> int apt_launch_mfma<2>(const ItemParams& p, int n_wg, hipStream_t st);
+template <> bool apt_setup_mfma<1>();
+template <> bool apt_setup_mfma<2>();
