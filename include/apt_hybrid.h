@@ -87,13 +87,19 @@ typedef struct apt_shape {
     int32_t out_dtype;          /* APT_F32 or the same as dtype                           */
     int32_t max_blocks_per_req; /* row length of block_tables                             */
     int32_t hidden_chunk;       /* tokens per hidden-kind work item; 0 = library default
-                                   (MFMA kernel: 256 or 320, default 320 for d_model >= 8192)  */
+                                   (MFMA kernel: 256 or 320, default 320 for d_model >= 8192;
+                                   VALU: at most 64 for fp32, 256 / 128 for 16-bit dtypes with
+                                   head_dim 64 / 128, there chosen by apt_plan for each batch:
+                                   the longest of 256 / 128 / 64 that still gives 200
+                                   hidden-kind items; apt_plan_info.hidden_chunk reports it)  */
     int32_t kv_chunk;           /* tokens per KV-kind work item, whole blocks, at most 256
                                    of them; 0 = chosen by apt_plan for each batch: the
                                    longest of 2048 / 1024 / 512 that still gives 2048
                                    KV-kind items (apt_plan_info.kv_chunk reports it)      */
     int32_t hidden_impl;        /* APT_HIDDEN_AUTO: MFMA kernel for 16-bit dtypes with
-                                   head_dim 128, plain-ALU kernel otherwise.
+                                   head_dim 128, otherwise _VALU: raw weights, on the
+                                   plain ALUs for fp32 and on the matrix cores for 16-bit
+                                   dtypes (any head_dim; no packed copy needed).
                                    APT_HIDDEN_ABSORBED (never chosen by AUTO): the same
                                    output without projecting K and V, see below           */
     float softmax_scale;        /* multiplies <q, k>; 1/sqrt(head_dim) in Eq. 2's
@@ -235,7 +241,7 @@ int apt_pack_weights(const apt_shape* s, const void* W_K, const void* W_V, void*
  *               share one plan_dev must be ordered on one stream (calls for successive layers
  *               are); everything else in it is read-only
  *   q, k_pages, v_pages, hidden_pages, b_K, b_V, block_tables, out   device, see layout
- *   W_K, W_V    device, raw [d_in][d_out]; read only by the plain-ALU hidden kernel
+ *   W_K, W_V    device, raw [d_in][d_out]; not read by the MFMA hidden kernel
  *               (may be NULL when the resolved hidden_impl is MFMA or no request is
  *               hidden-kind)
  *   W_packed    device, from apt_pack_weights; read only by the MFMA hidden kernel

@@ -25,8 +25,7 @@ static __device__ __align__(256) unsigned char scratch[APT_STATIC_WORKSPACE_BYTE
 namespace {
 
 // ---------------------------------------------------------------------------------
-// hidden-kind item, plain-ALU version (fp32 configs and shapes the MFMA kernel
-// does not cover).  chunk <= 64 tokens.
+// hidden-kind item, plain-ALU version (fp32 inputs).  chunk <= 64 tokens.
 // ---------------------------------------------------------------------------------
 template <int DT, int HD>
 __device__ __forceinline__ void hidden_item_valu(const ItemParams& p, int r, int h, int t0, int t1, char* lds) {
@@ -336,7 +335,7 @@ int launch_items(const ItemParams& p, size_t lds_bytes, hipStream_t st) {
 #include "apt_absorbed.inc"
 
 template <int DT, int HD>
-int launch_items_impl(const ItemParams& p_in, int himpl, char* out, int out_dtype, int n_wg, hipStream_t st) {
+int launch_items_impl(const ItemParams& p_in, int himpl, char* out, int out_dtype, int n_wg, int queue_len, hipStream_t st) {
     constexpr int EB = Elt<DT>::bytes;
     constexpr int LPR = HD * EB / 16;
     constexpr int G = 4 * (64 / LPR);
@@ -350,8 +349,12 @@ int launch_items_impl(const ItemParams& p_in, int himpl, char* out, int out_dtyp
         return launch_items<DT, HD, 0>(p, kv_lds, st);
     }
     if (himpl == APT_HIDDEN_VALU) {
-        size_t v = (size_t)(2 * p.hidden_chunk * (HD + 1) + 64 + 2) * 4;
-        return launch_items<DT, HD, 1>(p, v > kv_lds ? v : kv_lds, st);
+        if constexpr (DT == 0) {
+            size_t v = (size_t)(2 * p.hidden_chunk * (HD + 1) + 64 + 2) * 4;
+            return launch_items<DT, HD, 1>(p, v > kv_lds ? v : kv_lds, st);
+        } else {
+            return apt_launch_raw16(p, DT, HD, queue_len, st);
+        }
     }
     if constexpr (DT != 0 && HD == 128) {
         return apt_launch_mfma<DT>(p, n_wg, st);
@@ -383,8 +386,7 @@ int device_setup(const DeviceState** out) {
         // every kernel that can be launched with more than 64 KB of dynamic LDS
         const bool ok = apt_setup_mfma<1>() && apt_setup_mfma<2>() &&
                         apt_raise_lds_limit(apt_items_kernel<0, 64, 1>) && apt_raise_lds_limit(apt_items_kernel<0, 128, 1>) &&
-                        apt_raise_lds_limit(apt_items_kernel<1, 64, 1>) && apt_raise_lds_limit(apt_items_kernel<1, 128, 1>) &&
-                        apt_raise_lds_limit(apt_items_kernel<2, 64, 1>) && apt_raise_lds_limit(apt_items_kernel<2, 128, 1>) &&
+                        apt_setup_raw16() &&
                         apt_raise_lds_limit(apt_absorb_score_kernel<0>) && apt_raise_lds_limit(apt_absorb_pv_kernel<0>) &&
                         apt_raise_lds_limit(apt_absorb_score_mfma_kernel<1>) && apt_raise_lds_limit(apt_absorb_score_mfma_kernel<2>) &&
                         apt_raise_lds_limit(apt_absorb_pv_mfma_kernel<1>) && apt_raise_lds_limit(apt_absorb_pv_mfma_kernel<2>);
@@ -520,13 +522,15 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     const int32_t* pw = (const int32_t*)plan_host;
     if (pw[APT_PW_MAGIC] != APT_PLAN_MAGIC) return APT_EINVAL;
     // the plan must have been made for this shape
-    if (pw[APT_PW_HEADS] != rs.s.n_heads || pw[APT_PW_HEAD_DIM] != rs.s.head_dim || pw[APT_PW_HCHUNK] != rs.s.hidden_chunk ||
+    if (pw[APT_PW_HEADS] != rs.s.n_heads || pw[APT_PW_HEAD_DIM] != rs.s.head_dim ||
         pw[APT_PW_HIMPL] != rs.s.hidden_impl || pw[APT_PW_D_MODEL] != rs.s.d_model ||
         pw[APT_PW_BLOCK_SIZE] != rs.s.block_size || pw[APT_PW_MAX_BLOCKS] != rs.s.max_blocks_per_req ||
         pw[APT_PW_DTYPE] != rs.s.dtype)
         return APT_ESHAPE;
-    // KV-kind range length: the caller's, or the planner's choice for this batch when the caller left it open
-    const int kv_chunk = pw[APT_PW_KCHUNK];
+    // hidden-kind and KV-kind range lengths: the caller's, or the planner's choice for this batch where the caller left them open
+    const int hidden_chunk = pw[APT_PW_HCHUNK], kv_chunk = pw[APT_PW_KCHUNK];
+    if (rs.hidden_auto ? (hidden_chunk < APT_RAW16_MIN_HIDDEN_CHUNK || hidden_chunk > rs.s.hidden_chunk) : hidden_chunk != rs.s.hidden_chunk)
+        return APT_ESHAPE;
     if (rs.kv_auto ? (kv_chunk < rs.s.kv_chunk || kv_chunk > APT_MAX_AUTO_KV_CHUNK || !apt_kv_chunk_ok(kv_chunk, rs.s.block_size))
                    : kv_chunk != rs.s.kv_chunk)
         return APT_ESHAPE;
@@ -583,18 +587,23 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     p.B = B; p.H = rs.s.n_heads; p.d = rs.s.d_model; p.bs = rs.s.block_size; p.log2_bs = log2_bs;
     p.max_blocks = rs.s.max_blocks_per_req;
     p.n_items = n_items; p.n_hidden_items = n_hidden;
-    p.hidden_chunk = rs.s.hidden_chunk; p.kv_chunk = kv_chunk; p.items_off = pw[APT_PW_ITEMS_OFF];
+    p.hidden_chunk = hidden_chunk; p.kv_chunk = kv_chunk; p.items_off = pw[APT_PW_ITEMS_OFF];
     p.scale_log2e = rs.s.softmax_scale * 1.4426950408889634f;
     hipStream_t st = (hipStream_t)stream;
 
+    int queue_len = 0;                       // longest hidden-kind queue
+    for (int x = 0; x < APT_N_QUEUES; ++x) {
+        const int n = pw[APT_PW_QUEUE0 + x + 1] - pw[APT_PW_QUEUE0 + x];
+        queue_len = n > queue_len ? n : queue_len;
+    }
     const int dt = rs.s.dtype, hd = rs.s.head_dim, hi = rs.s.hidden_impl;
     if (ev_begin && hipEventRecord((hipEvent_t)ev_begin, st) != hipSuccess) return APT_EHIP;
-    if (dt == APT_F32 && hd == 64) rc = launch_items_impl<0, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
-    else if (dt == APT_F32 && hd == 128) rc = launch_items_impl<0, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
-    else if (dt == APT_F16 && hd == 64) rc = launch_items_impl<1, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
-    else if (dt == APT_F16 && hd == 128) rc = launch_items_impl<1, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
-    else if (dt == APT_BF16 && hd == 64) rc = launch_items_impl<2, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
-    else rc = launch_items_impl<2, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
+    if (dt == APT_F32 && hd == 64) rc = launch_items_impl<0, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, queue_len, st);
+    else if (dt == APT_F32 && hd == 128) rc = launch_items_impl<0, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, queue_len, st);
+    else if (dt == APT_F16 && hd == 64) rc = launch_items_impl<1, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, queue_len, st);
+    else if (dt == APT_F16 && hd == 128) rc = launch_items_impl<1, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, queue_len, st);
+    else if (dt == APT_BF16 && hd == 64) rc = launch_items_impl<2, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, queue_len, st);
+    else rc = launch_items_impl<2, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, queue_len, st);
     if (rc) return rc;
     if (ev_end && hipEventRecord((hipEvent_t)ev_end, st) != hipSuccess) return APT_EHIP;
 

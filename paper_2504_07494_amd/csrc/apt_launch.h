@@ -14,3 +14,8 @@ template <> int apt_launch_mfma<1>(const ItemParams& p, int n_wg, hipStream_t st
 template <> int apt_launch_mfma<2>(const ItemParams& p, int n_wg, hipStream_t st);
 template <> bool apt_setup_mfma<1>();
 template <> bool apt_setup_mfma<2>();
+
+// apt_raw16.hip: 16-bit inputs, hidden-kind items on the raw weights (and the KV-kind items, in the same launch);
+// queue_len = longest of the eight hidden-kind queues
+int apt_launch_raw16(const ItemParams& p, int dtype, int head_dim, int queue_len, hipStream_t st);
+bool apt_setup_raw16();

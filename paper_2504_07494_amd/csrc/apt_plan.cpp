@@ -38,6 +38,7 @@ int apt_resolve(const apt_shape* in, apt_resolved* out) {
     if ((s.block_size * lanes_per_row) % 64 != 0) return APT_ESHAPE;
     if (!(s.softmax_scale == s.softmax_scale)) return APT_EINVAL;
 
+    out->hidden_auto = false;
     const bool mfma_ok = (s.dtype != APT_F32) && s.head_dim == 128 && (s.d_model % 128 == 0);
     if (s.hidden_impl == APT_HIDDEN_AUTO) s.hidden_impl = mfma_ok ? APT_HIDDEN_MFMA : APT_HIDDEN_VALU;
     if (s.hidden_impl == APT_HIDDEN_MFMA) {
@@ -53,8 +54,11 @@ int apt_resolve(const apt_shape* in, apt_resolved* out) {
         if (s.hidden_chunk == 0) s.hidden_chunk = APT_ABSORBED_CHUNK;
         if (s.hidden_chunk != APT_ABSORBED_CHUNK) return APT_ESHAPE;
     } else if (s.hidden_impl == APT_HIDDEN_VALU) {
-        if (s.hidden_chunk == 0) s.hidden_chunk = APT_DEFAULT_VALU_HIDDEN_CHUNK;
-        if (s.hidden_chunk < 1 || s.hidden_chunk > APT_MAX_VALU_HIDDEN_CHUNK) return APT_ESHAPE;
+        const bool raw16 = s.dtype != APT_F32;
+        const int most = raw16 ? APT_RAW16_MAX_HIDDEN_CHUNK(s.head_dim) : APT_MAX_VALU_HIDDEN_CHUNK;
+        out->hidden_auto = raw16 && s.hidden_chunk == 0;
+        if (s.hidden_chunk == 0) s.hidden_chunk = raw16 ? most : APT_DEFAULT_VALU_HIDDEN_CHUNK;
+        if (s.hidden_chunk < 1 || s.hidden_chunk > most) return APT_ESHAPE;
     } else {
         return APT_ESHAPE;
     }
@@ -79,7 +83,8 @@ extern "C" int apt_plan_max_bytes(const apt_shape* s, int B, int max_ctx, size_t
     int rc = apt_resolve(s, &rs);
     if (rc) return rc;
     if (B < 1 || max_ctx < 1 || !bytes) return APT_EINVAL;
-    const int cmin = rs.s.hidden_chunk < rs.s.kv_chunk ? rs.s.hidden_chunk : rs.s.kv_chunk;
+    const int hmin = rs.hidden_auto ? APT_RAW16_MIN_HIDDEN_CHUNK : rs.s.hidden_chunk;
+    const int cmin = hmin < rs.s.kv_chunk ? hmin : rs.s.kv_chunk;
     const int64_t n_items = (int64_t)B * rs.s.n_heads * ceil_div64(max_ctx, cmin);
     *bytes = plan_words(B, n_items) * 4;
     return APT_OK;
@@ -95,7 +100,14 @@ extern "C" int apt_workspace_bytes(const apt_shape* s, int max_batch, int max_ct
     // the layout of any batch: ranges are most numerous when every request is of the kind with the shorter
     // chunk; the sections of the absorbed-weight path are largest when every request is hidden-kind
     const int cmin = rs.s.hidden_chunk < rs.s.kv_chunk ? rs.s.hidden_chunk : rs.s.kv_chunk;
-    const int64_t n_partials = (int64_t)max_batch * ceil_div64(max_ctx, cmin);
+    int64_t n_partials = (int64_t)max_batch * ceil_div64(max_ctx, cmin);
+    if (rs.hidden_auto) {
+        // a range below the longest is chosen only while twice its length gives fewer than APT_RAW16_ITEMS_TARGET
+        // hidden-kind items, so it gives at most twice as many ranges as that; the KV-kind requests come on top
+        const int64_t few = 2 * ((int64_t)(APT_RAW16_ITEMS_TARGET - 1) / rs.s.n_heads) +
+                            (int64_t)max_batch * ceil_div64(max_ctx, rs.s.kv_chunk);
+        if (few > n_partials) n_partials = few;
+    }
     const int64_t hid_chunks = (int64_t)max_batch * ceil_div64(max_ctx, rs.s.hidden_chunk);
     if (n_partials * (int64_t)rs.s.n_heads > 0x7fffffff || (int64_t)max_batch * max_ctx > 0x7fffffff) return APT_ERANGE;
     if (dev_bytes)
@@ -113,6 +125,17 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
     if (!ctx_lens || !cache_kind || !plan_host || B < 1) return APT_EINVAL;
     const int H = rs.s.n_heads;
     const int64_t max_len = (int64_t)rs.s.max_blocks_per_req * rs.s.block_size;
+
+    if (rs.hidden_auto) {
+        auto hidden_items = [&](int c) {
+            int64_t n = 0;
+            for (int r = 0; r < B; ++r)
+                if (cache_kind[r] == APT_KIND_HIDDEN && ctx_lens[r] > 0) n += ceil_div64(ctx_lens[r], c) * H;
+            return n;
+        };
+        while (rs.s.hidden_chunk > APT_RAW16_MIN_HIDDEN_CHUNK && hidden_items(rs.s.hidden_chunk) < APT_RAW16_ITEMS_TARGET)
+            rs.s.hidden_chunk /= 2;
+    }
 
     // KV-kind range length left to the library: a short range costs an item's start-up and wind-down more often
     // per byte, a long one leaves too few items to fill the device; take the longest that still yields enough items

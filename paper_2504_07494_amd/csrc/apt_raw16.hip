@@ -1,0 +1,271 @@
+// Hidden-kind items straight from the raw weights (fp16 / bf16, head_dim 64 or 128): no packed copy is needed.
+#include <type_traits>
+#include "apt_device.h"
+#include "apt_launch.h"
+
+namespace {
+
+// One item = one head's K and V of a tile of T tokens: D[2 HD channels][T tokens] with k = d_model on
+// v_mfma_f32_16x16x32.  The four waves are (mat, th) as in the packed-weight kernel: mat 0 = K channels, 1 = V
+// channels; th = token blocks of 32 (2 b + th), so a wave owns HD channels x T / 2 tokens.
+//
+// The raw W is [d_in][d_out]: eight consecutive k of one channel, which is what an MFMA operand wants, are d_model
+// elements apart.  The k-tile is therefore copied as it lies in memory (32 rows of 2 HD channels, global -> LDS
+// without registers) and read with the transposing LDS read ds_read_b64_tr_b16: 16 lanes read 4 k-rows x 16 channels
+// and each lane receives the 4 k of one channel.  The 32-byte units of a row sit at u ^ wswz(k), so that the four
+// rows of such a read fall on different banks (rows are 256 or 512 bytes apart, the same bank otherwise).
+//
+// Tiles: at most 256 tokens x 128 channels (HD 64) or 128 x 256 (HD 128), 128 accumulator registers per wave, 24 KB
+// per k-tile and three stages, so that two workgroups share a CU and one's barriers and epilogue are covered by the
+// other's MFMAs.  Short ranges take the 128- or 64-token variant: less padding, and with the LDS this frees more
+// stages in flight.
+//
+// Bound by the matrix pipes and, like every dense product on this card, by board power: 48 requests of 32..1024 tokens
+// at d_model 2048, head_dim 64 (13 k hidden-kind tokens) take 0.247 ms for the whole step, 864 TFLOP/s on 4 d^2 per
+// token; the plain-ALU kernel that served these shapes before took 13.58 ms (16 TFLOP/s).
+template <int HD, int T> struct RawTile {
+    static constexpr int kChan = 2 * HD;
+    static constexpr int kWRow = kChan * 2;                    // bytes of a k-row of the W image
+    static constexpr int kWBytes = kBK * kWRow;
+    static constexpr int kXBytes = T * kBK * 2;
+    static constexpr int kStage = kWBytes + kXBytes;
+    static constexpr int kStages = 73728 / kStage < 6 ? 73728 / kStage : 6;
+    static constexpr int kWCopies = kWBytes / 4096;            // 1 KB copies per wave and k-tile
+    static constexpr int kXCopies = kXBytes / 4096;
+    static constexpr int kCopies = kWCopies + kXCopies;
+    static constexpr int kScratch = (T + 5 * HD + 8) * 4;
+    static constexpr int kLds = kStages * kStage + kScratch;
+    static_assert(T % 64 == 0 && kStages >= 3 && kLds <= 80 * 1024, "two workgroups per CU");
+};
+template <int HD> constexpr int raw_max_tile() { return 16384 / HD; }      // 256 or 128 tokens
+template <int HD> constexpr int raw_lds_bytes() {
+    int m = 0;
+    if (HD == 64) m = RawTile<HD, raw_max_tile<HD>()>::kLds;
+    m = m > RawTile<HD, 128>::kLds ? m : RawTile<HD, 128>::kLds;
+    return m > RawTile<HD, 64>::kLds ? m : RawTile<HD, 64>::kLds;
+}
+
+__device__ inline int wswz(int k) { return (k & 3) | ((k >> 1) & 4); }
+
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+// 4 k x 16 channels, transposed (see above); 16 consecutive lanes cover 4 rows x 32 bytes
+__device__ inline uint2 lds_read_tr(uint32_t addr) {
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(uintptr_t)addr));
+}
+
+template <int DT, int HD, int T>
+__device__ __forceinline__ void hidden_item_raw(const ItemParams& p, int r, int h, int t0, int t1, char* lds) {
+    using C = RawTile<HD, T>;
+    constexpr int CF = HD / 16, XF = T / 32;                   // channel and token fragments of a wave
+    constexpr int S = C::kStages;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, qd = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), mat = w >> 1, th = w & 1;
+    const int d = p.d, nkt = d / kBK, nvalid = t1 - t0;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+
+    // ---- copy sources of this lane.  W chunk n (1 KB, n = w + 4 i): rows of kWRow bytes; X chunk n: 16 token rows
+    const char* wsrc[C::kWCopies];
+    const char* xsrc[C::kXCopies];
+#pragma unroll
+    for (int i = 0; i < C::kWCopies; ++i) {
+        const int byte = (w + 4 * i) * 1024 + lane * 16;
+        const int k = byte / C::kWRow, u16 = (byte % C::kWRow) >> 4;
+        const int ch = ((u16 >> 1) ^ wswz(k)) * 16 + (u16 & 1) * 8;
+        wsrc[i] = (ch < HD ? p.W_K + ((int64_t)k * d + h * HD + ch) * 2 : p.W_V + ((int64_t)k * d + h * HD + ch - HD) * 2);
+    }
+#pragma unroll
+    for (int i = 0; i < C::kXCopies; ++i) {
+        const int row = 16 * (w + 4 * i) + (lane >> 2);
+        const int tok = min(t0 + row, t1 - 1);                 // rows past the range repeat its last token (masked later)
+        const int64_t blk = p.block_tables[(int64_t)r * 2 * p.max_blocks + (tok >> p.log2_bs)];
+        xsrc[i] = p.hidden_pages + ((blk * p.bs + (tok & (p.bs - 1))) * d) * 2 + (((lane & 3) ^ swz16(row)) << 4);
+    }
+    const int64_t wstep = (int64_t)kBK * d * 2;
+    auto issue = [&](int kt) {
+        const uint32_t st = lds0 + (kt % S) * C::kStage + w * 1024;
+#pragma unroll
+        for (int i = 0; i < C::kWCopies; ++i) gload_lds16(wsrc[i] + kt * wstep, st + i * 4096);
+#pragma unroll
+        for (int i = 0; i < C::kXCopies; ++i) gload_lds16(xsrc[i] + kt * (kBK * 2), st + C::kWBytes + i * 4096);
+    };
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s)
+        if (s < nkt) issue(s);
+
+    // ---- per-item constants of the epilogue
+    float* scr = (float*)(lds + S * C::kStage);
+    float* p_lds = scr;                     // [T] softmax weights (per token half, relative to its maximum)
+    float* qs_lds = scr + T;                // [HD] q * scale * log2(e)
+    float* bk_lds = qs_lds + HD;            // [HD]
+    float* bv_lds = bk_lds + HD;            // [HD]
+    float* o_lds = bv_lds + HD;             // [2][HD]
+    float* ml_lds = o_lds + 2 * HD;         // [2][2]
+    if (tid < HD) {
+        qs_lds[tid] = load_elem<DT>(p.q, ((int64_t)r * p.H + h) * HD + tid) * p.scale_log2e;
+        bk_lds[tid] = load_elem<DT>(p.b_K, (int64_t)h * HD + tid);
+        bv_lds[tid] = load_elem<DT>(p.b_V, (int64_t)h * HD + tid);
+    }
+
+    // ---- operand addresses: W fragment c (channels 16 c .. of this wave), X fragment t; further stages are a constant away
+    uint32_t waddr[CF];
+#pragma unroll
+    for (int c = 0; c < CF; ++c) {
+        const int k = 8 * qd + (l16 >> 2);
+        waddr[c] = lds0 + k * C::kWRow + (((mat * CF + c) ^ wswz(k)) << 5) + (l16 & 3) * 8;
+    }
+    const uint32_t xaddr = lds0 + C::kWBytes + (th * 32 + l16) * (kBK * 2) + ((qd ^ swz16(l16)) << 4);
+
+    f32x4_t acc[CF][XF];
+#pragma unroll
+    for (int c = 0; c < CF; ++c)
+#pragma unroll
+        for (int t = 0; t < XF; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[c][t][e] = 0.f;
+
+    auto k_loop = [&](auto is_v) {
+        int stage = 0;
+        for (int kt = 0; kt < nkt; ++kt) {
+            if (kt + S - 2 < nkt) wait_vmcnt<(S - 2) * C::kCopies>();
+            else wait_vmcnt<0>();
+            __syncthreads();        // k-tile kt has landed for every wave; nobody still reads the stage refilled next
+            if (kt + S - 1 < nkt) issue(kt + S - 1);
+            const uint32_t so = stage * C::kStage;
+            uint4 wf[CF], xf[XF];
+#pragma unroll
+            for (int c = 0; c < CF; ++c) {
+                const uint2 lo = lds_read_tr(waddr[c] + so), hi = lds_read_tr(waddr[c] + so + 4 * C::kWRow);
+                wf[c] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            }
+#pragma unroll
+            for (int t = 0; t < XF; ++t) xf[t] = lds_read16(xaddr + so + (64 * (t >> 1) + 16 * (t & 1)) * (kBK * 2));
+#pragma unroll
+            for (int t = 0; t < XF; ++t)
+#pragma unroll
+                for (int c = 0; c < CF; ++c)
+                    acc[c][t] = is_v ? mfma16<DT>(xf[t], wf[c], acc[c][t]) : mfma16<DT>(wf[c], xf[t], acc[c][t]);
+            stage = stage == S - 1 ? 0 : stage + 1;
+        }
+    };
+    if (mat == 0) k_loop(std::false_type{});
+    else k_loop(std::true_type{});
+
+    auto tok_row = [&](int t) { return th * 32 + 64 * (t >> 1) + 16 * (t & 1); };
+    if (mat == 0) {
+        // K wave: rows = channels 16 c + 4 qd + e, columns = tokens of fragment t
+        float sp[XF];
+#pragma unroll
+        for (int t = 0; t < XF; ++t) sp[t] = 0.f;
+        float qb = 0.f;
+#pragma unroll
+        for (int c = 0; c < CF; ++c) {
+            const float4 q4 = *(const float4*)(qs_lds + 16 * c + 4 * qd), b4 = *(const float4*)(bk_lds + 16 * c + 4 * qd);
+            qb = fmaf(q4.x, b4.x, fmaf(q4.y, b4.y, fmaf(q4.z, b4.z, fmaf(q4.w, b4.w, qb))));
+#pragma unroll
+            for (int t = 0; t < XF; ++t) {
+                sp[t] = fmaf(acc[c][t][0], q4.x, sp[t]);
+                sp[t] = fmaf(acc[c][t][1], q4.y, sp[t]);
+                sp[t] = fmaf(acc[c][t][2], q4.z, sp[t]);
+                sp[t] = fmaf(acc[c][t][3], q4.w, sp[t]);
+            }
+        }
+        float m = kSentinel;
+        bool ok[XF];
+#pragma unroll
+        for (int t = 0; t < XF; ++t) {
+            sp[t] += qb;                     // the lane group's share of q . b_K
+            sp[t] += __shfl_xor(sp[t], 16);
+            sp[t] += __shfl_xor(sp[t], 32);
+            ok[t] = tok_row(t) + l16 < nvalid;
+            sp[t] = ok[t] ? sp[t] : kSentinel;
+            m = fmaxf(m, sp[t]);
+        }
+        m = group_max<16>(m);                // the four lane groups hold the same scores
+        float l = 0.f;
+#pragma unroll
+        for (int t = 0; t < XF; ++t) {
+            const float pw = ok[t] ? fast_exp2(sp[t] - m) : 0.f;
+            l += pw;
+            if (qd == 0) p_lds[tok_row(t) + l16] = pw;
+        }
+        l = group_sum<16>(l);
+        if (lane == 0) { ml_lds[th * 2] = m; ml_lds[th * 2 + 1] = l; }
+    }
+    __syncthreads();
+    if (mat == 1) {
+        // V wave: rows = tokens 4 qd + e of fragment t, columns = channels 16 c + l16
+        float o[CF];
+#pragma unroll
+        for (int c = 0; c < CF; ++c) o[c] = 0.f;
+#pragma unroll
+        for (int t = 0; t < XF; ++t) {
+            const float4 p4 = *(const float4*)(p_lds + tok_row(t) + 4 * qd);
+#pragma unroll
+            for (int c = 0; c < CF; ++c) {
+                o[c] = fmaf(acc[c][t][0], p4.x, o[c]);
+                o[c] = fmaf(acc[c][t][1], p4.y, o[c]);
+                o[c] = fmaf(acc[c][t][2], p4.z, o[c]);
+                o[c] = fmaf(acc[c][t][3], p4.w, o[c]);
+            }
+        }
+        const float l = ml_lds[th * 2 + 1];
+#pragma unroll
+        for (int c = 0; c < CF; ++c) {
+            o[c] += __shfl_xor(o[c], 16);
+            o[c] += __shfl_xor(o[c], 32);
+            if (qd == 0) o_lds[th * HD + 16 * c + l16] = fmaf(l, bv_lds[16 * c + l16], o[c]);
+        }
+    }
+    __syncthreads();
+    if (tid < HD) {
+        const float m0 = ml_lds[0], l0 = ml_lds[1], m1 = ml_lds[2], l1 = ml_lds[3];
+        const float M = fmaxf(m0, m1);
+        const float w0 = fast_exp2(m0 - M), w1 = fast_exp2(m1 - M);
+        const int32_t* ws_offset = p.plan + APT_PW_HEADER + p.B;
+        const int64_t slot = ((int64_t)ws_offset[r] + t0 / p.hidden_chunk) * p.H + h;
+        p.ws_acc[slot * HD + tid] = o_lds[tid] * w0 + o_lds[HD + tid] * w1;
+        if (tid == 0) p.ws_ml[slot] = make_float2(M, l0 * w0 + l1 * w1);
+    }
+}
+
+// One workgroup per item.  Workgroup g runs on XCD g % 8: it takes item g / 8 of hidden queue g % 8, so that an XCD's
+// workgroups share the weights of few heads in its L2; the workgroups after 8 * queue_len take the KV-kind items.
+template <int DT, int HD>
+__global__ __launch_bounds__(kThreads, 2) void apt_items_raw_kernel(ItemParams p, int queue_len) {
+    extern __shared__ __align__(16) char lds[];
+    const int g = blockIdx.x;
+    const int4* items = (const int4*)(p.plan + p.items_off);
+    if (g < 8 * queue_len) {
+        const int i = p.plan[APT_PW_QUEUE0 + (g & 7)] + (g >> 3);
+        if (i >= p.plan[APT_PW_QUEUE0 + (g & 7) + 1]) return;
+        const int4 it = items[i];
+        const int n = it.w - it.z;
+        if (n <= 64) hidden_item_raw<DT, HD, 64>(p, it.x, it.y, it.z, it.w, lds);
+        else if (HD == 128 || n <= 128) hidden_item_raw<DT, HD, 128>(p, it.x, it.y, it.z, it.w, lds);
+        else if constexpr (HD == 64) hidden_item_raw<DT, HD, 256>(p, it.x, it.y, it.z, it.w, lds);
+    } else {
+        const int i = p.n_hidden_items + g - 8 * queue_len;
+        if (i >= p.n_items) return;
+        const int4 it = items[i];
+        kv_item<DT, HD>(p, it.x, it.y, it.z, it.w, lds);
+    }
+}
+
+template <int DT, int HD> int launch(const ItemParams& p, int queue_len, hipStream_t st) {
+    const unsigned grid = 8u * queue_len + (unsigned)(p.n_items - p.n_hidden_items);
+    hipLaunchKernelGGL((apt_items_raw_kernel<DT, HD>), dim3(grid), dim3(kThreads), raw_lds_bytes<HD>(), st, p, queue_len);
+    return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
+}
+
+}  // namespace
+
+int apt_launch_raw16(const ItemParams& p, int dtype, int head_dim, int queue_len, hipStream_t st) {
+    if (dtype == APT_F16) return head_dim == 64 ? launch<1, 64>(p, queue_len, st) : launch<1, 128>(p, queue_len, st);
+    return head_dim == 64 ? launch<2, 64>(p, queue_len, st) : launch<2, 128>(p, queue_len, st);
+}
+
+bool apt_setup_raw16() {
+    return apt_raise_lds_limit(apt_items_raw_kernel<1, 64>) && apt_raise_lds_limit(apt_items_raw_kernel<1, 128>) &&
+           apt_raise_lds_limit(apt_items_raw_kernel<2, 64>) && apt_raise_lds_limit(apt_items_raw_kernel<2, 128>);
+}

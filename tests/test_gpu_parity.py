@@ -104,6 +104,23 @@ def test_valu_hidden_and_kv_layout_variants(oracle, dtype, hd, H, bs):
     _check(got, _full(oracle, batch, layer), f"valu-{dtype}-hd{hd}-bs{bs}", 2e-4, 2e-3)
 
 
+@pytest.mark.parametrize("dtype,hd,H,bs,chunk", [("f16", 64, 3, 16, 256), ("bf16", 64, 1, 8, 128), ("f16", 64, 9, 32, 64), ("bf16", 64, 2, 16, 7),
+                                                  ("bf16", 128, 3, 16, 128), ("f16", 128, 1, 4, 64), ("f16", 64, 5, 16, 0)])
+def test_raw_weight_matrix_kernel_at_tile_edges(oracle, dtype, hd, H, bs, chunk):
+    """16-bit inputs without packed weights: every tile of the kernel (256, 128, 64 tokens), lengths around their
+    edges, ranges that fill no tile, and the range length the planner picks for a small batch (chunk 0)."""
+    print(f"[case] raw weights {dtype} hd={hd} H={H} bs={bs} chunk={chunk}", flush=True)
+    lens = np.array([1, 31, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 321, 513], dtype=np.int32)
+    kinds = np.array([HID] * 6 + [KV] + [HID] * 7, dtype=np.uint8)
+    cfg = wl.small_config(name="raw16", dtype=dtype, d_model=hd * H, n_heads=H, head_dim=hd, block_size=bs,
+                          batch=len(lens), len_lo=1, len_hi=513, hidden_ratio=0.5)
+    batch = wl.make_batch(cfg, lens, kinds)
+    layer = wl.make_layer(batch)
+    rn, got = _run(batch, layer, hidden_impl=ab.APT_HIDDEN_VALU, hidden_chunk=chunk)
+    assert rn.info.hidden_chunk == (chunk or 64)
+    _check(got, _full(oracle, batch, layer), f"raw16-{dtype}-hd{hd}-{chunk}", 2e-4, 2e-3)
+
+
 @pytest.mark.parametrize("dtype,hd,H,bs", [("f16", 128, 4, 16), ("bf16", 128, 4, 16), ("f32", 128, 2, 16),
                                             ("f16", 64, 6, 8), ("f32", 64, 5, 4)])
 def test_absorbed_weight_hidden_path(oracle, dtype, hd, H, bs):
