@@ -89,17 +89,17 @@ typedef struct apt_shape {
     int32_t hidden_chunk;       /* tokens per hidden-kind work item; 0 = library default
                                    (MFMA kernel: 256 or 320, default 320 for d_model >= 8192;
                                    VALU: at most 64 for fp32, 256 / 128 for 16-bit dtypes with
-                                   head_dim 64 / 128, there chosen by apt_plan for each batch:
-                                   the longest of 256 / 128 / 64 that still gives 200
+                                   head_dim 64 / 128; default chosen by apt_plan for each
+                                   batch: the longest of 256 (head_dim 128: 128) / 128 / 64,
+                                   fp32: of 32 / 16, that still gives 200
                                    hidden-kind items; apt_plan_info.hidden_chunk reports it)  */
     int32_t kv_chunk;           /* tokens per KV-kind work item, whole blocks, at most 256
                                    of them; 0 = chosen by apt_plan for each batch: the
                                    longest of 2048 / 1024 / 512 that still gives 2048
                                    KV-kind items (apt_plan_info.kv_chunk reports it)      */
     int32_t hidden_impl;        /* APT_HIDDEN_AUTO: MFMA kernel for 16-bit dtypes with
-                                   head_dim 128, otherwise _VALU: raw weights, on the
-                                   plain ALUs for fp32 and on the matrix cores for 16-bit
-                                   dtypes (any head_dim; no packed copy needed).
+                                   head_dim 128, otherwise _VALU: raw weights, any
+                                   dtype and head_dim (no packed copy needed).
                                    APT_HIDDEN_ABSORBED (never chosen by AUTO): the same
                                    output without projecting K and V, see below           */
     float softmax_scale;        /* multiplies <q, k>; 1/sqrt(head_dim) in Eq. 2's

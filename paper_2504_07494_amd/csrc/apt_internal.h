@@ -40,17 +40,19 @@ enum {
 #define APT_MFMA_HIDDEN_CHUNK 320       // token rows of the MFMA kernel's tile: 320 ...
 #define APT_MFMA_HIDDEN_CHUNK_SMALL 256 // ... or 256 (default for d_model < APT_MFMA_LARGE_TILE_D_MODEL)
 #define APT_MFMA_LARGE_TILE_D_MODEL 8192
-#define APT_DEFAULT_VALU_HIDDEN_CHUNK 32 // raw weights, fp32 inputs
-#define APT_MAX_VALU_HIDDEN_CHUNK 64
 // Raw weights, 16-bit inputs: the tile of the matrix kernel is 256 tokens (head_dim 64) or 128 (head_dim 128).  Left
 // open, the planner halves the range (to at least 64) while the batch yields fewer hidden-kind items than this, a bit
 // under one per CU: with fewer the chip idles, with more the longer range wins because it reads the weights less often.
 // Attention call at d_model 2048 (head_dim 64), us with ranges of 64 / 128 / 256 tokens: 1 request of 300 tokens 23 / 27 / 39
 // (160 / 96 / 64 items), 2 requests 47 / 32 / 40 (544 / 288 / 160), 4 requests 60 / 53 / 47 (1024 / 544 / 288),
 // 16 requests 151 / 121 / 111; at d_model 768, 4 requests 20 / 17.5 / 21 (384 / 204 / 108 items).
-#define APT_RAW16_MAX_HIDDEN_CHUNK(hd) (16384 / (hd))
-#define APT_RAW16_MIN_HIDDEN_CHUNK 64
-#define APT_RAW16_ITEMS_TARGET 200
+// fp32 inputs: 32 or 16 tokens by the same rule (64 when asked for: never the fastest).  us with ranges of 16 / 32 / 64: d_model 256,
+// 4 requests 12.2 / 12.8 / 16 (108 / 60 / 32 items); d_model 1024, 4 requests 63 / 45 / 70 (464 / 240 / 128), 64 requests
+// 501 / 488 / 572; d_model 512, 12 requests 45 / 39 / 52 (1008 / 528 / 288).
+#define APT_RAW_AUTO_HIDDEN_CHUNK(dtype, hd) ((dtype) == APT_F32 ? 32 : 16384 / (hd))
+#define APT_RAW_MAX_HIDDEN_CHUNK(dtype, hd) ((dtype) == APT_F32 ? 64 : 16384 / (hd))
+#define APT_RAW_MIN_HIDDEN_CHUNK(dtype) ((dtype) == APT_F32 ? 16 : 64)
+#define APT_RAW_ITEMS_TARGET 200
 #define APT_KV_MAX_PAGES_PER_WAVE 64
 #define APT_ABSORBED_HEAD_GROUPS 4       // absorbed-weight kernels: threads of a workgroup = 64 x 4 (token or column
 #define APT_ABSORBED_HEADS_PER_THREAD 10 // group, head group), 8 tokens/columns x 10 heads per thread
@@ -73,8 +75,8 @@ enum {
 struct apt_resolved {
     apt_shape s;        // chunks and hidden_impl filled in
     int elem_bytes;
-    bool hidden_auto;   // raw weights, 16-bit inputs and hidden_chunk was 0: s.hidden_chunk holds the longest range, the
-                        // planner may choose a shorter one, not below APT_RAW16_MIN_HIDDEN_CHUNK
+    bool hidden_auto;   // raw weights and hidden_chunk was 0: s.hidden_chunk holds the longest range, the
+                        // planner may choose a shorter one, not below APT_RAW_MIN_HIDDEN_CHUNK
     bool kv_auto;       // kv_chunk was 0: s.kv_chunk holds the shortest range, the planner may choose a longer one
 };
 

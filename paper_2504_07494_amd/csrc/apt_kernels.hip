@@ -25,95 +25,15 @@ static __device__ __align__(256) unsigned char scratch[APT_STATIC_WORKSPACE_BYTE
 namespace {
 
 // ---------------------------------------------------------------------------------
-// hidden-kind item, plain-ALU version (fp32 inputs).  chunk <= 64 tokens.
+// KV-kind items alone, one workgroup per item (plans without hidden-kind items; after the absorbed-weight kernels)
 // ---------------------------------------------------------------------------------
 template <int DT, int HD>
-__device__ __forceinline__ void hidden_item_valu(const ItemParams& p, int r, int h, int t0, int t1, char* lds) {
-    constexpr int NG = kThreads / HD;     // token groups
-    constexpr int TJ = 4;                 // tokens per pass of a thread
-    constexpr int LD = HD + 1;
-    const int C = p.hidden_chunk;
-    float* Ks = (float*)lds;              // [C][LD]
-    float* Vs = Ks + C * LD;              // [C][LD]
-    float* sc = Vs + C * LD;              // [64]
-    float* red = sc + 64;                 // [2]
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int c = tid % HD, g = tid / HD;
-    const int n = t1 - t0;
-    const int d = p.d;
-    const int64_t blk_elems = (int64_t)p.bs * d;
-
-    const float bk = load_elem<DT>(p.b_K, (int64_t)h * HD + c);
-    const float bv = load_elem<DT>(p.b_V, (int64_t)h * HD + c);
-    for (int j0 = g * TJ; j0 < n; j0 += NG * TJ) {
-        int64_t xoff[TJ];
-#pragma unroll
-        for (int t = 0; t < TJ; ++t) {
-            int tok = t0 + j0 + t;
-            tok = tok < t1 ? tok : t1 - 1;
-            const int64_t blk = p.block_tables[(int64_t)r * 2 * p.max_blocks + (tok >> p.log2_bs)];
-            xoff[t] = blk * blk_elems + (int64_t)(tok & (p.bs - 1)) * d;
-        }
-        float ak[TJ], av[TJ];
-#pragma unroll
-        for (int t = 0; t < TJ; ++t) { ak[t] = bk; av[t] = bv; }
-        for (int i = 0; i < d; ++i) {
-            const float wk = load_elem<DT>(p.W_K, (int64_t)i * d + (int64_t)h * HD + c);
-            const float wv = load_elem<DT>(p.W_V, (int64_t)i * d + (int64_t)h * HD + c);
-#pragma unroll
-            for (int t = 0; t < TJ; ++t) {
-                const float x = load_elem<DT>(p.hidden_pages, xoff[t] + i);
-                ak[t] = fmaf(x, wk, ak[t]);
-                av[t] = fmaf(x, wv, av[t]);
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < TJ; ++t)
-            if (j0 + t < n) { Ks[(j0 + t) * LD + c] = ak[t]; Vs[(j0 + t) * LD + c] = av[t]; }
-    }
-    __syncthreads();
-    for (int j = tid; j < n; j += kThreads) {
-        float s = 0.f;
-        for (int cc = 0; cc < HD; ++cc)
-            s = fmaf(Ks[j * LD + cc], load_elem<DT>(p.q, ((int64_t)r * p.H + h) * HD + cc), s);
-        sc[j] = s * p.scale_log2e;
-    }
-    __syncthreads();
-    if (w == 0) {
-        const float v = lane < n ? sc[lane] : kSentinel;
-        const float m = group_max<64>(v);
-        const float pw = lane < n ? fast_exp2(v - m) : 0.f;
-        const float l = group_sum<64>(pw);
-        sc[lane] = pw;
-        if (lane == 0) { red[0] = m; red[1] = l; }
-    }
-    __syncthreads();
-    if (tid < HD) {
-        float a = 0.f;
-        for (int j = 0; j < n; ++j) a = fmaf(sc[j], Vs[j * LD + tid], a);
-        const int32_t* split_count = p.plan + APT_PW_HEADER;
-        const int32_t* ws_offset = split_count + p.B;
-        const int64_t slot = ((int64_t)ws_offset[r] + t0 / p.hidden_chunk) * p.H + h;
-        p.ws_acc[slot * HD + tid] = a;
-        if (tid == 0) p.ws_ml[slot] = make_float2(red[0], red[1]);
-    }
-}
-
-// ---------------------------------------------------------------------------------
-// the items kernel, one workgroup per item.  HIMPL: 0 = no hidden-kind items in the plan,
-// 1 = plain-ALU hidden kernel.  (Plans with MFMA hidden items run apt_items_mfma_kernel.)
-// ---------------------------------------------------------------------------------
-template <int DT, int HD, int HIMPL>
 __global__ __launch_bounds__(kThreads) void apt_items_kernel(ItemParams p) {
     extern __shared__ __align__(16) char lds[];
     const int item = blockIdx.x + p.item_base;
     if (item >= p.n_items) return;
     const int4 it = ((const int4*)(p.plan + p.items_off))[item];
-    if (item < p.n_hidden_items) {
-        if constexpr (HIMPL == 1) hidden_item_valu<DT, HD>(p, it.x, it.y, it.z, it.w, lds);
-    } else {
-        kv_item<DT, HD>(p, it.x, it.y, it.z, it.w, lds);
-    }
+    kv_item<DT, HD>(p, it.x, it.y, it.z, it.w, lds);
 }
 
 // ---------------------------------------------------------------------------------
@@ -325,9 +245,9 @@ __global__ __launch_bounds__(kThreads) void apt_mfma_probe_kernel(float* out, in
 // ---------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------
-template <int DT, int HD, int HIMPL>
+template <int DT, int HD>
 int launch_items(const ItemParams& p, size_t lds_bytes, hipStream_t st) {
-    auto kern = apt_items_kernel<DT, HD, HIMPL>;
+    auto kern = apt_items_kernel<DT, HD>;
     hipLaunchKernelGGL(kern, dim3(p.n_items - p.item_base), dim3(kThreads), lds_bytes, st, p);
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
 }
@@ -341,20 +261,16 @@ int launch_items_impl(const ItemParams& p_in, int himpl, char* out, int out_dtyp
     constexpr int G = 4 * (64 / LPR);
     const size_t kv_lds = (size_t)(2 * G + G * HD) * 4;
     ItemParams p = p_in;
-    if (p.n_hidden_items == 0) return launch_items<DT, HD, 0>(p, kv_lds, st);
+    if (p.n_hidden_items == 0) return launch_items<DT, HD>(p, kv_lds, st);
     if (himpl == APT_HIDDEN_ABSORBED) {
         const int rc = launch_absorbed<DT>(p, out, out_dtype, HD, st);
         if (rc || p.n_hidden_items == p.n_items) return rc;
         p.item_base = p.n_hidden_items;          // the KV-kind items, one workgroup each
-        return launch_items<DT, HD, 0>(p, kv_lds, st);
+        return launch_items<DT, HD>(p, kv_lds, st);
     }
     if (himpl == APT_HIDDEN_VALU) {
-        if constexpr (DT == 0) {
-            size_t v = (size_t)(2 * p.hidden_chunk * (HD + 1) + 64 + 2) * 4;
-            return launch_items<DT, HD, 1>(p, v > kv_lds ? v : kv_lds, st);
-        } else {
-            return apt_launch_raw16(p, DT, HD, queue_len, st);
-        }
+        if constexpr (DT == 0) return apt_launch_raw32(p, HD, queue_len, st);
+        else return apt_launch_raw16(p, DT, HD, queue_len, st);
     }
     if constexpr (DT != 0 && HD == 128) {
         return apt_launch_mfma<DT>(p, n_wg, st);
@@ -385,7 +301,6 @@ int device_setup(const DeviceState** out) {
         ds.n_wg = cus >= 8 ? (cus / 8) * 8 : 8;
         // every kernel that can be launched with more than 64 KB of dynamic LDS
         const bool ok = apt_setup_mfma<1>() && apt_setup_mfma<2>() &&
-                        apt_raise_lds_limit(apt_items_kernel<0, 64, 1>) && apt_raise_lds_limit(apt_items_kernel<0, 128, 1>) &&
                         apt_setup_raw16() &&
                         apt_raise_lds_limit(apt_absorb_score_kernel<0>) && apt_raise_lds_limit(apt_absorb_pv_kernel<0>) &&
                         apt_raise_lds_limit(apt_absorb_score_mfma_kernel<1>) && apt_raise_lds_limit(apt_absorb_score_mfma_kernel<2>) &&
@@ -529,7 +444,7 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
         return APT_ESHAPE;
     // hidden-kind and KV-kind range lengths: the caller's, or the planner's choice for this batch where the caller left them open
     const int hidden_chunk = pw[APT_PW_HCHUNK], kv_chunk = pw[APT_PW_KCHUNK];
-    if (rs.hidden_auto ? (hidden_chunk < APT_RAW16_MIN_HIDDEN_CHUNK || hidden_chunk > rs.s.hidden_chunk) : hidden_chunk != rs.s.hidden_chunk)
+    if (rs.hidden_auto ? (hidden_chunk < APT_RAW_MIN_HIDDEN_CHUNK(rs.s.dtype) || hidden_chunk > rs.s.hidden_chunk) : hidden_chunk != rs.s.hidden_chunk)
         return APT_ESHAPE;
     if (rs.kv_auto ? (kv_chunk < rs.s.kv_chunk || kv_chunk > APT_MAX_AUTO_KV_CHUNK || !apt_kv_chunk_ok(kv_chunk, rs.s.block_size))
                    : kv_chunk != rs.s.kv_chunk)

@@ -19,3 +19,6 @@ template <> bool apt_setup_mfma<2>();
 // queue_len = longest of the eight hidden-kind queues
 int apt_launch_raw16(const ItemParams& p, int dtype, int head_dim, int queue_len, hipStream_t st);
 bool apt_setup_raw16();
+
+// apt_raw32.hip: fp32 inputs, the same
+int apt_launch_raw32(const ItemParams& p, int head_dim, int queue_len, hipStream_t st);

@@ -54,10 +54,9 @@ int apt_resolve(const apt_shape* in, apt_resolved* out) {
         if (s.hidden_chunk == 0) s.hidden_chunk = APT_ABSORBED_CHUNK;
         if (s.hidden_chunk != APT_ABSORBED_CHUNK) return APT_ESHAPE;
     } else if (s.hidden_impl == APT_HIDDEN_VALU) {
-        const bool raw16 = s.dtype != APT_F32;
-        const int most = raw16 ? APT_RAW16_MAX_HIDDEN_CHUNK(s.head_dim) : APT_MAX_VALU_HIDDEN_CHUNK;
-        out->hidden_auto = raw16 && s.hidden_chunk == 0;
-        if (s.hidden_chunk == 0) s.hidden_chunk = raw16 ? most : APT_DEFAULT_VALU_HIDDEN_CHUNK;
+        const int most = APT_RAW_MAX_HIDDEN_CHUNK(s.dtype, s.head_dim);
+        out->hidden_auto = s.hidden_chunk == 0;
+        if (s.hidden_chunk == 0) s.hidden_chunk = APT_RAW_AUTO_HIDDEN_CHUNK(s.dtype, s.head_dim);
         if (s.hidden_chunk < 1 || s.hidden_chunk > most) return APT_ESHAPE;
     } else {
         return APT_ESHAPE;
@@ -83,7 +82,7 @@ extern "C" int apt_plan_max_bytes(const apt_shape* s, int B, int max_ctx, size_t
     int rc = apt_resolve(s, &rs);
     if (rc) return rc;
     if (B < 1 || max_ctx < 1 || !bytes) return APT_EINVAL;
-    const int hmin = rs.hidden_auto ? APT_RAW16_MIN_HIDDEN_CHUNK : rs.s.hidden_chunk;
+    const int hmin = rs.hidden_auto ? APT_RAW_MIN_HIDDEN_CHUNK(rs.s.dtype) : rs.s.hidden_chunk;
     const int cmin = hmin < rs.s.kv_chunk ? hmin : rs.s.kv_chunk;
     const int64_t n_items = (int64_t)B * rs.s.n_heads * ceil_div64(max_ctx, cmin);
     *bytes = plan_words(B, n_items) * 4;
@@ -102,9 +101,9 @@ extern "C" int apt_workspace_bytes(const apt_shape* s, int max_batch, int max_ct
     const int cmin = rs.s.hidden_chunk < rs.s.kv_chunk ? rs.s.hidden_chunk : rs.s.kv_chunk;
     int64_t n_partials = (int64_t)max_batch * ceil_div64(max_ctx, cmin);
     if (rs.hidden_auto) {
-        // a range below the longest is chosen only while twice its length gives fewer than APT_RAW16_ITEMS_TARGET
+        // a range below the longest is chosen only while twice its length gives fewer than APT_RAW_ITEMS_TARGET
         // hidden-kind items, so it gives at most twice as many ranges as that; the KV-kind requests come on top
-        const int64_t few = 2 * ((int64_t)(APT_RAW16_ITEMS_TARGET - 1) / rs.s.n_heads) +
+        const int64_t few = 2 * ((int64_t)(APT_RAW_ITEMS_TARGET - 1) / rs.s.n_heads) +
                             (int64_t)max_batch * ceil_div64(max_ctx, rs.s.kv_chunk);
         if (few > n_partials) n_partials = few;
     }
@@ -133,7 +132,7 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
                 if (cache_kind[r] == APT_KIND_HIDDEN && ctx_lens[r] > 0) n += ceil_div64(ctx_lens[r], c) * H;
             return n;
         };
-        while (rs.s.hidden_chunk > APT_RAW16_MIN_HIDDEN_CHUNK && hidden_items(rs.s.hidden_chunk) < APT_RAW16_ITEMS_TARGET)
+        while (rs.s.hidden_chunk > APT_RAW_MIN_HIDDEN_CHUNK(rs.s.dtype) && hidden_items(rs.s.hidden_chunk) < APT_RAW_ITEMS_TARGET)
             rs.s.hidden_chunk /= 2;
     }
 

@@ -121,6 +121,23 @@ def test_raw_weight_matrix_kernel_at_tile_edges(oracle, dtype, hd, H, bs, chunk)
     _check(got, _full(oracle, batch, layer), f"raw16-{dtype}-hd{hd}-{chunk}", 2e-4, 2e-3)
 
 
+@pytest.mark.parametrize("hd,H,bs,chunk,want", [(64, 3, 16, 64, 64), (64, 1, 4, 32, 32), (128, 1, 16, 16, 16), (128, 3, 8, 64, 64),
+                                                 (64, 2, 16, 5, 5), (64, 4, 16, 0, 16), (128, 9, 32, 0, 16)])
+def test_raw_weight_fp32_kernel_at_fragment_edges(oracle, hd, H, bs, chunk, want):
+    """fp32 inputs: ranges of 1, 2 and 4 token fragments, lengths around their edges, d_model from 64 (fewer k blocks
+    than the prefetch depth) up, and the range length the planner picks (chunk 0)."""
+    print(f"[case] raw fp32 hd={hd} H={H} bs={bs} chunk={chunk}", flush=True)
+    lens = np.array([1, 15, 16, 17, 31, 32, 33, 48, 63, 64, 65, 130], dtype=np.int32)
+    kinds = np.array([HID] * 5 + [KV] + [HID] * 6, dtype=np.uint8)
+    cfg = wl.small_config(name="raw32", dtype="f32", d_model=hd * H, n_heads=H, head_dim=hd, block_size=bs,
+                          batch=len(lens), len_lo=1, len_hi=130, hidden_ratio=0.5)
+    batch = wl.make_batch(cfg, lens, kinds)
+    layer = wl.make_layer(batch)
+    rn, got = _run(batch, layer, hidden_chunk=chunk)
+    assert rn.info.hidden_impl == ab.APT_HIDDEN_VALU and rn.info.hidden_chunk == want
+    _check(got, _full(oracle, batch, layer), f"raw32-hd{hd}-{chunk}", 1e-5, 1e-3)
+
+
 @pytest.mark.parametrize("dtype,hd,H,bs", [("f16", 128, 4, 16), ("bf16", 128, 4, 16), ("f32", 128, 2, 16),
                                             ("f16", 64, 6, 8), ("f32", 64, 5, 4)])
 def test_absorbed_weight_hidden_path(oracle, dtype, hd, H, bs):
