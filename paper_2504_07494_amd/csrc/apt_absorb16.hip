@@ -1,0 +1,216 @@
+// Absorbed-weight hidden path, 16-bit inputs: the kernels that build the absorbed queries and the scores.
+#include "apt_device.h"
+#include "apt_launch.h"
+#include "apt_absorb_tile.h"
+
+namespace {
+
+// ---- absorbed queries: QT[hr][h][k] = scale * log2(e) * W_K[k, h] . q, as 16-bit parts in the order the score kernel
+// copies: [hr][k-tile][part * R + head][unit c at c ^ swizzle(head)], rows of KT values.
+// One wave per (head, 32 rows of W_K), all hidden-kind requests of its z-slice in turn, operands straight from memory
+// (both are 16-bit, so the products are exact).  D rows are k, columns are requests; the rows of the two W fragments are
+// dealt so that a lane ends with 8 consecutive k of one request: one 16-byte store per part, 64 contiguous bytes per
+// request.  Bound by the write of QT, R * parts * 2 bytes per k and request: 183 us for 72 heads, bf16, 96 requests at
+// d_model 9216 (425 MB; 246 us with 2-byte stores and heads padded to 128).
+constexpr int kAbQReq = 64;                              // requests per workgroup in z
+
+template <int DT, int HD, int NF>
+__global__ __launch_bounds__(kThreads) void apt_absorb_q16_kernel(ItemParams p) {
+    using C = AbTile<DT, NF>;
+    constexpr int NS = C::NS, KS = HD / 32;
+    const int lane = threadIdx.x & 63, l16 = lane & 15, qd = lane >> 4;
+    const int kb = blockIdx.x * 4 + (threadIdx.x >> 6);  // 32-row block of W_K
+    const int h = blockIdx.y;
+    if (kb * 32 >= p.d) return;
+    const int32_t* hid_req = plan_array(p, APT_PA_HID_REQ);
+    uint4 wf[2][KS];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+        const int k = kb * 32 + 8 * (l16 >> 2) + 4 * f + (l16 & 3);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) wf[f][s] = *(const uint4*)(p.W_K + ((int64_t)k * p.d + h * HD + 32 * s + 8 * qd) * 2);
+    }
+    const int k8 = kb * 4 + qd;                          // this lane's unit of 8 k
+    const int kt = k8 / (C::KT / 8), c = (k8 % (C::KT / 8)) ^ ab_swz<C::KT>(h);
+    const int hr_end = min(p.n_hid_req, (int)(blockIdx.z + 1) * kAbQReq);
+    for (int hr0 = blockIdx.z * kAbQReq; hr0 < hr_end; hr0 += 16) {
+        const int hr = min(hr0 + l16, p.n_hid_req - 1);
+        const char* qrow = p.q + ((int64_t)hid_req[hr] * p.H + h) * HD * 2;
+        uint4 qf[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qf[s] = *(const uint4*)(qrow + (32 * s + 8 * qd) * 2);
+        f32x4_t acc[2];
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[f][e] = 0.f;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) acc[f] = mfma16<DT>(wf[f][s], qf[s], acc[f]);
+        }
+        uint16_t part[8][NS];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) AbSplit<DT>::split(acc[e >> 2][e & 3] * p.scale_log2e, part[e]);
+        if (hr0 + l16 < p.n_hid_req) {
+            char* base = (char*)p.ab_qt + ((int64_t)hr * (p.d / C::KT) + kt) * C::kABytes + c * 16;
+#pragma unroll
+            for (int sp = 0; sp < NS; ++sp) *(uint4*)(base + (sp * C::R + h) * C::kRow) = ab_pack8<NS>(part, sp);
+        }
+        if (kb == 0) {                                   // CB = scale * log2(e) * q . b_K
+            float s = 0.f;
+#pragma unroll
+            for (int i = 0; i < KS; ++i) {
+                float qv[8], bv[8];
+                cvt16<DT>(qf[i], qv);
+                cvt16<DT>(*(const uint4*)(p.b_K + (h * HD + 32 * i + 8 * qd) * 2), bv);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s = fmaf(qv[e], bv[e], s);
+            }
+            s += __shfl_xor(s, 16);
+            s += __shfl_xor(s, 32);
+            if (qd == 0 && hr0 + l16 < p.n_hid_req) p.ab_cb[(int64_t)hr * p.H + h] = s * p.scale_log2e;
+        }
+    }
+}
+
+// ---- score partials: SP[slice][h][token] = <x_token, QT> over one slice of d_model
+// Workgroup = 256 tokens x one slice x all heads, eight waves: wave w takes tokens 64 (w % 4) .. + 63 and the first
+// (w < 4) or the second half of the head fragments, so that each SIMD has two waves, one of either half, and one's LDS
+// reads are covered by the other's MFMAs.  D rows are heads, columns tokens; the parts of a head are summed in one
+// accumulator.  k-tiles of X rows and of QT go global -> LDS without registers, as many stages as LDS holds (one
+// workgroup per CU).
+//
+// Bound by how memory serves the X rows, one 128-byte line per row and k-tile (rows lie 2 d_model apart): 64-wide k-tiles
+// in three stages take 87 us for 40 heads, fp16, 33.6 k tokens at d_model 5120 (344 MB of X), 32-wide ones in seven
+// stages, with more bytes in flight, 99 us.  The version with heads padded to 64, an accumulator per part and 512-wide
+// slices took 117 us there, and 1193 us against 594 us now for 72 heads, bf16, 102 k tokens at d_model 9216.
+template <int DT, int NF, int F0, int FN, typename Issue>
+__device__ __forceinline__ void score_loop(f32x4_t (*acc)[4], uint32_t lds0, int tg, int nkt, Issue issue) {
+    using C = AbTile<DT, NF>;
+    constexpr int NS = C::NS, KT = C::KT, S = C::S;
+    const int lane = threadIdx.x & 63, l16 = lane & 15, qd = lane >> 4;
+    int stage = 0;
+    for (int kt = 0; kt < nkt; ++kt) {
+        if (kt + S - 2 < nkt) wait_vmcnt<(S - 2) * C::kCopies>();
+        else wait_vmcnt<0>();
+        __syncthreads();            // k-tile kt has landed for every wave; nobody still reads the stage refilled next
+        if (kt + S - 1 < nkt) issue(kt + S - 1);
+        const uint32_t st = lds0 + stage * C::kStage;
+#pragma unroll
+        for (int ks = 0; ks < KT / 32; ++ks) {
+            const uint32_t off = (((4 * ks + qd) ^ ab_swz<KT>(l16)) << 4) + l16 * C::kRow;
+            uint4 x[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) x[t] = lds_read16(st + (64 * tg + 16 * t) * C::kRow + off);
+#pragma unroll
+            for (int f = 0; f < FN; ++f)
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    const uint4 a = lds_read16(st + C::kXBytes + (s * C::R + 16 * (F0 + f)) * C::kRow + off);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) acc[f][t] = mfma16<DT>(a, x[t], acc[f][t]);
+                }
+        }
+        stage = stage == S - 1 ? 0 : stage + 1;
+    }
+}
+
+template <int DT, int NF>
+__global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemParams p) {
+    using C = AbTile<DT, NF>;
+    constexpr int KT = C::KT, S = C::S, NF0 = C::NF0;
+    constexpr int RPC = 1024 / C::kRow;                  // rows per 1 KB copy
+    constexpr int UPR = KT / 8;                          // 16-byte units per row
+    extern __shared__ __align__(16) char lds[];
+    const int lane = threadIdx.x & 63, l16 = lane & 15, qd = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = w & 3, second = w >> 2;
+    // A group = eight neighbouring tiles, one slice: they share that slice of their requests' absorbed queries, so a
+    // group stays on one XCD (workgroup g runs on XCD g % 8); groups are dealt to the XCDs in turn
+    const int slot = blockIdx.x >> 3, group = (slot >> 3) * 8 + (blockIdx.x & 7);
+    const int ti = (group / p.ab_ks) * 8 + (slot & 7), slice = group % p.ab_ks;
+    if (ti >= p.ab_tiles) return;
+    const int tile = p.plan[p.ab_tiles_off + ti], range = tile >> 1;
+    const int4 it = ((const int4*)(p.plan + p.items_off))[range];
+    const int r = it.x, t1 = it.w, tb = it.z + kAbMT * (tile & 1);
+    const int hr = plan_array(p, APT_PA_HID_INDEX)[r];
+    const int64_t tok0 = (int64_t)plan_array(p, APT_PA_HID_TOK_OFF)[r] + tb;
+    const int n_kt = p.d / KT, kt0 = slice * n_kt / p.ab_ks, nkt = (slice + 1) * n_kt / p.ab_ks - kt0, k_begin = kt0 * KT;
+
+    const char* xsrc[C::kXCopies];
+#pragma unroll
+    for (int i = 0; i < C::kXCopies; ++i) {
+        const int row = RPC * (C::kXCopies * w + i) + lane / UPR;   // rows past the range repeat its last token (scores not stored)
+        xsrc[i] = hidden_row(p, r, min(tb + row, t1 - 1), 2) + (int64_t)k_begin * 2 + (((lane % UPR) ^ ab_swz<KT>(row)) << 4);
+    }
+    const char* asrc = (const char*)p.ab_qt + ((int64_t)hr * n_kt + kt0) * C::kABytes + lane * 16;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+    auto issue = [&](int kt) {
+        const uint32_t st = lds0 + (kt % S) * C::kStage;
+#pragma unroll
+        for (int i = 0; i < C::kXCopies; ++i) gload_lds16(xsrc[i] + kt * C::kRow, st + (C::kXCopies * w + i) * 1024);
+#pragma unroll
+        for (int i = 0; i < C::kACopies; ++i) {          // some waves copy the last chunk again (same bytes)
+            const int n = min(w + kAbWaves * i, C::kABytes / 1024 - 1);
+            gload_lds16(asrc + (int64_t)kt * C::kABytes + n * 1024, st + C::kXBytes + n * 1024);
+        }
+    };
+    f32x4_t acc[NF0][4];
+#pragma unroll
+    for (int f = 0; f < NF0; ++f)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[f][t][e] = 0.f;
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s)
+        if (s < nkt) issue(s);
+    if (!second) score_loop<DT, NF, 0, NF0>(acc, lds0, tg, nkt, issue);
+    else score_loop<DT, NF, NF0, NF - NF0>(acc, lds0, tg, nkt, issue);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int token = 64 * tg + 16 * t + l16;
+        if (tb + token >= t1) continue;
+#pragma unroll
+        for (int f = 0; f < NF0; ++f)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int h = 16 * (second * NF0 + f) + 4 * qd + e;
+                if ((f < NF - NF0 || !second) && h < p.H)
+                    p.ab_s[((int64_t)slice * p.H + h) * p.ab_tokens + tok0 + token] = acc[f][t][e];
+            }
+    }
+}
+
+template <int DT, int NF> int launch_scores(const ItemParams& p, int head_dim, hipStream_t st) {
+    using C = AbTile<DT, NF>;
+    const dim3 qgrid((p.d / 32 + 3) / 4, p.H, (p.n_hid_req + kAbQReq - 1) / kAbQReq);
+    if (head_dim == 128) hipLaunchKernelGGL((apt_absorb_q16_kernel<DT, 128, NF>), qgrid, dim3(kThreads), 0, st, p);
+    else hipLaunchKernelGGL((apt_absorb_q16_kernel<DT, 64, NF>), qgrid, dim3(kThreads), 0, st, p);
+    const unsigned groups = (unsigned)((p.ab_tiles + 7) / 8 * p.ab_ks);
+    hipLaunchKernelGGL((apt_absorb_score16_kernel<DT, NF>), dim3((groups + 7) / 8 * 64), dim3(kAbWaves * 64), C::S * C::kStage, st, p);
+    return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
+}
+
+template <int DT> int launch_scores_nf(const ItemParams& p, int head_dim, hipStream_t st) {
+    switch (ab_head_frags(p.H)) {
+    case 2: return launch_scores<DT, 2>(p, head_dim, st);
+    case 3: return launch_scores<DT, 3>(p, head_dim, st);
+    case 4: return launch_scores<DT, 4>(p, head_dim, st);
+    case 5: return launch_scores<DT, 5>(p, head_dim, st);
+    case 6: return launch_scores<DT, 6>(p, head_dim, st);
+    default: return launch_scores<DT, 8>(p, head_dim, st);
+    }
+}
+
+template <int DT> bool setup() {
+    return apt_raise_lds_limit(apt_absorb_score16_kernel<DT, 2>) && apt_raise_lds_limit(apt_absorb_score16_kernel<DT, 3>) &&
+           apt_raise_lds_limit(apt_absorb_score16_kernel<DT, 4>) && apt_raise_lds_limit(apt_absorb_score16_kernel<DT, 5>) &&
+           apt_raise_lds_limit(apt_absorb_score16_kernel<DT, 6>) && apt_raise_lds_limit(apt_absorb_score16_kernel<DT, 8>);
+}
+
+}  // namespace
+
+int apt_launch_absorb_scores16(const ItemParams& p, int dtype, int head_dim, hipStream_t st) {
+    return dtype == APT_F16 ? launch_scores_nf<1>(p, head_dim, st) : launch_scores_nf<2>(p, head_dim, st);
+}
+
+bool apt_setup_absorb_scores16() { return setup<1>() && setup<2>(); }

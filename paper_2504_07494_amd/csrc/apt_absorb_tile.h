@@ -1,0 +1,88 @@
+// What the kernels of the absorbed-weight hidden path share: plan lookups, the split of fp32 operands into 16-bit parts,
+// and (16-bit inputs) the tiles of the score and weighted-sum kernels.
+#pragma once
+#include "apt_device.h"
+
+namespace {
+
+__device__ inline const int32_t* plan_array(const ItemParams& p, int which) {
+    return p.plan + APT_PW_HEADER + (int64_t)which * p.B;
+}
+
+// address of the cached hidden row of a token
+__device__ inline const char* hidden_row(const ItemParams& p, int r, int token, int eb) {
+    const int32_t blk = p.block_tables[(int64_t)r * 2 * p.max_blocks + (token >> p.log2_bs)];
+    return p.hidden_pages + ((int64_t)blk * p.bs + (token & (p.bs - 1))) * p.d * eb;
+}
+
+// fp32 -> 16-bit parts for the matrix cores: fp16 hi + lo (22 bits), bf16 hi + mid + lo (24 bits).
+// The products of the parts with 16-bit inputs are exact in the fp32 accumulator.
+template <int DT> struct AbSplit;
+template <> struct AbSplit<1> {
+    static constexpr int parts = 2;
+    __device__ static inline void split(float v, uint16_t* out) {
+        const _Float16 hi = (_Float16)v;
+        const _Float16 lo = (_Float16)(v - (float)hi);
+        out[0] = __builtin_bit_cast(uint16_t, hi);
+        out[1] = __builtin_bit_cast(uint16_t, lo);
+    }
+};
+template <> struct AbSplit<2> {
+    static constexpr int parts = 3;
+    __device__ static inline void split(float v, uint16_t* out) {
+        out[0] = f32_to_bf16_rne(v);
+        const float r1 = v - bf16_to_f32(out[0]);
+        out[1] = f32_to_bf16_rne(r1);
+        out[2] = f32_to_bf16_rne(r1 - bf16_to_f32(out[1]));
+    }
+};
+// part sp of eight split values as one 16-byte unit
+template <int NS> __device__ inline uint4 ab_pack8(const uint16_t (*part)[NS], int sp) {
+    return make_uint4(part[0][sp] | ((uint32_t)part[1][sp] << 16), part[2][sp] | ((uint32_t)part[3][sp] << 16),
+                      part[4][sp] | ((uint32_t)part[5][sp] << 16), part[6][sp] | ((uint32_t)part[7][sp] << 16));
+}
+
+constexpr int kAbMT = 256;                                // tokens (score) / columns (weighted sum) per workgroup
+
+constexpr int kAbWaves = 8;                               // waves of such a workgroup
+
+// Workgroup g of a 1-D launch runs on XCD g % 8.  Work unit of workgroup g when every XCD is to walk a
+// contiguous eighth of the units in order (units that share operands are then neighbours in time on
+// one XCD and meet in its L2); -1 if the workgroup has nothing to do.  The grid holds 8 * ceil(total / 8).
+__device__ inline int xcd_contiguous_unit(int total) {
+    const int per = (total + 7) >> 3;
+    const int xcd = (int)(blockIdx.x & 7), slot = (int)(blockIdx.x >> 3);
+    const int unit = xcd * per + slot;
+    return slot < per && unit < total ? unit : -1;
+}
+
+// Operand fragments of 16 heads the kernels are built for; heads are padded to 16 * this many rows per part (padded
+// rows hold anything: they only reach outputs that are not stored).  An instantiation per count keeps padding and
+// registers small: 72 heads are 5 fragments, not the 8 of a multiple of 64.
+static inline int ab_head_frags(int H) {
+    const int nf = (H + 15) / 16;
+    return nf < 2 ? 2 : nf == 7 ? 8 : nf;
+}
+
+// LDS tile of KT values of k per row: the fp32 operand as NS parts of R = 16 NF rows, and 256 rows of X.  KT = 64 (whole
+// 128-byte lines of X per row) where three stages fit, else 32.
+template <int DT, int NF> struct AbTile {
+    static constexpr int NS = AbSplit<DT>::parts;
+    static constexpr int R = 16 * NF;
+    static constexpr int kLdsMost = 158 * 1024;
+    static constexpr int KT = 3 * (kAbMT + R * NS) * 128 <= kLdsMost ? 64 : 32;
+    static constexpr int kRow = KT * 2;
+    static constexpr int kABytes = R * NS * kRow;
+    static constexpr int kXBytes = kAbMT * kRow;
+    static constexpr int kStage = kABytes + kXBytes;
+    static constexpr int S = kLdsMost / kStage < 7 ? kLdsMost / kStage : 7;
+    static constexpr int kXCopies = kXBytes / 1024 / kAbWaves;    // 1 KB copies per wave and k-tile
+    static constexpr int kACopies = (kABytes / 1024 + kAbWaves - 1) / kAbWaves;
+    static constexpr int NF0 = (NF + 1) / 2;                    // head fragments of waves 0..3; waves 4..7 take the rest
+    static constexpr int kCopies = kXCopies + kACopies;
+    static_assert(S >= 3 && (S - 2) * kCopies <= 63, "stages / vmcnt range");
+};
+// unit c of a row sits at c ^ ab_swz(row): the 16-row operand reads are free of bank conflicts
+template <int KT> __host__ __device__ inline int ab_swz(int row) { return (row >> 1) & (KT / 8 - 1); }
+
+}  // namespace

@@ -34,6 +34,8 @@ struct ItemParams {
     void* ab_pp;                  // 16-bit inputs: softmax weights as 16-bit parts, [16 n_hidden_items][parts * 64][32]
     int64_t ab_tokens;            // cached tokens of all hidden-kind requests
     int32_t n_hid_req;
+    int32_t ab_ks;                // slices of d_model in the score partials
+    int32_t ab_tiles, ab_tiles_off;   // 256-token tiles of all hidden-kind requests, their place in the plan
 };
 
 namespace {

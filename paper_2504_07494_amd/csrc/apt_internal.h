@@ -28,6 +28,7 @@ enum {
     APT_PW_MAX_BLOCKS = 28,
     APT_PW_DTYPE = 29,
     APT_PW_NHIDREQ = 30,    // number of hidden-kind requests
+    APT_PW_TILES_OFF = 31,  // absorbed-weight path: word offset of the tiles (up to the end of the blob), else 0
     APT_PW_HEADER = 32
 };
 #define APT_N_QUEUES 8
@@ -57,6 +58,7 @@ enum {
 #define APT_ABSORBED_HEAD_GROUPS 4       // absorbed-weight kernels: threads of a workgroup = 64 x 4 (token or column
 #define APT_ABSORBED_HEADS_PER_THREAD 10 // group, head group), 8 tokens/columns x 10 heads per thread
 #define APT_ABSORBED_CHUNK 512           // = 64 groups x 8 tokens
+#define APT_ABSORBED_TILE 256            // tokens of a tile of the 16-bit score kernel: one or two tiles per range
 #define APT_ABSORBED_OUT_ROWS 256        // d_model rows per partial of the output projection
 
 // per-request arrays of the plan blob, each B words, starting at APT_PW_HEADER

@@ -17,6 +17,7 @@
 #include "apt_device.h"
 #include "apt_hybrid_bench.h"
 #include "apt_launch.h"
+#include "apt_absorb_tile.h"
 
 // Workspace of apt_hybrid_decode_attn_static: one copy per device, held until the process ends.  In host code this
 // name is only a handle for hipGetSymbolAddress; the device address is looked up once per device (device_setup).
@@ -303,7 +304,7 @@ int device_setup(const DeviceState** out) {
         const bool ok = apt_setup_mfma<1>() && apt_setup_mfma<2>() &&
                         apt_setup_raw16() &&
                         apt_raise_lds_limit(apt_absorb_score_kernel<0>) && apt_raise_lds_limit(apt_absorb_pv_kernel<0>) &&
-                        apt_raise_lds_limit(apt_absorb_score_mfma_kernel<1>) && apt_raise_lds_limit(apt_absorb_score_mfma_kernel<2>) &&
+                        apt_setup_absorb_scores16() &&
                         apt_raise_lds_limit(apt_absorb_pv_mfma_kernel<1>) && apt_raise_lds_limit(apt_absorb_pv_mfma_kernel<2>);
         if (!ok) return APT_EHIP;
         void* ptr = nullptr;
@@ -499,6 +500,9 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     p.ab_tokens = hidden_tokens;
     p.n_hid_req = pw[APT_PW_NHIDREQ];
     p.item_base = 0;
+    p.ab_ks = 0;
+    p.ab_tiles_off = pw[APT_PW_TILES_OFF];
+    p.ab_tiles = p.ab_tiles_off ? pw[APT_PW_WORDS] - p.ab_tiles_off : 0;
     p.B = B; p.H = rs.s.n_heads; p.d = rs.s.d_model; p.bs = rs.s.block_size; p.log2_bs = log2_bs;
     p.max_blocks = rs.s.max_blocks_per_req;
     p.n_items = n_items; p.n_hidden_items = n_hidden;

@@ -22,3 +22,7 @@ bool apt_setup_raw16();
 
 // apt_raw32.hip: fp32 inputs, the same
 int apt_launch_raw32(const ItemParams& p, int head_dim, int queue_len, hipStream_t st);
+
+// apt_absorb16.hip: absorbed-weight path, 16-bit inputs
+int apt_launch_absorb_scores16(const ItemParams& p, int dtype, int head_dim, hipStream_t st);
+bool apt_setup_absorb_scores16();

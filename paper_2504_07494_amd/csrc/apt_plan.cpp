@@ -71,11 +71,11 @@ int apt_resolve(const apt_shape* in, apt_resolved* out) {
 
 static int64_t ceil_div64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-static size_t plan_words(int B, int64_t n_items) {
-    size_t w = APT_PW_HEADER + APT_PA_COUNT * (size_t)B;
-    w = (w + 3) & ~(size_t)3;
-    return w + 4 * (size_t)n_items;
+static size_t plan_items_off(int B) {
+    const size_t w = APT_PW_HEADER + APT_PA_COUNT * (size_t)B;
+    return (w + 3) & ~(size_t)3;
 }
+static size_t plan_words(int B, int64_t n_items, int64_t n_tiles) { return plan_items_off(B) + 4 * (size_t)n_items + (size_t)n_tiles; }
 
 extern "C" int apt_plan_max_bytes(const apt_shape* s, int B, int max_ctx, size_t* bytes) {
     apt_resolved rs;
@@ -85,7 +85,8 @@ extern "C" int apt_plan_max_bytes(const apt_shape* s, int B, int max_ctx, size_t
     const int hmin = rs.hidden_auto ? APT_RAW_MIN_HIDDEN_CHUNK(rs.s.dtype) : rs.s.hidden_chunk;
     const int cmin = hmin < rs.s.kv_chunk ? hmin : rs.s.kv_chunk;
     const int64_t n_items = (int64_t)B * rs.s.n_heads * ceil_div64(max_ctx, cmin);
-    *bytes = plan_words(B, n_items) * 4;
+    const int64_t n_tiles = rs.s.hidden_impl == APT_HIDDEN_ABSORBED ? (int64_t)B * ceil_div64(max_ctx, APT_ABSORBED_TILE) : 0;
+    *bytes = plan_words(B, n_items, n_tiles) * 4;
     return APT_OK;
 }
 
@@ -150,7 +151,7 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
 
     // pass 1: validate and count
     const bool absorbed = rs.s.hidden_impl == APT_HIDDEN_ABSORBED;
-    int64_t n_partials = 0, n_hidden_items = 0, n_items = 0, tok = 0, htok = 0, n_hid_req = 0;
+    int64_t n_partials = 0, n_hidden_items = 0, n_items = 0, tok = 0, htok = 0, n_hid_req = 0, n_tiles = 0;
     for (int r = 0; r < B; ++r) {
         const int n = ctx_lens[r];
         if (n < 1) return APT_EINVAL;
@@ -161,15 +162,15 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
         const int64_t per_range = (hid && absorbed) ? 1 : H;      // absorbed: one item serves all heads
         n_partials += sp;
         n_items += sp * per_range;
-        if (hid) { n_hidden_items += sp * per_range; htok += n; ++n_hid_req; }
+        if (hid) { n_hidden_items += sp * per_range; htok += n; ++n_hid_req; if (absorbed) n_tiles += ceil_div64(n, APT_ABSORBED_TILE); }
         tok += n;
     }
     if (n_items > 0x7fffffff || n_partials * (int64_t)H > 0x7fffffff || htok > 0x7fffffff) return APT_ERANGE;
-    const size_t words = plan_words(B, n_items);
+    const size_t words = plan_words(B, n_items, n_tiles);
     if (plan_bytes < words * 4) return APT_EWORKSPACE;
 
     int32_t* w = (int32_t*)plan_host;
-    const size_t items_off = words - 4 * (size_t)n_items;
+    const size_t items_off = plan_items_off(B);
     memset(w, 0, items_off * 4);
     w[APT_PW_MAGIC] = APT_PLAN_MAGIC;
     w[APT_PW_BATCH] = B;
@@ -192,6 +193,7 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
     w[APT_PW_MAX_BLOCKS] = rs.s.max_blocks_per_req;
     w[APT_PW_DTYPE] = rs.s.dtype;
     w[APT_PW_NHIDREQ] = (int32_t)n_hid_req;
+    w[APT_PW_TILES_OFF] = absorbed ? (int32_t)(items_off + 4 * (size_t)n_items) : 0;
 
     int32_t* split_count = w + APT_PW_HEADER + APT_PA_SPLIT_COUNT * B;
     int32_t* ws_offset = w + APT_PW_HEADER + APT_PA_WS_OFFSET * B;
@@ -263,6 +265,10 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
     }
     w[APT_PW_QUEUE0 + APT_N_QUEUES] = (int32_t)((it - it0) / 4);
     emit_kind(APT_KIND_KV, rs.s.kv_chunk, 0, 1);
+    // absorbed-weight path: the 256-token tiles of the hidden-kind ranges in their order, 2 * item + half
+    if (absorbed)
+        for (int32_t i = 0, *tile = w + w[APT_PW_TILES_OFF]; i < (int32_t)n_hidden_items; ++i)
+            for (int half = 0; half * APT_ABSORBED_TILE < it0[4 * i + 3] - it0[4 * i + 2]; ++half) *tile++ = 2 * i + half;
     if (info) return apt_plan_get_info(plan_host, info);
     return APT_OK;
 }

@@ -166,6 +166,23 @@ def test_absorbed_path_more_than_64_heads(oracle, dtype):
     _check(got, _full(oracle, batch, layer), f"absorbed-66-{dtype}", 2e-4, 2e-3)
 
 
+@pytest.mark.parametrize("dtype,H", [("f16", 33), ("bf16", 48), ("f16", 64), ("bf16", 80), ("f16", 81), ("bf16", 97), ("f16", 128)])
+def test_absorbed_path_head_fragment_counts(oracle, dtype, H):
+    """One head count per instantiation of the 16-bit kernels (3, 4, 5, 6 and 8 fragments of 16 heads), some of them
+    filling their last fragment and some not; tiles of 256 tokens with ragged ends.  First, last and fragment-edge heads
+    of every request against the oracle."""
+    print(f"[case] absorbed {H} heads {dtype}", flush=True)
+    cfg = wl.small_config(name="absorbedH", dtype=dtype, d_model=H * 64, n_heads=H, head_dim=64, block_size=16,
+                          batch=5, len_lo=1, len_hi=600, hidden_ratio=0.5)
+    batch = wl.make_batch(cfg, np.array([256, 1, 257, 40, 600], dtype=np.int32), np.array([HID, HID, HID, KV, HID], dtype=np.uint8))
+    layer = wl.make_layer(batch)
+    _, got = _run(batch, layer, hidden_impl=ab.APT_HIDDEN_ABSORBED)
+    pairs = [(r, h) for r in range(batch.B) for h in sorted({0, 15, 16, H // 2, H - 1})]
+    want = oracle_attn(oracle, batch, layer, pairs=pairs).reshape(len(pairs), 64)
+    _check(np.stack([got[r, h] for r, h in pairs]), want, f"absorbed-{H}-{dtype}", 2e-4, 2e-3)
+    assert np.all(np.isfinite(got))
+
+
 def test_absorbed_path_requests_longer_than_2048_tokens(oracle):
     # more than 256 runs of 8 tokens per (request, head): the statistics kernel's second and third pass
     print("[case] absorbed long requests", flush=True)
