@@ -177,8 +177,10 @@ int apt_plan_max_bytes(const apt_shape* s, int B, int max_ctx, size_t* bytes);
  *                     then ws_offset[B] and six more per-request arrays of B words (cache
  *                     kind, length; index, first token and first range among the hidden-kind
  *                     requests; the list of hidden-kind requests), then (padded to a multiple of 4 words)
- *                     items[n_items][4] = (request, head, t0, t1), and with APT_HIDDEN_ABSORBED the
- *                     256-token tiles of the hidden-kind items, one word each: 2 * item + half
+ *                     items[n_items][4] = (request, head, t0, t1), and with APT_HIDDEN_ABSORBED two
+ *                     counts (256-token tiles of the hidden-kind items; ranges per unit of the weighted
+ *                     sums), the tiles, one word each: 2 * item + half, and the units, one word each: the
+ *                     item of their first range, longest first
  *   info            optional, receives the counts and the workspace size
  * The rule: a request of n tokens is cut into ceil(n/C) ranges [s*C, min(n,(s+1)*C)),
  * C = hidden_chunk or kv_chunk by kind; ws_offset is the exclusive prefix sum of

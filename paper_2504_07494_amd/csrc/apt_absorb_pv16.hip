@@ -1,0 +1,181 @@
+// Absorbed-weight hidden path, 16-bit inputs: the weighted sums of the cached rows.
+#include "apt_device.h"
+#include "apt_launch.h"
+#include "apt_absorb_tile.h"
+
+namespace {
+
+// YP[range][h][:] = sum_j 2^(s_j - m) x_j over the ranges of one unit (one to four 512-token ranges of a request, listed
+// in the plan; the result lies at the unit's first range).
+//
+// Workgroup = one unit x CW columns x all heads, eight waves, a wave owns CW / 8 columns.  D rows are columns of x, D
+// columns are heads, k = tokens on v_mfma_f32_16x16x32; the 16-bit parts of a weight are summed in one accumulator.
+// k-tiles of 32 tokens go global -> LDS without registers, as many stages as LDS holds: X rows as they lie (1 KB or 512
+// contiguous bytes of a row; read with the transposing LDS read, which gives a lane the four tokens of one column, the
+// 32-byte units of a row at u ^ wswz(token) so that its four rows fall on different banks) and the weight parts in the
+// order the statistics kernel wrote them.
+//
+// Bound by memory and the matrix pipes together (X once, and NS parts of every head per column).  512 columns halve the
+// weight bytes an X byte brings along; 256 are for shapes whose stages do not fit and for batches that would leave CUs
+// without a unit.
+//
+// 72 heads, bf16, 96 requests with 102 k tokens at d_model 9216 (1.9 GB of X): 480-520 us, 1200 us with heads padded to 128
+// in two passes over X, a 16-bit gather per operand and sums per 512-token range.  40 heads, fp16, 33.6 k tokens at
+// d_model 5120 (344 MB): 83 us on both sides, memory.
+template <int DT, int NF, int CW> struct PvTile {
+    static constexpr int NS = AbSplit<DT>::parts;
+    static constexpr int R = 16 * NF;
+    static constexpr int kRow = CW * 2;
+    static constexpr int kXBytes = 32 * kRow;
+    static constexpr int kPBytes = R * NS * 64;
+    static constexpr int kStage = kXBytes + kPBytes;
+    static constexpr int kLdsMost = 156 * 1024;
+    static constexpr int S = kLdsMost / kStage < 6 ? kLdsMost / kStage : 6;
+    static constexpr int kXCopies = kXBytes / 1024 / kAbWaves;     // 1 KB copies per wave and k-tile
+    static constexpr int kPCopies = (kPBytes / 1024 + kAbWaves - 1) / kAbWaves;
+    static constexpr int kCopies = kXCopies + kPCopies;
+    static constexpr int CF = CW / kAbWaves / 16;                  // column fragments of a wave
+    static constexpr bool kFits = S >= 3;
+    static_assert((S - 2) * kCopies <= 63, "vmcnt range");
+};
+constexpr int kPvBlkBytes = APT_ABSORBED_MAX_GROUP * APT_ABSORBED_CHUNK / 4 * 4;      // block ids of a unit, blocks of 4 tokens at least
+
+template <int DT, int NF, int CW>
+__global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_pv16_kernel(ItemParams p, int n_cslices) {
+    using C = PvTile<DT, NF, CW>;
+    constexpr int NS = C::NS, S = C::S, CF = C::CF;
+    constexpr int RPC = 1024 / C::kRow;                  // rows per 1 KB copy
+    extern __shared__ __align__(16) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, qd = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // longest units first, the column slices of a unit side by side (dealt over the XCDs, which balances them; each XCD
+    // then reads the weights of every unit once, a small part of what it reads of X)
+    const int c0 = (int)(blockIdx.x % n_cslices) * CW;
+    const int range = p.plan[p.ab_units_off + blockIdx.x / n_cslices];
+    const int4 it = ((const int4*)(p.plan + p.items_off))[range];
+    const int r = it.x, t0 = it.z;
+    const int len = min(plan_array(p, APT_PA_CTX_LEN)[r] - t0, p.ab_group * kAbTok);
+    const int nkt = (len + 31) >> 5;
+    int32_t* blk = (int32_t*)(lds + S * C::kStage);
+    const int nblk = (len + p.bs - 1) >> p.log2_bs;
+    for (int i = tid; i < nblk; i += kAbWaves * 64)
+        blk[i] = p.block_tables[(int64_t)r * 2 * p.max_blocks + (t0 >> p.log2_bs) + i];
+    __syncthreads();
+
+    const char* psrc = (const char*)p.ab_pp + ((int64_t)plan_array(p, APT_PA_HID_CHUNK_OFF)[r] * (kAbTok / 32) + (t0 >> 5)) * C::kPBytes + lane * 16;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+    int row_of[C::kXCopies], col_of[C::kXCopies];        // row of the k-tile and byte offset in a token row this lane copies
+#pragma unroll
+    for (int i = 0; i < C::kXCopies; ++i) {
+        const int at = lane * 16 % C::kRow;
+        row_of[i] = RPC * (C::kXCopies * w + i) + lane * 16 / C::kRow;
+        // columns past d_model repeat the last eight (never stored)
+        col_of[i] = min(c0 + ((at >> 5) ^ wswz(row_of[i])) * 16 + ((at >> 4) & 1) * 8, p.d - 8) * 2;
+    }
+    auto issue = [&](int kt) {
+        const uint32_t st = lds0 + (kt % S) * C::kStage;
+#pragma unroll
+        for (int i = 0; i < C::kXCopies; ++i) {
+            const int rel = min(kt * 32 + row_of[i], len - 1);     // rows past the range repeat its last token (their weights are zero)
+            const char* src = p.hidden_pages + ((int64_t)blk[rel >> p.log2_bs] * p.bs + (rel & (p.bs - 1))) * p.d * 2 + col_of[i];
+            gload_lds16(src, st + (C::kXCopies * w + i) * 1024);
+        }
+#pragma unroll
+        for (int i = 0; i < C::kPCopies; ++i) {          // some waves copy the last chunk again (same bytes)
+            const int n = min(w + kAbWaves * i, C::kPBytes / 1024 - 1);
+            gload_lds16(psrc + (int64_t)kt * C::kPBytes + n * 1024, st + C::kXBytes + n * 1024);
+        }
+    };
+    uint32_t xaddr[CF];
+#pragma unroll
+    for (int c = 0; c < CF; ++c) {
+        const int k = 8 * qd + (l16 >> 2);
+        xaddr[c] = lds0 + k * C::kRow + (((w * CF + c) ^ wswz(k)) << 5) + (l16 & 3) * 8;
+    }
+    const uint32_t paddr = lds0 + C::kXBytes + l16 * 64 + ((qd ^ ab_swz<32>(l16)) << 4);
+    f32x4_t acc[NF][CF], sum[NF][CF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int c = 0; c < CF; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[f][c][e] = sum[f][c][e] = 0.f;
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s)
+        if (s < nkt) issue(s);
+    int stage = 0;
+    for (int kt = 0; kt < nkt; ++kt) {
+        if (kt + S - 2 < nkt) wait_vmcnt<(S - 2) * C::kCopies>();
+        else wait_vmcnt<0>();
+        __syncthreads();            // k-tile kt has landed for every wave; nobody still reads the stage refilled next
+        if (kt + S - 1 < nkt) issue(kt + S - 1);
+        const uint32_t so = stage * C::kStage;
+        uint4 xf[CF];
+#pragma unroll
+        for (int c = 0; c < CF; ++c) {
+            const uint2 lo = lds_read_tr(xaddr[c] + so), hi = lds_read_tr(xaddr[c] + so + 4 * C::kRow);
+            xf[c] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        }
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const uint4 pf = lds_read16(paddr + so + (s * C::R + 16 * f) * 64);
+#pragma unroll
+                for (int c = 0; c < CF; ++c) acc[f][c] = mfma16<DT>(xf[c], pf, acc[f][c]);
+            }
+        stage = stage == S - 1 ? 0 : stage + 1;
+        if ((kt + 1) % (kAbFold / 32) == 0) ab_fold<CF>(acc, sum, NF);
+    }
+    ab_fold<CF>(acc, sum, NF);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        const int h = 16 * f + l16;
+        if (h >= p.H) continue;
+        float* y = p.ab_yp + ((int64_t)range * p.H + h) * p.d;
+#pragma unroll
+        for (int c = 0; c < CF; ++c) {
+            const int col = c0 + 16 * (w * CF + c) + 4 * qd;
+            if (col < p.d) *(f32x4_t*)(y + col) = sum[f][c];
+        }
+    }
+}
+
+template <int DT, int NF, int CW> int launch_cw(const ItemParams& p, hipStream_t st) {
+    using C = PvTile<DT, NF, CW>;
+    const int n_cslices = (p.d + CW - 1) / CW;
+    hipLaunchKernelGGL((apt_absorb_pv16_kernel<DT, NF, CW>), dim3((unsigned)(p.ab_units * n_cslices)), dim3(kAbWaves * 64),
+                       C::S * C::kStage + kPvBlkBytes, st, p, n_cslices);
+    return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
+}
+template <int DT, int NF> int launch_nf(const ItemParams& p, int n_cus, hipStream_t st) {
+    if constexpr (PvTile<DT, NF, 512>::kFits)
+        if ((int64_t)p.ab_units * ((p.d + 511) / 512) >= n_cus) return launch_cw<DT, NF, 512>(p, st);
+    return launch_cw<DT, NF, 256>(p, st);
+}
+template <int DT> int launch(const ItemParams& p, int n_cus, hipStream_t st) {
+    switch (ab_head_frags(p.H)) {
+    case 2: return launch_nf<DT, 2>(p, n_cus, st);
+    case 3: return launch_nf<DT, 3>(p, n_cus, st);
+    case 4: return launch_nf<DT, 4>(p, n_cus, st);
+    case 5: return launch_nf<DT, 5>(p, n_cus, st);
+    case 6: return launch_nf<DT, 6>(p, n_cus, st);
+    default: return launch_nf<DT, 8>(p, n_cus, st);
+    }
+}
+template <int DT, int NF> bool setup_nf() {
+    if constexpr (PvTile<DT, NF, 512>::kFits)
+        if (!apt_raise_lds_limit(apt_absorb_pv16_kernel<DT, NF, 512>)) return false;
+    return apt_raise_lds_limit(apt_absorb_pv16_kernel<DT, NF, 256>);
+}
+template <int DT> bool setup() {
+    return setup_nf<DT, 2>() && setup_nf<DT, 3>() && setup_nf<DT, 4>() && setup_nf<DT, 5>() && setup_nf<DT, 6>() && setup_nf<DT, 8>();
+}
+
+}  // namespace
+
+int apt_launch_absorb_pv16(const ItemParams& p, int dtype, int n_cus, hipStream_t st) {
+    return dtype == APT_F16 ? launch<1>(p, n_cus, st) : launch<2>(p, n_cus, st);
+}
+
+bool apt_setup_absorb_pv16() { return setup<1>() && setup<2>(); }

@@ -36,6 +36,9 @@ struct ItemParams {
     int32_t n_hid_req;
     int32_t ab_ks;                // slices of d_model in the score partials
     int32_t ab_tiles, ab_tiles_off;   // 256-token tiles of all hidden-kind requests, their place in the plan
+    int32_t ab_units, ab_units_off;   // units of the weighted sums, their place in the plan
+    int32_t ab_group;                 // ranges per unit
+    int32_t ab_rows;                  // 16-bit inputs: rows per part of the weights (heads padded to whole fragments)
 };
 
 namespace {
@@ -298,6 +301,16 @@ typedef __attribute__((address_space(3))) u32x4_t lds_u32x4_t;
 __device__ inline uint4 lds_read16(uint32_t addr) {
     const u32x4_t v = *(const lds_u32x4_t*)(uintptr_t)addr;
     return make_uint4(v.x, v.y, v.z, v.w);
+}
+// Transposing LDS read of an MFMA operand whose k runs over LDS rows: 16 consecutive lanes cover 4 rows x 32 bytes, lane i
+// reads 8 bytes at its address and receives the 4 k of column i.  Unit u (32 bytes) of row k sits at u ^ wswz(k) where the
+// rows are a multiple of 256 bytes apart, so that the rows of a read fall on different banks.
+__device__ inline int wswz(int k) { return (k & 3) | ((k >> 1) & 4); }
+
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+__device__ inline uint2 lds_read_tr(uint32_t addr) {
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(uintptr_t)addr));
 }
 template <int N> __device__ inline void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 

@@ -28,7 +28,8 @@ enum {
     APT_PW_MAX_BLOCKS = 28,
     APT_PW_DTYPE = 29,
     APT_PW_NHIDREQ = 30,    // number of hidden-kind requests
-    APT_PW_TILES_OFF = 31,  // absorbed-weight path: word offset of the tiles (up to the end of the blob), else 0
+    APT_PW_TILES_OFF = 31,  // absorbed-weight path: word offset of its lists (tiles, ranges per unit, tile words, unit
+                            // words up to the end of the blob), else 0
     APT_PW_HEADER = 32
 };
 #define APT_N_QUEUES 8
@@ -59,6 +60,11 @@ enum {
 #define APT_ABSORBED_HEADS_PER_THREAD 10 // group, head group), 8 tokens/columns x 10 heads per thread
 #define APT_ABSORBED_CHUNK 512           // = 64 groups x 8 tokens
 #define APT_ABSORBED_TILE 256            // tokens of a tile of the 16-bit score kernel: one or two tiles per range
+// Weighted sums of the 16-bit path: a unit is 1, 2 or 4 ranges of a request, the most with which the batch still gives this
+// many units of 512 columns (three per CU, so that the longest do not decide when the kernel ends).  Longer units write and
+// read again fewer fp32 sums: 72 heads, 96 requests, 102 k tokens: 255 MB with 4 ranges per unit, 637 MB with 1.
+#define APT_ABSORBED_MAX_GROUP 4
+#define APT_ABSORBED_UNITS_TARGET 768
 #define APT_ABSORBED_OUT_ROWS 256        // d_model rows per partial of the output projection
 
 // per-request arrays of the plan blob, each B words, starting at APT_PW_HEADER

@@ -264,7 +264,7 @@ int launch_items_impl(const ItemParams& p_in, int himpl, char* out, int out_dtyp
     ItemParams p = p_in;
     if (p.n_hidden_items == 0) return launch_items<DT, HD>(p, kv_lds, st);
     if (himpl == APT_HIDDEN_ABSORBED) {
-        const int rc = launch_absorbed<DT>(p, out, out_dtype, HD, st);
+        const int rc = launch_absorbed<DT>(p, out, out_dtype, HD, n_wg, st);
         if (rc || p.n_hidden_items == p.n_items) return rc;
         p.item_base = p.n_hidden_items;          // the KV-kind items, one workgroup each
         return launch_items<DT, HD>(p, kv_lds, st);
@@ -305,7 +305,7 @@ int device_setup(const DeviceState** out) {
                         apt_setup_raw16() &&
                         apt_raise_lds_limit(apt_absorb_score_kernel<0>) && apt_raise_lds_limit(apt_absorb_pv_kernel<0>) &&
                         apt_setup_absorb_scores16() &&
-                        apt_raise_lds_limit(apt_absorb_pv_mfma_kernel<1>) && apt_raise_lds_limit(apt_absorb_pv_mfma_kernel<2>);
+                        apt_setup_absorb_pv16();
         if (!ok) return APT_EHIP;
         void* ptr = nullptr;
         if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return APT_EHIP;
@@ -460,6 +460,7 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     if ((!static_ws && !aligned16(workspace)) || !aligned16(q) || !aligned16(k_pages) || !aligned16(v_pages) || !aligned16(hidden_pages) ||
         !aligned16(W_K) || !aligned16(W_V) || !aligned16(W_packed) || !aligned16(b_K) || !aligned16(b_V) || !aligned16(plan_dev))
         return APT_EINVAL;
+    if (rs.s.hidden_impl == APT_HIDDEN_ABSORBED && n_hidden > 0 && !pw[APT_PW_TILES_OFF]) return APT_EINVAL;   // a blob without the lists
     if (n_hidden < n_items && (!k_pages || !v_pages)) return APT_EINVAL;
     if (n_hidden > 0) {
         if (!hidden_pages || !b_K || !b_V) return APT_EINVAL;
@@ -502,7 +503,14 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     p.item_base = 0;
     p.ab_ks = 0;
     p.ab_tiles_off = pw[APT_PW_TILES_OFF];
-    p.ab_tiles = p.ab_tiles_off ? pw[APT_PW_WORDS] - p.ab_tiles_off : 0;
+    p.ab_tiles = p.ab_units = p.ab_units_off = p.ab_group = p.ab_rows = 0;
+    if (p.ab_tiles_off) {
+        p.ab_tiles = pw[p.ab_tiles_off];
+        p.ab_group = pw[p.ab_tiles_off + 1];
+        p.ab_tiles_off += 2;
+        p.ab_units_off = p.ab_tiles_off + p.ab_tiles;
+        p.ab_units = pw[APT_PW_WORDS] - p.ab_units_off;
+    }
     p.B = B; p.H = rs.s.n_heads; p.d = rs.s.d_model; p.bs = rs.s.block_size; p.log2_bs = log2_bs;
     p.max_blocks = rs.s.max_blocks_per_req;
     p.n_items = n_items; p.n_hidden_items = n_hidden;

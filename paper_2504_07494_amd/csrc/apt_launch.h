@@ -26,3 +26,5 @@ int apt_launch_raw32(const ItemParams& p, int head_dim, int queue_len, hipStream
 // apt_absorb16.hip: absorbed-weight path, 16-bit inputs
 int apt_launch_absorb_scores16(const ItemParams& p, int dtype, int head_dim, hipStream_t st);
 bool apt_setup_absorb_scores16();
+int apt_launch_absorb_pv16(const ItemParams& p, int dtype, int n_cus, hipStream_t st);
+bool apt_setup_absorb_pv16();

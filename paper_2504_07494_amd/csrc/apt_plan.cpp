@@ -75,7 +75,8 @@ static size_t plan_items_off(int B) {
     const size_t w = APT_PW_HEADER + APT_PA_COUNT * (size_t)B;
     return (w + 3) & ~(size_t)3;
 }
-static size_t plan_words(int B, int64_t n_items, int64_t n_tiles) { return plan_items_off(B) + 4 * (size_t)n_items + (size_t)n_tiles; }
+// n_lists: words of the lists of the absorbed-weight path
+static size_t plan_words(int B, int64_t n_items, int64_t n_lists) { return plan_items_off(B) + 4 * (size_t)n_items + (size_t)n_lists; }
 
 extern "C" int apt_plan_max_bytes(const apt_shape* s, int B, int max_ctx, size_t* bytes) {
     apt_resolved rs;
@@ -85,8 +86,9 @@ extern "C" int apt_plan_max_bytes(const apt_shape* s, int B, int max_ctx, size_t
     const int hmin = rs.hidden_auto ? APT_RAW_MIN_HIDDEN_CHUNK(rs.s.dtype) : rs.s.hidden_chunk;
     const int cmin = hmin < rs.s.kv_chunk ? hmin : rs.s.kv_chunk;
     const int64_t n_items = (int64_t)B * rs.s.n_heads * ceil_div64(max_ctx, cmin);
-    const int64_t n_tiles = rs.s.hidden_impl == APT_HIDDEN_ABSORBED ? (int64_t)B * ceil_div64(max_ctx, APT_ABSORBED_TILE) : 0;
-    *bytes = plan_words(B, n_items, n_tiles) * 4;
+    const int64_t n_lists = rs.s.hidden_impl == APT_HIDDEN_ABSORBED
+        ? 2 + (int64_t)B * (ceil_div64(max_ctx, APT_ABSORBED_TILE) + ceil_div64(max_ctx, APT_ABSORBED_CHUNK)) : 0;
+    *bytes = plan_words(B, n_items, n_lists) * 4;
     return APT_OK;
 }
 
@@ -166,7 +168,18 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
         tok += n;
     }
     if (n_items > 0x7fffffff || n_partials * (int64_t)H > 0x7fffffff || htok > 0x7fffffff) return APT_ERANGE;
-    const size_t words = plan_words(B, n_items, n_tiles);
+    // absorbed-weight path: ranges per unit of the weighted sums (fp32 inputs: one)
+    int group = 1;
+    int64_t n_units = n_hidden_items;
+    if (absorbed && rs.s.dtype != APT_F32) {
+        for (int g = APT_ABSORBED_MAX_GROUP; g > 1; g /= 2) {
+            int64_t n = 0;
+            for (int r = 0; r < B; ++r)
+                if (cache_kind[r] == APT_KIND_HIDDEN) n += ceil_div64(ctx_lens[r], (int64_t)g * APT_ABSORBED_CHUNK);
+            if (n * ceil_div64(rs.s.d_model, 512) >= APT_ABSORBED_UNITS_TARGET) { group = g; n_units = n; break; }
+        }
+    }
+    const size_t words = plan_words(B, n_items, absorbed ? 2 + n_tiles + n_units : 0);
     if (plan_bytes < words * 4) return APT_EWORKSPACE;
 
     int32_t* w = (int32_t*)plan_host;
@@ -265,10 +278,22 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
     }
     w[APT_PW_QUEUE0 + APT_N_QUEUES] = (int32_t)((it - it0) / 4);
     emit_kind(APT_KIND_KV, rs.s.kv_chunk, 0, 1);
-    // absorbed-weight path: the 256-token tiles of the hidden-kind ranges in their order, 2 * item + half
-    if (absorbed)
-        for (int32_t i = 0, *tile = w + w[APT_PW_TILES_OFF]; i < (int32_t)n_hidden_items; ++i)
-            for (int half = 0; half * APT_ABSORBED_TILE < it0[4 * i + 3] - it0[4 * i + 2]; ++half) *tile++ = 2 * i + half;
+    // absorbed-weight path: the 256-token tiles of the hidden-kind ranges in their order, 2 * item + half; then the units
+    // (their first ranges), longest first
+    if (absorbed) {
+        int32_t* at = w + w[APT_PW_TILES_OFF];
+        *at++ = (int32_t)n_tiles;
+        *at++ = group;
+        for (int32_t i = 0; i < (int32_t)n_hidden_items; ++i)
+            for (int half = 0; half * APT_ABSORBED_TILE < it0[4 * i + 3] - it0[4 * i + 2]; ++half) *at++ = 2 * i + half;
+        int32_t* const units = at;
+        const int unit_tokens = group * APT_ABSORBED_CHUNK;
+        for (int32_t i = 0; i < (int32_t)n_hidden_items; ++i)
+            if (it0[4 * i + 2] % unit_tokens == 0) *at++ = i;
+        std::stable_sort(units, at, [&](int32_t a, int32_t b) {
+            return std::min(ctx_lens[it0[4 * a]] - it0[4 * a + 2], unit_tokens) > std::min(ctx_lens[it0[4 * b]] - it0[4 * b + 2], unit_tokens);
+        });
+    }
     if (info) return apt_plan_get_info(plan_host, info);
     return APT_OK;
 }

@@ -45,15 +45,6 @@ template <int HD> constexpr int raw_lds_bytes() {
     return m > RawTile<HD, 64>::kLds ? m : RawTile<HD, 64>::kLds;
 }
 
-__device__ inline int wswz(int k) { return (k & 3) | ((k >> 1) & 4); }
-
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
-// 4 k x 16 channels, transposed (see above); 16 consecutive lanes cover 4 rows x 32 bytes
-__device__ inline uint2 lds_read_tr(uint32_t addr) {
-    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(uintptr_t)addr));
-}
-
 template <int DT, int HD, int T>
 __device__ __forceinline__ void hidden_item_raw(const ItemParams& p, int r, int h, int t0, int t1, char* lds) {
     using C = RawTile<HD, T>;

@@ -183,6 +183,25 @@ def test_absorbed_path_head_fragment_counts(oracle, dtype, H):
     assert np.all(np.isfinite(got))
 
 
+@pytest.mark.parametrize("dtype,n_long,n_short", [("f16", 5, 190), ("bf16", 8, 180), ("f16", 3, 100), ("bf16", 2, 5)])
+def test_absorbed_path_units_of_one_two_and_four_ranges(oracle, dtype, n_long, n_short):
+    """Weighted sums over units of 4, 2, 1 and 1 ranges (the last with 256 columns per workgroup), lengths around the ends
+    of ranges and units, several groups of requests in the output projection."""
+    print(f"[case] absorbed units {dtype} {n_long}+{n_short}", flush=True)
+    lens = np.array([2048, 2049, 1537, 513, 1024, 2048, 1025, 1023][:n_long] + [1 + i % 5 for i in range(n_short)], dtype=np.int32)
+    if n_long == 8:
+        lens[:8] = 2048
+    cfg = wl.small_config(name="absorbedunits", dtype=dtype, d_model=2048, n_heads=16, head_dim=128, block_size=16,
+                          batch=len(lens), len_lo=1, len_hi=2049, hidden_ratio=1.0)
+    batch = wl.make_batch(cfg, lens, np.full(len(lens), HID, dtype=np.uint8))
+    layer = wl.make_layer(batch)
+    rn, got = _run(batch, layer, hidden_impl=ab.APT_HIDDEN_ABSORBED)
+    pairs = [(r, h) for r in list(range(min(n_long, 4))) + [n_long, n_long + n_short // 2, len(lens) - 1] for h in (0, 15)]
+    want = oracle_attn(oracle, batch, layer, pairs=pairs).reshape(len(pairs), 128)
+    _check(np.stack([got[r, h] for r, h in pairs]), want, f"absorbed-units-{dtype}", 2e-4, 2e-3)
+    assert np.all(np.isfinite(got))
+
+
 def test_absorbed_path_requests_longer_than_2048_tokens(oracle):
     # more than 256 runs of 8 tokens per (request, head): the statistics kernel's second and third pass
     print("[case] absorbed long requests", flush=True)
