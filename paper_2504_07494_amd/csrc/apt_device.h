@@ -38,6 +38,7 @@ struct ItemParams {
     int32_t ab_tiles, ab_tiles_off;   // 256-token tiles of all hidden-kind requests, their place in the plan
     int32_t ab_units, ab_units_off;   // units of the weighted sums, their place in the plan
     int32_t ab_group;                 // ranges per unit
+    int32_t ab_os;                    // slices of d_model in the output partials
     int32_t ab_rows;                  // 16-bit inputs: rows per part of the weights (heads padded to whole fragments)
 };
 

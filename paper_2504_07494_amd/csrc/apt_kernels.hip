@@ -305,7 +305,7 @@ int device_setup(const DeviceState** out) {
                         apt_setup_raw16() &&
                         apt_raise_lds_limit(apt_absorb_score_kernel<0>) && apt_raise_lds_limit(apt_absorb_pv_kernel<0>) &&
                         apt_setup_absorb_scores16() &&
-                        apt_setup_absorb_pv16();
+                        apt_setup_absorb_pv16() && apt_setup_absorb_out16();
         if (!ok) return APT_EHIP;
         void* ptr = nullptr;
         if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return APT_EHIP;
@@ -503,7 +503,7 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     p.item_base = 0;
     p.ab_ks = 0;
     p.ab_tiles_off = pw[APT_PW_TILES_OFF];
-    p.ab_tiles = p.ab_units = p.ab_units_off = p.ab_group = p.ab_rows = 0;
+    p.ab_tiles = p.ab_units = p.ab_units_off = p.ab_group = p.ab_rows = p.ab_os = 0;
     if (p.ab_tiles_off) {
         p.ab_tiles = pw[p.ab_tiles_off];
         p.ab_group = pw[p.ab_tiles_off + 1];

@@ -28,3 +28,6 @@ int apt_launch_absorb_scores16(const ItemParams& p, int dtype, int head_dim, hip
 bool apt_setup_absorb_scores16();
 int apt_launch_absorb_pv16(const ItemParams& p, int dtype, int n_cus, hipStream_t st);
 bool apt_setup_absorb_pv16();
+int apt_absorb_out16_slices(const ItemParams& p, int n_cus, int most);
+int apt_launch_absorb_out16(const ItemParams& p, int dtype, int head_dim, hipStream_t st);
+bool apt_setup_absorb_out16();
