@@ -47,13 +47,15 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_q16_kernel(ItemParams p) 
 #pragma unroll
             for (int s = 0; s < KS; ++s) acc[f] = mfma16<DT>(wf[f][s], qf[s], acc[f]);
         }
-        uint16_t part[8][NS];
+        float v[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) AbSplit<DT>::split(acc[e >> 2][e & 3] * p.scale_log2e, part[e]);
+        for (int e = 0; e < 8; ++e) v[e] = acc[e >> 2][e & 3] * p.scale_log2e;
+        uint4 part[NS];
+        AbSplit<DT>::split8(v, part);
         if (hr0 + l16 < p.n_hid_req) {
             char* base = (char*)p.ab_qt + ((int64_t)hr * (p.d / C::KT) + kt) * C::kABytes + c * 16;
 #pragma unroll
-            for (int sp = 0; sp < NS; ++sp) *(uint4*)(base + (sp * C::R + h) * C::kRow) = ab_pack8<NS>(part, sp);
+            for (int sp = 0; sp < NS; ++sp) *(uint4*)(base + (sp * C::R + h) * C::kRow) = part[sp];
         }
         if (kb == 0) {                                   // CB = scale * log2(e) * q . b_K
             float s = 0.f;

@@ -14,9 +14,10 @@ namespace {
 // softmax denominator first, so that they stay in range, and the low part is kept 2^11 times larger, so that it is not
 // subnormal, in accumulators of its own.
 //
-// Bound by the reads of YP (fp32, H d_model values per unit) and of W_V, once per group of 16 RF requests: 127-144 us for
-// 72 heads, bf16, 96 requests at d_model 9216 (255 MB of YP, W_V twice; 480 us on the plain ALUs, whose output partials per
-// 256 rows took the last kernel another 30 us), 28 us for 40 heads, fp16, 32 requests (70 us).
+// Bound by the reads of YP (fp32, H d_model values per unit) and of W_V, once per group of 16 RF requests: 108 us for
+// 72 heads, bf16, 96 requests at d_model 9216 (255 MB of YP, W_V twice; 142 us with a conversion of four instructions per
+// value and part, 480 us on the plain ALUs, whose output partials per 256 rows took the last kernel another 30 us), 28 us for
+// 40 heads, fp16, 32 requests (70 us).
 template <int DT, int HD, int RF> struct OutTile {
     static constexpr int NS = AbSplit<DT>::parts;
     static constexpr int NA = DT == 1 ? 2 : 1;              // accumulator sets
@@ -144,23 +145,16 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_out16_kernel(ItemParams p
         }
 #pragma unroll
         for (int f = 0; f < RF; ++f) {
-            uint16_t part[8][NS];
+            float v[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float v = y[f][e] * scale[f];
-                if constexpr (DT == 1) {
-                    const _Float16 hi = (_Float16)v;
-                    part[e][0] = __builtin_bit_cast(uint16_t, hi);
-                    part[e][1] = __builtin_bit_cast(uint16_t, (_Float16)((v - (float)hi) * kLoScale));
-                } else {
-                    AbSplit<DT>::split(v, part[e]);
-                }
-            }
+            for (int e = 0; e < 8; ++e) v[e] = y[f][e] * scale[f];
+            uint4 part[NS];
+            if constexpr (DT == 1) AbSplit<DT>::split8(v, part, kLoScale);
+            else AbSplit<DT>::split8(v, part);
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                const uint4 yf = ab_pack8<NS>(part, s);
 #pragma unroll
-                for (int c = 0; c < CF; ++c) acc[C::NA == 2 ? s : 0][c][f] = mfma16<DT>(wf[c], yf, acc[C::NA == 2 ? s : 0][c][f]);
+                for (int c = 0; c < CF; ++c) acc[C::NA == 2 ? s : 0][c][f] = mfma16<DT>(wf[c], part[s], acc[C::NA == 2 ? s : 0][c][f]);
             }
         }
         ws ^= 1;

@@ -15,32 +15,51 @@ __device__ inline const char* hidden_row(const ItemParams& p, int r, int token, 
     return p.hidden_pages + ((int64_t)blk * p.bs + (token & (p.bs - 1))) * p.d * eb;
 }
 
-// fp32 -> 16-bit parts for the matrix cores: fp16 hi + lo (22 bits), bf16 hi + mid + lo (24 bits).
-// The products of the parts with 16-bit inputs are exact in the fp32 accumulator.
+// Eight fp32 values -> 16-bit parts for the matrix cores, a 16-byte unit per part: fp16 hi + lo (22 bits), bf16 hi + mid + lo
+// (24 bits).  The products of the parts with 16-bit inputs are exact in the fp32 accumulator.  Pairs of values go through the
+// packed conversions (round to nearest even).
 template <int DT> struct AbSplit;
 template <> struct AbSplit<1> {
     static constexpr int parts = 2;
-    __device__ static inline void split(float v, uint16_t* out) {
-        const _Float16 hi = (_Float16)v;
-        const _Float16 lo = (_Float16)(v - (float)hi);
-        out[0] = __builtin_bit_cast(uint16_t, hi);
-        out[1] = __builtin_bit_cast(uint16_t, lo);
+    typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
+    // the low part times lo_scale (a power of two)
+    __device__ static inline void split8(const float* v, uint4* out, float lo_scale = 1.f) {
+        uint32_t w[2][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float a = v[2 * i], b = v[2 * i + 1];
+            // rounded to fp32 here: contracted with the product behind them, the two uses of hi below could round differently
+            asm("" : "+v"(a), "+v"(b));
+            const h2_t hi = {(_Float16)a, (_Float16)b};
+            const h2_t lo = {(_Float16)((a - (float)hi.x) * lo_scale), (_Float16)((b - (float)hi.y) * lo_scale)};
+            w[0][i] = __builtin_bit_cast(uint32_t, hi);
+            w[1][i] = __builtin_bit_cast(uint32_t, lo);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) out[s] = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
     }
 };
 template <> struct AbSplit<2> {
     static constexpr int parts = 3;
-    __device__ static inline void split(float v, uint16_t* out) {
-        out[0] = f32_to_bf16_rne(v);
-        const float r1 = v - bf16_to_f32(out[0]);
-        out[1] = f32_to_bf16_rne(r1);
-        out[2] = f32_to_bf16_rne(r1 - bf16_to_f32(out[1]));
+    typedef __bf16 b2_t __attribute__((ext_vector_type(2)));
+    __device__ static inline void split8(const float* v, uint4* out) {
+        uint32_t w[3][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float a = v[2 * i], b = v[2 * i + 1];
+            asm("" : "+v"(a), "+v"(b));
+#pragma unroll
+            for (int s = 0; s < 3; ++s) {
+                const b2_t r = {(__bf16)a, (__bf16)b};
+                w[s][i] = __builtin_bit_cast(uint32_t, r);
+                a -= __uint_as_float(w[s][i] << 16);
+                b -= __uint_as_float(w[s][i] & 0xffff0000u);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 3; ++s) out[s] = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
     }
 };
-// part sp of eight split values as one 16-byte unit
-template <int NS> __device__ inline uint4 ab_pack8(const uint16_t (*part)[NS], int sp) {
-    return make_uint4(part[0][sp] | ((uint32_t)part[1][sp] << 16), part[2][sp] | ((uint32_t)part[3][sp] << 16),
-                      part[4][sp] | ((uint32_t)part[5][sp] << 16), part[6][sp] | ((uint32_t)part[7][sp] << 16));
-}
 
 constexpr int kAbTok = APT_ABSORBED_CHUNK;                // tokens per range
 constexpr int kAbMT = 256;                                // tokens per workgroup of the score kernel
@@ -56,10 +75,11 @@ static inline int ab_head_frags(int H) {
 }
 
 // Long fp32 sums on the matrix cores round at the size of the running sum, once per part and 32 k: every kAbFold k the
-// accumulators are added to a second set and cleared, so that the sum is one of short sums.  Error of the hidden-kind
-// outputs against 64 bits, 40 heads, fp16, 32 requests of 128..2048 tokens: 1.23e-6 in one run over a slice or unit,
-// 9.4e-7 folded, 9.3e-7 with an accumulator per part over 512 k.
-constexpr int kAbFold = 256;
+// accumulators are added to a second set and cleared, so that the sum is one of short sums.  Error of the outputs against
+// 64 bits with an accumulator per part over 512 k / one run over a slice or unit / folded every 512 / 256 / 128 k: 40 heads,
+// fp16, 32 requests of 128..2048 tokens 9.3e-7 / 1.23e-6 / 9.6e-7 / 9.2e-7 / 9.05e-7; bf16, 8 requests 4.1e-7 / - / 5.4e-7 /
+// 4.2e-7 / 3.7e-7; 72 heads, bf16, 6 requests 5.3e-7 / - / 6.8e-7 / 5.6e-7 / 5.3e-7.
+constexpr int kAbFold = 128;
 
 template <int N> __device__ inline void ab_fold(f32x4_t (*acc)[N], f32x4_t (*sum)[N], int rows) {
 #pragma unroll

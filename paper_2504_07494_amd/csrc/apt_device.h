@@ -266,11 +266,8 @@ __device__ __forceinline__ void kv_item(const ItemParams& p, int r, int h, int t
 // ---------------------------------------------------------------------------------
 constexpr int kBK = 32;                                // k extent of one LDS tile of the matrix kernels
 
-// Position swizzles of the 16-byte units of 64-byte LDS rows, measured free of bank conflicts (SQ_LDS_BANK_CONFLICT = 0,
-// 4 cycles per ds_read_b128) for the operand reads of the two MFMA forms: swz for 32x32x16 (a read covers 32 consecutive
-// rows, two units; used by the absorbed-weight kernels), swz16 for 16x16x32 (16 consecutive rows, all four units; with
-// swz it takes 8 cycles).
-__host__ __device__ inline int swz(int row) { return (row >> 2) & 3; }
+// Position swizzle of the 16-byte units of 64-byte LDS rows, measured free of bank conflicts (SQ_LDS_BANK_CONFLICT = 0,
+// 4 cycles per ds_read_b128) for the operand reads of 16x16x32 MFMAs (16 consecutive rows, all four units).
 __host__ __device__ inline int swz16(int row) { return (row >> 1) & 3; }
 
 template <int DT> __device__ inline f32x16_t mfma32(const uint4& a, const uint4& b, f32x16_t c) {
