@@ -208,7 +208,10 @@ int apt_plan_get_info(const void* plan_host, apt_plan_info* info);
  * info.plan_bytes bytes; helper of apt_plan: the device half of the work partition).  plan_host
  * must stay unchanged until the copy is done (re-planning into the same host buffer before that
  * tears the copy: use one host buffer per step in flight, or wait for an event recorded after
- * this call); use page-locked host memory for a truly asynchronous copy. */
+ * this call); use page-locked host memory for a truly asynchronous copy.  A blob of at most
+ * APT_PLAN_INLINE_BYTES travels with a kernel launch instead and has been read when the call
+ * returns, unless the stream is being captured (a captured copy reads plan_host at every replay). */
+#define APT_PLAN_INLINE_BYTES 3840
 int apt_plan_upload(const void* plan_host, void* plan_dev, void* stream);
 
 /*

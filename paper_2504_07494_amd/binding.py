@@ -18,6 +18,7 @@ APT_F32, APT_F16, APT_BF16 = 0, 1, 2
 APT_KIND_KV, APT_KIND_HIDDEN = 0, 1
 APT_HIDDEN_AUTO, APT_HIDDEN_VALU, APT_HIDDEN_MFMA, APT_HIDDEN_ABSORBED = 0, 1, 2, 3
 APT_OK, APT_EINVAL, APT_ESHAPE, APT_EDTYPE, APT_EWORKSPACE, APT_EHIP, APT_ERANGE, APT_EFULL = 0, -1, -2, -3, -4, -5, -6, -7
+APT_PLAN_INLINE_BYTES = 3840        # a plan blob of at most this size has been read when apt_plan_upload returns
 DTYPE_CODES = {"f32": APT_F32, "f16": APT_F16, "bf16": APT_BF16}
 
 # include/apt_hybrid.h (the product interface) and include/apt_hybrid_bench.h (measurement tooling)
@@ -64,6 +65,13 @@ def lib():
         for name in EXPORTS[1:] + BENCH_EXPORTS:
             getattr(_lib, name).restype = C.c_int
         _lib.apt_pool_destroy.restype = None
+        # the calls of a decode step take plain addresses: ctypes converts them without an object per argument
+        p, i, n = C.c_void_p, C.c_int, C.c_size_t
+        _lib.apt_plan.argtypes = [p, p, p, i, p, n, p]
+        _lib.apt_plan_upload.argtypes = [p, p, p]
+        _lib.apt_hybrid_decode_attn.argtypes = [p] * 15 + [n, p]
+        _lib.apt_cache_append.argtypes = [p, i] + [p] * 10
+        _lib.apt_cache_write.argtypes = [p, i, p, C.c_int32] + [p] * 10
     return _lib
 
 
@@ -80,6 +88,16 @@ def _ptr(x):
     if hasattr(x, "data_ptr"):
         return C.c_void_p(x.data_ptr())
     return C.cast(C.byref(x), C.c_void_p)
+
+
+def _addr(x):
+    """The same as a plain address, for functions with argument types."""
+    if x is None or isinstance(x, int):
+        return x
+    try:
+        return x.data_ptr()
+    except AttributeError:
+        return x.__array_interface__["data"][0] if isinstance(x, np.ndarray) else _ptr(x).value
 
 
 def _check(rc, where):
@@ -123,9 +141,9 @@ def apt_plan(shape, ctx_lens_host: np.ndarray, cache_kind_host: np.ndarray, plan
     """plan_host: numpy int32 array or page-locked torch int32 CPU tensor that receives the blob."""
     assert ctx_lens_host.dtype == np.int32 and cache_kind_host.dtype == np.uint8
     info = apt_plan_info()
-    nbytes = plan_host.nbytes if isinstance(plan_host, np.ndarray) else plan_host.numel() * plan_host.element_size()
-    _check(lib().apt_plan(C.byref(shape), _ptr(ctx_lens_host), _ptr(cache_kind_host), C.c_int(len(ctx_lens_host)),
-                          _ptr(plan_host), C.c_size_t(nbytes), C.byref(info)), "apt_plan")
+    nbytes = plan_host.nbytes
+    _check(lib().apt_plan(C.byref(shape), _addr(ctx_lens_host), _addr(cache_kind_host), len(ctx_lens_host),
+                          _addr(plan_host), nbytes, C.byref(info)), "apt_plan")
     return info
 
 
@@ -136,7 +154,7 @@ def apt_plan_get_info(plan_host) -> apt_plan_info:
 
 
 def apt_plan_upload(plan_host, plan_dev, stream=0):
-    _check(lib().apt_plan_upload(_ptr(plan_host), _ptr(plan_dev), C.c_void_p(stream)), "apt_plan_upload")
+    _check(lib().apt_plan_upload(_addr(plan_host), _addr(plan_dev), stream), "apt_plan_upload")
 
 
 def apt_validate_host(shape, ctx_lens_host, cache_kind_host, block_tables_host, n_pool_blocks):
@@ -158,10 +176,10 @@ def apt_pack_weights(shape, W_K, W_V, packed, stream=0):
 
 def apt_hybrid_decode_attn(shape, plan_host, plan_dev, q, k_pages, v_pages, hidden_pages, W_K, W_V, W_packed,
                            b_K, b_V, block_tables, out, workspace, workspace_bytes, stream=0):
-    _check(lib().apt_hybrid_decode_attn(C.byref(shape), _ptr(plan_host), _ptr(plan_dev), _ptr(q), _ptr(k_pages),
-                                        _ptr(v_pages), _ptr(hidden_pages), _ptr(W_K), _ptr(W_V), _ptr(W_packed),
-                                        _ptr(b_K), _ptr(b_V), _ptr(block_tables), _ptr(out), _ptr(workspace),
-                                        C.c_size_t(workspace_bytes), C.c_void_p(stream)), "apt_hybrid_decode_attn")
+    _check(lib().apt_hybrid_decode_attn(C.byref(shape), _addr(plan_host), _addr(plan_dev), _addr(q), _addr(k_pages),
+                                        _addr(v_pages), _addr(hidden_pages), _addr(W_K), _addr(W_V), _addr(W_packed),
+                                        _addr(b_K), _addr(b_V), _addr(block_tables), _addr(out), _addr(workspace),
+                                        workspace_bytes, stream), "apt_hybrid_decode_attn")
 
 
 APT_STATIC_WORKSPACE_BYTES = 64 << 20
@@ -187,17 +205,17 @@ def apt_hybrid_decode_attn_timed(shape, plan_host, plan_dev, q, k_pages, v_pages
 
 def apt_cache_append(shape, B, x_new, k_new, v_new, k_pages, v_pages, hidden_pages, block_tables, ctx_lens_dev,
                      cache_kind_dev, stream=0):
-    _check(lib().apt_cache_append(C.byref(shape), C.c_int(B), _ptr(x_new), _ptr(k_new), _ptr(v_new), _ptr(k_pages),
-                                  _ptr(v_pages), _ptr(hidden_pages), _ptr(block_tables), _ptr(ctx_lens_dev),
-                                  _ptr(cache_kind_dev), C.c_void_p(stream)), "apt_cache_append")
+    _check(lib().apt_cache_append(C.byref(shape), B, _addr(x_new), _addr(k_new), _addr(v_new), _addr(k_pages),
+                                  _addr(v_pages), _addr(hidden_pages), _addr(block_tables), _addr(ctx_lens_dev),
+                                  _addr(cache_kind_dev), stream), "apt_cache_append")
 
 
 def apt_cache_write(shape, B, new_offsets_dev, max_new_tokens, x_new, k_new, v_new, k_pages, v_pages, hidden_pages,
                     block_tables, ctx_lens_dev, cache_kind_dev, stream=0):
-    _check(lib().apt_cache_write(C.byref(shape), C.c_int(B), _ptr(new_offsets_dev), C.c_int32(max_new_tokens),
-                                 _ptr(x_new), _ptr(k_new), _ptr(v_new), _ptr(k_pages), _ptr(v_pages),
-                                 _ptr(hidden_pages), _ptr(block_tables), _ptr(ctx_lens_dev), _ptr(cache_kind_dev),
-                                 C.c_void_p(stream)), "apt_cache_write")
+    _check(lib().apt_cache_write(C.byref(shape), B, _addr(new_offsets_dev), max_new_tokens, _addr(x_new), _addr(k_new),
+                                 _addr(v_new), _addr(k_pages), _addr(v_pages), _addr(hidden_pages),
+                                 _addr(block_tables), _addr(ctx_lens_dev), _addr(cache_kind_dev), stream),
+           "apt_cache_write")
 
 
 # --- hybrid cache assigner (host-side pool bookkeeping); `pool` is the opaque handle --------------

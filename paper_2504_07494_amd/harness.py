@@ -55,6 +55,7 @@ class DecodeRunner:
         cfg = batch.cfg
         self.batch, self.cfg = batch, cfg
         self.device = torch.device(device)
+        self._device_index = self.device.index if self.device.index is not None else torch.cuda.current_device()
         self.out_dtype = out_dtype
         self.shape = ab.make_shape(cfg.d_model, cfg.n_heads, cfg.head_dim, cfg.block_size, cfg.dtype,
                                    batch.max_blocks, cfg.softmax_scale if scale is None else scale,
@@ -65,9 +66,11 @@ class DecodeRunner:
         ws_bytes, plan_bytes = ab.apt_workspace_bytes(self.shape, batch.B, max_ctx)
         # The plan blob is written on the host and copied asynchronously: a host buffer is rewritten only after the
         # copy that last read it has completed (one event per buffer), so steps can be planned back to back
-        # without a device synchronisation and without tearing a pending copy.
+        # without a device synchronisation and without tearing a pending copy.  A small blob has been read when the
+        # upload returns and needs no event.
         self._plan_bufs = [torch.empty(plan_bytes // 4, dtype=torch.int32, pin_memory=True) for _ in range(2)]
-        self._plan_events = [None] * len(self._plan_bufs)
+        self._plan_events = [torch.cuda.Event() for _ in self._plan_bufs]
+        self._plan_pending = [False] * len(self._plan_bufs)
         self._plan_i = 0
         self.plan_host = self._plan_bufs[0]
         self.plan_dev = torch.empty(plan_bytes // 4, dtype=torch.int32, device=self.device)
@@ -79,7 +82,7 @@ class DecodeRunner:
         self.plan()
 
     def stream(self) -> int:
-        return torch.cuda.current_stream(self.device).cuda_stream
+        return torch._C._cuda_getCurrentRawStream(self._device_index)
 
     def plan(self, ctx_lens=None, cache_kind=None):
         """a1: partition on the host, copy the blob to the device.  ctx_lens / cache_kind: this step's lengths and
@@ -87,14 +90,15 @@ class DecodeRunner:
         ctx_lens = self.batch.ctx_lens if ctx_lens is None else np.ascontiguousarray(ctx_lens, dtype=np.int32)
         cache_kind = self.batch.cache_kind if cache_kind is None else np.ascontiguousarray(cache_kind, dtype=np.uint8)
         i = self._plan_i = (self._plan_i + 1) % len(self._plan_bufs)
-        if self._plan_events[i] is not None:
+        if self._plan_pending[i]:
             self._plan_events[i].synchronize()        # the copy out of this host buffer is done
         self.plan_host = self._plan_bufs[i]
         self.info = ab.apt_plan(self.shape, ctx_lens, cache_kind, self.plan_host)
         ab.apt_plan_upload(self.plan_host, self.plan_dev, self.stream())
-        ev = torch.cuda.Event()
-        ev.record(torch.cuda.current_stream(self.device))
-        self._plan_events[i] = ev
+        self._plan_pending[i] = (self.info.plan_bytes > ab.APT_PLAN_INLINE_BYTES or
+                                 torch.cuda.is_current_stream_capturing())
+        if self._plan_pending[i]:
+            self._plan_events[i].record(torch.cuda.current_stream(self.device))
         assert int(self.info.workspace_bytes) <= self.workspace.numel()
         return self.info
 

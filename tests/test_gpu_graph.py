@@ -50,3 +50,33 @@ def test_captured_attention_call_replays_like_the_eager_call(oracle, impl):
     from tests.helpers import oracle_attn
     want = oracle_attn(oracle, batch, layer).reshape(batch.B, cfg.n_heads, cfg.head_dim)
     assert np.max(np.abs(out_graph.float().cpu().numpy().astype(np.float64) - want)) < 2e-4
+
+
+@pytest.mark.parametrize("n_requests", [1, 77, 78, 200])
+def test_plan_upload_small_blobs_are_read_at_once_and_captured_ones_at_replay(n_requests):
+    """Blobs below, just below (77 requests: 3824 bytes), just above and far above the size that travels with a kernel launch."""
+    print(f"[case] plan upload {n_requests}", flush=True)
+    shape = ab.make_shape(128, 1, 128, 16, "f16", 8, 1.0)
+    lens, kinds = np.full(n_requests, 17, dtype=np.int32), np.zeros(n_requests, dtype=np.uint8)
+    kinds[::2] = 1
+    host = torch.zeros(ab.apt_plan_max_bytes(shape, n_requests, 128) // 4, dtype=torch.int32, pin_memory=True)
+    info = ab.apt_plan(shape, lens, kinds, host)
+    n = int(info.plan_bytes) // 4
+    assert (info.plan_bytes <= ab.APT_PLAN_INLINE_BYTES) == (n_requests <= 77)
+    want = host[:n].clone()
+    dev = torch.full((n + 1,), -7, dtype=torch.int32, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    ab.apt_plan_upload(host, dev, stream)
+    if info.plan_bytes <= ab.APT_PLAN_INLINE_BYTES:
+        host.fill_(5)                       # already read
+    torch.cuda.synchronize()
+    assert torch.equal(dev[:n].cpu(), want) and int(dev[n]) == -7
+    host[:n] = want
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=side):
+        ab.apt_plan_upload(host, dev, side.cuda_stream)
+    for value in (1, 2):
+        host[17] = value                    # a replay reads the host buffer as it is then
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(dev[:n].cpu(), host[:n])
