@@ -16,12 +16,13 @@ namespace {
 // order the statistics kernel wrote them.
 //
 // Bound by memory and the matrix pipes together (X once, and NS parts of every head per column).  512 columns halve the
-// weight bytes an X byte brings along; 256 are for shapes whose stages do not fit and for batches that would leave CUs
-// without a unit.
+// weight bytes an X byte brings along.  256 are taken where three stages then fit in half of LDS (fp16 up to 80 heads, bf16 up
+// to 48), so that one workgroup's start-up and stores are covered by the other's loop, where the stages of 512 do not fit at
+// all, and in batches that would leave CUs without a unit.
 //
 // 72 heads, bf16, 96 requests with 102 k tokens at d_model 9216 (1.9 GB of X): 480-520 us, 1200 us with heads padded to 128
 // in two passes over X, a 16-bit gather per operand and sums per 512-token range.  40 heads, fp16, 33.6 k tokens at
-// d_model 5120 (344 MB): 83 us on both sides, memory.
+// d_model 5120 (344 MB): 80 us with 256 columns and two workgroups per CU, 87 us with 512 and one, 86 us before.
 template <int DT, int NF, int CW> struct PvTile {
     static constexpr int NS = AbSplit<DT>::parts;
     static constexpr int R = 16 * NF;
@@ -29,7 +30,9 @@ template <int DT, int NF, int CW> struct PvTile {
     static constexpr int kXBytes = 32 * kRow;
     static constexpr int kPBytes = R * NS * 64;
     static constexpr int kStage = kXBytes + kPBytes;
-    static constexpr int kLdsMost = 156 * 1024;
+    // three stages of a 256-column tile in half of LDS: two workgroups share a CU
+    static constexpr bool kTwo = CW == 256 && 3 * kStage <= 78 * 1024;
+    static constexpr int kLdsMost = (kTwo ? 78 : 156) * 1024;
     static constexpr int S = kLdsMost / kStage < 6 ? kLdsMost / kStage : 6;
     static constexpr int kXCopies = kXBytes / 1024 / kAbWaves;     // 1 KB copies per wave and k-tile
     static constexpr int kPCopies = (kPBytes / 1024 + kAbWaves - 1) / kAbWaves;
@@ -149,7 +152,7 @@ template <int DT, int NF, int CW> int launch_cw(const ItemParams& p, hipStream_t
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
 }
 template <int DT, int NF> int launch_nf(const ItemParams& p, int n_cus, hipStream_t st) {
-    if constexpr (PvTile<DT, NF, 512>::kFits)
+    if constexpr (PvTile<DT, NF, 512>::kFits && !PvTile<DT, NF, 256>::kTwo)
         if ((int64_t)p.ab_units * ((p.d + 511) / 512) >= n_cus) return launch_cw<DT, NF, 512>(p, st);
     return launch_cw<DT, NF, 256>(p, st);
 }
@@ -164,7 +167,7 @@ template <int DT> int launch(const ItemParams& p, int n_cus, hipStream_t st) {
     }
 }
 template <int DT, int NF> bool setup_nf() {
-    if constexpr (PvTile<DT, NF, 512>::kFits)
+    if constexpr (PvTile<DT, NF, 512>::kFits && !PvTile<DT, NF, 256>::kTwo)
         if (!apt_raise_lds_limit(apt_absorb_pv16_kernel<DT, NF, 512>)) return false;
     return apt_raise_lds_limit(apt_absorb_pv16_kernel<DT, NF, 256>);
 }

@@ -185,7 +185,7 @@ def test_absorbed_path_head_fragment_counts(oracle, dtype, H):
 
 @pytest.mark.parametrize("dtype,n_long,n_short", [("f16", 5, 190), ("bf16", 8, 180), ("f16", 3, 100), ("bf16", 2, 5)])
 def test_absorbed_path_units_of_one_two_and_four_ranges(oracle, dtype, n_long, n_short):
-    """Weighted sums over units of 4, 2, 1 and 1 ranges (the last with 256 columns per workgroup), lengths around the ends
+    """Weighted sums over units of 4, 2, 1 and 1 ranges (16 heads: 256 columns, two workgroups per CU), lengths around the ends
     of ranges and units, several groups of requests in the output projection."""
     print(f"[case] absorbed units {dtype} {n_long}+{n_short}", flush=True)
     lens = np.array([2048, 2049, 1537, 513, 1024, 2048, 1025, 1023][:n_long] + [1 + i % 5 for i in range(n_short)], dtype=np.int32)
