@@ -265,7 +265,7 @@ int launch_items(const ItemParams& p, size_t lds_bytes, hipStream_t st) {
 #include "apt_absorbed.inc"
 
 template <int DT, int HD>
-int launch_items_impl(const ItemParams& p_in, int himpl, char* out, int out_dtype, int n_wg, int queue_len, hipStream_t st) {
+int launch_items_impl(const ItemParams& p_in, int himpl, char* out, int out_dtype, int n_wg, hipStream_t st) {
     constexpr int EB = Elt<DT>::bytes;
     constexpr int LPR = HD * EB / 16;
     constexpr int G = 4 * (64 / LPR);
@@ -279,8 +279,8 @@ int launch_items_impl(const ItemParams& p_in, int himpl, char* out, int out_dtyp
         return launch_items<DT, HD>(p, kv_lds, st);
     }
     if (himpl == APT_HIDDEN_VALU) {
-        if constexpr (DT == 0) return apt_launch_raw32(p, HD, queue_len, st);
-        else return apt_launch_raw16(p, DT, HD, queue_len, st);
+        if constexpr (DT == 0) return apt_launch_raw32(p, HD, st);
+        else return apt_launch_raw16(p, DT, HD, st);
     }
     if constexpr (DT != 0 && HD == 128) {
         return apt_launch_mfma<DT>(p, n_wg, st);
@@ -541,19 +541,14 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     p.scale_log2e = rs.s.softmax_scale * 1.4426950408889634f;
     hipStream_t st = (hipStream_t)stream;
 
-    int queue_len = 0;                       // longest hidden-kind queue
-    for (int x = 0; x < APT_N_QUEUES; ++x) {
-        const int n = pw[APT_PW_QUEUE0 + x + 1] - pw[APT_PW_QUEUE0 + x];
-        queue_len = n > queue_len ? n : queue_len;
-    }
     const int dt = rs.s.dtype, hd = rs.s.head_dim, hi = rs.s.hidden_impl;
     if (ev_begin && hipEventRecord((hipEvent_t)ev_begin, st) != hipSuccess) return APT_EHIP;
-    if (dt == APT_F32 && hd == 64) rc = launch_items_impl<0, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, queue_len, st);
-    else if (dt == APT_F32 && hd == 128) rc = launch_items_impl<0, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, queue_len, st);
-    else if (dt == APT_F16 && hd == 64) rc = launch_items_impl<1, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, queue_len, st);
-    else if (dt == APT_F16 && hd == 128) rc = launch_items_impl<1, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, queue_len, st);
-    else if (dt == APT_BF16 && hd == 64) rc = launch_items_impl<2, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, queue_len, st);
-    else rc = launch_items_impl<2, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, queue_len, st);
+    if (dt == APT_F32 && hd == 64) rc = launch_items_impl<0, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
+    else if (dt == APT_F32 && hd == 128) rc = launch_items_impl<0, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
+    else if (dt == APT_F16 && hd == 64) rc = launch_items_impl<1, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
+    else if (dt == APT_F16 && hd == 128) rc = launch_items_impl<1, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
+    else if (dt == APT_BF16 && hd == 64) rc = launch_items_impl<2, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
+    else rc = launch_items_impl<2, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
     if (rc) return rc;
     if (ev_end && hipEventRecord((hipEvent_t)ev_end, st) != hipSuccess) return APT_EHIP;
 

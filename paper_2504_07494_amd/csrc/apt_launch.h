@@ -15,13 +15,12 @@ template <> int apt_launch_mfma<2>(const ItemParams& p, int n_wg, hipStream_t st
 template <> bool apt_setup_mfma<1>();
 template <> bool apt_setup_mfma<2>();
 
-// apt_raw16.hip: 16-bit inputs, hidden-kind items on the raw weights (and the KV-kind items, in the same launch);
-// queue_len = longest of the eight hidden-kind queues
-int apt_launch_raw16(const ItemParams& p, int dtype, int head_dim, int queue_len, hipStream_t st);
+// apt_raw16.hip: 16-bit inputs, hidden-kind items on the raw weights (and the KV-kind items, in the same launch)
+int apt_launch_raw16(const ItemParams& p, int dtype, int head_dim, hipStream_t st);
 bool apt_setup_raw16();
 
 // apt_raw32.hip: fp32 inputs, the same
-int apt_launch_raw32(const ItemParams& p, int head_dim, int queue_len, hipStream_t st);
+int apt_launch_raw32(const ItemParams& p, int head_dim, hipStream_t st);
 
 // apt_absorb16.hip: absorbed-weight path, 16-bit inputs
 int apt_launch_absorb_scores16(const ItemParams& p, int dtype, int head_dim, hipStream_t st);

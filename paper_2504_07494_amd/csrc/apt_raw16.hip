@@ -220,40 +220,40 @@ __device__ __forceinline__ void hidden_item_raw(const ItemParams& p, int r, int 
     }
 }
 
-// One workgroup per item.  Workgroup g runs on XCD g % 8: it takes item g / 8 of hidden queue g % 8, so that an XCD's
-// workgroups share the weights of few heads in its L2; the workgroups after 8 * queue_len take the KV-kind items.
+// One workgroup per item: the hidden-kind items as dealt to the XCDs (apt_dealt_item), then the KV-kind items.
 template <int DT, int HD>
-__global__ __launch_bounds__(kThreads, 2) void apt_items_raw_kernel(ItemParams p, int queue_len) {
+__global__ __launch_bounds__(kThreads, 2) void apt_items_raw_kernel(ItemParams p, int share) {
     extern __shared__ __align__(16) char lds[];
     const int g = blockIdx.x;
     const int4* items = (const int4*)(p.plan + p.items_off);
-    if (g < 8 * queue_len) {
-        const int i = p.plan[APT_PW_QUEUE0 + (g & 7)] + (g >> 3);
-        if (i >= p.plan[APT_PW_QUEUE0 + (g & 7) + 1]) return;
+    if (g < 8 * share) {
+        const int i = apt_dealt_item(p.plan + APT_PW_QUEUE0, share, g);
+        if (i < 0) return;
         const int4 it = items[i];
         const int n = it.w - it.z;
         if (n <= 64) hidden_item_raw<DT, HD, 64>(p, it.x, it.y, it.z, it.w, lds);
         else if (HD == 128 || n <= 128) hidden_item_raw<DT, HD, 128>(p, it.x, it.y, it.z, it.w, lds);
         else if constexpr (HD == 64) hidden_item_raw<DT, HD, 256>(p, it.x, it.y, it.z, it.w, lds);
     } else {
-        const int i = p.n_hidden_items + g - 8 * queue_len;
+        const int i = p.n_hidden_items + g - 8 * share;
         if (i >= p.n_items) return;
         const int4 it = items[i];
         kv_item<DT, HD>(p, it.x, it.y, it.z, it.w, lds);
     }
 }
 
-template <int DT, int HD> int launch(const ItemParams& p, int queue_len, hipStream_t st) {
-    const unsigned grid = 8u * queue_len + (unsigned)(p.n_items - p.n_hidden_items);
-    hipLaunchKernelGGL((apt_items_raw_kernel<DT, HD>), dim3(grid), dim3(kThreads), raw_lds_bytes<HD>(), st, p, queue_len);
+template <int DT, int HD> int launch(const ItemParams& p, hipStream_t st) {
+    const int share = (p.n_hidden_items + 7) / 8;
+    const unsigned grid = 8u * share + (unsigned)(p.n_items - p.n_hidden_items);
+    hipLaunchKernelGGL((apt_items_raw_kernel<DT, HD>), dim3(grid), dim3(kThreads), raw_lds_bytes<HD>(), st, p, share);
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
 }
 
 }  // namespace
 
-int apt_launch_raw16(const ItemParams& p, int dtype, int head_dim, int queue_len, hipStream_t st) {
-    if (dtype == APT_F16) return head_dim == 64 ? launch<1, 64>(p, queue_len, st) : launch<1, 128>(p, queue_len, st);
-    return head_dim == 64 ? launch<2, 64>(p, queue_len, st) : launch<2, 128>(p, queue_len, st);
+int apt_launch_raw16(const ItemParams& p, int dtype, int head_dim, hipStream_t st) {
+    if (dtype == APT_F16) return head_dim == 64 ? launch<1, 64>(p, st) : launch<1, 128>(p, st);
+    return head_dim == 64 ? launch<2, 64>(p, st) : launch<2, 128>(p, st);
 }
 
 bool apt_setup_raw16() {

@@ -143,39 +143,40 @@ __device__ __forceinline__ void hidden_item_f32(const ItemParams& p, int r, int 
     }
 }
 
-// grid as for the 16-bit kernel: hidden queue g % 8 (the XCD), then the KV-kind items
+// grid as for the 16-bit kernel
 template <int HD>
-__global__ __launch_bounds__(kThreads) void apt_items_f32_kernel(ItemParams p, int queue_len) {
+__global__ __launch_bounds__(kThreads) void apt_items_f32_kernel(ItemParams p, int share) {
     extern __shared__ __align__(16) char lds[];
     const int g = blockIdx.x;
     const int4* items = (const int4*)(p.plan + p.items_off);
-    if (g < 8 * queue_len) {
-        const int i = p.plan[APT_PW_QUEUE0 + (g & 7)] + (g >> 3);
-        if (i >= p.plan[APT_PW_QUEUE0 + (g & 7) + 1]) return;
+    if (g < 8 * share) {
+        const int i = apt_dealt_item(p.plan + APT_PW_QUEUE0, share, g);
+        if (i < 0) return;
         const int4 it = items[i];
         const int n = it.w - it.z;
         if (n <= 16) hidden_item_f32<HD, 1>(p, it.x, it.y, it.z, it.w, (float*)lds);
         else if (n <= 32) hidden_item_f32<HD, 2>(p, it.x, it.y, it.z, it.w, (float*)lds);
         else hidden_item_f32<HD, 4>(p, it.x, it.y, it.z, it.w, (float*)lds);
     } else {
-        const int i = p.n_hidden_items + g - 8 * queue_len;
+        const int i = p.n_hidden_items + g - 8 * share;
         if (i >= p.n_items) return;
         const int4 it = items[i];
         kv_item<0, HD>(p, it.x, it.y, it.z, it.w, lds);
     }
 }
 
-template <int HD> int launch(const ItemParams& p, int queue_len, hipStream_t st) {
+template <int HD> int launch(const ItemParams& p, hipStream_t st) {
+    const int share = (p.n_hidden_items + 7) / 8;
     constexpr int G = 4 * (64 / (HD / 4));                     // lane groups of a KV-kind item
     constexpr size_t kv_lds = (size_t)(2 * G + G * HD) * 4;
     static_assert(kv_lds >= 384 * 4, "LDS of a hidden-kind item");
-    const unsigned grid = 8u * queue_len + (unsigned)(p.n_items - p.n_hidden_items);
-    hipLaunchKernelGGL(apt_items_f32_kernel<HD>, dim3(grid), dim3(kThreads), kv_lds, st, p, queue_len);
+    const unsigned grid = 8u * share + (unsigned)(p.n_items - p.n_hidden_items);
+    hipLaunchKernelGGL(apt_items_f32_kernel<HD>, dim3(grid), dim3(kThreads), kv_lds, st, p, share);
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
 }
 
 }  // namespace
 
-int apt_launch_raw32(const ItemParams& p, int head_dim, int queue_len, hipStream_t st) {
-    return head_dim == 64 ? launch<64>(p, queue_len, st) : launch<128>(p, queue_len, st);
+int apt_launch_raw32(const ItemParams& p, int head_dim, hipStream_t st) {
+    return head_dim == 64 ? launch<64>(p, st) : launch<128>(p, st);
 }

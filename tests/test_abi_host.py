@@ -161,6 +161,47 @@ def test_absorbed_plan_has_one_hidden_item_per_range_and_the_request_maps():
             _plan(_shape(hidden_impl=ab.APT_HIDDEN_ABSORBED, **bad), lens, kinds)
 
 
+def test_hidden_items_are_dealt_once_each_and_evenly(tmp_path):
+    """apt_dealt_item over 8 * share places: every item exactly once, the same number of places per XCD, its own queue first.  Compiled
+    for the host from the library's header; queues of every head count from 1 to 26 and hand-made uneven ones."""
+    import subprocess
+    src = tmp_path / "deal.cpp"
+    src.write_text(r"""
+#include <stdio.h>
+#include "apt_internal.h"
+int main() {
+    int q[9], share;
+    while (scanf("%d", &share) == 1) {
+        for (int i = 0; i < 9; ++i)
+            if (scanf("%d", q + i) != 1) return 1;
+        for (int g = 0; g < 8 * share; ++g) printf("%d ", apt_dealt_item(q, share, g));
+        printf("\n");
+    }
+}
+""")
+    exe = tmp_path / "deal"
+    subprocess.run(["g++", "-O1", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2504_07494_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    queues = []
+    for H in range(1, 27):
+        lens, kinds = np.array([300, 17, 640, 90, 1]), np.array([1, 1, 1, 0, 1])
+        queues.append(po.plan(lens, kinds, H, 64, 512)["queue_offset"])
+    g = np.random.default_rng(3)
+    for _ in range(60):
+        queues.append([0] + np.cumsum(g.integers(0, 40, size=8) * g.integers(0, 2, size=8)).tolist())
+    queues += [[0] * 9, [0] * 8 + [5], [0, 9] + [9] * 7]
+    shares = [-(-q[8] // 8) for q in queues]
+    out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, [s, *q])) for s, q in zip(shares, queues)), text=True,
+                         capture_output=True, check=True).stdout.split("\n")
+    for q, share, line in zip(queues, shares, out):
+        got = [int(v) for v in line.split()]
+        assert len(got) == 8 * share < q[8] + 8
+        assert sorted(i for i in got if i >= 0) == list(range(q[8]))
+        for x in range(8):
+            own = got[x::8][:q[x + 1] - q[x]]
+            assert own == list(range(q[x], q[x] + len(own)))
+
+
 def test_plan_rejects_bad_arguments():
     shape = _shape()
     buf = np.zeros(1 << 16, dtype=np.int32)

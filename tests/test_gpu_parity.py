@@ -229,6 +229,50 @@ def test_absorbed_path_many_requests_pure_hidden_and_sixteen_bit_output(oracle):
     assert np.max(np.abs(got - mf)) < 1e-4
 
 
+@pytest.mark.parametrize("H,dtype", [(1, "f32"), (3, "f32"), (12, "f32"), (2, "f16"), (9, "bf16"), (12, "f16")])
+def test_raw_weight_items_dealt_over_uneven_queues(oracle, H, dtype):
+    """Head counts that leave the eight queues empty or uneven, with more items than a round of the device holds."""
+    print(f"[case] uneven queues H={H} {dtype}", flush=True)
+    g = np.random.default_rng(H)
+    lens = g.integers(1, 400, size=40).astype(np.int32)
+    kinds = (np.arange(40) % 5 != 0).astype(np.uint8)
+    cfg = wl.small_config(name="uneven", dtype=dtype, d_model=64 * H, n_heads=H, head_dim=64, block_size=16, batch=40,
+                          len_lo=1, len_hi=400, hidden_ratio=0.8)
+    batch = wl.make_batch(cfg, lens, kinds)
+    layer = wl.make_layer(batch)
+    rn, got = _run(batch, layer, hidden_chunk=16)
+    assert rn.info.n_hidden_items > 256 * min(H, 2)
+    _check(got, _full(oracle, batch, layer), f"uneven-{H}-{dtype}", 1e-5 if dtype == "f32" else 2e-4, 2e-3)
+
+
+def test_raw_weight_launch_stays_within_the_item_count(oracle):
+    """One head and 2.25 million one-token ranges: eight workgroups per item would be more threads than a launch can have.
+    All requests share one set of blocks, so the reference is one softmax per request over the same 2048 rows."""
+    print("[case] 2.25 million hidden-kind items of one head", flush=True)
+    n, B, bs, d = 2048, 1100, 16, 64
+    shape = ab.make_shape(d, 1, 64, bs, "f32", n // bs, 0.125, hidden_chunk=1)
+    lens, kinds = np.full(B, n, dtype=np.int32), np.full(B, HID, dtype=np.uint8)
+    host = torch.empty(ab.apt_plan_max_bytes(shape, B, n) // 4, dtype=torch.int32, pin_memory=True)
+    info = ab.apt_plan(shape, lens, kinds, host)
+    assert info.n_items == n * B
+    plan_dev = torch.empty(len(host), dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    rnd = lambda *dims, std=1.0: torch.randn(*dims, device="cuda", generator=g) * std
+    pool, q, W_K, W_V, b_K, b_V = rnd(n // bs, bs * d), rnd(B, 1, d), rnd(d, d, std=0.1), rnd(d, d, std=0.1), rnd(d), rnd(d)
+    tables = torch.zeros(B, 2, n // bs, dtype=torch.int32, device="cuda")
+    tables[:, 0] = torch.arange(n // bs, device="cuda")
+    out = torch.empty(B, 1, d, device="cuda")
+    ws = torch.empty(int(info.workspace_bytes), dtype=torch.uint8, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    ab.apt_plan_upload(host, plan_dev, stream)
+    ab.apt_hybrid_decode_attn(shape, host, plan_dev, q, None, None, pool, W_K, W_V, None, b_K, b_V, tables, out, ws, ws.numel(), stream)
+    x = pool.view(n, d).double()
+    k, v = x @ W_K.double() + b_K.double(), x @ W_V.double() + b_V.double()
+    want = torch.softmax(q[:, 0].double() @ k.T * 0.125, -1) @ v
+    assert torch.isfinite(out).all() and float((out[:, 0].double() - want).norm() / want.norm()) < 5e-6
+
+
 def test_mfma_and_valu_hidden_kernels_agree(oracle):
     print("[case] mfma vs valu", flush=True)
     cfg = wl.small_config(name="agree", dtype="f16", **{**MID, "batch": 3})
