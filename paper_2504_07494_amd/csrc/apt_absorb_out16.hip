@@ -10,9 +10,13 @@ namespace {
 // Workgroup = one head, 16 RF requests, one slice of d_model; its four waves take every fourth step of 32 rows and run
 // without barriers, each with its own two LDS stages: the 32 rows of W_V as they lie (read with the transposing LDS read)
 // and 32 fp32 values of YP per request.  YP is split into 16-bit parts in registers and multiplied on v_mfma_f32_16x16x32
-// (D rows = channels, columns = requests).  fp16 parts: the sums are scaled by a power of two at least as large as the
-// softmax denominator first, so that they stay in range, and the low part is kept 2^11 times larger, so that it is not
-// subnormal, in accumulators of its own.
+// (D rows = channels, columns = requests).  fp16 parts: a request's sums are scaled by a power of two that puts the largest
+// of the wave's first step at 4 to 8, so that they keep their bits whatever their magnitude; the low part is kept 2^11 times
+// larger, so that it is not subnormal, in accumulators of its own.  Where a later sum passes 2^15 (4096 times the first ones)
+// the wave does its steps again with the scale of the largest: rescaling the accumulators on the way takes registers that
+// three request fragments do not have.  Error of the outputs against 64 bits, hidden vectors of magnitude 1 / 1e-3 / 1e-4 / 1e-5, 32 heads:
+// 6.0e-7 / 1.7e-7 / 1.7e-7 / 1.5e-7 (fp32 products on the plain ALUs 6.4e-7 / 2.2e-7 / 2.3e-7 / 1.7e-7; scaled by the softmax
+// denominator only 6.0e-7 / 3.7e-7 / 3.3e-6 / 2.7e-5), at the same time.
 //
 // Bound by the reads of YP (fp32, H d_model values per unit) and of W_V, once per group of 16 RF requests: 108 us for
 // 72 heads, bf16, 96 requests at d_model 9216 (255 MB of YP, W_V twice; 142 us with a conversion of four instructions per
@@ -33,9 +37,10 @@ template <int HD> __device__ inline int out_swz(int k) {     // 32-byte units of
     return HD == 128 ? wswz(k) : ((k >> 1) & 1) | ((k >> 2) & 2);
 }
 constexpr float kLoScale = 2048.f;
+constexpr int kTopBits = 3, kRangeBits = 15;                 // scaled sums: largest at first, most
 
 template <int DT, int HD, int RF>
-__global__ __launch_bounds__(kThreads) void apt_absorb_out16_kernel(ItemParams p) {
+__global__ __launch_bounds__(kThreads, HD == 64 ? 2 : 1) void apt_absorb_out16_kernel(ItemParams p) {
     using C = OutTile<DT, HD, RF>;
     constexpr int NS = C::NS, CF = C::CF;
     extern __shared__ __align__(16) char lds[];
@@ -66,12 +71,12 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_out16_kernel(ItemParams p
     }
     // this lane's requests as columns of D
     int count[RF], most = 1;
-    float scale[RF];
+    int ex[RF];                                              // fp16: exponent of the largest sum the scale was chosen for
 #pragma unroll
     for (int f = 0; f < RF; ++f) {
         const int hr = slot_of(16 * f + l16);
         count[f] = units_of(hr);
-        scale[f] = DT == 1 ? __builtin_amdgcn_ldexpf(1.f, -__builtin_amdgcn_frexp_expf(p.ab_ml[(int64_t)hr * p.H + h].y)) : 1.f;
+        ex[f] = -100;
         most = max(most, count[f]);
     }
 #pragma unroll
@@ -98,67 +103,101 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_out16_kernel(ItemParams p
     const uint32_t yaddr[2] = {yst + l16 * 128 + (((2 * qd) ^ (l16 & 7)) << 4), yst + l16 * 128 + (((2 * qd + 1) ^ (l16 & 7)) << 4)};
 
     f32x4_t acc[C::NA][CF][RF];
-#pragma unroll
-    for (int a = 0; a < C::NA; ++a)
-#pragma unroll
-        for (int c = 0; c < CF; ++c)
-#pragma unroll
-            for (int f = 0; f < RF; ++f)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[a][c][f][e] = 0.f;
     float y[RF][8];
-    int ys = 0, ws = 0;
-    if (s_begin < s_end) {
-        issue_w(s_begin, 0);
-        issue_y(s_begin, 0, 0);
-    }
-    for (int step = s_begin; step < s_end; step += 4) {
-        for (int u = 0; u < most; ++u) {
-            // the next (step, unit) is on its way while this one is used; this wave's LDS reads of the stages it refills are done
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            if (u + 1 < most) {
-                issue_y(step, u + 1, ys ^ 1);
-                wait_vmcnt<C::kYCopies>();
-            } else if (step + 4 < s_end) {
-                issue_w(step + 4, ws ^ 1);
-                issue_y(step + 4, 0, ys ^ 1);
-                wait_vmcnt<C::kWCopies + C::kYCopies>();
-            } else {
-                wait_vmcnt<0>();
-            }
+    float top[RF];                                            // fp16: largest sum of this lane
 #pragma unroll
-            for (int f = 0; f < RF; ++f)
+    for (int f = 0; f < RF; ++f) top[f] = 0.f;
+    // whether a sum seen so far is too large for the scale; if so, the exponents of the largest ones are taken
+    auto outgrown = [&]() {
+        bool over = false;
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    float v[4];
-                    cvt16<0>(lds_read16(yaddr[i] + ys * C::kYBytes + f * 2048), v);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) y[f][4 * i + e] = (u == 0 ? 0.f : y[f][4 * i + e]) + (u < count[f] ? v[e] : 0.f);
-                }
-            ys ^= 1;
-        }
-        uint4 wf[CF];
-#pragma unroll
-        for (int c = 0; c < CF; ++c) {
-            const uint2 lo = lds_read_tr(waddr[c] + ws * C::kWBytes), hi = lds_read_tr(waddr[c] + ws * C::kWBytes + 4 * C::kWRow);
-            wf[c] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-        }
+        for (int f = 0; f < RF; ++f) over |= top[f] >= __builtin_amdgcn_ldexpf(1.f, ex[f] + kRangeBits - kTopBits);
+        if (!__any(over)) return false;
+        bool grown = false;
 #pragma unroll
         for (int f = 0; f < RF; ++f) {
-            float v[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = y[f][e] * scale[f];
-            uint4 part[NS];
-            if constexpr (DT == 1) AbSplit<DT>::split8(v, part, kLoScale);
-            else AbSplit<DT>::split8(v, part);
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-#pragma unroll
-                for (int c = 0; c < CF; ++c) acc[C::NA == 2 ? s : 0][c][f] = mfma16<DT>(wf[c], part[s], acc[C::NA == 2 ? s : 0][c][f]);
-            }
+            // the four lane groups hold a request's 32 sums of a step (an infinite one has exponent 0 here)
+            top[f] = fmaxf(top[f], __shfl_xor(top[f], 16));
+            top[f] = fmaxf(top[f], __shfl_xor(top[f], 32));
+            const int now = top[f] > 0.f ? __builtin_amdgcn_frexp_expf(top[f]) : ex[f];
+            grown |= now > ex[f];
+            ex[f] = max(ex[f], now);
         }
-        ws ^= 1;
-    }
+        return (bool)__any(grown);
+    };
+    do {
+#pragma unroll
+        for (int a = 0; a < C::NA; ++a)
+#pragma unroll
+            for (int c = 0; c < CF; ++c)
+#pragma unroll
+                for (int f = 0; f < RF; ++f)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[a][c][f][e] = 0.f;
+        int ys = 0, ws = 0;
+        if (s_begin < s_end) {
+            issue_w(s_begin, 0);
+            issue_y(s_begin, 0, 0);
+        }
+        for (int step = s_begin; step < s_end; step += 4) {
+            for (int u = 0; u < most; ++u) {
+                // the next (step, unit) is on its way while this one is used; this wave's LDS reads of the stages it refills are done
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                if (u + 1 < most) {
+                    issue_y(step, u + 1, ys ^ 1);
+                    wait_vmcnt<C::kYCopies>();
+                } else if (step + 4 < s_end) {
+                    issue_w(step + 4, ws ^ 1);
+                    issue_y(step + 4, 0, ys ^ 1);
+                    wait_vmcnt<C::kWCopies + C::kYCopies>();
+                } else {
+                    wait_vmcnt<0>();
+                }
+#pragma unroll
+                for (int f = 0; f < RF; ++f)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        float v[4];
+                        cvt16<0>(lds_read16(yaddr[i] + ys * C::kYBytes + f * 2048), v);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) y[f][4 * i + e] = (u == 0 ? 0.f : y[f][4 * i + e]) + (u < count[f] ? v[e] : 0.f);
+                    }
+                ys ^= 1;
+            }
+            if constexpr (DT == 1) {
+#pragma unroll
+                for (int f = 0; f < RF; ++f)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) top[f] = fmaxf(top[f], fabsf(y[f][e]));
+                if (step == s_begin) outgrown();
+            }
+            uint4 wf[CF];
+#pragma unroll
+            for (int c = 0; c < CF; ++c) {
+                const uint2 lo = lds_read_tr(waddr[c] + ws * C::kWBytes), hi = lds_read_tr(waddr[c] + ws * C::kWBytes + 4 * C::kWRow);
+                wf[c] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            }
+#pragma unroll
+            for (int f = 0; f < RF; ++f) {
+                uint4 part[NS];
+                if constexpr (DT == 1) {
+                    const float scale = __builtin_amdgcn_ldexpf(1.f, kTopBits - ex[f]);
+                    float v[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[e] = y[f][e] * scale;
+                    AbSplit<DT>::split8(v, part, kLoScale);
+                } else {
+                    AbSplit<DT>::split8(y[f], part);
+                }
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+#pragma unroll
+                    for (int c = 0; c < CF; ++c) acc[C::NA == 2 ? s : 0][c][f] = mfma16<DT>(wf[c], part[s], acc[C::NA == 2 ? s : 0][c][f]);
+                }
+            }
+            ws ^= 1;
+        }
+    } while (DT == 1 && outgrown());
     // the waves' sums meet in LDS, each in the wave's own stages
 #pragma unroll
     for (int c = 0; c < CF; ++c)
@@ -167,7 +206,7 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_out16_kernel(ItemParams p
             f32x4_t v = acc[0][c][f];
             if constexpr (C::NA == 2)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = fmaf(acc[1][c][f][e], 1.f / kLoScale, v[e]) * (1.f / scale[f]);
+                for (int e = 0; e < 4; ++e) v[e] = fmaf(acc[1][c][f][e], 1.f / kLoScale, v[e]) * __builtin_amdgcn_ldexpf(1.f, ex[f] - kTopBits);
             *(f32x4_t*)(lds + w * C::kWave + ((c * RF + f) * 64 + lane) * 16) = v;
         }
     __syncthreads();

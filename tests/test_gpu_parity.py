@@ -202,6 +202,41 @@ def test_absorbed_path_units_of_one_two_and_four_ranges(oracle, dtype, n_long, n
     assert np.all(np.isfinite(got))
 
 
+def _norm_error(got, want):
+    return float(np.linalg.norm(got - want) / np.linalg.norm(want))
+
+
+# Small vectors make the scores nearly equal, so only the weighted sums and their projection round: fp32 sums of n terms of
+# mixed signs, each rounding 2^-25 of the running sum on average, folded every 128: about sqrt(128 + 16) 2^-25 / 3 = 1.2e-7 of
+# the norm (8e-8 seen); twice that is allowed.  A fixed fp16 grain of 2^-36 gave 2.6e-7..3.1e-7 at 1e-4 and 2e-6 at 1e-5.
+# Vectors of ordinary size: the scores' error, 2^-24 of scores of some 10, comes on top (5e-7..7e-7 seen).
+SMALL_SUMS_LIMIT, ORDINARY_SUMS_LIMIT = 2.4e-7, 2e-6
+
+
+@pytest.mark.parametrize("hd,H,n_req", [(64, 16, 5), (128, 8, 20), (128, 8, 40), (64, 9, 33)])
+@pytest.mark.parametrize("magnitude", [1e-4, 1e-5, "growing"])
+def test_absorbed_fp16_projection_keeps_its_bits_at_any_magnitude(oracle, hd, H, n_req, magnitude):
+    """Hidden vectors far below 1, and vectors whose later components are 10^5 times the first ones (a wave's scale is chosen
+    in its first step): the fp16 parts of the weighted sums must not lose bits against fp32.  One to three request fragments."""
+    print(f"[case] small weighted sums hd={hd} H={H} n={n_req} x*{magnitude}", flush=True)
+    lens = np.array([700, 33, 1, 257, 130] + [20 + i for i in range(n_req - 5)], dtype=np.int32)
+    cfg = wl.small_config(name="smallsums", dtype="f16", d_model=hd * H, n_heads=H, head_dim=hd, block_size=16, batch=n_req,
+                          len_lo=1, len_hi=700, hidden_ratio=1.0)
+    batch = wl.make_batch(cfg, lens, np.full(n_req, HID, dtype=np.uint8))
+    layer = wl.make_layer(batch)
+    d = cfg.d_model
+    factor = np.full(d, magnitude, dtype=np.float32) if magnitude != "growing" else \
+        np.where(np.arange(d) % 256 < 128, 1e-4, np.where(np.arange(d) % 256 < 192, 1e-2, 10.0)).astype(np.float32)
+    layer.pool[...] = (layer.pool.astype(np.float32).reshape(-1, cfg.block_size, d) * factor).astype(np.float16).reshape(layer.pool.shape)
+    layer.b_V[...] = 0
+    _, got = _run(batch, layer, hidden_impl=ab.APT_HIDDEN_ABSORBED)
+    pairs = [(r, h) for r in (0, 1, 2, 3, n_req - 1) for h in (0, H // 2, H - 1)]
+    want = oracle_attn(oracle, batch, layer, pairs=pairs).reshape(len(pairs), hd)
+    err = _norm_error(np.stack([got[r, h] for r, h in pairs]), want)
+    print(f"[error] {err:.3g}", flush=True)
+    assert err < (ORDINARY_SUMS_LIMIT if magnitude == "growing" else SMALL_SUMS_LIMIT)
+
+
 def test_absorbed_path_requests_longer_than_2048_tokens(oracle):
     # more than 256 runs of 8 tokens per (request, head): the statistics kernel's second and third pass
     print("[case] absorbed long requests", flush=True)
