@@ -192,12 +192,13 @@ __device__ __forceinline__ void hidden_item_raw(const ItemParams& p, int r, int 
 #pragma unroll
         for (int t = 0; t < XF; ++t) {
             const float4 p4 = *(const float4*)(p_lds + tok_row(t) + 4 * qd);
+            const int rest = nvalid - tok_row(t) - 4 * qd;     // rows past the range: left out, not multiplied by zero (V may be infinite)
 #pragma unroll
             for (int c = 0; c < CF; ++c) {
-                o[c] = fmaf(acc[c][t][0], p4.x, o[c]);
-                o[c] = fmaf(acc[c][t][1], p4.y, o[c]);
-                o[c] = fmaf(acc[c][t][2], p4.z, o[c]);
-                o[c] = fmaf(acc[c][t][3], p4.w, o[c]);
+                o[c] = fmaf(rest > 0 ? acc[c][t][0] : 0.f, p4.x, o[c]);
+                o[c] = fmaf(rest > 1 ? acc[c][t][1] : 0.f, p4.y, o[c]);
+                o[c] = fmaf(rest > 2 ? acc[c][t][2] : 0.f, p4.z, o[c]);
+                o[c] = fmaf(rest > 3 ? acc[c][t][3] : 0.f, p4.w, o[c]);
             }
         }
         const float l = ml_lds[th * 2 + 1];
@@ -205,7 +206,7 @@ __device__ __forceinline__ void hidden_item_raw(const ItemParams& p, int r, int 
         for (int c = 0; c < CF; ++c) {
             o[c] += __shfl_xor(o[c], 16);
             o[c] += __shfl_xor(o[c], 32);
-            if (qd == 0) o_lds[th * HD + 16 * c + l16] = fmaf(l, bv_lds[16 * c + l16], o[c]);
+            if (qd == 0) o_lds[th * HD + 16 * c + l16] = l > 0.f ? fmaf(l, bv_lds[16 * c + l16], o[c]) : o[c];
         }
     }
     __syncthreads();

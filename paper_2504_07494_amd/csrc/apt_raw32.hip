@@ -121,12 +121,13 @@ __device__ __forceinline__ void hidden_item_f32(const ItemParams& p, int r, int 
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const float4 p4 = *(const float4*)(p_lds + sub * 64 + 16 * t + 4 * qd);
+            const int rest = nvalid - 16 * t - 4 * qd;         // rows past the range: left out, not multiplied by zero (V may be infinite)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                o[c] = fmaf(acc[c][t][0], p4.x, o[c]);
-                o[c] = fmaf(acc[c][t][1], p4.y, o[c]);
-                o[c] = fmaf(acc[c][t][2], p4.z, o[c]);
-                o[c] = fmaf(acc[c][t][3], p4.w, o[c]);
+                o[c] = fmaf(rest > 0 ? acc[c][t][0] : 0.f, p4.x, o[c]);
+                o[c] = fmaf(rest > 1 ? acc[c][t][1] : 0.f, p4.y, o[c]);
+                o[c] = fmaf(rest > 2 ? acc[c][t][2] : 0.f, p4.z, o[c]);
+                o[c] = fmaf(rest > 3 ? acc[c][t][3] : 0.f, p4.w, o[c]);
             }
         }
 #pragma unroll

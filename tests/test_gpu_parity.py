@@ -280,6 +280,28 @@ def test_raw_weight_items_dealt_over_uneven_queues(oracle, H, dtype):
     _check(got, _full(oracle, batch, layer), f"uneven-{H}-{dtype}", 1e-5 if dtype == "f32" else 2e-4, 2e-3)
 
 
+@pytest.mark.parametrize("dtype,hd", [("f16", 64), ("bf16", 64), ("f16", 128), ("f32", 64), ("f32", 128)])
+def test_raw_weight_kernels_leave_infinities_where_they_belong(dtype, hd):
+    """An infinite weight or bias of V makes its own output channel infinite and no other one; rows past a range and empty
+    halves of a tile must not turn it into NaN (0 * inf)."""
+    print(f"[case] infinite V {dtype} hd={hd}", flush=True)
+    H, lens = 2, np.array([1, 5, 16, 31, 33, 64, 65, 130, 257], dtype=np.int32)
+    cfg = wl.small_config(name="inf", dtype=dtype, d_model=hd * H, n_heads=H, head_dim=hd, block_size=16, batch=len(lens),
+                          len_lo=1, len_hi=257, hidden_ratio=1.0)
+    batch = wl.make_batch(cfg, lens, np.full(len(lens), HID, dtype=np.uint8))
+    layer = wl.make_layer(batch)
+    inf = {"f16": np.float16(np.inf), "bf16": np.uint16(0x7f80), "f32": np.float32(np.inf)}[dtype]
+    sign = {"f16": 0x7fff, "bf16": 0x7fff, "f32": 0x7fffffff}[dtype]
+    pool = layer.pool.view(np.uint32 if dtype == "f32" else np.uint16)
+    pool &= sign                                    # every hidden component positive: V of the channel is +inf for all tokens
+    for chunk in (0, 64):
+        layer.W_V[3, 7] = layer.b_V[hd + 2] = inf
+        _, got = _run(batch, layer, hidden_impl=ab.APT_HIDDEN_VALU, hidden_chunk=chunk)
+        got = got.reshape(batch.B, -1)
+        assert np.all(got[:, 7] == np.inf) and np.all(got[:, hd + 2] == np.inf)
+        assert np.all(np.isfinite(np.delete(got, (7, hd + 2), axis=1)))
+
+
 def test_raw_weight_launch_stays_within_the_item_count(oracle):
     """One head and 2.25 million one-token ranges: eight workgroups per item would be more threads than a launch can have.
     All requests share one set of blocks, so the reference is one softmax per request over the same 2048 rows."""
