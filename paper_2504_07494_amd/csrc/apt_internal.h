@@ -55,6 +55,7 @@ enum {
 #define APT_RAW_MAX_HIDDEN_CHUNK(dtype, hd) ((dtype) == APT_F32 ? 64 : 16384 / (hd))
 #define APT_RAW_MIN_HIDDEN_CHUNK(dtype) ((dtype) == APT_F32 ? 16 : 64)
 #define APT_RAW_ITEMS_TARGET 200
+#define APT_RAW_PLAN_HIDDEN_CHUNK 32     // a call that leaves the range open also takes a plan of this length (any length runs)
 #define APT_KV_MAX_PAGES_PER_WAVE 64
 #define APT_ABSORBED_HEAD_GROUPS 4       // absorbed-weight kernels: threads of a workgroup = 64 x 4 (token or column
 #define APT_ABSORBED_HEADS_PER_THREAD 10 // group, head group), 8 tokens/columns x 10 heads per thread

@@ -14,6 +14,7 @@
 // Scores are kept in base-2 units: s2 = softmax_scale*log2(e)*<q,k>, weights 2^(s2 - m).
 #include <stdlib.h>
 #include <string.h>
+#include <algorithm>
 #include <mutex>
 #include "apt_device.h"
 #include "apt_hybrid_bench.h"
@@ -468,7 +469,8 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
         return APT_ESHAPE;
     // hidden-kind and KV-kind range lengths: the caller's, or the planner's choice for this batch where the caller left them open
     const int hidden_chunk = pw[APT_PW_HCHUNK], kv_chunk = pw[APT_PW_KCHUNK];
-    if (rs.hidden_auto ? (hidden_chunk < APT_RAW_MIN_HIDDEN_CHUNK(rs.s.dtype) || hidden_chunk > rs.s.hidden_chunk) : hidden_chunk != rs.s.hidden_chunk)
+    const int shortest = std::min(APT_RAW_MIN_HIDDEN_CHUNK(rs.s.dtype), APT_RAW_PLAN_HIDDEN_CHUNK);
+    if (rs.hidden_auto ? (hidden_chunk < shortest || hidden_chunk > rs.s.hidden_chunk) : hidden_chunk != rs.s.hidden_chunk)
         return APT_ESHAPE;
     if (rs.kv_auto ? (kv_chunk < rs.s.kv_chunk || kv_chunk > APT_MAX_AUTO_KV_CHUNK || !apt_kv_chunk_ok(kv_chunk, rs.s.block_size))
                    : kv_chunk != rs.s.kv_chunk)

@@ -291,6 +291,20 @@ def test_attention_call_rejects_bad_arguments_before_any_launch():
     assert e.value.status == ab.APT_EWORKSPACE
 
 
+@pytest.mark.parametrize("dtype,hd,taken,refused", [("f16", 64, (32, 64, 200, 256), (1, 31)), ("bf16", 128, (32, 128), (5,)),
+                                                    ("f32", 64, (16, 32), (8, 64))])
+def test_open_hidden_chunk_takes_plans_of_32_tokens_and_of_what_the_planner_chooses(dtype, hd, taken, refused):
+    # raw weights, hidden_chunk left open in the call: such a plan passes the shape checks (the call then stops at the
+    # workspace size; no device is touched), one of another length does not
+    kw = dict(d_model=4 * hd, n_heads=4, head_dim=hd, dtype=dtype, hidden_impl=ab.APT_HIDDEN_VALU)
+    for chunk in taken + refused:
+        buf, info = _plan(_shape(hidden_chunk=chunk, **kw), [300, 40], [1, 1])
+        assert info.hidden_chunk == chunk
+        with pytest.raises(ab.AptError) as e:
+            ab.apt_hybrid_decode_attn(_shape(**kw), buf, 16, 16, 16, 16, 16, 16, 16, None, 16, 16, 16, 16, 16, 8)
+        assert e.value.status == (ab.APT_EWORKSPACE if chunk in taken else ab.APT_ESHAPE), (dtype, chunk)
+
+
 def test_static_workspace_call_rejects_bad_arguments_before_any_launch():
     # the entry point that allocates nothing validates like the ordinary one, and also refuses what its fixed
     # workspace cannot hold and the absorbed-weight path (no device is touched by any of these calls)
