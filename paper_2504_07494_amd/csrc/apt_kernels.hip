@@ -347,9 +347,11 @@ extern "C" int apt_plan_upload(const void* plan_host, void* plan_dev, void* stre
     if (capture == hipStreamCaptureStatusNone) {
         PlanWords blob;
         memcpy(blob.w, plan_host, info.plan_bytes);
-        hipLaunchKernelGGL(apt_plan_store_kernel, dim3(1), dim3(kThreads), 0, (hipStream_t)stream, (int32_t*)plan_dev, blob,
-                           (int)(info.plan_bytes / 4));
-        return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
+        // the launch's own status: like the copy, this call neither fails for an error an earlier call left nor clears it
+        int n = (int)(info.plan_bytes / 4);
+        void* args[] = {&plan_dev, &blob, &n};
+        return hipLaunchKernel((const void*)apt_plan_store_kernel, dim3(1), dim3(kThreads), args, 0, (hipStream_t)stream) == hipSuccess
+                   ? APT_OK : APT_EHIP;
     }
     if (hipMemcpyAsync(plan_dev, plan_host, info.plan_bytes, hipMemcpyHostToDevice, (hipStream_t)stream) != hipSuccess)
         return APT_EHIP;

@@ -2,6 +2,8 @@
 allocation, no synchronisation, no memset nodes), so it can be captured once and replayed.  Every
 replay is compared with the eager call on the same inputs, with eager work and synchronisations
 between the replays."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -80,3 +82,26 @@ def test_plan_upload_small_blobs_are_read_at_once_and_captured_ones_at_replay(n_
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(dev[:n].cpu(), host[:n])
+
+
+@pytest.mark.parametrize("n_requests", [1, 200])
+def test_plan_upload_is_not_disturbed_by_an_error_an_earlier_call_left(n_requests):
+    """A failed HIP call of the program leaves its error in the runtime; the upload (small blob: a launch, large blob: a copy)
+    reports its own outcome only."""
+    print(f"[case] plan upload after an error {n_requests}", flush=True)
+    shape = ab.make_shape(128, 1, 128, 16, "f16", 8, 1.0)
+    host = torch.zeros(ab.apt_plan_max_bytes(shape, n_requests, 128) // 4, dtype=torch.int32, pin_memory=True)
+    info = ab.apt_plan(shape, np.full(n_requests, 17, dtype=np.int32), np.zeros(n_requests, dtype=np.uint8), host)
+    n = int(info.plan_bytes) // 4
+    dev = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    torch.cuda.synchronize()
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    try:
+        assert hip.hipSetDevice(9999) != 0            # refused on the host
+        ab.apt_plan_upload(host, dev, stream)
+    finally:
+        hip.hipGetLastError()                         # clears it
+    torch.cuda.synchronize()
+    assert torch.equal(dev.cpu(), host[:n])
