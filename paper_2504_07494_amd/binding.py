@@ -59,19 +59,20 @@ def lib():
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python paper_2504_07494_amd/build.py` "
                                "(there is no CPU fallback)")
-        _lib = C.CDLL(LIB_PATH)
-        _lib.apt_strerror.restype = C.c_char_p
-        _lib.apt_strerror.argtypes = [C.c_int]
+        loaded = C.CDLL(LIB_PATH)
+        loaded.apt_strerror.restype = C.c_char_p
+        loaded.apt_strerror.argtypes = [C.c_int]
         for name in EXPORTS[1:] + BENCH_EXPORTS:
-            getattr(_lib, name).restype = C.c_int
-        _lib.apt_pool_destroy.restype = None
+            getattr(loaded, name).restype = C.c_int
+        loaded.apt_pool_destroy.restype = None
         # the calls of a decode step take plain addresses: ctypes converts them without an object per argument
         p, i, n = C.c_void_p, C.c_int, C.c_size_t
-        _lib.apt_plan.argtypes = [p, p, p, i, p, n, p]
-        _lib.apt_plan_upload.argtypes = [p, p, p]
-        _lib.apt_hybrid_decode_attn.argtypes = [p] * 15 + [n, p]
-        _lib.apt_cache_append.argtypes = [p, i] + [p] * 10
-        _lib.apt_cache_write.argtypes = [p, i, p, C.c_int32] + [p] * 10
+        loaded.apt_plan.argtypes = [p, p, p, i, p, n, p]
+        loaded.apt_plan_upload.argtypes = [p, p, p]
+        loaded.apt_hybrid_decode_attn.argtypes = [p] * 15 + [n, p]
+        loaded.apt_cache_append.argtypes = [p, i] + [p] * 10
+        loaded.apt_cache_write.argtypes = [p, i, p, C.c_int32] + [p] * 10
+        _lib = loaded             # published last: another thread's first call must find the argument types set
     return _lib
 
 

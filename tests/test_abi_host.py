@@ -38,6 +38,27 @@ def test_library_exports_every_declared_symbol():
     assert ab.apt_strerror(0) == "ok" and "shape" in ab.apt_strerror(ab.APT_ESHAPE)
 
 
+def test_library_is_published_only_after_its_calls_are_set_up(monkeypatch):
+    """A second thread that makes its first call while the library is being loaded must not see it without argument types
+    (a plain address would be cut to a C int)."""
+    published_early = []
+
+    class Function:
+        def __setattr__(self, name, value):
+            published_early.append(ab._lib is not None)
+
+    class Library:
+        def __getattr__(self, name):
+            return Function()
+
+    assert ab.lib() is ab.lib()
+    monkeypatch.setattr(ab, "_lib", None)
+    monkeypatch.setattr(ab.C, "CDLL", lambda path: Library())
+    loaded = ab.lib()
+    assert isinstance(loaded, Library) and ab._lib is loaded
+    assert len(published_early) > len(ab.EXPORTS) and not any(published_early)
+
+
 @pytest.mark.parametrize("himpl", [ab.APT_HIDDEN_AUTO, ab.APT_HIDDEN_VALU, ab.APT_HIDDEN_MFMA, ab.APT_HIDDEN_ABSORBED])
 def test_workspace_bound_covers_every_batch(himpl):
     """apt_workspace_bytes(max_batch, max_ctx) is at least what any batch within those limits needs, for every
