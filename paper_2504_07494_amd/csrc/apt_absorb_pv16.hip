@@ -17,8 +17,8 @@ namespace {
 //
 // Bound by memory and the matrix pipes together (X once, and NS parts of every head per column).  512 columns halve the
 // weight bytes an X byte brings along.  256 are taken where three stages then fit in half of LDS (fp16 up to 80 heads, bf16 up
-// to 48), so that one workgroup's start-up and stores are covered by the other's loop, where the stages of 512 do not fit at
-// all, and in batches that would leave CUs without a unit.
+// to 48), so that one workgroup's start-up and stores are covered by the other's loop, where the stages or accumulators of 512 do
+// not fit at all, and in batches that would leave CUs without a unit.
 //
 // 72 heads, bf16, 96 requests with 102 k tokens at d_model 9216 (1.9 GB of X): 480-520 us, 1200 us with heads padded to 128
 // in two passes over X, a 16-bit gather per operand and sums per 512-token range.  40 heads, fp16, 33.6 k tokens at
@@ -38,7 +38,9 @@ template <int DT, int NF, int CW> struct PvTile {
     static constexpr int kPCopies = (kPBytes / 1024 + kAbWaves - 1) / kAbWaves;
     static constexpr int kCopies = kXCopies + kPCopies;
     static constexpr int CF = CW / kAbWaves / 16;                  // column fragments of a wave
-    static constexpr bool kFits = S >= 3;
+    // stages in LDS, and both accumulator sets in the 256 registers of a wave (two per SIMD) with room for the rest: 8 head
+    // fragments x 512 columns would need all 256 (103 spilled; fp16, 112 heads of 128, 48 requests 1366 us, 1066 with 256 columns)
+    static constexpr bool kFits = S >= 3 && 2 * NF * CF * 4 <= 192;
     static_assert((S - 2) * kCopies <= 63, "vmcnt range");
 };
 constexpr int kPvBlkBytes = APT_ABSORBED_MAX_GROUP * APT_ABSORBED_CHUNK / 4 * 4;      // block ids of a unit, blocks of 4 tokens at least

@@ -59,6 +59,46 @@ def test_library_is_published_only_after_its_calls_are_set_up(monkeypatch):
     assert len(published_early) > len(ab.EXPORTS) and not any(published_early)
 
 
+def _kernel_metadata():
+    """{kernel name: metadata} of the device code in the built library: its offload bundles (magic, count, then offset, size,
+    triple of each entry), the AMDGPU note of each code object (msgpack)."""
+    import msgpack
+    import struct
+    lib, magic, kernels = open(ab.LIB_PATH, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", {}
+    at = lib.find(magic)
+    while at >= 0:
+        pos = at + len(magic) + 8
+        for _ in range(struct.unpack_from("<Q", lib, at + len(magic))[0]):
+            off, size, n = struct.unpack_from("<QQQ", lib, pos)
+            triple = lib[pos + 24:pos + 24 + n]
+            pos += 24 + n
+            elf = lib[at + off:at + off + size]
+            if b"gfx950" not in triple or not elf.startswith(b"\x7fELF"):
+                continue
+            sh_off, (sh_size, sh_n) = struct.unpack_from("<Q", elf, 40)[0], struct.unpack_from("<HH", elf, 58)
+            for i in range(sh_n):
+                kind, _, _, o, length = struct.unpack_from("<IQQQQ", elf, sh_off + i * sh_size + 4)
+                if kind != 7:                                    # SHT_NOTE
+                    continue
+                name_len, desc_len, note = struct.unpack_from("<III", elf, o)
+                if note == 32:                                   # NT_AMDGPU_METADATA
+                    desc = o + 12 + (name_len + 3) // 4 * 4
+                    for k in msgpack.unpackb(elf[desc:desc + desc_len])["amdhsa.kernels"]:
+                        kernels[k[".name"]] = k
+        at = lib.find(magic, at + 1)
+    return kernels
+
+
+def test_kernels_with_counted_copies_do_not_spill():
+    """The waits of these kernels count the global -> LDS copies in flight; a spilled register's reload is one more memory
+    operation among them and its wait drains the copies.  (The packed-weight kernel keeps its reloads out of its k loop.)"""
+    kernels = {n: k for n, k in _kernel_metadata().items() if re.search(r"apt_absorb_(score16|pv16|out16|q16)_kernel|apt_items_(raw|f32)_kernel", n)}
+    assert len(kernels) >= 60
+    spilled = {n: (k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for n, k in kernels.items()
+               if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
+    assert not spilled, spilled
+
+
 @pytest.mark.parametrize("himpl", [ab.APT_HIDDEN_AUTO, ab.APT_HIDDEN_VALU, ab.APT_HIDDEN_MFMA, ab.APT_HIDDEN_ABSORBED])
 def test_workspace_bound_covers_every_batch(himpl):
     """apt_workspace_bytes(max_batch, max_ctx) is at least what any batch within those limits needs, for every
