@@ -26,6 +26,13 @@ against it bit for bit:
   that consists of whole blocks, at most 256 of them, and with which the KV-kind
   requests of the batch still make at least 2048 items (ranges x heads); 512 if neither
   of the longer ones does (auto_kv_chunk below).
+* when the caller leaves hidden_chunk open and K and V are projected from the raw weights, it is the longest of the lengths
+  below with which the hidden-kind requests of the batch make at least 200 items (ranges x heads), the shortest if none does:
+  fp32 inputs 32 or 16 tokens; 16-bit inputs 256 (head_dim 64 only), 128 or 64 (auto_hidden_chunk below).
+* the absorbed-weight path adds two lists (absorbed_lists below).  Tiles: every hidden-kind item is cut into tiles of 256
+  tokens, one or two; a tile is the word 2 * item + (0 or 1), in item order.  Units: 1, 2 or 4 neighbouring ranges of one
+  request are summed together, the most with which the batch still has 768 units x ceil(d_model / 512) column slices (fp32
+  inputs, and batches that never have: 1); a unit is the word of its first item, longest unit first, ties in item order.
 
 Block arithmetic of the cache map (Section 4.3): token j of a request lives in
 its (j // block_size)-th block at slot j % block_size; a request of n tokens owns
@@ -50,6 +57,35 @@ def auto_kv_chunk(ctx_lens, cache_kind, n_heads, block_size):
         if sum(ceil_div(n, c) for n in kv_lens) * n_heads >= 2048:
             return c
     return 512
+
+
+def auto_hidden_chunk(ctx_lens, cache_kind, n_heads, dtype, head_dim):
+    """The range length of hidden-kind requests with raw weights when the caller does not fix it."""
+    hid_lens = [int(n) for n, k in zip(ctx_lens, cache_kind) if int(k) == KIND_HIDDEN]
+    choices = (32, 16) if dtype == "f32" else (256, 128, 64) if head_dim == 64 else (128, 64)
+    for c in choices:
+        if sum(ceil_div(n, c) for n in hid_lens) * n_heads >= 200:
+            return c
+    return choices[-1]
+
+
+def absorbed_lists(ctx_lens, cache_kind, d_model, dtype):
+    """(tiles, ranges per unit, units) of the absorbed-weight path; items are its 512-token ranges by request."""
+    hid = [r for r in range(len(ctx_lens)) if int(cache_kind[r]) == KIND_HIDDEN]
+    ranges = [(r, t0) for r in hid for t0 in range(0, int(ctx_lens[r]), 512)]
+    tiles = []
+    for i, (r, t0) in enumerate(ranges):
+        tiles.append(2 * i)
+        if int(ctx_lens[r]) - t0 > 256:
+            tiles.append(2 * i + 1)
+    group = 1
+    if dtype != "f32":
+        for g in (2, 4):
+            if sum(ceil_div(int(ctx_lens[r]), 512 * g) for r in hid) * ceil_div(d_model, 512) >= 768:
+                group = g
+    units = [i for i, (r, t0) in enumerate(ranges) if t0 % (512 * group) == 0]
+    units.sort(key=lambda i: -min(512 * group, int(ctx_lens[ranges[i][0]]) - ranges[i][1]))
+    return tiles, group, units
 
 
 def plan(ctx_lens, cache_kind, n_heads, hidden_chunk, kv_chunk, hidden_item_per_head=True):

@@ -263,6 +263,69 @@ int main() {
             assert own == list(range(q[x], q[x] + len(own)))
 
 
+@pytest.mark.parametrize("dtype,hd", [("f32", 64), ("f32", 128), ("f16", 64), ("bf16", 128)])
+def test_hidden_range_length_left_open_follows_the_batch(dtype, hd):
+    """hidden_chunk = 0 with raw weights: the longest length that gives 200 hidden-kind items, around every switch and for
+    random batches, with the plan itself; lengths the caller fixes are taken as they are."""
+    top = {("f32", 64): 32, ("f32", 128): 32, ("f16", 64): 256, ("bf16", 128): 128}[dtype, hd]
+    g = np.random.default_rng(hd)
+    H = 10
+    cases = []
+    c = top
+    least = 16 if dtype == "f32" else 64
+    while c >= least:
+        # 20 ranges of 10 heads, 20 with the last of one token, 19
+        cases += [([20 * c], [1], c), ([19 * c + 1, 9 * c], [1, 0], c), ([19 * c], [1], max(c // 2, least))]
+        c //= 2
+    for _ in range(20):
+        B = int(g.integers(1, 30))
+        cases.append((g.integers(1, 700, size=B).tolist(), g.integers(0, 2, size=B).tolist(), None))
+    shape = _shape(d_model=H * hd, n_heads=H, head_dim=hd, dtype=dtype, hidden_impl=ab.APT_HIDDEN_VALU, max_blocks_per_req=320)
+    for i, (lens, kinds, want) in enumerate(cases):
+        buf, info = _plan(shape, lens, kinds)
+        assert info.hidden_chunk == po.auto_hidden_chunk(lens, kinds, H, dtype, hd), (i, lens)
+        assert want is None or info.hidden_chunk == want
+        assert ab.decode_plan(buf) == po.plan(lens, kinds, H, info.hidden_chunk, info.kv_chunk)
+    _, info = _plan(_shape(d_model=H * hd, n_heads=H, head_dim=hd, dtype=dtype, hidden_impl=ab.APT_HIDDEN_VALU, hidden_chunk=17), [700], [1])
+    assert info.hidden_chunk == 17
+
+
+@pytest.mark.parametrize("dtype,H,hd", [("f32", 4, 64), ("f32", 1, 128), ("f16", 3, 64), ("bf16", 7, 128)])
+def test_workspace_bound_of_small_batches_with_an_open_hidden_range(dtype, H, hd):
+    """Few requests: the planner goes below the longest range, so there are more partials than of that length.  Every mix of
+    kinds of one to three requests, lengths up to the limit."""
+    shape = _shape(d_model=H * hd, n_heads=H, head_dim=hd, dtype=dtype, hidden_impl=ab.APT_HIDDEN_VALU, max_blocks_per_req=64)
+    top = 32 if dtype == "f32" else 16384 // hd
+    shorter = False
+    for B in (1, 2, 3):
+        for max_ctx in (64, 130, 700, 1024):
+            dev, host = ab.apt_workspace_bytes(shape, B, max_ctx)
+            for kinds in range(1 << B):
+                for n in {1, max_ctx // 2 + 1, max_ctx}:
+                    lens = [max_ctx] + [n] * (B - 1)
+                    buf, info = _plan(shape, lens, [kinds >> i & 1 for i in range(B)])
+                    assert info.workspace_bytes <= dev and info.plan_bytes <= host
+                    shorter |= info.workspace_bytes > B * -(-max_ctx // top) * H * (hd + 2) * 4
+    assert shorter                        # some batch needs more than ranges of the longest length would
+
+
+@pytest.mark.parametrize("dtype,d_model,H,seed", [("f16", 5120, 40, 1), ("bf16", 4160, 65, 2), ("f16", 2048, 16, 3), ("f32", 640, 10, 4)])
+def test_absorbed_plan_lists_tiles_and_units(dtype, d_model, H, seed):
+    """The lists behind the items: batches whose units hold 1, 2 and 4 ranges, lengths around the ends of tiles and units."""
+    g = np.random.default_rng(seed)
+    shape = _shape(d_model=d_model, n_heads=H, head_dim=d_model // H, dtype=dtype, hidden_impl=ab.APT_HIDDEN_ABSORBED, max_blocks_per_req=256)
+    edges = [1, 255, 256, 257, 511, 512, 513, 768, 769, 1024, 1025, 2047, 2048, 2049, 2561, 4096]
+    groups = set()
+    for B in (1, 7, 40, 65, 70, 75, 80, 130, 165, 200, 400):
+        lens, kinds = g.choice(edges, size=B), (g.random(B) < 0.8).astype(np.uint8)
+        buf, info = _plan(shape, lens, kinds)
+        tiles, group, units = po.absorbed_lists(lens, kinds, d_model, dtype)
+        w = buf[:info.plan_bytes // 4]
+        assert w[-2 - len(tiles) - len(units):].tolist() == [len(tiles), group, *tiles, *units]
+        groups.add(group)
+    assert groups == ({1} if dtype == "f32" else {1, 2, 4})
+
+
 def test_plan_rejects_bad_arguments():
     shape = _shape()
     buf = np.zeros(1 << 16, dtype=np.int32)

@@ -183,6 +183,29 @@ def test_absorbed_path_head_fragment_counts(oracle, dtype, H):
     assert np.all(np.isfinite(got))
 
 
+@pytest.mark.parametrize("dtype,H,n_hid", [("bf16", 50, 40), ("bf16", 72, 32), ("bf16", 83, 30), ("f16", 83, 60), ("f16", 98, 30)])
+def test_absorbed_path_batches_wide_enough_for_512_columns(oracle, dtype, H, n_hid):
+    """Enough units for the 512-column form of the weighted sums (4, 5 and 6 head fragments bf16, 6 fp16; 8 stay with 256), a last
+    column slice that is partly past d_model, units around the ends of 512, 1024 and 2048 tokens, and 64-wide heads with
+    two and three request fragments (and two groups of them) in the output projection."""
+    print(f"[case] absorbed 512 columns {dtype} H={H} n={n_hid}", flush=True)
+    lens = np.array([2048, 2047, 1025, 1024, 513, 511] + [1 + 7 * i % 90 for i in range(n_hid - 6)] + [100], dtype=np.int32)
+    kinds = np.array([HID] * n_hid + [KV], dtype=np.uint8)
+    d = H * 64
+    cfg = wl.small_config(name="wide", dtype=dtype, d_model=d, n_heads=H, head_dim=64, block_size=16, batch=len(lens),
+                          len_lo=1, len_hi=2048, hidden_ratio=1.0, permute_pages=True)
+    batch = wl.make_batch(cfg, lens, kinds)
+    layer = wl.make_layer(batch)
+    rn, got = _run(batch, layer, hidden_impl=ab.APT_HIDDEN_ABSORBED)
+    w = rn.plan_host.numpy()
+    n_units = int(w[15]) - (int(w[31]) + 2 + int(w[w[31]]))      # words of the blob behind the tiles
+    assert n_units * -(-d // 512) >= torch.cuda.get_device_properties(0).multi_processor_count
+    pairs = [(r, h) for r in (0, 1, 2, 3, 4, 5, 6, 16, 17, n_hid // 2, n_hid - 1) for h in (0, H // 2, H - 1)]
+    want = oracle_attn(oracle, batch, layer, pairs=pairs).reshape(len(pairs), 64)
+    _check(np.stack([got[r, h] for r, h in pairs]), want, f"wide-{dtype}-{H}", 2e-4, 2e-3)
+    assert np.all(np.isfinite(got))
+
+
 @pytest.mark.parametrize("dtype,n_long,n_short", [("f16", 5, 190), ("bf16", 8, 180), ("f16", 3, 100), ("bf16", 2, 5)])
 def test_absorbed_path_units_of_one_two_and_four_ranges(oracle, dtype, n_long, n_short):
     """Weighted sums over units of 4, 2, 1 and 1 ranges (16 heads: 256 columns, two workgroups per CU), lengths around the ends
@@ -211,6 +234,7 @@ def _norm_error(got, want):
 # the norm (8e-8 seen); twice that is allowed.  A fixed fp16 grain of 2^-36 gave 2.6e-7..3.1e-7 at 1e-4 and 2e-6 at 1e-5.
 # Vectors of ordinary size: the scores' error, 2^-24 of scores of some 10, comes on top (5e-7..7e-7 seen).
 SMALL_SUMS_LIMIT, ORDINARY_SUMS_LIMIT = 2.4e-7, 2e-6
+
 
 
 @pytest.mark.parametrize("hd,H,n_req", [(64, 16, 5), (128, 8, 20), (128, 8, 40), (64, 9, 33)])
