@@ -86,7 +86,7 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_q16_kernel(ItemParams p) 
 // stages, with more bytes in flight, 99 us.  The version with heads padded to 64, an accumulator per part and 512-wide
 // slices took 117 us there, and 1193 us against 594 us now for 72 heads, bf16, 102 k tokens at d_model 9216.
 template <int DT, int NF, int F0, int FN, typename Issue>
-__device__ __forceinline__ void score_loop(f32x4_t (*acc)[4], f32x4_t (*sum)[4], uint32_t lds0, int tg, int nkt, Issue issue) {
+__device__ __forceinline__ void score_loop(f32x4_t (*acc)[4], f32x4_t (*sum)[4], f32x4_t (*total)[4], uint32_t lds0, int tg, int nkt, Issue issue) {
     using C = AbTile<DT, NF>;
     constexpr int NS = C::NS, KT = C::KT, S = C::S;
     const int lane = threadIdx.x & 63, l16 = lane & 15, qd = lane >> 4;
@@ -114,8 +114,10 @@ __device__ __forceinline__ void score_loop(f32x4_t (*acc)[4], f32x4_t (*sum)[4],
         }
         stage = stage == S - 1 ? 0 : stage + 1;
         if ((kt + 1) % (kAbFold / KT) == 0) ab_fold<4>(acc, sum, FN);
+        if ((kt + 1) % (kAbFoldSums / KT) == 0) ab_fold<4>(sum, total, FN);
     }
     ab_fold<4>(acc, sum, FN);
+    ab_fold<4>(sum, total, FN);
 }
 
 template <int DT, int NF>
@@ -157,18 +159,18 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemP
             gload_lds16(asrc + (int64_t)kt * C::kABytes + n * 1024, st + C::kXBytes + n * 1024);
         }
     };
-    f32x4_t acc[NF0][4], sum[NF0][4];
+    f32x4_t acc[NF0][4], sum[NF0][4], total[NF0][4];
 #pragma unroll
     for (int f = 0; f < NF0; ++f)
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[f][t][e] = sum[f][t][e] = 0.f;
+            for (int e = 0; e < 4; ++e) acc[f][t][e] = sum[f][t][e] = total[f][t][e] = 0.f;
 #pragma unroll
     for (int s = 0; s < S - 1; ++s)
         if (s < nkt) issue(s);
-    if (!second) score_loop<DT, NF, 0, NF0>(acc, sum, lds0, tg, nkt, issue);
-    else score_loop<DT, NF, NF0, NF - NF0>(acc, sum, lds0, tg, nkt, issue);
+    if (!second) score_loop<DT, NF, 0, NF0>(acc, sum, total, lds0, tg, nkt, issue);
+    else score_loop<DT, NF, NF0, NF - NF0>(acc, sum, total, lds0, tg, nkt, issue);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         const int token = 64 * tg + 16 * t + l16;
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemP
             for (int e = 0; e < 4; ++e) {
                 const int h = 16 * (second * NF0 + f) + 4 * qd + e;
                 if ((f < NF - NF0 || !second) && h < p.H)
-                    p.ab_s[((int64_t)slice * p.H + h) * p.ab_tokens + tok0 + token] = sum[f][t][e];
+                    p.ab_s[((int64_t)slice * p.H + h) * p.ab_tokens + tok0 + token] = total[f][t][e];
             }
     }
 }

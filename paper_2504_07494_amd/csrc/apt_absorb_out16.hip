@@ -18,13 +18,13 @@ namespace {
 // 6.0e-7 / 1.7e-7 / 1.7e-7 / 1.5e-7 (fp32 products on the plain ALUs 6.4e-7 / 2.2e-7 / 2.3e-7 / 1.7e-7; scaled by the softmax
 // denominator only 6.0e-7 / 3.7e-7 / 3.3e-6 / 2.7e-5), at the same time.
 //
-// Bound by the reads of YP (fp32, H d_model values per unit) and of W_V, once per group of 16 RF requests: 108 us for
-// 72 heads, bf16, 96 requests at d_model 9216 (255 MB of YP, W_V twice; 142 us with a conversion of four instructions per
-// value and part, 480 us on the plain ALUs, whose output partials per 256 rows took the last kernel another 30 us), 28 us for
-// 40 heads, fp16, 32 requests (70 us).
+// Bound by the reads of YP (fp32, H d_model values per unit) and of W_V, once per group of 16 RF requests: 114-125 us for
+// 72 heads, bf16, 96 requests at d_model 9216 (255 MB of YP, W_V twice; 108 us without folding the sums, 480 us on the plain
+// ALUs, whose output partials per 256 rows took the last kernel another 30 us), 28 us for 40 heads, fp16, 32 requests (70 us).
 template <int DT, int HD, int RF> struct OutTile {
     static constexpr int NS = AbSplit<DT>::parts;
     static constexpr int NA = DT == 1 ? 2 : 1;              // accumulator sets
+    static constexpr bool kFolded = DT == 2;                // long sums folded (kAbFold); the two fp16 sets leave no registers for it
     static constexpr int CF = HD / 16;
     static constexpr int kWRow = HD * 2;
     static constexpr int kWBytes = 32 * kWRow;
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kThreads, HD == 64 ? 2 : 1) void apt_absorb_out16_k
     }
     const uint32_t yaddr[2] = {yst + l16 * 128 + (((2 * qd) ^ (l16 & 7)) << 4), yst + l16 * 128 + (((2 * qd + 1) ^ (l16 & 7)) << 4)};
 
-    f32x4_t acc[C::NA][CF][RF];
+    f32x4_t acc[C::NA][CF][RF], sum[C::kFolded ? CF : 1][RF];
     float y[RF][8];
     float top[RF];                                            // fp16: largest sum of this lane
 #pragma unroll
@@ -134,6 +134,13 @@ __global__ __launch_bounds__(kThreads, HD == 64 ? 2 : 1) void apt_absorb_out16_k
                 for (int f = 0; f < RF; ++f)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) acc[a][c][f][e] = 0.f;
+        if constexpr (C::kFolded)
+#pragma unroll
+            for (int c = 0; c < CF; ++c)
+#pragma unroll
+                for (int f = 0; f < RF; ++f)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[c][f][e] = 0.f;
         int ys = 0, ws = 0;
         if (s_begin < s_end) {
             issue_w(s_begin, 0);
@@ -196,6 +203,8 @@ __global__ __launch_bounds__(kThreads, HD == 64 ? 2 : 1) void apt_absorb_out16_k
                 }
             }
             ws ^= 1;
+            if constexpr (C::kFolded)
+                if ((step - s_begin) % (4 * kAbFold / 32) == 4 * (kAbFold / 32 - 1)) ab_fold<RF>(acc[0], sum, CF);
         }
     } while (DT == 1 && outgrown());
     // the waves' sums meet in LDS, each in the wave's own stages
@@ -204,6 +213,7 @@ __global__ __launch_bounds__(kThreads, HD == 64 ? 2 : 1) void apt_absorb_out16_k
 #pragma unroll
         for (int f = 0; f < RF; ++f) {
             f32x4_t v = acc[0][c][f];
+            if constexpr (C::kFolded) v += sum[c][f];
             if constexpr (C::NA == 2)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] = fmaf(acc[1][c][f][e], 1.f / kLoScale, v[e]) * __builtin_amdgcn_ldexpf(1.f, ex[f] - kTopBits);

@@ -75,11 +75,17 @@ static inline int ab_head_frags(int H) {
 }
 
 // Long fp32 sums on the matrix cores round at the size of the running sum, once per part and 32 k: every kAbFold k the
-// accumulators are added to a second set and cleared, so that the sum is one of short sums.  Error of the outputs against
-// 64 bits with an accumulator per part over 512 k / one run over a slice or unit / folded every 512 / 256 / 128 k: 40 heads,
-// fp16, 32 requests of 128..2048 tokens 9.3e-7 / 1.23e-6 / 9.6e-7 / 9.2e-7 / 9.05e-7; bf16, 8 requests 4.1e-7 / - / 5.4e-7 /
-// 4.2e-7 / 3.7e-7; 72 heads, bf16, 6 requests 5.3e-7 / - / 6.8e-7 / 5.6e-7 / 5.3e-7.
+// accumulators are added to a second set and cleared, so that the sum is one of short sums.  Scores of large batches run over
+// all of d_model in one slice: their second set goes into a third every kAbFoldSums k.  Error of the hidden-kind outputs
+// against 64 bits: an accumulator per part over 512 k, those added in fp32, projection on the plain ALUs / two sets in the scores,
+// none in the bf16 projection / as it is:
+//     72 heads, 96 requests of 64..2048 tokens, bf16    5.1e-7  / 7.7e-7  / 4.9e-7      fp16  1.15e-6 / 1.26e-6 / 1.15e-6
+//     55 heads, 169 requests of 15..79, bf16            3.5e-7  / 5.3e-7  / 3.0e-7
+//     40 heads, 32 requests of 128..2048, bf16          4.0e-7  / 3.75e-7 / 3.4e-7      fp16  9.2e-7  / 9.0e-7  / 8.9e-7
+//     geometric mean of 52 batches, bf16                3.9e-7  / 3.8e-7  / 3.4e-7
+// The third set costs no time; the folded projection 10 us of 1420 (first line; 64 instead of 128 everywhere: another 30).
 constexpr int kAbFold = 128;
+constexpr int kAbFoldSums = 512;
 
 template <int N> __device__ inline void ab_fold(f32x4_t (*acc)[N], f32x4_t (*sum)[N], int rows) {
 #pragma unroll

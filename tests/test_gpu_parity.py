@@ -234,7 +234,10 @@ def _norm_error(got, want):
 # the norm (8e-8 seen); twice that is allowed.  A fixed fp16 grain of 2^-36 gave 2.6e-7..3.1e-7 at 1e-4 and 2e-6 at 1e-5.
 # Vectors of ordinary size: the scores' error, 2^-24 of scores of some 10, comes on top (5e-7..7e-7 seen).
 SMALL_SUMS_LIMIT, ORDINARY_SUMS_LIMIT = 2.4e-7, 2e-6
-
+# Error of the same sums with an accumulator per operand part over 512 terms, the sums of 512 added in fp32 and the projection
+# in fp32 on the plain ALUs: folding and sharing accumulators must not cost bits against that.
+LONG_SUMS_LIMIT = {("f16", "long"): 7.8e-7, ("f16", "long small"): 2.7e-7, ("f16", "wide"): 7.2e-7,
+                   ("bf16", "long"): 4.0e-7, ("bf16", "long small"): 2.4e-7, ("bf16", "wide"): 3.1e-7}
 
 
 @pytest.mark.parametrize("hd,H,n_req", [(64, 16, 5), (128, 8, 20), (128, 8, 40), (64, 9, 33)])
@@ -259,6 +262,29 @@ def test_absorbed_fp16_projection_keeps_its_bits_at_any_magnitude(oracle, hd, H,
     err = _norm_error(np.stack([got[r, h] for r, h in pairs]), want)
     print(f"[error] {err:.3g}", flush=True)
     assert err < (ORDINARY_SUMS_LIMIT if magnitude == "growing" else SMALL_SUMS_LIMIT)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("shape", ["long", "long small", "wide"])
+def test_absorbed_path_error_of_long_sums(oracle, dtype, shape):
+    """Norm of the error over long sums.  long: 4096 components, units of four ranges of 512 tokens, also with vectors of 1e-4
+    (equal weights: the weighted sums and the projection alone).  wide: 170 short requests, so many tiles that a score runs over
+    all 5120 components in one slice.  What keeps it here: all parts of the split operands, and running sums folded."""
+    print(f"[case] absorbed error {dtype} {shape}", flush=True)
+    H, lens = (40, [15 + 7 * i % 65 for i in range(170)]) if shape == "wide" else (32, [2048, 2049, 1900] + [1 + i % 3 for i in range(94)])
+    cfg = wl.small_config(name="longsums", dtype=dtype, d_model=128 * H, n_heads=H, head_dim=128, block_size=16, batch=len(lens),
+                          len_lo=1, len_hi=2049, hidden_ratio=1.0)
+    batch = wl.make_batch(cfg, np.array(lens, dtype=np.int32), np.full(len(lens), HID, dtype=np.uint8))
+    layer = wl.make_layer(batch)
+    if shape == "long small":
+        layer.pool[...] = wl.round_to_dtype((wl.to_f64(layer.pool, dtype) * 1e-4).astype(np.float32), dtype).reshape(layer.pool.shape)
+        layer.b_V[...] = 0
+    _, got = _run(batch, layer, hidden_impl=ab.APT_HIDDEN_ABSORBED)
+    pairs = [(r, h) for r in range(0, 170, 7) for h in (3, 20, 39)] if shape == "wide" else [(0, 0), (0, 31), (1, 16), (2, 5)]
+    want = oracle_attn(oracle, batch, layer, pairs=pairs).reshape(len(pairs), 128)
+    err = _norm_error(np.stack([got[r, h] for r, h in pairs]), want)
+    print(f"[error] {err:.3g}", flush=True)
+    assert err < LONG_SUMS_LIMIT[dtype, shape]
 
 
 def test_absorbed_path_requests_longer_than_2048_tokens(oracle):
