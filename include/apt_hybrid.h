@@ -76,6 +76,7 @@ typedef enum apt_status {
 
 enum { APT_F32 = 0, APT_F16 = 1, APT_BF16 = 2 };
 enum { APT_KIND_KV = 0, APT_KIND_HIDDEN = 1 };
+/* VALU: raw weights (the name is from its first, plain-ALU kernels); MFMA: packed weights; both use the matrix cores */
 enum { APT_HIDDEN_AUTO = 0, APT_HIDDEN_VALU = 1, APT_HIDDEN_MFMA = 2, APT_HIDDEN_ABSORBED = 3 };
 
 typedef struct apt_shape {
@@ -255,8 +256,9 @@ int apt_pack_weights(const apt_shape* s, const void* W_K, const void* W_V, void*
  *   workspace   device, at least info.workspace_bytes bytes; holds the per-range
  *               partial results (running maximum, sum, un-normalised output) that the
  *               merge kernel combines; contents are undefined afterwards
- * Two kernels are enqueued on `stream`: the item kernel (one workgroup per work item,
- * hidden-kind and KV-kind items in the same launch) and the merge kernel.
+ * Two kernels are enqueued on `stream`: the item kernel (hidden-kind and KV-kind items in the
+ * same launch) and the merge kernel; with APT_HIDDEN_ABSORBED the hidden-kind requests take six
+ * kernels of their own before it.
  * Errors: APT_EINVAL (null pointer that is needed), APT_EWORKSPACE, APT_ESHAPE,
  * APT_EDTYPE, APT_EHIP (launch failure; nothing is written in the other cases).
  */
@@ -273,7 +275,9 @@ int apt_hybrid_decode_attn(const apt_shape* s, const void* plan_host, void* plan
  * out = (sum_j a_j x_j) W_V[:, h] + b_V[h].  The cached hidden rows are then read twice (scores,
  * weighted sum) like the K and V rows of a KV-kind request, and the two projections shrink to one
  * matrix-vector product per request and head.  Work per hidden token: 4 * d_model * n_heads flops
- * instead of 4 * d_model^2.  Results agree with the other implementations to fp32 rounding.  Needs
+ * instead of 4 * d_model^2.  Results agree with the other implementations to fp32 rounding for finite
+ * inputs (16-bit operands of the sums are split into parts, so an infinite weight or hidden component gives NaN where the
+ * others may give an infinity; fp16: |scale * log2(e) * W_K q| must stay below 65504).  Needs
  * the raw W_K, W_V (not W_packed), d_model a multiple of 32, n_heads <= 128 (fp32 inputs: <= 40), and a larger workspace
  * (apt_plan_info.workspace_bytes says how much); hidden_chunk must be 0 or 512.
  */

@@ -81,9 +81,10 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_q16_kernel(ItemParams p) 
 // accumulator.  k-tiles of X rows and of QT go global -> LDS without registers, as many stages as LDS holds (one
 // workgroup per CU).
 //
-// Bound by how memory serves the X rows, one 128-byte line per row and k-tile (rows lie 2 d_model apart): 64-wide k-tiles
-// in three stages take 87 us for 40 heads, fp16, 33.6 k tokens at d_model 5120 (344 MB of X), 32-wide ones in seven
-// stages, with more bytes in flight, 99 us.  The version with heads padded to 64, an accumulator per part and 512-wide
+// Bound by how memory serves the X rows, one 128-byte line per row and 64 k (rows lie 2 d_model apart): 64-wide k-tiles
+// in three stages take 87 us for 40 heads, fp16, 33.6 k tokens at d_model 5120 (344 MB of X; 0.40 GB of 128-byte line reads, 4.5
+// TB/s), 32-wide ones in seven stages, with more bytes in flight, 99 us.  72 heads, bf16, have room for 32-wide ones only: the two
+// halves of a line are joined in L2 (2.80 GB of line reads where X and the queries are 2.31 GB, 4.5 TB/s).  The version with heads padded to 64, an accumulator per part and 512-wide
 // slices took 117 us there, and 1193 us against 594 us now for 72 heads, bf16, 102 k tokens at d_model 9216.
 template <int DT, int NF, int F0, int FN, typename Issue>
 __device__ __forceinline__ void score_loop(f32x4_t (*acc)[4], f32x4_t (*sum)[4], f32x4_t (*total)[4], uint32_t lds0, int tg, int nkt, Issue issue) {

@@ -25,13 +25,13 @@ struct ItemParams {
     float scale_log2e;
     int32_t item_base;            // one-workgroup-per-item launch: first item of the grid
     // absorbed-weight hidden path: workspace sections (fp32)
-    float* ab_qt;                 // [n_hid_req][H][d]
+    float* ab_qt;                 // [n_hid_req][H][d], 16-bit inputs: parts in the score kernel's order
     float* ab_cb;                 // [n_hid_req][H]
-    float* ab_s;                  // [KS][H][ab_tokens] partial scores over d_model slices; slice 0 ends as the scores
+    float* ab_s;                  // [ab_ks][H][ab_tokens] partial scores over d_model slices; slice 0 ends as the scores
     float2* ab_ml;                // [n_hid_req][H]
-    float* ab_yp;                 // [n_hidden_items][H][d]
-    float* ab_op;                 // [KS][n_hid_req][H][HD]
-    void* ab_pp;                  // 16-bit inputs: softmax weights as 16-bit parts, [16 n_hidden_items][parts * 64][32]
+    float* ab_yp;                 // [n_hidden_items][H][d], the sum of a unit at its first range
+    float* ab_op;                 // [ab_os][n_hid_req][H][HD]
+    void* ab_pp;                  // 16-bit inputs: softmax weights as 16-bit parts, [16 n_hidden_items][parts * ab_rows][32]
     int64_t ab_tokens;            // cached tokens of all hidden-kind requests
     int32_t n_hid_req;
     int32_t ab_ks;                // slices of d_model in the score partials
@@ -288,11 +288,6 @@ template <int DT> __device__ inline f32x4_t mfma16(const uint4& a, const uint4& 
 // lds_addr + 16 i.  The LDS address goes through M0 and must be wave-uniform.
 __device__ inline void gload_lds16(const void* g, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(g) : "memory", "m0");
-}
-// The same with a wave-uniform 64-bit base and a 32-bit byte offset per lane.
-__device__ inline void gload_lds16_base(const void* base, uint32_t lane_off, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(lane_off), "s"(base)
-                 : "memory", "m0");
 }
 typedef __attribute__((address_space(3))) u32x4_t lds_u32x4_t;
 // 16-byte LDS read at an absolute LDS address (the dynamic LDS base is folded into the operand addresses once)

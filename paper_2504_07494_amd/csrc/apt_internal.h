@@ -45,12 +45,13 @@ enum {
 // Raw weights, 16-bit inputs: the tile of the matrix kernel is 256 tokens (head_dim 64) or 128 (head_dim 128).  Left
 // open, the planner halves the range (to at least 64) while the batch yields fewer hidden-kind items than this, a bit
 // under one per CU: with fewer the chip idles, with more the longer range wins because it reads the weights less often.
-// Attention call at d_model 2048 (head_dim 64), us with ranges of 64 / 128 / 256 tokens: 1 request of 300 tokens 23 / 27 / 39
-// (160 / 96 / 64 items), 2 requests 47 / 32 / 40 (544 / 288 / 160), 4 requests 60 / 53 / 47 (1024 / 544 / 288),
-// 16 requests 151 / 121 / 111; at d_model 768, 4 requests 20 / 17.5 / 21 (384 / 204 / 108 items).
-// fp32 inputs: 32 or 16 tokens by the same rule (64 when asked for: never the fastest).  us with ranges of 16 / 32 / 64: d_model 256,
-// 4 requests 12.2 / 12.8 / 16 (108 / 60 / 32 items); d_model 1024, 4 requests 63 / 45 / 70 (464 / 240 / 128), 64 requests
-// 501 / 488 / 572; d_model 512, 12 requests 45 / 39 / 52 (1008 / 528 / 288).
+// Attention call at d_model 2048 (head_dim 64), us with ranges of 64 / 128 / 256 tokens: 1 request of 300 tokens 23 / 27 / 40
+// (160 / 96 / 64 items), 2 requests 49 / 34 / 41 (608 / 320 / 192), 4 requests 71 / 62 / 48 (1152 / 608 / 352),
+// 16 requests 167 / 131 / 125; at d_model 768, 4 requests 21 / 18 / 21 (432 / 228 / 132 items).
+// fp32 inputs: 32 or 16 tokens by the same rule.  us with ranges of 16 / 32 / 64: d_model 256, 4 requests 12.6 / 12.8 / 16.7
+// (108 / 60 / 32 items); d_model 1024, 4 requests 67 / 59 / 88 (1024 / 512 / 272), 64 requests 540 / 469 / 496; d_model 512,
+// 12 requests 44 / 38 / 49 (1000 / 520 / 288).  Very few heads would gain from longer ranges, whose merge is shorter (1 head of
+// 64, 8 requests, 2661 tokens: 19 / 14.5 / 13; 2 heads, fp16, 16 requests, 64 / 128 / 256: 13.3 / 11.3 / 11.1): not in the rule.
 #define APT_RAW_AUTO_HIDDEN_CHUNK(dtype, hd) ((dtype) == APT_F32 ? 32 : 16384 / (hd))
 #define APT_RAW_MAX_HIDDEN_CHUNK(dtype, hd) ((dtype) == APT_F32 ? 64 : 16384 / (hd))
 #define APT_RAW_MIN_HIDDEN_CHUNK(dtype) ((dtype) == APT_F32 ? 16 : 64)
@@ -100,10 +101,13 @@ int apt_resolve(const apt_shape* in, apt_resolved* out);
 static inline uint64_t apt_align256(uint64_t v) { return (v + 255u) & ~(uint64_t)255u; }
 
 // Workspace sections.  Always: the partials (per slot head_dim floats of un-normalised output, then (m, l)).
-// Absorbed-weight hidden path in addition (fp32), with KS = ceil(d / 512) slices of d_model: absorbed queries
-// QT [n_hid_req][H][d] (16-bit inputs: [n_hid_req][d / 32][parts * 64][32] 16-bit parts), score offsets CB [n_hid_req][H], score partials S [KS][H][hidden_tokens] (slice 0 then
-// holds the scores), statistics ML [n_hid_req][H] (m, l), the partial weighted sums YP [n_hidden_chunks][H][d]
-// the output partials OP [ceil(d / 256)][n_hid_req][H][hd], and (16-bit inputs) the softmax weights PP as 16-bit parts.
+// Absorbed-weight hidden path in addition (fp32): absorbed queries QT [n_hid_req][H][d] (16-bit inputs: 16-bit parts,
+// [n_hid_req][d / KT][parts * R][KT] with R heads rounded up to whole fragments of 16 and k-tiles of KT = 32 or 64), score
+// offsets CB [n_hid_req][H], score partials S [slices][H][hidden_tokens] (slice 0 then holds the scores), statistics
+// ML [n_hid_req][H] (m, l), the weighted sums YP [n_hidden_chunks][H][d] (16-bit inputs: one per unit, at its first range),
+// the output partials OP [slices][n_hid_req][H][hd], and (16-bit inputs) the softmax weights PP as 16-bit parts
+// [16 n_hidden_chunks][parts * R][32].  The sizes are bounds that hold for every plan of the shape: S for ceil(d / 512) slices,
+// OP for ceil(d / 256), QT and PP for heads padded to a multiple of 64, YP for a sum per range.
 struct apt_ws_layout {
     uint64_t acc, ml, qt, cb, s, stat, yp, op, pp, total;
 };
@@ -118,7 +122,7 @@ static inline apt_ws_layout apt_ws_sections(int64_t n_partials, int H, int hd, i
     if (himpl == APT_HIDDEN_ABSORBED) {
         const uint64_t ks = (uint64_t)(d + APT_ABSORBED_CHUNK - 1) / APT_ABSORBED_CHUNK;
         L.qt = apt_align256(end);
-        // 16-bit inputs: QT is kept as 16-bit parts (2 for fp16, 3 for bf16) of the heads padded to a multiple of 64 instead
+        // 16-bit inputs: QT is kept as 16-bit parts (2 for fp16, 3 for bf16), here of the heads padded to a multiple of 64
         const uint64_t head_groups = (uint64_t)(H + 63) / 64;
         const uint64_t qt_per_elem = dtype == APT_F32 ? (uint64_t)H * 4u : head_groups * (dtype == APT_F16 ? 256u : 384u);
         L.cb = apt_align256(L.qt + (uint64_t)n_hid_req * d * qt_per_elem);
@@ -128,7 +132,7 @@ static inline apt_ws_layout apt_ws_sections(int64_t n_partials, int H, int hd, i
         L.op = apt_align256(L.yp + (uint64_t)n_hid_chunks * H * d * 4u);
         const uint64_t os = (uint64_t)(d + APT_ABSORBED_OUT_ROWS - 1) / APT_ABSORBED_OUT_ROWS;
         L.pp = apt_align256(L.op + os * (uint64_t)n_hid_req * H * hd * 4u);
-        // 16-bit inputs: the softmax weights as 16-bit parts, 16 tiles of 32 tokens per range, 64 padded heads
+        // 16-bit inputs: the softmax weights as 16-bit parts, 16 tiles of 32 tokens per range
         end = L.pp + (dtype == APT_F32 ? 0u : (uint64_t)n_hid_chunks * 16u * 32u * qt_per_elem);
     }
     L.total = end;

@@ -3,12 +3,13 @@
 //   items kernel   one workgroup (4 wavefronts of 64) per work item of the plan:
 //                    KV-kind item      streams the K and V rows of one head over a token
 //                                      range, online softmax per 16-lane group (HBM bound)
-//                    hidden-kind item  projects K_h, V_h of a 256-token tile from the
-//                                      gathered hidden rows on MFMA (or on plain ALUs
-//                                      for fp32) and attends to them from registers
+//                    hidden-kind item  projects K_h, V_h of a tile of tokens from the gathered
+//                                      hidden rows on the matrix cores (apt_mfma.inc packed
+//                                      weights, apt_raw16.hip and apt_raw32.hip raw ones) and
+//                                      attends to them from registers
 //                  every item writes one partial (m, l, acc[head_dim]) in fp32
 //   merge kernel   combines a request's partials per head and normalises
-//   apt_absorbed.inc: the hidden-kind requests without the projection (opt-in, APT_HIDDEN_ABSORBED)
+//   apt_absorbed.inc, apt_absorb*.hip: the hidden-kind requests without the projection (opt-in, APT_HIDDEN_ABSORBED)
 //   cache append / cache write, weight packing, calibration kernels
 //
 // Scores are kept in base-2 units: s2 = softmax_scale*log2(e)*<q,k>, weights 2^(s2 - m).

@@ -156,7 +156,7 @@ def test_absorbed_weight_hidden_path(oracle, dtype, hd, H, bs):
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_absorbed_path_more_than_64_heads(oracle, dtype):
-    # 66 heads: two groups of operand rows, the second with two heads only
+    # 66 heads: five fragments of 16 operand rows, the last with two heads only
     print(f"[case] absorbed 66 heads {dtype}", flush=True)
     cfg = wl.small_config(name="absorbed66", dtype=dtype, d_model=66 * 64, n_heads=66, head_dim=64, block_size=16,
                           batch=4, len_lo=1, len_hi=600, hidden_ratio=0.5)
