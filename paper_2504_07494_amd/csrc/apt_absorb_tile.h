@@ -82,7 +82,7 @@ static inline int ab_head_frags(int H) {
 //     72 heads, 96 requests of 64..2048 tokens, bf16    5.1e-7  / 7.7e-7  / 4.9e-7      fp16  1.15e-6 / 1.26e-6 / 1.15e-6
 //     55 heads, 169 requests of 15..79, bf16            3.5e-7  / 5.3e-7  / 3.0e-7
 //     40 heads, 32 requests of 128..2048, bf16          4.0e-7  / 3.75e-7 / 3.4e-7      fp16  9.2e-7  / 9.0e-7  / 8.9e-7
-//     geometric mean of 52 batches, bf16                3.9e-7  / 3.8e-7  / 3.4e-7
+//     geometric mean of 53 batches, bf16                3.9e-7  / 3.8e-7  / 3.4e-7
 // The third set costs no time; the folded projection 10 us of 1420 (first line; 64 instead of 128 everywhere: another 30).
 constexpr int kAbFold = 128;
 constexpr int kAbFoldSums = 512;
