@@ -193,7 +193,8 @@ int apt_plan_max_bytes(const apt_shape* s, int B, int max_ctx, size_t* bytes);
  * decreasing range length (ties by request, range, head).  With APT_HIDDEN_ABSORBED a hidden-kind
  * item covers all heads of its range: one item (request, 0, t0, t1) per range, all in queue 0, by
  * request and range.  The order only steers which workgroup takes which item (cache locality,
- * balance); every item is independent.
+ * balance); every item is independent.  With packed weights, word 31 says how far the short last ranges of a queue's requests
+ * share the tiles of the projection kernel (four bits per queue, 0: not at all); it changes neither items nor partials.
  * Integer-only; the same inputs always give the same bytes.
  * Errors: APT_EINVAL (null, B < 1, length < 1, unknown kind), APT_ERANGE (length
  * beyond max_blocks_per_req*block_size), APT_EWORKSPACE (plan_bytes too small),

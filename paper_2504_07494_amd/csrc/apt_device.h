@@ -23,6 +23,7 @@ struct ItemParams {
     int32_t B, H, d, bs, log2_bs, max_blocks;
     int32_t n_items, n_hidden_items, hidden_chunk, kv_chunk, items_off;
     float scale_log2e;
+    int32_t wide_tiles;           // packed weights, ranges of 256 tokens: tiles of 320 rows (apt_pack.h)
     int32_t item_base;            // one-workgroup-per-item launch: first item of the grid
     // absorbed-weight hidden path: workspace sections (fp32)
     float* ab_qt;                 // [n_hid_req][H][d], 16-bit inputs: parts in the score kernel's order
@@ -105,14 +106,33 @@ __device__ inline uint16_t f32_to_bf16_rne(float f) {
 template <int CTRL> __device__ inline float dpp_mov(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
 }
+// Exchange between two registers: the odd 16-lane rows of a with the even rows of b (swap16), the upper half of a with the
+// lower half of b (swap32).  With a == b each then holds one of the two values a lane pair is to combine.
+__device__ inline void swap16(float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
+}
+__device__ inline void swap32(float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
+}
+// Sums over the four 16-lane rows of four values at once: row i of the result holds the sum of s_i, (row 0 + row 1) + (row 2 +
+// row 3).  Three exchanges, where a butterfly for each value takes eight through LDS.
+__device__ inline float sum_rows4(float s0, float s1, float s2, float s3) {
+    swap16(s0, s1);
+    swap16(s2, s3);
+    s0 += s1, s2 += s3;
+    swap32(s0, s2);
+    return s0 + s2;
+}
 // Sum over the aligned group of LANES lanes a lane belongs to; every lane gets the sum.
 template <int LANES> __device__ inline float group_sum(float x) {
     x += dpp_mov<0xB1>(x);                          // quad_perm [1,0,3,2]
     x += dpp_mov<0x4E>(x);                          // quad_perm [2,3,0,1]
     if constexpr (LANES >= 8) x += dpp_mov<0x141>(x);   // row_half_mirror
     if constexpr (LANES >= 16) x += dpp_mov<0x140>(x);  // row_mirror
-    if constexpr (LANES >= 32) x += __shfl_xor(x, 16);
-    if constexpr (LANES >= 64) x += __shfl_xor(x, 32);
+    if constexpr (LANES >= 32) { float y = x; swap16(x, y); x += y; }
+    if constexpr (LANES >= 64) { float y = x; swap32(x, y); x += y; }
     return x;
 }
 template <int LANES> __device__ inline float group_max(float x) {
@@ -120,8 +140,8 @@ template <int LANES> __device__ inline float group_max(float x) {
     x = fmaxf(x, dpp_mov<0x4E>(x));
     if constexpr (LANES >= 8) x = fmaxf(x, dpp_mov<0x141>(x));
     if constexpr (LANES >= 16) x = fmaxf(x, dpp_mov<0x140>(x));
-    if constexpr (LANES >= 32) x = fmaxf(x, __shfl_xor(x, 16));
-    if constexpr (LANES >= 64) x = fmaxf(x, __shfl_xor(x, 32));
+    if constexpr (LANES >= 32) { float y = x; swap16(x, y); x = fmaxf(x, y); }
+    if constexpr (LANES >= 64) { float y = x; swap32(x, y); x = fmaxf(x, y); }
     return x;
 }
 

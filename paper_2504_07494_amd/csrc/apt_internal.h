@@ -30,6 +30,8 @@ enum {
     APT_PW_NHIDREQ = 30,    // number of hidden-kind requests
     APT_PW_TILES_OFF = 31,  // absorbed-weight path: word offset of its lists (tiles, ranges per unit, tile words, unit
                             // words up to the end of the blob), else 0
+    APT_PW_SHARED_TILES = 31, // packed-weight path: blocks that a tile shared by short ranges may fill, four bits per
+                            // queue from bit 0 on (apt_pack.h); 0: no shared tiles
     APT_PW_HEADER = 32
 };
 #define APT_N_QUEUES 8

@@ -21,6 +21,7 @@
 #include "apt_hybrid_bench.h"
 #include "apt_launch.h"
 #include "apt_absorb_tile.h"
+#include "apt_pack.h"
 
 // Workspace of apt_hybrid_decode_attn_static: one copy per device, held until the process ends.  In host code this
 // name is only a handle for hipGetSymbolAddress; the device address is looked up once per device (device_setup).
@@ -528,9 +529,10 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     p.ab_pp = ws + L.pp;
     p.ab_tokens = hidden_tokens;
     p.n_hid_req = pw[APT_PW_NHIDREQ];
+    p.wide_tiles = apt_pack_wide((uint32_t)pw[APT_PW_SHARED_TILES]);
     p.item_base = 0;
     p.ab_ks = 0;
-    p.ab_tiles_off = pw[APT_PW_TILES_OFF];
+    p.ab_tiles_off = rs.s.hidden_impl == APT_HIDDEN_ABSORBED ? pw[APT_PW_TILES_OFF] : 0;
     p.ab_tiles = p.ab_units = p.ab_units_off = p.ab_group = p.ab_rows = p.ab_os = 0;
     if (p.ab_tiles_off) {
         p.ab_tiles = pw[p.ab_tiles_off];

@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <vector>
 #include "apt_internal.h"
+#include "apt_pack.h"
 
 extern "C" const char* apt_strerror(int status) {
     switch (status) {
@@ -117,6 +118,97 @@ extern "C" int apt_workspace_bytes(const apt_shape* s, int max_batch, int max_ct
                                              (int64_t)max_batch * max_ctx, hid_chunks, rs.s.d_model, rs.s.dtype).total;
     if (host_bytes) return apt_plan_max_bytes(s, max_batch, max_ctx, host_bytes);
     return APT_OK;
+}
+
+// The cap of a head queue's shared tiles and when its last workgroup ends with it.
+struct SharedTiles { int cap; double end; };
+
+// Tiles of NC blocks for a head queue of n_heads heads.  full: ranges of full_blocks blocks, the longest; count[c]: shorter ranges
+// of c blocks; kv: time of the KV-kind items, which even the workgroups out.  Up to one tile per workgroup nothing is shared: a
+// fuller tile only takes longer.  Beyond that, the cap (0: a tile per range, not where full ranges are shorter than the tile) is
+// the one with which the workgroup that is last ends first, the tiles dealt as the kernel deals them (rounds, every second one
+// backwards).  Unit of time: 5 us at d_model 5120, proportional to d_model; measured with all workgroups busy, tiles of 1, 2 .. blocks:
+// NC 8, d_model 5120: 59, 58, 67, 78, 91, 100, 117, 126 us; NC 10, d_model 9216: 129, 140, 159, 186, 199, 218, 225, 242, 267, 282
+// (the copies of a k-tile do not shrink with the rows that hold tokens).
+template <int NC>
+static SharedTiles shared_tiles(int64_t full, int full_blocks, const int32_t* count, int64_t n_heads, double kv) {
+    constexpr int kWorkgroups = 32;                        // per queue, on 256 compute units
+    double load[kWorkgroups], all, total;
+    int64_t at;
+    auto begin = [&] {
+        at = 0;
+        all = total = 0.0;
+        for (double& l : load) l = 0.0;
+    };
+    auto deal = [&](int blocks, int64_t tiles) {
+        const double cost = NC == 10 ? 11.5 + 2.0 * std::max(blocks, 2) : 7.0 + 2.25 * std::max(blocks, 2);
+        const int64_t pairs = tiles / (2 * kWorkgroups);   // two rounds give every workgroup two tiles, wherever they begin
+        all += 2.0 * cost * (double)pairs;
+        total += cost * (double)tiles;
+        for (tiles -= pairs * 2 * kWorkgroups; tiles > 0; --tiles, ++at) {
+            const int i = (int)(at % kWorkgroups);
+            load[(at / kWorkgroups) & 1 ? kWorkgroups - 1 - i : i] += cost;
+        }
+    };
+    auto ends = [&] { return std::max(all + *std::max_element(load, load + kWorkgroups), total / kWorkgroups + kv); };
+    SharedTiles best = {0, 1e300};
+    const bool whole = full_blocks == NC;                  // a full range is a tile of its own
+    int64_t tails = 0;
+    for (int c = 1; c < APT_PACK_MAX_BLOCKS + 1; ++c) tails += count[c];
+    if (whole) {
+        begin();
+        deal(NC, full * n_heads);
+        for (int c = NC; c >= 1; --c) deal(c, count[c] * n_heads);
+        best.end = ends();
+        if (tails < 2 || (full + tails) * n_heads <= kWorkgroups) return best;
+    }
+    for (int k = NC; k >= (whole ? 4 : full_blocks + 1); --k) {
+        int32_t left[NC + 1];
+        std::copy(count, count + NC + 1, left);
+        if (!whole) left[full_blocks] += (int32_t)full;
+        begin();
+        if (whole) deal(NC, full * n_heads);
+        apt_pack_patterns<NC>(left, k, [&](int32_t reps, const int32_t* take) {
+            int blocks = 0;
+            for (int c = 1; c <= NC; ++c) blocks += c * take[c];
+            deal(blocks, (int64_t)reps * n_heads);
+        });
+        const double t = ends();
+        if (t < best.end) best = {k, t};
+    }
+    return best;
+}
+
+// The word APT_PW_SHARED_TILES of a batch with packed weights.
+static uint32_t shared_tiles_word(const int32_t* ctx_lens, const uint8_t* cache_kind, int B, int H, int chunk, int64_t kv_tokens) {
+    int64_t full = 0;
+    int32_t count[APT_PACK_MAX_BLOCKS + 1] = {0};
+    for (int r = 0; r < B; ++r) {
+        if (cache_kind[r] != APT_KIND_HIDDEN) continue;
+        full += ctx_lens[r] / chunk;
+        if (ctx_lens[r] % chunk) ++count[ceil_div64(ctx_lens[r] % chunk, APT_PACK_BLOCK)];
+    }
+    const double kv = (double)kv_tokens * 7.4e-4;          // 4 d bytes a token at 5.5 TB/s
+    uint32_t word = 0, wide = 0;
+    double end = 0.0, wide_end = 0.0;
+    const bool large = chunk == APT_MFMA_HIDDEN_CHUNK;
+    SharedTiles t = {0, 0.0}, tw = {0, 0.0};
+    for (int x = 0, prev = -1; x < APT_N_QUEUES; ++x) {
+        const int nh = (H - x + APT_N_QUEUES - 1) / APT_N_QUEUES;      // two numbers of heads at most, the larger first
+        if (nh == 0) break;
+        if (nh != prev) {
+            t = large ? shared_tiles<10>(full, 10, count, nh, kv) : shared_tiles<8>(full, 8, count, nh, kv);
+            if (!large) tw = shared_tiles<10>(full, 8, count, nh, kv);
+        }
+        prev = nh;
+        word |= (uint32_t)t.cap << (4 * x);
+        wide |= (uint32_t)tw.cap << (4 * x);
+        end = std::max(end, t.end);
+        wide_end = std::max(wide_end, tw.end);
+    }
+    // Ranges of 256 tokens in tiles of 320 rows, a full range beside a short one, where that saves a round: 40 heads, requests of
+    // 415, 513 and 619 tokens (40 tiles a queue, then 30) 193 -> 166 us a step.
+    return !large && wide_end < end ? wide : word;
 }
 
 extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8_t* cache_kind, int B,
@@ -277,6 +369,8 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
         }
     }
     w[APT_PW_QUEUE0 + APT_N_QUEUES] = (int32_t)((it - it0) / 4);
+    if (rs.s.hidden_impl == APT_HIDDEN_MFMA && n_hidden_items > 0)
+        w[APT_PW_SHARED_TILES] = (int32_t)shared_tiles_word(ctx_lens, cache_kind, B, H, rs.s.hidden_chunk, tok - htok);
     emit_kind(APT_KIND_KV, rs.s.kv_chunk, 0, 1);
     // absorbed-weight path: the 256-token tiles of the hidden-kind ranges in their order, 2 * item + half; then the units
     // (their first ranges), longest first
