@@ -12,15 +12,17 @@ namespace {
 // dealt so that a lane ends with 8 consecutive k of one request: one 16-byte store per part, 64 contiguous bytes per
 // request.  Bound by the write of QT, R * parts * 2 bytes per k and request: 183 us for 72 heads, bf16, 96 requests at
 // d_model 9216 (425 MB; 246 us with 2-byte stores and heads padded to 128).
-constexpr int kAbQReq = 64;                              // requests per workgroup in z
+constexpr int kAbQReq = 64;                              // requests per workgroup
+__host__ __device__ inline int ab_q_row_blocks(int d) { return (d / 32 + 3) / 4; }
 
 template <int DT, int HD, int NF>
-__global__ __launch_bounds__(kThreads) void apt_absorb_q16_kernel(ItemParams p) {
+__device__ __forceinline__ void absorb_q16(const ItemParams& p, int block) {
     using C = AbTile<DT, NF>;
     constexpr int NS = C::NS, KS = HD / 32;
     const int lane = threadIdx.x & 63, l16 = lane & 15, qd = lane >> 4;
-    const int kb = blockIdx.x * 4 + (threadIdx.x >> 6);  // 32-row block of W_K
-    const int h = blockIdx.y;
+    const int row_blocks = ab_q_row_blocks(p.d);
+    const int kb = block % row_blocks * 4 + (threadIdx.x >> 6);   // 32-row block of W_K
+    const int h = block / row_blocks % p.H, z = block / row_blocks / p.H;
     if (kb * 32 >= p.d) return;
     const int32_t* hid_req = plan_array(p, APT_PA_HID_REQ);
     uint4 wf[2][KS];
@@ -32,8 +34,8 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_q16_kernel(ItemParams p) 
     }
     const int k8 = kb * 4 + qd;                          // this lane's unit of 8 k
     const int kt = k8 / (C::KT / 8), c = (k8 % (C::KT / 8)) ^ ab_swz<C::KT>(h);
-    const int hr_end = min(p.n_hid_req, (int)(blockIdx.z + 1) * kAbQReq);
-    for (int hr0 = blockIdx.z * kAbQReq; hr0 < hr_end; hr0 += 16) {
+    const int hr_end = min(p.n_hid_req, (z + 1) * kAbQReq);
+    for (int hr0 = z * kAbQReq; hr0 < hr_end; hr0 += 16) {
         const int hr = min(hr0 + l16, p.n_hid_req - 1);
         const char* qrow = p.q + ((int64_t)hid_req[hr] * p.H + h) * HD * 2;
         uint4 qf[KS];
@@ -71,6 +73,22 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_q16_kernel(ItemParams p) 
             s += __shfl_xor(s, 32);
             if (qd == 0 && hr0 + l16 < p.n_hid_req) p.ab_cb[(int64_t)hr * p.H + h] = s * p.scale_log2e;
         }
+    }
+}
+
+// The KV-kind items of the batch and the absorbed queries in one launch: neither needs the other, the items (longest first) keep
+// memory busy, and the queries fill the CUs that the last items leave.  The step, items in a launch of their own at its end / here:
+// 40 heads, 32 + 32 requests of 128..2048 tokens 371 / 363 us; 57
+// heads, 7 requests of 158..617 tokens 110 / 101 us (1.4 us of either from the two last kernels in one).
+template <int DT, int HD, int NF>
+__global__ __launch_bounds__(kThreads) void apt_absorb_first_kernel(ItemParams p) {
+    extern __shared__ __align__(16) char lds[];
+    const int n_kv = p.n_items - p.n_hidden_items;
+    if ((int)blockIdx.x < n_kv) {
+        const int4 it = ((const int4*)(p.plan + p.items_off))[p.n_hidden_items + blockIdx.x];
+        kv_item<DT, HD>(p, it.x, it.y, it.z, it.w, lds);
+    } else {
+        absorb_q16<DT, HD, NF>(p, blockIdx.x - n_kv);
     }
 }
 
@@ -189,9 +207,10 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemP
 
 template <int DT, int NF> int launch_scores(const ItemParams& p, int head_dim, hipStream_t st) {
     using C = AbTile<DT, NF>;
-    const dim3 qgrid((p.d / 32 + 3) / 4, p.H, (p.n_hid_req + kAbQReq - 1) / kAbQReq);
-    if (head_dim == 128) hipLaunchKernelGGL((apt_absorb_q16_kernel<DT, 128, NF>), qgrid, dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL((apt_absorb_q16_kernel<DT, 64, NF>), qgrid, dim3(kThreads), 0, st, p);
+    const unsigned first = (unsigned)(p.n_items - p.n_hidden_items) +
+                           (unsigned)(ab_q_row_blocks(p.d) * p.H * ((p.n_hid_req + kAbQReq - 1) / kAbQReq));
+    if (head_dim == 128) hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 128, NF>), dim3(first), dim3(kThreads), (kv_lds_bytes<DT, 128>()), st, p);
+    else hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 64, NF>), dim3(first), dim3(kThreads), (kv_lds_bytes<DT, 64>()), st, p);
     const unsigned groups = (unsigned)((p.ab_tiles + 7) / 8 * p.ab_ks);
     hipLaunchKernelGGL((apt_absorb_score16_kernel<DT, NF>), dim3((groups + 7) / 8 * 64), dim3(kAbWaves * 64), C::S * C::kStage, st, p);
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
@@ -216,6 +235,7 @@ template <int DT> bool setup() {
 
 }  // namespace
 
+// the KV-kind items, the absorbed queries, the scores
 int apt_launch_absorb_scores16(const ItemParams& p, int dtype, int head_dim, hipStream_t st) {
     return dtype == APT_F16 ? launch_scores_nf<1>(p, head_dim, st) : launch_scores_nf<2>(p, head_dim, st);
 }

@@ -156,6 +156,12 @@ __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // sees; the groups are combined through LDS at the end.
 constexpr int kKvUnits = 4;   // 1 KB loads of K (and of V) per pipeline stage
 
+// LDS of an item
+template <int DT, int HD> constexpr int kv_lds_bytes() {
+    constexpr int groups = 4 * (64 / (HD * Elt<DT>::bytes / 16));
+    return (2 * groups + groups * HD) * 4;
+}
+
 template <int DT, int HD>
 __device__ __forceinline__ void kv_item(const ItemParams& p, int r, int h, int t0, int t1, char* lds) {
     constexpr int EB = Elt<DT>::bytes;

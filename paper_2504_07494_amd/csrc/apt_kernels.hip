@@ -30,7 +30,7 @@ static __device__ __align__(256) unsigned char scratch[APT_STATIC_WORKSPACE_BYTE
 namespace {
 
 // ---------------------------------------------------------------------------------
-// KV-kind items alone, one workgroup per item (plans without hidden-kind items; after the absorbed-weight kernels)
+// KV-kind items alone, one workgroup per item (plans without hidden-kind items; fp32, before the absorbed-weight kernels)
 // ---------------------------------------------------------------------------------
 template <int DT, int HD>
 __global__ __launch_bounds__(kThreads) void apt_items_kernel(ItemParams p) {
@@ -44,36 +44,36 @@ __global__ __launch_bounds__(kThreads) void apt_items_kernel(ItemParams p) {
 // ---------------------------------------------------------------------------------
 // merge kernel: out[r][h][c] = sum_s acc_s[c] 2^(m_s - M) / sum_s l_s 2^(m_s - M)
 // ---------------------------------------------------------------------------------
-template <int ODT>
-__global__ __launch_bounds__(kThreads) void apt_merge_kernel(const int32_t* plan, const float* ws_acc, const float2* ws_ml,
-                                                             char* out, int B, int H, int HD, int32_t* kv_ticket,
-                                                             int skip_hidden) {
-    const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (gid == 0) *kv_ticket = 0;           // the item kernel of this call is done: ready for the next call
-    if (gid >= (int64_t)B * H * HD) return;
-    const int c = (int)(gid % HD);
-    const int64_t pair = gid / HD;
-    const int h = (int)(pair % H), r = (int)(pair / H);
-    const int32_t* split_count = plan + APT_PW_HEADER + APT_PA_SPLIT_COUNT * B;
-    const int32_t* ws_offset = plan + APT_PW_HEADER + APT_PA_WS_OFFSET * B;
-    // absorbed-weight path: the outputs of hidden-kind requests are already written
-    if (skip_hidden && plan[APT_PW_HEADER + APT_PA_KIND * B + r] == APT_KIND_HIDDEN) return;
+template <int ODT> __device__ inline void store_out(char* out, int64_t i, float o) {
+    if constexpr (ODT == 0) ((float*)out)[i] = o;
+    else if constexpr (ODT == 1) ((_Float16*)out)[i] = (_Float16)o;
+    else ((uint16_t*)out)[i] = f32_to_bf16_rne(o);
+}
+__device__ inline float merged(const ItemParams& p, int r, int h, int c, int HD) {
+    const int32_t* split_count = p.plan + APT_PW_HEADER + APT_PA_SPLIT_COUNT * p.B;
+    const int32_t* ws_offset = p.plan + APT_PW_HEADER + APT_PA_WS_OFFSET * p.B;
     const int ns = split_count[r];
-    const int64_t base = (int64_t)ws_offset[r] * H + h;
+    const int64_t base = (int64_t)ws_offset[r] * p.H + h;
     float M = kSentinel;
-    for (int s = 0; s < ns; ++s) M = fmaxf(M, ws_ml[base + (int64_t)s * H].x);
+    for (int s = 0; s < ns; ++s) M = fmaxf(M, p.ws_ml[base + (int64_t)s * p.H].x);
     float L = 0.f, A = 0.f;
     for (int s = 0; s < ns; ++s) {
-        const int64_t slot = base + (int64_t)s * H;
-        const float2 ml = ws_ml[slot];
+        const int64_t slot = base + (int64_t)s * p.H;
+        const float2 ml = p.ws_ml[slot];
         const float wgt = fast_exp2(ml.x - M);
         L = fmaf(ml.y, wgt, L);
-        A = fmaf(ws_acc[slot * HD + c], wgt, A);
+        A = fmaf(p.ws_acc[slot * HD + c], wgt, A);
     }
-    const float o = A / L;
-    if constexpr (ODT == 0) ((float*)out)[gid] = o;
-    else if constexpr (ODT == 1) ((_Float16*)out)[gid] = (_Float16)o;
-    else ((uint16_t*)out)[gid] = f32_to_bf16_rne(o);
+    return A / L;
+}
+
+template <int ODT>
+__global__ __launch_bounds__(kThreads) void apt_merge_kernel(ItemParams p, char* out, int HD) {
+    const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (gid == 0) *p.kv_ticket = 0;         // the item kernel of this call is done: ready for the next call
+    if (gid >= (int64_t)p.B * p.H * HD) return;
+    const int64_t pair = gid / HD;
+    store_out<ODT>(out, gid, merged(p, (int)(pair / p.H), (int)(pair % p.H), (int)(gid % HD), HD));
 }
 
 // ---------------------------------------------------------------------------------
@@ -268,18 +268,16 @@ int launch_items(const ItemParams& p, size_t lds_bytes, hipStream_t st) {
 #include "apt_absorbed.inc"
 
 template <int DT, int HD>
-int launch_items_impl(const ItemParams& p_in, int himpl, char* out, int out_dtype, int n_wg, hipStream_t st) {
-    constexpr int EB = Elt<DT>::bytes;
-    constexpr int LPR = HD * EB / 16;
-    constexpr int G = 4 * (64 / LPR);
-    const size_t kv_lds = (size_t)(2 * G + G * HD) * 4;
-    ItemParams p = p_in;
+int launch_items_impl(ItemParams& p, int himpl, int n_wg, hipStream_t st) {
+    constexpr int kv_lds = kv_lds_bytes<DT, HD>();
     if (p.n_hidden_items == 0) return launch_items<DT, HD>(p, kv_lds, st);
     if (himpl == APT_HIDDEN_ABSORBED) {
-        const int rc = launch_absorbed<DT>(p, out, out_dtype, HD, n_wg, st);
-        if (rc || p.n_hidden_items == p.n_items) return rc;
-        p.item_base = p.n_hidden_items;          // the KV-kind items, one workgroup each
-        return launch_items<DT, HD>(p, kv_lds, st);
+        if (DT == 0 && p.n_hidden_items < p.n_items) {
+            p.item_base = p.n_hidden_items;      // the KV-kind items, one workgroup each (16-bit inputs: with the absorbed queries)
+            const int rc = launch_items<DT, HD>(p, kv_lds, st);
+            if (rc) return rc;
+        }
+        return launch_absorbed<DT>(p, HD, n_wg, st);
     }
     if (himpl == APT_HIDDEN_VALU) {
         if constexpr (DT == 0) return apt_launch_raw32(p, HD, st);
@@ -550,24 +548,24 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
 
     const int dt = rs.s.dtype, hd = rs.s.head_dim, hi = rs.s.hidden_impl;
     if (ev_begin && hipEventRecord((hipEvent_t)ev_begin, st) != hipSuccess) return APT_EHIP;
-    if (dt == APT_F32 && hd == 64) rc = launch_items_impl<0, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
-    else if (dt == APT_F32 && hd == 128) rc = launch_items_impl<0, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
-    else if (dt == APT_F16 && hd == 64) rc = launch_items_impl<1, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
-    else if (dt == APT_F16 && hd == 128) rc = launch_items_impl<1, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
-    else if (dt == APT_BF16 && hd == 64) rc = launch_items_impl<2, 64>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
-    else rc = launch_items_impl<2, 128>(p, hi, (char*)out, rs.s.out_dtype, ds->n_wg, st);
+    if (dt == APT_F32 && hd == 64) rc = launch_items_impl<0, 64>(p, hi, ds->n_wg, st);
+    else if (dt == APT_F32 && hd == 128) rc = launch_items_impl<0, 128>(p, hi, ds->n_wg, st);
+    else if (dt == APT_F16 && hd == 64) rc = launch_items_impl<1, 64>(p, hi, ds->n_wg, st);
+    else if (dt == APT_F16 && hd == 128) rc = launch_items_impl<1, 128>(p, hi, ds->n_wg, st);
+    else if (dt == APT_BF16 && hd == 64) rc = launch_items_impl<2, 64>(p, hi, ds->n_wg, st);
+    else rc = launch_items_impl<2, 128>(p, hi, ds->n_wg, st);
     if (rc) return rc;
     if (ev_end && hipEventRecord((hipEvent_t)ev_end, st) != hipSuccess) return APT_EHIP;
 
-    const int skip_hidden = hi == APT_HIDDEN_ABSORBED;
-    const int64_t total = (int64_t)B * rs.s.n_heads * hd;
-    const unsigned blocks = (unsigned)((total + kThreads - 1) / kThreads);
-    if (rs.s.out_dtype == APT_F32)
-        hipLaunchKernelGGL(apt_merge_kernel<0>, dim3(blocks), dim3(kThreads), 0, st, p.plan, p.ws_acc, p.ws_ml, (char*)out, B, rs.s.n_heads, hd, p.kv_ticket, skip_hidden);
-    else if (rs.s.out_dtype == APT_F16)
-        hipLaunchKernelGGL(apt_merge_kernel<1>, dim3(blocks), dim3(kThreads), 0, st, p.plan, p.ws_acc, p.ws_ml, (char*)out, B, rs.s.n_heads, hd, p.kv_ticket, skip_hidden);
-    else
-        hipLaunchKernelGGL(apt_merge_kernel<2>, dim3(blocks), dim3(kThreads), 0, st, p.plan, p.ws_acc, p.ws_ml, (char*)out, B, rs.s.n_heads, hd, p.kv_ticket, skip_hidden);
+    const unsigned blocks = (unsigned)(((int64_t)B * rs.s.n_heads * hd + kThreads - 1) / kThreads);
+    auto launch_merge = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, st, p, (char*)out, hd); };
+    if (hi == APT_HIDDEN_ABSORBED && n_hidden > 0) {
+        if (rs.s.out_dtype == APT_F32) launch_merge(dt == APT_F32 ? apt_absorb_merge_kernel<0, 0> : dt == APT_F16 ? apt_absorb_merge_kernel<1, 0> : apt_absorb_merge_kernel<2, 0>);
+        else if (rs.s.out_dtype == APT_F16) launch_merge(apt_absorb_merge_kernel<1, 1>);
+        else launch_merge(apt_absorb_merge_kernel<2, 2>);
+    } else {
+        launch_merge(rs.s.out_dtype == APT_F32 ? apt_merge_kernel<0> : rs.s.out_dtype == APT_F16 ? apt_merge_kernel<1> : apt_merge_kernel<2>);
+    }
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
 }
 
