@@ -209,8 +209,8 @@ template <int DT, int NF> int launch_scores(const ItemParams& p, int head_dim, h
     using C = AbTile<DT, NF>;
     const unsigned first = (unsigned)(p.n_items - p.n_hidden_items) +
                            (unsigned)(ab_q_row_blocks(p.d) * p.H * ((p.n_hid_req + kAbQReq - 1) / kAbQReq));
-    if (head_dim == 128) hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 128, NF>), dim3(first), dim3(kThreads), (kv_lds_bytes<DT, 128>()), st, p);
-    else hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 64, NF>), dim3(first), dim3(kThreads), (kv_lds_bytes<DT, 64>()), st, p);
+    if (head_dim == 128) hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 128, NF>), dim3(first), dim3(kThreads), (KvItem<DT, 128, 4>::kLds), st, p);
+    else hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 64, NF>), dim3(first), dim3(kThreads), (KvItem<DT, 64, 4>::kLds), st, p);
     const unsigned groups = (unsigned)((p.ab_tiles + 7) / 8 * p.ab_ks);
     hipLaunchKernelGGL((apt_absorb_score16_kernel<DT, NF>), dim3((groups + 7) / 8 * 64), dim3(kAbWaves * 64), C::S * C::kStage, st, p);
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;

@@ -147,6 +147,13 @@ template <int LANES> __device__ inline float group_max(float x) {
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// ODT: element type of the output
+template <int ODT> __device__ inline void store_out(char* out, int64_t i, float o) {
+    if constexpr (ODT == 0) ((float*)out)[i] = o;
+    else if constexpr (ODT == 1) ((_Float16*)out)[i] = (_Float16)o;
+    else ((uint16_t*)out)[i] = f32_to_bf16_rne(o);
+}
+
 // ---------------------------------------------------------------------------------
 // KV-kind item
 // ---------------------------------------------------------------------------------
@@ -156,19 +163,22 @@ __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // sees; the groups are combined through LDS at the end.
 constexpr int kKvUnits = 4;   // 1 KB loads of K (and of V) per pipeline stage
 
-// LDS of an item
-template <int DT, int HD> constexpr int kv_lds_bytes() {
-    constexpr int groups = 4 * (64 / (HD * Elt<DT>::bytes / 16));
-    return (2 * groups + groups * HD) * 4;
-}
+// NW waves share an item.  The lane groups are combined in up to two rounds: with more than four waves, every HD threads
+// combine the groups of four waves, or fewer, and the first HD then those sums.
+template <int DT, int HD, int NW> struct KvItem {
+    static constexpr int kGroups = NW * (64 / (HD * Elt<DT>::bytes / 16));
+    static constexpr int kParts = NW > 4 ? NW * 64 / HD : 1;
+    static constexpr int kLds = (kGroups + (kParts > 1 ? kParts : 0)) * (2 + HD) * 4;
+};
 
-template <int DT, int HD>
-__device__ __forceinline__ void kv_item(const ItemParams& p, int r, int h, int t0, int t1, char* lds) {
+// done(c, M, L, A): thread c < HD has the sums of channel c over the range
+template <int DT, int HD, int NW, typename Done>
+__device__ __forceinline__ void kv_range(const ItemParams& p, int r, int h, int t0, int t1, char* lds, Done done) {
     constexpr int EB = Elt<DT>::bytes;
     constexpr int EPL = Elt<DT>::per16;          // elements per lane per load
     constexpr int LPR = HD * EB / 16;            // lanes per row
     constexpr int RPL = 64 / LPR;                // rows per 1 KB load
-    constexpr int G = 4 * RPL;                   // lane groups in the workgroup
+    constexpr int G = NW * RPL;                  // lane groups in the workgroup
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int bs = p.bs;
@@ -179,14 +189,14 @@ __device__ __forceinline__ void kv_item(const ItemParams& p, int r, int h, int t
 
     const int p0 = t0 >> p.log2_bs;
     const int p1 = (t1 + bs - 1) >> p.log2_bs;
-    // pages of this wave: p0 + w, p0 + w + 4, ...
-    const int npg = (p1 - p0 - w + 3) >> 2;
+    // pages of this wave: p0 + w, p0 + w + NW, ...
+    const int npg = (p1 - p0 - w + NW - 1) / NW;
     const int nunits = npg > 0 ? (npg << log2_nl) : 0;
 
     // lane i holds the block ids of the wave's i-th page
     int32_t kid = 0, vid = 0;
     if (lane < npg) {
-        const int64_t e = (int64_t)r * 2 * p.max_blocks + p0 + w + 4 * lane;
+        const int64_t e = (int64_t)r * 2 * p.max_blocks + p0 + w + NW * lane;
         kid = p.block_tables[e];
         vid = p.block_tables[e + p.max_blocks];
     }
@@ -194,9 +204,9 @@ __device__ __forceinline__ void kv_item(const ItemParams& p, int r, int h, int t
     // q for the lane's channels, pre-scaled
     const int c0 = (lane % LPR) * EPL;
     float qf[EPL];
+    cvt16<DT>(*(const uint4*)(p.q + (((int64_t)r * p.H + h) * HD + c0) * EB), qf);
 #pragma unroll
-    for (int i = 0; i < EPL; ++i)
-        qf[i] = load_elem<DT>(p.q, ((int64_t)r * p.H + h) * HD + c0 + i) * p.scale_log2e;
+    for (int i = 0; i < EPL; ++i) qf[i] *= p.scale_log2e;
 
     float m = kSentinel, l = 0.f, acc[EPL];
 #pragma unroll
@@ -225,7 +235,7 @@ __device__ __forceinline__ void kv_item(const ItemParams& p, int r, int h, int t
         for (int i = 0; i < kKvUnits; ++i) {
             const int u = g * kKvUnits + i;
             const int pg = u >> log2_nl;
-            const int tok = ((p0 + w + 4 * pg) << p.log2_bs) + (u & nl_mask) * RPL + lane / LPR;
+            const int tok = ((p0 + w + NW * pg) << p.log2_bs) + (u & nl_mask) * RPL + lane / LPR;
             ok[i] = (u < nunits) && (tok < t1);
             float kf[EPL];
             cvt16<DT>(kbuf[i], kf);
@@ -270,21 +280,45 @@ __device__ __forceinline__ void kv_item(const ItemParams& p, int r, int h, int t
 #pragma unroll
     for (int e = 0; e < EPL; ++e) ga[grp * HD + c0 + e] = acc[e];
     __syncthreads();
-    if (tid < HD) {
-        float M = kSentinel;
-        for (int g = 0; g < G; ++g) M = fmaxf(M, gm[g]);
-        float L = 0.f, A = 0.f;
-        for (int g = 0; g < G; ++g) {
-            const float wgt = fast_exp2(gm[g] - M);
-            L = fmaf(gl[g], wgt, L);
-            A = fmaf(ga[g * HD + tid], wgt, A);
+    constexpr int P = KvItem<DT, HD, NW>::kParts;
+    auto combine = [&](const float* sm, const float* sl, const float* sa, int n, int c, float& M, float& L, float& A) {
+        M = kSentinel;
+        for (int g = 0; g < n; ++g) M = fmaxf(M, sm[g]);
+        L = A = 0.f;
+        for (int g = 0; g < n; ++g) {
+            const float wgt = fast_exp2(sm[g] - M);
+            L = fmaf(sl[g], wgt, L);
+            A = fmaf(sa[g * HD + c], wgt, A);
         }
-        const int32_t* split_count = p.plan + APT_PW_HEADER;
-        const int32_t* ws_offset = split_count + p.B;
-        const int64_t slot = ((int64_t)ws_offset[r] + t0 / p.kv_chunk) * p.H + h;
-        p.ws_acc[slot * HD + tid] = A;
-        if (tid == 0) p.ws_ml[slot] = make_float2(M, L);
+    };
+    float M, L, A;
+    if constexpr (P > 1) {
+        static_assert(G % P == 0, "groups of a part");
+        float* pm = ga + G * HD;
+        float* pl = pm + P;
+        float* pa = pl + P;
+        const int part = tid / HD, g = part * (G / P), c = tid % HD;
+        combine(gm + g, gl + g, ga + g * HD, G / P, c, M, L, A);
+        if (c == 0) { pm[part] = M; pl[part] = L; }
+        pa[tid] = A;
+        __syncthreads();
+        gm = pm, gl = pl, ga = pa;
     }
+    if (tid < HD) {
+        combine(gm, gl, ga, P > 1 ? P : G, tid, M, L, A);
+        done(tid, M, L, A);
+    }
+}
+
+// A range of the plan: its partial goes to the workspace
+template <int DT, int HD, int NW = 4>
+__device__ __forceinline__ void kv_item(const ItemParams& p, int r, int h, int t0, int t1, char* lds) {
+    kv_range<DT, HD, NW>(p, r, h, t0, t1, lds, [&](int c, float M, float L, float A) {
+        const int32_t* ws_offset = p.plan + APT_PW_HEADER + APT_PA_WS_OFFSET * p.B;
+        const int64_t slot = ((int64_t)ws_offset[r] + t0 / p.kv_chunk) * p.H + h;
+        p.ws_acc[slot * HD + c] = A;
+        if (c == 0) p.ws_ml[slot] = make_float2(M, L);
+    });
 }
 
 // ---------------------------------------------------------------------------------

@@ -17,6 +17,7 @@
 #include <string.h>
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include "apt_device.h"
 #include "apt_hybrid_bench.h"
 #include "apt_launch.h"
@@ -32,23 +33,32 @@ namespace {
 // ---------------------------------------------------------------------------------
 // KV-kind items alone, one workgroup per item (plans without hidden-kind items; fp32, before the absorbed-weight kernels)
 // ---------------------------------------------------------------------------------
-template <int DT, int HD>
-__global__ __launch_bounds__(kThreads) void apt_items_kernel(ItemParams p) {
+template <int DT, int HD, int NW>
+__global__ __launch_bounds__(NW * 64) void apt_items_kernel(ItemParams p) {
     extern __shared__ __align__(16) char lds[];
     const int item = blockIdx.x + p.item_base;
     if (item >= p.n_items) return;
     const int4 it = ((const int4*)(p.plan + p.items_off))[item];
-    kv_item<DT, HD>(p, it.x, it.y, it.z, it.w, lds);
+    kv_item<DT, HD, NW>(p, it.x, it.y, it.z, it.w, lds);
+}
+
+// Whole contexts, one workgroup per request and head, straight to the output: no partials and no merge (see launch_whole).
+// in_items: the plan has one item per request and head (longest first), else they are taken as they come.
+template <int DT, int HD, int NW, int ODT>
+__global__ __launch_bounds__(NW * 64) void apt_whole_kernel(ItemParams p, char* out, int in_items) {
+    extern __shared__ __align__(16) char lds[];
+    int r = blockIdx.x / p.H, h = blockIdx.x % p.H;
+    if (in_items) {
+        const int4 it = ((const int4*)(p.plan + p.items_off))[blockIdx.x];
+        r = it.x, h = it.y;
+    }
+    const int n = p.plan[APT_PW_HEADER + APT_PA_CTX_LEN * p.B + r];
+    kv_range<DT, HD, NW>(p, r, h, 0, n, lds, [&](int c, float, float L, float A) { store_out<ODT>(out, ((int64_t)r * p.H + h) * HD + c, A / L); });
 }
 
 // ---------------------------------------------------------------------------------
 // merge kernel: out[r][h][c] = sum_s acc_s[c] 2^(m_s - M) / sum_s l_s 2^(m_s - M)
 // ---------------------------------------------------------------------------------
-template <int ODT> __device__ inline void store_out(char* out, int64_t i, float o) {
-    if constexpr (ODT == 0) ((float*)out)[i] = o;
-    else if constexpr (ODT == 1) ((_Float16*)out)[i] = (_Float16)o;
-    else ((uint16_t*)out)[i] = f32_to_bf16_rne(o);
-}
 __device__ inline float merged(const ItemParams& p, int r, int h, int c, int HD) {
     const int32_t* split_count = p.plan + APT_PW_HEADER + APT_PA_SPLIT_COUNT * p.B;
     const int32_t* ws_offset = p.plan + APT_PW_HEADER + APT_PA_WS_OFFSET * p.B;
@@ -258,10 +268,42 @@ __global__ __launch_bounds__(kThreads) void apt_mfma_probe_kernel(float* out, in
 // ---------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------
-template <int DT, int HD>
-int launch_items(const ItemParams& p, size_t lds_bytes, hipStream_t st) {
-    auto kern = apt_items_kernel<DT, HD>;
-    hipLaunchKernelGGL(kern, dim3(p.n_items - p.item_base), dim3(kThreads), lds_bytes, st, p);
+// A CU holds 16 waves of these kernels.  Up to one workgroup per CU, a workgroup has all of them: the range of a lone 1237-token
+// request of 40 heads takes 8.8 us instead of 11.4 (of 1000 tokens, three such requests of 49 heads, 10.5 instead of 12.6).
+// Eight waves for up to two workgroups per CU gave nothing (320 to 448 items 16.4 us, with four 15.4).
+template <int DT, int HD> int launch_items(const ItemParams& p, int n_cus, hipStream_t st) {
+    const int n = p.n_items - p.item_base;
+    if (n <= n_cus) hipLaunchKernelGGL((apt_items_kernel<DT, HD, 16>), dim3(n), dim3(1024), (KvItem<DT, HD, 16>::kLds), st, p);
+    else hipLaunchKernelGGL((apt_items_kernel<DT, HD, 4>), dim3(n), dim3(kThreads), (KvItem<DT, HD, 4>::kLds), st, p);
+    return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
+}
+
+// Batches of KV-kind requests that need no partials.  Every context is one range of the plan; or there are no more (request, head)
+// pairs than CUs, and the longest context alone does not take longer than ranges of it on more CUs and the merge would: a CU
+// reads 57 KB per us with 16 waves, the ranges take 7 us or the time of all their bytes at 6.3 TB/s, the merge and its launch
+// 5 us.  Step, 40 heads, fp16, ranges and merge / whole: one request of 500 tokens 17.9 / 14.7 us, of 1237 with the append
+// 22.7 / 21.5, of 2048 18.5 / 26.9 (not taken), six of 2000 to 2048 52.3 / 47.8, 200 of 10 to 500 203.0 / 196.7.
+bool takes_whole(const ItemParams& p, const int32_t* pw, int row_bytes, int n_cus) {
+    if (p.n_hidden_items > 0) return false;
+    if (pw[APT_PW_NPARTIALS] == p.B) return true;
+    if ((int64_t)p.B * p.H > n_cus || p.max_blocks > 16 * APT_KV_MAX_PAGES_PER_WAVE) return false;
+    const int32_t* lens = pw + APT_PW_HEADER + APT_PA_CTX_LEN * p.B;
+    int64_t longest = 0, all = 0;
+    for (int r = 0; r < p.B; ++r) {
+        longest = std::max<int64_t>(longest, lens[r]);
+        all += lens[r];
+    }
+    const double us = std::max(7.0, (double)all * p.H * 2 * row_bytes / 6.3e6) + 5.0;
+    return (double)longest * 2 * row_bytes <= 57e3 * us;
+}
+template <int DT, int HD, int NW, int ODT> void launch_whole_nw(const ItemParams& p, char* out, int in_items, hipStream_t st) {
+    hipLaunchKernelGGL((apt_whole_kernel<DT, HD, NW, ODT>), dim3(p.B * p.H), dim3(NW * 64), (KvItem<DT, HD, NW>::kLds), st, p, out, in_items);
+}
+template <int DT, int HD> int launch_whole(const ItemParams& p, const int32_t* pw, char* out, int out_dtype, int n_cus, hipStream_t st) {
+    const int in_items = pw[APT_PW_NPARTIALS] == p.B;
+    const bool few = (int64_t)p.B * p.H <= n_cus;
+    if (DT == 0 || out_dtype == APT_F32) few ? launch_whole_nw<DT, HD, 16, 0>(p, out, in_items, st) : launch_whole_nw<DT, HD, 4, 0>(p, out, in_items, st);
+    else few ? launch_whole_nw<DT, HD, 16, DT>(p, out, in_items, st) : launch_whole_nw<DT, HD, 4, DT>(p, out, in_items, st);
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
 }
 
@@ -269,12 +311,11 @@ int launch_items(const ItemParams& p, size_t lds_bytes, hipStream_t st) {
 
 template <int DT, int HD>
 int launch_items_impl(ItemParams& p, int himpl, int n_wg, hipStream_t st) {
-    constexpr int kv_lds = kv_lds_bytes<DT, HD>();
-    if (p.n_hidden_items == 0) return launch_items<DT, HD>(p, kv_lds, st);
+    if (p.n_hidden_items == 0) return launch_items<DT, HD>(p, n_wg, st);
     if (himpl == APT_HIDDEN_ABSORBED) {
         if (DT == 0 && p.n_hidden_items < p.n_items) {
             p.item_base = p.n_hidden_items;      // the KV-kind items, one workgroup each (16-bit inputs: with the absorbed queries)
-            const int rc = launch_items<DT, HD>(p, kv_lds, st);
+            const int rc = launch_items<DT, HD>(p, n_wg, st);
             if (rc) return rc;
         }
         return launch_absorbed<DT>(p, HD, n_wg, st);
@@ -548,14 +589,21 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
 
     const int dt = rs.s.dtype, hd = rs.s.head_dim, hi = rs.s.hidden_impl;
     if (ev_begin && hipEventRecord((hipEvent_t)ev_begin, st) != hipSuccess) return APT_EHIP;
-    if (dt == APT_F32 && hd == 64) rc = launch_items_impl<0, 64>(p, hi, ds->n_wg, st);
-    else if (dt == APT_F32 && hd == 128) rc = launch_items_impl<0, 128>(p, hi, ds->n_wg, st);
-    else if (dt == APT_F16 && hd == 64) rc = launch_items_impl<1, 64>(p, hi, ds->n_wg, st);
-    else if (dt == APT_F16 && hd == 128) rc = launch_items_impl<1, 128>(p, hi, ds->n_wg, st);
-    else if (dt == APT_BF16 && hd == 64) rc = launch_items_impl<2, 64>(p, hi, ds->n_wg, st);
-    else rc = launch_items_impl<2, 128>(p, hi, ds->n_wg, st);
+    const bool whole = takes_whole(p, pw, hd * rs.elem_bytes, ds->n_wg);
+    auto launch = [&](auto dtype, auto head_dim) {
+        constexpr int DT = decltype(dtype)::value, HD = decltype(head_dim)::value;
+        return whole ? launch_whole<DT, HD>(p, pw, (char*)out, rs.s.out_dtype, ds->n_wg, st) : launch_items_impl<DT, HD>(p, hi, ds->n_wg, st);
+    };
+    auto launch_hd = [&](auto dtype) {
+        return hd == 64 ? launch(dtype, std::integral_constant<int, 64>{}) : launch(dtype, std::integral_constant<int, 128>{});
+    };
+    if (dt == APT_F32) rc = launch_hd(std::integral_constant<int, 0>{});
+    else if (dt == APT_F16) rc = launch_hd(std::integral_constant<int, 1>{});
+    else rc = launch_hd(std::integral_constant<int, 2>{});
     if (rc) return rc;
     if (ev_end && hipEventRecord((hipEvent_t)ev_end, st) != hipSuccess) return APT_EHIP;
+
+    if (whole) return APT_OK;
 
     const unsigned blocks = (unsigned)(((int64_t)B * rs.s.n_heads * hd + kThreads - 1) / kThreads);
     auto launch_merge = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, st, p, (char*)out, hd); };

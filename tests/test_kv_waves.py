@@ -1,0 +1,38 @@
+"""Batches of KV-kind requests alone, against the CPU oracle, on every path that the launch takes for them: whole contexts with
+sixteen waves (as many (request, head) pairs as CUs, or fewer) or with four (every context one range), and ranges with a merge.
+fp32 sums of at most 1037 weights and 128 products: errors of the scores and of the value sums are a few hundred times 2^-24 of
+their size, 1e-4 is ten times that."""
+import numpy as np
+import pytest
+
+from paper_2504_07494_amd import workloads as wl
+from paper_2504_07494_amd.harness import DecodeRunner
+from tests.helpers import oracle_attn
+
+pytestmark = pytest.mark.gpu
+
+
+# lengths around a page of every wave (4 and 16 waves; pages of 4 to 32 tokens), a lone token, whole and open ranges of 512 tokens
+SHORT = [1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 255, 257, 511, 512]
+LONG = SHORT + [513, 1037]
+
+
+@pytest.mark.parametrize("dtype,out,hd,bs", [("f16", "f32", 128, 16), ("bf16", "bf16", 128, 8), ("f16", "f16", 64, 32), ("bf16", "f32", 64, 8),
+                                             ("f32", "f32", 128, 16), ("f32", "f32", 64, 4)])
+@pytest.mark.parametrize("lens,n_heads", [(SHORT, 4), (SHORT, 18), (SHORT, 19), (LONG, 4), (LONG, 16), (LONG, 17)])
+def test_kv_batches_with_and_without_partials(oracle, dtype, out, hd, bs, lens, n_heads):
+    print(f"[case] {dtype} hd={hd} bs={bs} heads={n_heads} requests={len(lens)}", flush=True)
+    cfg = wl.small_config(name="kvwaves", dtype=dtype, d_model=hd * n_heads, n_heads=n_heads, head_dim=hd, block_size=bs,
+                          batch=len(lens), len_lo=1, len_hi=max(lens), hidden_ratio=0.0, permute_pages=True)
+    batch = wl.make_batch(cfg, np.array(lens, dtype=np.int32), np.full(len(lens), wl.KIND_KV, dtype=np.uint8))
+    layer = wl.make_layer(batch)
+    rn = DecodeRunner(batch, out_dtype=out)
+    rn.out.fill_(float("nan"))
+    rn.run(rn.upload(layer))
+    got = rn.out_f64()
+    want = oracle_attn(oracle, batch, layer).reshape(got.shape)
+    assert np.all(np.isfinite(got))
+    err = np.abs(got - want)
+    print(f"[parity] max_abs={err.max():.3e}", flush=True)
+    # the last rounding of a 16-bit output: half a unit in the last place of its 11 or 8 bits
+    assert np.all(err <= 1e-4 + np.abs(want) * {"f32": 0.0, "f16": 2.0 ** -11, "bf16": 2.0 ** -8}[out])
