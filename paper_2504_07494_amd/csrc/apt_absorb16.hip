@@ -1,4 +1,5 @@
 // Absorbed-weight hidden path, 16-bit inputs: the kernels that build the absorbed queries and the scores.
+#include <algorithm>
 #include "apt_device.h"
 #include "apt_launch.h"
 #include "apt_absorb_tile.h"
@@ -7,40 +8,56 @@ namespace {
 
 // ---- absorbed queries: QT[hr][h][k] = scale * log2(e) * W_K[k, h] . q, as 16-bit parts in the order the score kernel
 // copies: [hr][k-tile][part * R + head][unit c at c ^ swizzle(head)], rows of KT values.
-// One wave per (head, 32 rows of W_K), all hidden-kind requests of its z-slice in turn, operands straight from memory
-// (both are 16-bit, so the products are exact).  D rows are k, columns are requests; the rows of the two W fragments are
-// dealt so that a lane ends with 8 consecutive k of one request: one 16-byte store per part, 64 contiguous bytes per
-// request.  Bound by the write of QT, R * parts * 2 bytes per k and request: 183 us for 72 heads, bf16, 96 requests at
-// d_model 9216 (425 MB; 246 us with 2-byte stores and heads padded to 128).
-constexpr int kAbQReq = 64;                              // requests per workgroup
-__host__ __device__ inline int ab_q_row_blocks(int d) { return (d / 32 + 3) / 4; }
+// One wave per (head, 32 rows of W_K), the requests of its z-slice in turn; both operands are 16-bit, so the products are exact.
+// D rows are k, columns are requests; the rows of the two W fragments are dealt so that a lane ends with 8 consecutive k of
+// one request: one 16-byte store per part, 64 contiguous bytes per request.  Eight neighbouring heads of the same rows stay
+// together on one XCD (workgroup g runs on XCD g % 8): their stores meet in the same 128-byte lines.  The queries of all the
+// requests are put into LDS first: loads between the stores would wait for them, the two share a counter.
+// Bound by the write of QT, R * parts * 2 bytes per k and request (a fill of its size takes 62 us), and by each workgroup's
+// start, W_K and the queries behind their indexes.  72 heads, bf16, 96 requests at d_model 9216 (425 MB): 195 us with
+// queries from memory, 187 in this order, 155 through LDS, 147 with 128 requests to a workgroup.
+//
+// 128 requests where that leaves two workgroups per CU (short contexts, 64 / 128, the whole call: 24 heads, 128 requests 113.1 /
+// 110.4 us, 32 heads, 100 requests 142.5 / 135.5; 16 heads, 100 requests 64.4 / 66.1, not taken).
+__host__ __device__ inline int ab_q_reqs(const ItemParams& p) { return (p.d / 32 + 3) / 4 * p.H >= 512 ? 128 : 64; }
+__host__ __device__ inline int ab_q_z_blocks(const ItemParams& p) { return (p.n_hid_req + ab_q_reqs(p) - 1) / ab_q_reqs(p); }
+inline int ab_q_groups(const ItemParams& p) { return (p.d / 32 + 3) / 4 * ((p.H + 7) / 8) * ab_q_z_blocks(p); }
+
+template <int HD> __device__ inline int ab_q_swz(int row) { return HD == 128 ? row & 15 : (row >> 1) & 7; }
 
 template <int DT, int HD, int NF>
-__device__ __forceinline__ void absorb_q16(const ItemParams& p, int block) {
+__device__ __forceinline__ void absorb_q16(const ItemParams& p, int block, char* lds) {
     using C = AbTile<DT, NF>;
-    constexpr int NS = C::NS, KS = HD / 32;
+    constexpr int NS = C::NS, KS = HD / 32, UPR = HD / 8;
     const int lane = threadIdx.x & 63, l16 = lane & 15, qd = lane >> 4;
-    const int row_blocks = ab_q_row_blocks(p.d);
-    const int kb = block % row_blocks * 4 + (threadIdx.x >> 6);   // 32-row block of W_K
-    const int h = block / row_blocks % p.H, z = block / row_blocks / p.H;
-    if (kb * 32 >= p.d) return;
-    const int32_t* hid_req = plan_array(p, APT_PA_HID_REQ);
+    const int slot = block >> 3, group = (slot >> 3) * 8 + (block & 7);
+    const int head_groups = (p.H + 7) / 8, z_blocks = ab_q_z_blocks(p);
+    const int h = group % head_groups * 8 + (slot & 7), z = group / head_groups % z_blocks;
+    const int kb = group / head_groups / z_blocks * 4 + (threadIdx.x >> 6);   // 32-row block of W_K
+    if (h >= p.H) return;
     uint4 wf[2][KS];
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
-        const int k = kb * 32 + 8 * (l16 >> 2) + 4 * f + (l16 & 3);
+        const int k = min(kb * 32 + 8 * (l16 >> 2) + 4 * f + (l16 & 3), p.d - 1);
 #pragma unroll
         for (int s = 0; s < KS; ++s) wf[f][s] = *(const uint4*)(p.W_K + ((int64_t)k * p.d + h * HD + 32 * s + 8 * qd) * 2);
     }
+    // the queries of this head: 16-byte unit u of a row at u ^ ab_q_swz(row), free of bank conflicts; rows past the last request repeat it
+    const int hr_begin = z * ab_q_reqs(p), n = min(p.n_hid_req - hr_begin, ab_q_reqs(p));
+    const int32_t* hid_req = plan_array(p, APT_PA_HID_REQ);
+    for (int i = threadIdx.x; i < (n + 15) / 16 * 16 * UPR; i += kThreads) {
+        const int row = i / UPR, u = i % UPR, r = hid_req[hr_begin + min(row, n - 1)];
+        *(uint4*)(lds + (row * UPR + (u ^ ab_q_swz<HD>(row))) * 16) = *(const uint4*)(p.q + (((int64_t)r * p.H + h) * HD + u * 8) * 2);
+    }
+    __syncthreads();
+    if (kb * 32 >= p.d) return;
     const int k8 = kb * 4 + qd;                          // this lane's unit of 8 k
     const int kt = k8 / (C::KT / 8), c = (k8 % (C::KT / 8)) ^ ab_swz<C::KT>(h);
-    const int hr_end = min(p.n_hid_req, (z + 1) * kAbQReq);
-    for (int hr0 = z * kAbQReq; hr0 < hr_end; hr0 += 16) {
-        const int hr = min(hr0 + l16, p.n_hid_req - 1);
-        const char* qrow = p.q + ((int64_t)hid_req[hr] * p.H + h) * HD * 2;
+    for (int row0 = 0; row0 < n; row0 += 16) {
+        const int row = row0 + l16, hr = hr_begin + row;
         uint4 qf[KS];
 #pragma unroll
-        for (int s = 0; s < KS; ++s) qf[s] = *(const uint4*)(qrow + (32 * s + 8 * qd) * 2);
+        for (int s = 0; s < KS; ++s) qf[s] = *(const uint4*)(lds + (row * UPR + ((4 * s + qd) ^ ab_q_swz<HD>(row))) * 16);
         f32x4_t acc[2];
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
@@ -54,7 +71,7 @@ __device__ __forceinline__ void absorb_q16(const ItemParams& p, int block) {
         for (int e = 0; e < 8; ++e) v[e] = acc[e >> 2][e & 3] * p.scale_log2e;
         uint4 part[NS];
         AbSplit<DT>::split8(v, part);
-        if (hr0 + l16 < p.n_hid_req) {
+        if (row < n) {
             char* base = (char*)p.ab_qt + ((int64_t)hr * (p.d / C::KT) + kt) * C::kABytes + c * 16;
 #pragma unroll
             for (int sp = 0; sp < NS; ++sp) *(uint4*)(base + (sp * C::R + h) * C::kRow) = part[sp];
@@ -71,7 +88,7 @@ __device__ __forceinline__ void absorb_q16(const ItemParams& p, int block) {
             }
             s += __shfl_xor(s, 16);
             s += __shfl_xor(s, 32);
-            if (qd == 0 && hr0 + l16 < p.n_hid_req) p.ab_cb[(int64_t)hr * p.H + h] = s * p.scale_log2e;
+            if (qd == 0 && row < n) p.ab_cb[(int64_t)hr * p.H + h] = s * p.scale_log2e;
         }
     }
 }
@@ -88,7 +105,7 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_first_kernel(ItemParams p
         const int4 it = ((const int4*)(p.plan + p.items_off))[p.n_hidden_items + blockIdx.x];
         kv_item<DT, HD>(p, it.x, it.y, it.z, it.w, lds);
     } else {
-        absorb_q16<DT, HD, NF>(p, blockIdx.x - n_kv);
+        absorb_q16<DT, HD, NF>(p, blockIdx.x - n_kv, lds);
     }
 }
 
@@ -208,9 +225,10 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemP
 template <int DT, int NF> int launch_scores(const ItemParams& p, int head_dim, hipStream_t st) {
     using C = AbTile<DT, NF>;
     const unsigned first = (unsigned)(p.n_items - p.n_hidden_items) +
-                           (unsigned)(ab_q_row_blocks(p.d) * p.H * ((p.n_hid_req + kAbQReq - 1) / kAbQReq));
-    if (head_dim == 128) hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 128, NF>), dim3(first), dim3(kThreads), (KvItem<DT, 128, 4>::kLds), st, p);
-    else hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 64, NF>), dim3(first), dim3(kThreads), (KvItem<DT, 64, 4>::kLds), st, p);
+                           (unsigned)((ab_q_groups(p) + 7) / 8 * 64);
+    const int q_lds = (std::min(p.n_hid_req, ab_q_reqs(p)) + 15) / 16 * 16 * head_dim * 2;
+    if (head_dim == 128) hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 128, NF>), dim3(first), dim3(kThreads), std::max(q_lds, KvItem<DT, 128, 4>::kLds), st, p);
+    else hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 64, NF>), dim3(first), dim3(kThreads), std::max(q_lds, KvItem<DT, 64, 4>::kLds), st, p);
     const unsigned groups = (unsigned)((p.ab_tiles + 7) / 8 * p.ab_ks);
     hipLaunchKernelGGL((apt_absorb_score16_kernel<DT, NF>), dim3((groups + 7) / 8 * 64), dim3(kAbWaves * 64), C::S * C::kStage, st, p);
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
