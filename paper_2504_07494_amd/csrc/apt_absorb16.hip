@@ -118,37 +118,43 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_first_kernel(ItemParams p
 //
 // Bound by how memory serves the X rows, one 128-byte line per row and 64 k (rows lie 2 d_model apart): 64-wide k-tiles
 // in three stages take 87 us for 40 heads, fp16, 33.6 k tokens at d_model 5120 (344 MB of X; 0.40 GB of 128-byte line reads, 4.5
-// TB/s), 32-wide ones in seven stages, with more bytes in flight, 99 us.  72 heads, bf16, have room for 32-wide ones only: the two
-// halves of a line are joined in L2 (2.80 GB of line reads where X and the queries are 2.31 GB, 4.5 TB/s).  The version with heads padded to 64, an accumulator per part and 512-wide
-// slices took 117 us there, and 1193 us against 594 us now for 72 heads, bf16, 102 k tokens at d_model 9216.
+// TB/s), 32-wide ones in seven stages, with more bytes in flight, 99 us.  Where both do not fit 64 wide, X is 64 wide in three stages beside four 32-wide ones of the
+// queries (kWideX; two k-tiles share an X tile and its copies): the 32-wide halves of a line, joined in L2, made 2.80 GB of line
+// reads for 72 heads, bf16, 102 k tokens at d_model 9216, where X and the queries are 2.31 GB.  Whole call there 1405 / 1373 us
+// (32 / 64 wide), 49 heads, 64 requests of 64..1024 tokens 386 / 374, 65 heads, 16 requests of 20..500 150 / 147.  The version
+// with heads padded to 64, an accumulator per part and 512-wide slices took 117 us for the 40 heads, and 1193 us for the 72.
 template <int DT, int NF, int F0, int FN, typename Issue>
 __device__ __forceinline__ void score_loop(f32x4_t (*acc)[4], f32x4_t (*sum)[4], f32x4_t (*total)[4], uint32_t lds0, int tg, int nkt, Issue issue) {
     using C = AbTile<DT, NF>;
-    constexpr int NS = C::NS, KT = C::KT, S = C::S;
+    constexpr int NS = C::NS, KT = C::KT, S = C::S, XPT = C::XPT;
     const int lane = threadIdx.x & 63, l16 = lane & 15, qd = lane >> 4;
-    int stage = 0;
+    int stage = 0, xstage = 0;
     for (int kt = 0; kt < nkt; ++kt) {
-        if (kt + S - 2 < nkt) wait_vmcnt<(S - 2) * C::kCopies>();
+        // the copies of this k-tile were issued S - 1 of them ago; the last X tile's go out a k-tile before the last queries'
+        if (kt + S - 3 + XPT < nkt) wait_vmcnt<(S - 2) * C::kCopies>();
         else wait_vmcnt<0>();
-        __syncthreads();            // k-tile kt has landed for every wave; nobody still reads the stage refilled next
-        if (kt + S - 1 < nkt) issue(kt + S - 1);
-        const uint32_t st = lds0 + stage * C::kStage;
+        __syncthreads();            // k-tile kt has landed for every wave; nobody still reads the stages refilled next
+        issue(kt);
+        const uint32_t xst = lds0 + xstage * C::kXBytes, ast = lds0 + C::SX * C::kXBytes + stage * C::kABytes;
 #pragma unroll
         for (int ks = 0; ks < KT / 32; ++ks) {
+            const int xu = 4 * ks + qd + (XPT == 2 ? 4 * (kt & 1) : 0);
+            const uint32_t xoff = ((xu ^ ab_swz<KT * XPT>(l16)) << 4) + l16 * C::kXRow;
             const uint32_t off = (((4 * ks + qd) ^ ab_swz<KT>(l16)) << 4) + l16 * C::kRow;
             uint4 x[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) x[t] = lds_read16(st + (64 * tg + 16 * t) * C::kRow + off);
+            for (int t = 0; t < 4; ++t) x[t] = lds_read16(xst + (64 * tg + 16 * t) * C::kXRow + xoff);
 #pragma unroll
             for (int f = 0; f < FN; ++f)
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
-                    const uint4 a = lds_read16(st + C::kXBytes + (s * C::R + 16 * (F0 + f)) * C::kRow + off);
+                    const uint4 a = lds_read16(ast + (s * C::R + 16 * (F0 + f)) * C::kRow + off);
 #pragma unroll
                     for (int t = 0; t < 4; ++t) acc[f][t] = mfma16<DT>(a, x[t], acc[f][t]);
                 }
         }
         stage = stage == S - 1 ? 0 : stage + 1;
+        if ((kt + 1) % XPT == 0) xstage = xstage == C::SX - 1 ? 0 : xstage + 1;
         if ((kt + 1) % (kAbFold / KT) == 0) ab_fold<4>(acc, sum, FN);
         if ((kt + 1) % (kAbFoldSums / KT) == 0) ab_fold<4>(sum, total, FN);
     }
@@ -159,9 +165,9 @@ __device__ __forceinline__ void score_loop(f32x4_t (*acc)[4], f32x4_t (*sum)[4],
 template <int DT, int NF>
 __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemParams p) {
     using C = AbTile<DT, NF>;
-    constexpr int KT = C::KT, S = C::S, NF0 = C::NF0;
-    constexpr int RPC = 1024 / C::kRow;                  // rows per 1 KB copy
-    constexpr int UPR = KT / 8;                          // 16-byte units per row
+    constexpr int KT = C::KT, S = C::S, SX = C::SX, XPT = C::XPT, NF0 = C::NF0;
+    constexpr int RPC = 1024 / C::kXRow;                 // rows per 1 KB copy
+    constexpr int UPR = C::kXRow / 16;                   // 16-byte units per row
     extern __shared__ __align__(16) char lds[];
     const int lane = threadIdx.x & 63, l16 = lane & 15, qd = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = w & 3, second = w >> 2;
@@ -175,25 +181,37 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemP
     const int r = it.x, t1 = it.w, tb = it.z + kAbMT * (tile & 1);
     const int hr = plan_array(p, APT_PA_HID_INDEX)[r];
     const int64_t tok0 = (int64_t)plan_array(p, APT_PA_HID_TOK_OFF)[r] + tb;
-    const int n_kt = p.d / KT, kt0 = slice * n_kt / p.ab_ks, nkt = (slice + 1) * n_kt / p.ab_ks - kt0, k_begin = kt0 * KT;
+    const int n_xt = p.d / (KT * XPT), xt0 = slice * n_xt / p.ab_ks, nxt = (slice + 1) * n_xt / p.ab_ks - xt0;
+    const int n_kt = n_xt * XPT, kt0 = xt0 * XPT, nkt = nxt * XPT, k_begin = kt0 * KT;
 
     const char* xsrc[C::kXCopies];
 #pragma unroll
     for (int i = 0; i < C::kXCopies; ++i) {
         const int row = RPC * (C::kXCopies * w + i) + lane / UPR;   // rows past the range repeat its last token (scores not stored)
-        xsrc[i] = hidden_row(p, r, min(tb + row, t1 - 1), 2) + (int64_t)k_begin * 2 + (((lane % UPR) ^ ab_swz<KT>(row)) << 4);
+        xsrc[i] = hidden_row(p, r, min(tb + row, t1 - 1), 2) + (int64_t)k_begin * 2 + (((lane % UPR) ^ ab_swz<KT * XPT>(row)) << 4);
     }
     const char* asrc = (const char*)p.ab_qt + ((int64_t)hr * n_kt + kt0) * C::kABytes + lane * 16;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+    auto copy_x = [&](int xt, int i) {
+        gload_lds16(xsrc[i] + xt * C::kXRow, lds0 + (xt % SX) * C::kXBytes + (C::kXCopies * w + i) * 1024);
+    };
+    // k-tile kt: the queries S - 1 k-tiles ahead, and the X tile SX - 1 ahead (two k-tiles share a wide one's copies)
     auto issue = [&](int kt) {
-        const uint32_t st = lds0 + (kt % S) * C::kStage;
+        const int xt = (kt + XPT * SX) / XPT - 1, at = kt + S - 1;
+        if (xt >= 0 && xt < nxt) {
+            if (XPT == 1 || (kt & 1) == 0)
 #pragma unroll
-        for (int i = 0; i < C::kXCopies; ++i) gload_lds16(xsrc[i] + kt * C::kRow, st + (C::kXCopies * w + i) * 1024);
+                for (int i = 0; i < C::kXCopies / XPT; ++i) copy_x(xt, i);
+            else
 #pragma unroll
-        for (int i = 0; i < C::kACopies; ++i) {          // some waves copy the last chunk again (same bytes)
-            const int n = min(w + kAbWaves * i, C::kABytes / 1024 - 1);
-            gload_lds16(asrc + (int64_t)kt * C::kABytes + n * 1024, st + C::kXBytes + n * 1024);
+                for (int i = C::kXCopies / XPT; i < C::kXCopies; ++i) copy_x(xt, i);
         }
+        if (at >= 0 && at < nkt)
+#pragma unroll
+            for (int i = 0; i < C::kACopies; ++i) {      // some waves copy the last chunk again (same bytes)
+                const int n = min(w + kAbWaves * i, C::kABytes / 1024 - 1);
+                gload_lds16(asrc + (int64_t)at * C::kABytes + n * 1024, lds0 + SX * C::kXBytes + (at % S) * C::kABytes + n * 1024);
+            }
     };
     f32x4_t acc[NF0][4], sum[NF0][4], total[NF0][4];
 #pragma unroll
@@ -203,8 +221,7 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemP
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[f][t][e] = sum[f][t][e] = total[f][t][e] = 0.f;
 #pragma unroll
-    for (int s = 0; s < S - 1; ++s)
-        if (s < nkt) issue(s);
+    for (int kt = -XPT * (SX - 1); kt < 0; ++kt) issue(kt);
     if (!second) score_loop<DT, NF, 0, NF0>(acc, sum, total, lds0, tg, nkt, issue);
     else score_loop<DT, NF, NF0, NF - NF0>(acc, sum, total, lds0, tg, nkt, issue);
 #pragma unroll
@@ -230,7 +247,7 @@ template <int DT, int NF> int launch_scores(const ItemParams& p, int head_dim, h
     if (head_dim == 128) hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 128, NF>), dim3(first), dim3(kThreads), std::max(q_lds, KvItem<DT, 128, 4>::kLds), st, p);
     else hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 64, NF>), dim3(first), dim3(kThreads), std::max(q_lds, KvItem<DT, 64, 4>::kLds), st, p);
     const unsigned groups = (unsigned)((p.ab_tiles + 7) / 8 * p.ab_ks);
-    hipLaunchKernelGGL((apt_absorb_score16_kernel<DT, NF>), dim3((groups + 7) / 8 * 64), dim3(kAbWaves * 64), C::S * C::kStage, st, p);
+    hipLaunchKernelGGL((apt_absorb_score16_kernel<DT, NF>), dim3((groups + 7) / 8 * 64), dim3(kAbWaves * 64), C::kLds, st, p);
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
 }
 

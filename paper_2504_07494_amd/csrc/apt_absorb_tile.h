@@ -100,7 +100,7 @@ template <int N> __device__ inline void ab_fold(f32x4_t (*acc)[N], f32x4_t (*sum
 }
 
 // LDS tile of KT values of k per row: the fp32 operand as NS parts of R = 16 NF rows, and 256 rows of X.  KT = 64 (whole
-// 128-byte lines of X per row) where three stages fit, else 32.
+// 128-byte lines of X per row) where three stages fit, else 32, with X 64 wide all the same where that fits (kWideX).
 template <int DT, int NF> struct AbTile {
     static constexpr int NS = AbSplit<DT>::parts;
     static constexpr int R = 16 * NF;
@@ -108,13 +108,18 @@ template <int DT, int NF> struct AbTile {
     static constexpr int KT = 3 * (kAbMT + R * NS) * 128 <= kLdsMost ? 64 : 32;
     static constexpr int kRow = KT * 2;
     static constexpr int kABytes = R * NS * kRow;
-    static constexpr int kXBytes = kAbMT * kRow;
-    static constexpr int kStage = kABytes + kXBytes;
-    static constexpr int S = kLdsMost / kStage < 7 ? kLdsMost / kStage : 7;
-    static constexpr int kXCopies = kXBytes / 1024 / kAbWaves;    // 1 KB copies per wave and k-tile
+    // 64-wide X tiles, three stages, beside four of 32-wide operand tiles: a k-tile's copies of either were issued three k-tiles ago
+    static constexpr bool kWideX = KT == 32 && 4 * kABytes + 3 * kAbMT * 128 <= kLdsMost;
+    static constexpr int XPT = kWideX ? 2 : 1;                    // k-tiles per X tile
+    static constexpr int kXRow = kRow * XPT;
+    static constexpr int kXBytes = kAbMT * kXRow;
+    static constexpr int S = kWideX ? 4 : kLdsMost / (kABytes + kXBytes) < 7 ? kLdsMost / (kABytes + kXBytes) : 7;
+    static constexpr int SX = kWideX ? 3 : S;
+    static constexpr int kLds = SX * kXBytes + S * kABytes;
+    static constexpr int kXCopies = kXBytes / 1024 / kAbWaves;    // 1 KB copies per wave and X tile
     static constexpr int kACopies = (kABytes / 1024 + kAbWaves - 1) / kAbWaves;
     static constexpr int NF0 = (NF + 1) / 2;                    // head fragments of waves 0..3; waves 4..7 take the rest
-    static constexpr int kCopies = kXCopies + kACopies;
+    static constexpr int kCopies = kXCopies / XPT + kACopies;     // per wave and k-tile
     static_assert(S >= 3 && (S - 2) * kCopies <= 63, "stages / vmcnt range");
 };
 // unit c of a row sits at c ^ ab_swz(row): the 16-row operand reads are free of bank conflicts
