@@ -10,12 +10,12 @@ namespace {
 // copies: [hr][k-tile][part * R + head][unit c at c ^ swizzle(head)], rows of KT values.
 // One wave per (head, 32 rows of W_K), the requests of its z-slice in turn; both operands are 16-bit, so the products are exact.
 // D rows are k, columns are requests; the rows of the two W fragments are dealt so that a lane ends with 8 consecutive k of
-// one request: one 16-byte store per part, 64 contiguous bytes per request.  Eight neighbouring heads of the same rows stay
-// together on one XCD (workgroup g runs on XCD g % 8): their stores meet in the same 128-byte lines.  The queries of all the
+// one request: one 16-byte store per part, 64 contiguous bytes per request.  Eight neighbouring heads of the same rows run
+// together on one XCD (workgroup g runs on XCD g % 8), as their stores lie in the same lines.  The queries of all the
 // requests are put into LDS first: loads between the stores would wait for them, the two share a counter.
 // Bound by the write of QT, R * parts * 2 bytes per k and request (a fill of its size takes 62 us), and by each workgroup's
-// start, W_K and the queries behind their indexes.  72 heads, bf16, 96 requests at d_model 9216 (425 MB): 195 us with
-// queries from memory, 187 in this order, 155 through LDS, 147 with 128 requests to a workgroup.
+// start, W_K and the queries behind their indexes.  72 heads, bf16, 96 requests at d_model 9216 (382 MB, 441 counted at
+// memory): 195 us with queries from memory, 187 in this order, 155 through LDS, 131 with 128 requests to a workgroup.
 //
 // 128 requests where that leaves two workgroups per CU (short contexts, 64 / 128, the whole call: 24 heads, 128 requests 113.1 /
 // 110.4 us, 32 heads, 100 requests 142.5 / 135.5; 16 heads, 100 requests 64.4 / 66.1, not taken).
@@ -118,10 +118,12 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_first_kernel(ItemParams p
 //
 // Bound by how memory serves the X rows, one 128-byte line per row and 64 k (rows lie 2 d_model apart): 64-wide k-tiles
 // in three stages take 87 us for 40 heads, fp16, 33.6 k tokens at d_model 5120 (344 MB of X; 0.40 GB of 128-byte line reads, 4.5
-// TB/s), 32-wide ones in seven stages, with more bytes in flight, 99 us.  Where both do not fit 64 wide, X is 64 wide in three stages beside four 32-wide ones of the
-// queries (kWideX; two k-tiles share an X tile and its copies): the 32-wide halves of a line, joined in L2, made 2.80 GB of line
-// reads for 72 heads, bf16, 102 k tokens at d_model 9216, where X and the queries are 2.31 GB.  Whole call there 1405 / 1373 us
-// (32 / 64 wide), 49 heads, 64 requests of 64..1024 tokens 386 / 374, 65 heads, 16 requests of 20..500 150 / 147.  The version
+// TB/s), 32-wide ones in seven stages, with more bytes in flight, 99 us.  Where both do not fit 64 wide, X is 64 wide in three
+// stages beside four 32-wide ones of the queries (kWideX; two k-tiles share an X tile and its copies): 2.70 GB of memory reads
+// instead of 2.80 for 72 heads, bf16, 102 k tokens at d_model 9216 (X is 1.885 GB; the rest are the queries, 0.4 GB, read by each
+// of the groups that a request's tiles fall into).  Whole call there 1405 / 1373 us (32 / 64 wide), 49 heads, 64 requests of
+// 64..1024 tokens 386 / 374, 65 heads, 16 requests of 20..500 150 / 147.  A start of the k loop that differs between the groups,
+// so that they read other memory channels, changed nothing.  The version
 // with heads padded to 64, an accumulator per part and 512-wide slices took 117 us for the 40 heads, and 1193 us for the 72.
 template <int DT, int NF, int F0, int FN, typename Issue>
 __device__ __forceinline__ void score_loop(f32x4_t (*acc)[4], f32x4_t (*sum)[4], f32x4_t (*total)[4], uint32_t lds0, int tg, int nkt, Issue issue) {

@@ -59,7 +59,16 @@ __global__ __launch_bounds__(NW * 64) void apt_whole_kernel(ItemParams p, char* 
 // ---------------------------------------------------------------------------------
 // merge kernel: out[r][h][c] = sum_s acc_s[c] 2^(m_s - M) / sum_s l_s 2^(m_s - M)
 // ---------------------------------------------------------------------------------
-__device__ inline float merged(const ItemParams& p, int r, int h, int c, int HD) {
+// The merge's own parameters: 56 bytes of kernel arguments, not the 300 of ItemParams (step of the smallest batches 0.2-0.3 us less).
+struct MergeParams {
+    const int32_t* plan;
+    int32_t* kv_ticket;
+    const float* ws_acc;
+    const float2* ws_ml;
+    int32_t B, H;
+};
+
+template <typename Params> __device__ inline float merged(const Params& p, int r, int h, int c, int HD) {
     const int32_t* split_count = p.plan + APT_PW_HEADER + APT_PA_SPLIT_COUNT * p.B;
     const int32_t* ws_offset = p.plan + APT_PW_HEADER + APT_PA_WS_OFFSET * p.B;
     const int ns = split_count[r];
@@ -78,7 +87,7 @@ __device__ inline float merged(const ItemParams& p, int r, int h, int c, int HD)
 }
 
 template <int ODT>
-__global__ __launch_bounds__(kThreads) void apt_merge_kernel(ItemParams p, char* out, int HD) {
+__global__ __launch_bounds__(kThreads) void apt_merge_kernel(MergeParams p, char* out, int HD) {
     const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (gid == 0) *p.kv_ticket = 0;         // the item kernel of this call is done: ready for the next call
     if (gid >= (int64_t)p.B * p.H * HD) return;
@@ -606,13 +615,14 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     if (whole) return APT_OK;
 
     const unsigned blocks = (unsigned)(((int64_t)B * rs.s.n_heads * hd + kThreads - 1) / kThreads);
-    auto launch_merge = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, st, p, (char*)out, hd); };
+    auto launch_merge = [&](auto kern, const auto& params) { hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, st, params, (char*)out, hd); };
     if (hi == APT_HIDDEN_ABSORBED && n_hidden > 0) {
-        if (rs.s.out_dtype == APT_F32) launch_merge(dt == APT_F32 ? apt_absorb_merge_kernel<0, 0> : dt == APT_F16 ? apt_absorb_merge_kernel<1, 0> : apt_absorb_merge_kernel<2, 0>);
-        else if (rs.s.out_dtype == APT_F16) launch_merge(apt_absorb_merge_kernel<1, 1>);
-        else launch_merge(apt_absorb_merge_kernel<2, 2>);
+        if (rs.s.out_dtype == APT_F32) launch_merge(dt == APT_F32 ? apt_absorb_merge_kernel<0, 0> : dt == APT_F16 ? apt_absorb_merge_kernel<1, 0> : apt_absorb_merge_kernel<2, 0>, p);
+        else if (rs.s.out_dtype == APT_F16) launch_merge(apt_absorb_merge_kernel<1, 1>, p);
+        else launch_merge(apt_absorb_merge_kernel<2, 2>, p);
     } else {
-        launch_merge(rs.s.out_dtype == APT_F32 ? apt_merge_kernel<0> : rs.s.out_dtype == APT_F16 ? apt_merge_kernel<1> : apt_merge_kernel<2>);
+        const MergeParams mp = {p.plan, p.kv_ticket, p.ws_acc, p.ws_ml, p.B, p.H};
+        launch_merge(rs.s.out_dtype == APT_F32 ? apt_merge_kernel<0> : rs.s.out_dtype == APT_F16 ? apt_merge_kernel<1> : apt_merge_kernel<2>, mp);
     }
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
 }
