@@ -98,7 +98,7 @@ __device__ __forceinline__ void absorb_q16(const ItemParams& p, int block, char*
 // 40 heads, 32 + 32 requests of 128..2048 tokens 371 / 363 us; 57
 // heads, 7 requests of 158..617 tokens 110 / 101 us (1.4 us of either from the two last kernels in one).
 template <int DT, int HD, int NF>
-__global__ __launch_bounds__(kThreads) void apt_absorb_first_kernel(ItemParams p) {
+__global__ __launch_bounds__(kThreads) void apt_absorb_q16_kernel(ItemParams p) {
     extern __shared__ __align__(16) char lds[];
     const int n_kv = p.n_items - p.n_hidden_items;
     if ((int)blockIdx.x < n_kv) {
@@ -246,8 +246,8 @@ template <int DT, int NF> int launch_scores(const ItemParams& p, int head_dim, h
     const unsigned first = (unsigned)(p.n_items - p.n_hidden_items) +
                            (unsigned)((ab_q_groups(p) + 7) / 8 * 64);
     const int q_lds = (std::min(p.n_hid_req, ab_q_reqs(p)) + 15) / 16 * 16 * head_dim * 2;
-    if (head_dim == 128) hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 128, NF>), dim3(first), dim3(kThreads), std::max(q_lds, KvItem<DT, 128, 4>::kLds), st, p);
-    else hipLaunchKernelGGL((apt_absorb_first_kernel<DT, 64, NF>), dim3(first), dim3(kThreads), std::max(q_lds, KvItem<DT, 64, 4>::kLds), st, p);
+    if (head_dim == 128) hipLaunchKernelGGL((apt_absorb_q16_kernel<DT, 128, NF>), dim3(first), dim3(kThreads), std::max(q_lds, KvItem<DT, 128, 4>::kLds), st, p);
+    else hipLaunchKernelGGL((apt_absorb_q16_kernel<DT, 64, NF>), dim3(first), dim3(kThreads), std::max(q_lds, KvItem<DT, 64, 4>::kLds), st, p);
     const unsigned groups = (unsigned)((p.ab_tiles + 7) / 8 * p.ab_ks);
     hipLaunchKernelGGL((apt_absorb_score16_kernel<DT, NF>), dim3((groups + 7) / 8 * 64), dim3(kAbWaves * 64), C::kLds, st, p);
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
