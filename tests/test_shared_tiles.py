@@ -174,3 +174,26 @@ def test_a_request_with_infinities_leaves_the_others_of_its_tile_alone():
     got = rn.out_f64()
     good = np.setdiff1d(np.arange(len(lens)), bad)
     assert np.array_equal(got[good], want[good]) and not np.isfinite(got[bad]).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_kv", [0, 3])
+def test_a_cap_for_a_queue_without_heads_is_passed_over(n_kv):
+    """Queue 7 of 7 heads holds no items: what follows it in the list are KV-kind ranges of up to 512 tokens, or nothing.  Queues of
+    a plan without heads have no cap; one that is there all the same changes nothing."""
+    from paper_2504_07494_amd.harness import DecodeRunner
+    print(f"[case] cap for an empty queue, {n_kv} KV-kind requests", flush=True)
+    lens = np.array([31, 64, 100, 1] * 10 + [600, 512, 90][:n_kv], dtype=np.int32)
+    cfg = wl.small_config(name="emptyqueue", dtype="f16", d_model=128 * 7, n_heads=7, head_dim=128, block_size=16, batch=len(lens),
+                          len_lo=1, len_hi=600, hidden_ratio=1.0)
+    batch = wl.make_batch(cfg, lens, np.array([HID] * 40 + [KV] * n_kv, dtype=np.uint8))
+    rn = DecodeRunner(batch)
+    caps = _caps(rn.info, rn.plan_host.numpy())
+    assert min(caps[:7]) > 0 and caps[7] == 0
+    dl = rn.upload(wl.make_layer(batch))
+    rn.run(dl)
+    want = rn.out.clone()
+    torch.cuda.synchronize()
+    rn.plan_dev[31] = int(rn.plan_dev[31]) | 5 << 28
+    rn.run(dl)
+    assert torch.equal(rn.out, want) and bool(torch.isfinite(want).all())
