@@ -197,3 +197,41 @@ def test_a_cap_for_a_queue_without_heads_is_passed_over(n_kv):
     rn.plan_dev[31] = int(rn.plan_dev[31]) | 5 << 28
     rn.run(dl)
     assert torch.equal(rn.out, want) and bool(torch.isfinite(want).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,tile,H,bs", [("f16", 256, 8, 16), ("bf16", 256, 9, 8), ("f16", 320, 3, 32), ("bf16", 320, 8, 16)])
+def test_output_of_a_hidden_kind_request_does_not_depend_on_the_batch(dtype, tile, H, bs):
+    """Bit for bit: with shared tiles of every cap, with a tile per range, in tiles of 320 rows for ranges of 256 tokens, and each
+    request in a batch of its own."""
+    from paper_2504_07494_amd.harness import DecodeRunner
+    print(f"[case] batch invariance {dtype} tile {tile} heads {H}", flush=True)
+    lens = np.array(LENS[tile] + LENS[tile][:16] + [33, 34, 64, 95] * 4 + [1, 30], dtype=np.int32)
+    lens = lens[np.random.default_rng(tile + H).permutation(len(lens))]
+    cfg = wl.small_config(name="invariant", dtype=dtype, d_model=128 * H, n_heads=H, head_dim=128, block_size=bs, batch=len(lens),
+                          len_lo=1, len_hi=700, hidden_ratio=1.0)
+    batch = wl.make_batch(cfg, lens, np.full(len(lens), HID, dtype=np.uint8))
+    layer = wl.make_layer(batch)
+    rn = DecodeRunner(batch, hidden_chunk=tile)
+    assert _caps(rn.info, rn.plan_host.numpy())[0] > 0
+    dl = rn.upload(layer)
+    rn.run(dl)
+    want = rn.out.clone()
+    torch.cuda.synchronize()
+    queues = min(H, 8)
+    for wide in (0, 1) if tile == 256 else (0,):                  # the host's word picks the kernel, the device's the caps
+        for cap in (0, 4, 5, 6, 7, 8, 9, 10):
+            word = sum(cap << 4 * x for x in range(queues))
+            rn.plan_host[31] = 10 * wide
+            rn.plan_dev[31] = word - (1 << 32) if word >= 1 << 31 else word
+            rn.out.fill_(float("nan"))
+            rn.run(dl)
+            assert torch.equal(rn.out, want), (wide, cap)
+    for r in range(0, len(lens), 3):
+        one = wl.make_batch(wl.replace(cfg, batch=1), lens[r:r + 1], np.array([HID], dtype=np.uint8))
+        rn1 = DecodeRunner(one, hidden_chunk=tile)
+        rn1.block_tables = rn.block_tables[r:r + 1, :, :one.max_blocks].contiguous()     # its blocks in the same pool
+        dl.q, q = dl.q[r:r + 1].contiguous(), dl.q
+        rn1.run(dl)
+        dl.q = q
+        assert torch.equal(rn1.out[0], want[r]), int(lens[r])
