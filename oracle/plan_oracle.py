@@ -33,6 +33,7 @@ against it bit for bit:
   tokens, one or two; a tile is the word 2 * item + (0 or 1), in item order.  Units: 1, 2 or 4 neighbouring ranges of one
   request are summed together, the most with which the batch still has 768 units x ceil(d_model / 512) column slices (fp32
   inputs, and batches that never have: 1); a unit is the word of its first item, longest unit first, ties in item order.
+* with packed weights the plan's word 31 says how the shorter last ranges share tiles (shared_tiles_word below).
 
 Block arithmetic of the cache map (Section 4.3): token j of a request lives in
 its (j // block_size)-th block at slot j % block_size; a request of n tokens owns
@@ -86,6 +87,90 @@ def absorbed_lists(ctx_lens, cache_kind, d_model, dtype):
     units = [i for i, (r, t0) in enumerate(ranges) if t0 % (512 * group) == 0]
     units.sort(key=lambda i: -min(512 * group, int(ctx_lens[ranges[i][0]]) - ranges[i][1]))
     return tiles, group, units
+
+
+def tile_patterns(count, cap, blocks):
+    """Which ranges share a tile of `blocks` blocks of 32 rows of which `cap` may be filled.  count[c]: ranges of c blocks.  A tile takes as
+    many of the largest class as fit and are left, then of the next smaller one, and so on, at most 6 (tile of 10 blocks) or 8
+    ranges; a range longer than the cap is alone.  The pattern is used as often as the ranges last.  [(tiles, {class: ranges})]."""
+    left, out = dict(enumerate(count)), []
+    most = 6 if blocks == 10 else 8
+    while any(left[c] for c in range(1, blocks + 1)):
+        take, room = {}, cap
+        for c in range(blocks, 0, -1):
+            t = min(room // c, most - sum(take.values()), left[c])
+            if not take and left[c] and c > room:
+                t = 1
+            if t:
+                take[c] = t
+                room = max(0, room - t * c)
+        tiles = min(left[c] // t for c, t in take.items())
+        for c, t in take.items():
+            left[c] -= tiles * t
+        out.append((tiles, take))
+    return out
+
+
+def _end_of_queue(tiles, kv):
+    """When the last of a queue's 32 workgroups ends, times 32.  tiles: costs in the order of the queue, dealt in rounds, every second
+    one backwards; the KV-kind items (kv) even the workgroups out."""
+    load = [0] * 32
+    for i, cost in enumerate(tiles):
+        load[i % 32 if (i // 32) % 2 == 0 else 31 - i % 32] += cost
+    return max(32 * max(load), sum(tiles) + 32 * kv)
+
+
+def _tile_cost(blocks, filled):
+    return 1150000 + 200000 * max(filled, 2) if blocks == 10 else 700000 + 225000 * max(filled, 2)
+
+
+def _cap_of_queue(n_full, full_blocks, count, heads, kv, blocks):
+    """(end, cap) of a queue with `heads` heads.  Full ranges as long as the tile have tiles of their own; shorter ones are ranges
+    like the others, and then there is no cap 0."""
+    own = full_blocks == blocks
+    best = None
+    if own:
+        tiles = [_tile_cost(blocks, blocks)] * (n_full * heads)
+        for c in range(blocks, 0, -1):
+            tiles += [_tile_cost(blocks, c)] * (count[c] * heads)
+        best = (_end_of_queue(tiles, kv), 0)
+        if sum(count) < 2 or len(tiles) <= 32:
+            return best
+    for cap in range(blocks, 3 if own else full_blocks, -1):
+        tiles = [_tile_cost(blocks, blocks)] * (n_full * heads if own else 0)
+        ranges = list(count)
+        if not own:
+            ranges[full_blocks] += n_full
+        for n, take in tile_patterns(ranges, cap, blocks):
+            tiles += [_tile_cost(blocks, sum(c * t for c, t in take.items()))] * (n * heads)
+        end = _end_of_queue(tiles, kv)
+        if best is None or end < best[0]:
+            best = (end, cap)
+    return best
+
+
+def shared_tiles_word(ctx_lens, cache_kind, n_heads, hidden_chunk):
+    """Word 31 of a plan with packed weights and hidden-kind requests: four bits per queue, the blocks a shared tile may fill (0: a
+    tile per range).  Tiles have hidden_chunk rows, or 320 rows for ranges of 256 where every queue is done sooner with them."""
+    hid = [int(n) for n, k in zip(ctx_lens, cache_kind) if int(k) == KIND_HIDDEN]
+    kv = 74 * sum(int(n) for n, k in zip(ctx_lens, cache_kind) if int(k) == KIND_KV)
+    count = [0] * 11
+    for n in hid:
+        if n % hidden_chunk:
+            count[ceil_div(n % hidden_chunk, 32)] += 1
+    n_full = sum(n // hidden_chunk for n in hid)
+    heads = [ceil_div(n_heads - x, N_QUEUES) for x in range(min(n_heads, N_QUEUES))]
+
+    def choice(blocks):
+        per = {h: _cap_of_queue(n_full, hidden_chunk // 32, count, h, kv, blocks) for h in set(heads)}
+        return max(per[h][0] for h in heads), sum(per[h][1] << 4 * x for x, h in enumerate(heads))
+
+    own = choice(hidden_chunk // 32)
+    if hidden_chunk == 256:
+        wide = choice(10)
+        if wide[0] < own[0]:
+            return wide[1]
+    return own[1]
 
 
 def plan(ctx_lens, cache_kind, n_heads, hidden_chunk, kv_chunk, hidden_item_per_head=True):

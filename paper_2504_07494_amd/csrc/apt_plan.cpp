@@ -120,38 +120,36 @@ extern "C" int apt_workspace_bytes(const apt_shape* s, int max_batch, int max_ct
     return APT_OK;
 }
 
-// The cap of a head queue's shared tiles and when its last workgroup ends with it.
-struct SharedTiles { int cap; double end; };
+// The cap of a head queue's shared tiles and when its last workgroup ends with it, in 32nds of a cost unit.
+struct SharedTiles { int cap; int64_t end; };
 
 // Tiles of NC blocks for a head queue of n_heads heads.  full: ranges of full_blocks blocks, the longest; count[c]: shorter ranges
 // of c blocks; kv: time of the KV-kind items, which even the workgroups out.  Up to one tile per workgroup nothing is shared: a
 // fuller tile only takes longer.  Beyond that, the cap (0: a tile per range, not where full ranges are shorter than the tile) is
 // the one with which the workgroup that is last ends first, the tiles dealt as the kernel deals them (rounds, every second one
-// backwards).  Unit of time: 5 us at d_model 5120, proportional to d_model; measured with all workgroups busy, tiles of 1, 2 .. blocks:
+// backwards).  Unit of cost: 50 ps at d_model 5120, proportional to d_model; measured with all workgroups busy, tiles of 1, 2 .. blocks:
 // NC 8, d_model 5120: 59, 58, 67, 78, 91, 100, 117, 126 us; NC 10, d_model 9216: 129, 140, 159, 186, 199, 218, 225, 242, 267, 282
 // (the copies of a k-tile do not shrink with the rows that hold tokens).
 template <int NC>
-static SharedTiles shared_tiles(int64_t full, int full_blocks, const int32_t* count, int64_t n_heads, double kv) {
+static SharedTiles shared_tiles(int64_t full, int full_blocks, const int32_t* count, int64_t n_heads, int64_t kv) {
     constexpr int kWorkgroups = 32;                        // per queue, on 256 compute units
-    double load[kWorkgroups], all, total;
-    int64_t at;
+    int64_t load[kWorkgroups], all, total, at;
     auto begin = [&] {
-        at = 0;
-        all = total = 0.0;
-        for (double& l : load) l = 0.0;
+        at = all = total = 0;
+        for (int64_t& l : load) l = 0;
     };
     auto deal = [&](int blocks, int64_t tiles) {
-        const double cost = NC == 10 ? 11.5 + 2.0 * std::max(blocks, 2) : 7.0 + 2.25 * std::max(blocks, 2);
+        const int64_t cost = NC == 10 ? 1150000 + 200000 * std::max(blocks, 2) : 700000 + 225000 * std::max(blocks, 2);
         const int64_t pairs = tiles / (2 * kWorkgroups);   // two rounds give every workgroup two tiles, wherever they begin
-        all += 2.0 * cost * (double)pairs;
-        total += cost * (double)tiles;
+        all += 2 * cost * pairs;
+        total += cost * tiles;
         for (tiles -= pairs * 2 * kWorkgroups; tiles > 0; --tiles, ++at) {
             const int i = (int)(at % kWorkgroups);
             load[(at / kWorkgroups) & 1 ? kWorkgroups - 1 - i : i] += cost;
         }
     };
-    auto ends = [&] { return std::max(all + *std::max_element(load, load + kWorkgroups), total / kWorkgroups + kv); };
-    SharedTiles best = {0, 1e300};
+    auto ends = [&] { return std::max((all + *std::max_element(load, load + kWorkgroups)) * kWorkgroups, total + kv * kWorkgroups); };
+    SharedTiles best = {0, INT64_MAX};
     const bool whole = full_blocks == NC;                  // a full range is a tile of its own
     int64_t tails = 0;
     for (int c = 1; c < APT_PACK_MAX_BLOCKS + 1; ++c) tails += count[c];
@@ -173,13 +171,14 @@ static SharedTiles shared_tiles(int64_t full, int full_blocks, const int32_t* co
             for (int c = 1; c <= NC; ++c) blocks += c * take[c];
             deal(blocks, (int64_t)reps * n_heads);
         });
-        const double t = ends();
+        const int64_t t = ends();
         if (t < best.end) best = {k, t};
     }
     return best;
 }
 
-// The word APT_PW_SHARED_TILES of a batch with packed weights.
+// The word APT_PW_SHARED_TILES of a batch with packed weights.  Integers throughout, so that a batch has one plan whatever the compiler
+// makes of sums and ties.
 static uint32_t shared_tiles_word(const int32_t* ctx_lens, const uint8_t* cache_kind, int B, int H, int chunk, int64_t kv_tokens) {
     int64_t full = 0;
     int32_t count[APT_PACK_MAX_BLOCKS + 1] = {0};
@@ -188,11 +187,11 @@ static uint32_t shared_tiles_word(const int32_t* ctx_lens, const uint8_t* cache_
         full += ctx_lens[r] / chunk;
         if (ctx_lens[r] % chunk) ++count[ceil_div64(ctx_lens[r] % chunk, APT_PACK_BLOCK)];
     }
-    const double kv = (double)kv_tokens * 7.4e-4;          // 4 d bytes a token at 5.5 TB/s
+    const int64_t kv = kv_tokens * 74;                     // 4 d bytes a token at 5.5 TB/s
     uint32_t word = 0, wide = 0;
-    double end = 0.0, wide_end = 0.0;
+    int64_t end = 0, wide_end = 0;
     const bool large = chunk == APT_MFMA_HIDDEN_CHUNK;
-    SharedTiles t = {0, 0.0}, tw = {0, 0.0};
+    SharedTiles t = {0, 0}, tw = {0, 0};
     for (int x = 0, prev = -1; x < APT_N_QUEUES; ++x) {
         const int nh = (H - x + APT_N_QUEUES - 1) / APT_N_QUEUES;      // two numbers of heads at most, the larger first
         if (nh == 0) break;

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import plan_oracle as po
 from paper_2504_07494_amd import binding as ab
 from paper_2504_07494_amd import workloads as wl
 from tests.helpers import oracle_attn
@@ -85,6 +86,24 @@ def test_planner_shares_tiles_only_beyond_one_tile_per_workgroup():
     assert _plan([256] * 28 + [257, 300, 320, 316], [HID] * 32, heads=8) == [10] * 8
     assert _plan([256] * 28 + [257, 300, 320, 316], [HID] * 32, heads=7) == [10] * 7 + [0]
     assert _plan([320] * 640, [HID] * 640, heads=8) == [8] * 8
+
+
+def test_planner_word_against_the_plain_rule():
+    """Few and many heads, queues of two sizes, batches of one round and of many, both chunks, any share of KV-kind requests."""
+    g = np.random.default_rng(31)
+    seen = set()
+    for i in range(1200):
+        heads = int(g.integers(1, 73))
+        B = int(10 ** g.uniform(0, 2.4))
+        top = int(10 ** g.uniform(1, 3.3))
+        lens = g.integers(1, top + 1, size=B) if i % 4 else np.minimum(2048, 32 * g.integers(1, 20, size=B))
+        kinds = (g.random(B) < g.choice([0.1, 0.5, 0.9, 1.0])).astype(np.uint8)
+        tile = int(g.choice([256, 320]))
+        caps = _plan(lens, kinds, heads=heads, tile=tile)
+        word = po.shared_tiles_word(lens, kinds, heads, tile) if kinds.any() else 0
+        assert caps == [(word >> 4 * x) & 15 for x in range(8)], (heads, tile, lens.tolist(), kinds.tolist())
+        seen.update((tile, c) for c in caps)
+    assert seen == {(t, c) for t in (256, 320) for c in [0, *range(4, 11)]}
 
 
 LENS = {256: [255, 225, 224, 193, 161, 160, 129, 128, 97, 96, 65, 64, 63, 33, 32, 31, 2, 1, 256, 257, 300, 511, 700],
