@@ -59,10 +59,7 @@ APT_HOST_DEVICE static inline void apt_pack_patterns(int32_t* left, int cap, Emi
             n += t;
             room -= t * c;
             if (room < 0) room = 0;
-            if (t > 0) {
-                const int32_t r = t == 1 ? left[c] : left[c] / t;
-                reps = r < reps ? r : reps;
-            }
+            if (t > 0 && (int64_t)reps * t > left[c]) reps = t == 1 ? left[c] : left[c] / t;
         }
         if (n == 0) return;
 #pragma unroll

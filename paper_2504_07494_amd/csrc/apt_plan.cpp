@@ -130,51 +130,66 @@ struct SharedTiles { int cap; int64_t end; };
 // backwards).  Unit of cost: 50 ps at d_model 5120, proportional to d_model; measured with all workgroups busy, tiles of 1, 2 .. blocks:
 // NC 8, d_model 5120: 59, 58, 67, 78, 91, 100, 117, 126 us; NC 10, d_model 9216: 129, 140, 159, 186, 199, 218, 225, 242, 267, 282
 // (the copies of a k-tile do not shrink with the rows that hold tokens).
-template <int NC>
-static SharedTiles shared_tiles(int64_t full, int full_blocks, const int32_t* count, int64_t n_heads, int64_t kv) {
-    constexpr int kWorkgroups = 32;                        // per queue, on 256 compute units
-    int64_t load[kWorkgroups], all, total, at;
-    auto begin = [&] {
-        at = all = total = 0;
-        for (int64_t& l : load) l = 0;
-    };
-    auto deal = [&](int blocks, int64_t tiles) {
-        const int64_t cost = NC == 10 ? 1150000 + 200000 * std::max(blocks, 2) : 700000 + 225000 * std::max(blocks, 2);
-        const int64_t pairs = tiles / (2 * kWorkgroups);   // two rounds give every workgroup two tiles, wherever they begin
-        all += 2 * cost * pairs;
+// Tiles of a head queue, dealt to its workgroups in rounds, every second one backwards.  Runs of equal tiles are added as differences
+// between neighbouring workgroups, at most three to a run, so the time does not grow with the tiles.
+struct Deal {
+    static constexpr int kWorkgroups = 32;                 // per queue, on 256 compute units
+    int64_t step[kWorkgroups + 1] = {0}, all = 0, total = 0;
+    int at = 0;                                            // place in the current pair of rounds
+    void add(int64_t cost, int64_t tiles) {
+        all += tiles / (2 * kWorkgroups) * 2 * cost;       // two rounds give every workgroup two tiles, wherever they begin
         total += cost * tiles;
-        for (tiles -= pairs * 2 * kWorkgroups; tiles > 0; --tiles, ++at) {
-            const int i = (int)(at % kWorkgroups);
-            load[(at / kWorkgroups) & 1 ? kWorkgroups - 1 - i : i] += cost;
+        for (int left = (int)(tiles % (2 * kWorkgroups)); left > 0;) {
+            const int n = std::min(left, kWorkgroups - at % kWorkgroups);
+            const int first = at < kWorkgroups ? at : 2 * kWorkgroups - at - n;
+            step[first] += cost;
+            step[first + n] -= cost;
+            at = (at + n) % (2 * kWorkgroups);
+            left -= n;
         }
-    };
-    auto ends = [&] { return std::max((all + *std::max_element(load, load + kWorkgroups)) * kWorkgroups, total + kv * kWorkgroups); };
-    SharedTiles best = {0, INT64_MAX};
+    }
+    int64_t ends(int64_t kv) const {
+        int64_t most = 0, load = 0;
+        for (int i = 0; i < kWorkgroups; ++i) most = std::max(most, load += step[i]);
+        return std::max((all + most) * kWorkgroups, total + kv * kWorkgroups);
+    }
+};
+
+// n_heads: heads of the queues, nq = one or two numbers; best[i] for n_heads[i].
+template <int NC>
+static void shared_tiles(int64_t full, int full_blocks, const int32_t* count, const int64_t* n_heads, int nq, int64_t kv, SharedTiles* best) {
     const bool whole = full_blocks == NC;                  // a full range is a tile of its own
+    auto cost = [](int blocks) -> int64_t { return NC == 10 ? 1150000 + 200000 * std::max(blocks, 2) : 700000 + 225000 * std::max(blocks, 2); };
+    bool share[2] = {true, true};
     int64_t tails = 0;
     for (int c = 1; c < APT_PACK_MAX_BLOCKS + 1; ++c) tails += count[c];
-    if (whole) {
-        begin();
-        deal(NC, full * n_heads);
-        for (int c = NC; c >= 1; --c) deal(c, count[c] * n_heads);
-        best.end = ends();
-        if (tails < 2 || (full + tails) * n_heads <= kWorkgroups) return best;
+    for (int i = 0; i < nq; ++i) {
+        best[i] = {0, INT64_MAX};
+        if (!whole) continue;
+        Deal d;
+        d.add(cost(NC), full * n_heads[i]);
+        for (int c = NC; c >= 1; --c) d.add(cost(c), count[c] * n_heads[i]);
+        best[i].end = d.ends(kv);
+        share[i] = tails >= 2 && (full + tails) * n_heads[i] > Deal::kWorkgroups;
     }
+    if (!share[0] && (nq == 1 || !share[1])) return;
     for (int k = NC; k >= (whole ? 4 : full_blocks + 1); --k) {
         int32_t left[NC + 1];
         std::copy(count, count + NC + 1, left);
         if (!whole) left[full_blocks] += (int32_t)full;
-        begin();
-        if (whole) deal(NC, full * n_heads);
+        Deal d[2];
+        for (int i = 0; i < nq; ++i)
+            if (whole) d[i].add(cost(NC), full * n_heads[i]);
         apt_pack_patterns<NC>(left, k, [&](int32_t reps, const int32_t* take) {
             int blocks = 0;
             for (int c = 1; c <= NC; ++c) blocks += c * take[c];
-            deal(blocks, (int64_t)reps * n_heads);
+            for (int i = 0; i < nq; ++i) d[i].add(cost(blocks), reps * n_heads[i]);
         });
-        const int64_t t = ends();
-        if (t < best.end) best = {k, t};
+        for (int i = 0; i < nq; ++i) {
+            const int64_t t = d[i].ends(kv);
+            if (share[i] && t < best[i].end) best[i] = {k, t};
+        }
     }
-    return best;
 }
 
 // The word APT_PW_SHARED_TILES of a batch with packed weights.  Integers throughout, so that a batch has one plan whatever the compiler
@@ -188,26 +203,25 @@ static uint32_t shared_tiles_word(const int32_t* ctx_lens, const uint8_t* cache_
         if (ctx_lens[r] % chunk) ++count[ceil_div64(ctx_lens[r] % chunk, APT_PACK_BLOCK)];
     }
     const int64_t kv = kv_tokens * 74;                     // 4 d bytes a token at 5.5 TB/s
-    uint32_t word = 0, wide = 0;
-    int64_t end = 0, wide_end = 0;
+    // two numbers of heads at most, the larger first
+    const int64_t n_heads[2] = {(H + APT_N_QUEUES - 1) / APT_N_QUEUES, H / APT_N_QUEUES};
+    const int nq = n_heads[1] > 0 && n_heads[1] < n_heads[0] ? 2 : 1;
     const bool large = chunk == APT_MFMA_HIDDEN_CHUNK;
-    SharedTiles t = {0, 0}, tw = {0, 0};
-    for (int x = 0, prev = -1; x < APT_N_QUEUES; ++x) {
-        const int nh = (H - x + APT_N_QUEUES - 1) / APT_N_QUEUES;      // two numbers of heads at most, the larger first
-        if (nh == 0) break;
-        if (nh != prev) {
-            t = large ? shared_tiles<10>(full, 10, count, nh, kv) : shared_tiles<8>(full, 8, count, nh, kv);
-            if (!large) tw = shared_tiles<10>(full, 8, count, nh, kv);
-        }
-        prev = nh;
-        word |= (uint32_t)t.cap << (4 * x);
-        wide |= (uint32_t)tw.cap << (4 * x);
-        end = std::max(end, t.end);
-        wide_end = std::max(wide_end, tw.end);
+    SharedTiles t[2], tw[2];
+    if (large) shared_tiles<10>(full, 10, count, n_heads, nq, kv, t);
+    else {
+        shared_tiles<8>(full, 8, count, n_heads, nq, kv, t);
+        shared_tiles<10>(full, 8, count, n_heads, nq, kv, tw);
     }
+    auto word_of = [&](const SharedTiles* s) {
+        uint32_t word = 0;
+        for (int x = 0; x < APT_N_QUEUES && x < H; ++x) word |= (uint32_t)s[nq == 2 && x >= H % APT_N_QUEUES].cap << (4 * x);
+        return word;
+    };
+    auto end_of = [&](const SharedTiles* s) { return nq == 2 ? std::max(s[0].end, s[1].end) : s[0].end; };
     // Ranges of 256 tokens in tiles of 320 rows, a full range beside a short one, where that saves a round: 40 heads, requests of
     // 415, 513 and 619 tokens (40 tiles a queue, then 30) 193 -> 166 us a step.
-    return !large && wide_end < end ? wide : word;
+    return !large && end_of(tw) < end_of(t) ? word_of(tw) : word_of(t);
 }
 
 extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8_t* cache_kind, int B,
@@ -327,7 +341,16 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
     // decreasing length.  Then the KV kind by decreasing range length.
     int32_t* it = w + items_off;
     int32_t* const it0 = it;
-    std::vector<int32_t> tails;     // requests with a shorter last range, to be ordered by its length
+    // Requests with a shorter last range, by its length: the same for every queue of a kind.  apt_plan, us, sorted for every queue /
+    // once: 64 requests, 40 heads 34.3 / 19.5, 256 requests, 71 heads 149.9 / 75.0.
+    std::vector<int32_t> tails;
+    auto order_tails = [&](uint8_t want, int c) {
+        tails.clear();
+        for (int r = 0; r < B; ++r)
+            if (cache_kind[r] == want && ctx_lens[r] % c != 0) tails.push_back(r);
+        std::stable_sort(tails.begin(), tails.end(),
+                         [&](int32_t a, int32_t b) { return ctx_lens[a] % c > ctx_lens[b] % c; });
+    };
     auto emit_kind = [&](uint8_t want, int c, int h_first, int h_step) {
         for (int r = 0; r < B; ++r) {       // full ranges
             if (cache_kind[r] != want) continue;
@@ -338,11 +361,6 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
                     it += 4;
                 }
         }
-        tails.clear();
-        for (int r = 0; r < B; ++r)
-            if (cache_kind[r] == want && ctx_lens[r] % c != 0) tails.push_back(r);
-        std::stable_sort(tails.begin(), tails.end(),
-                         [&](int32_t a, int32_t b) { return ctx_lens[a] % c > ctx_lens[b] % c; });
         for (int32_t r : tails) {
             const int t0 = (ctx_lens[r] / c) * c;
             for (int h = h_first; h < H; h += h_step) {
@@ -351,6 +369,7 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
             }
         }
     };
+    if (!absorbed) order_tails(APT_KIND_HIDDEN, rs.s.hidden_chunk);
     for (int x = 0; x < APT_N_QUEUES; ++x) {
         w[APT_PW_QUEUE0 + x] = (int32_t)((it - it0) / 4);
         if (!absorbed) {
@@ -370,6 +389,7 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
     w[APT_PW_QUEUE0 + APT_N_QUEUES] = (int32_t)((it - it0) / 4);
     if (rs.s.hidden_impl == APT_HIDDEN_MFMA && n_hidden_items > 0)
         w[APT_PW_SHARED_TILES] = (int32_t)shared_tiles_word(ctx_lens, cache_kind, B, H, rs.s.hidden_chunk, tok - htok);
+    order_tails(APT_KIND_KV, rs.s.kv_chunk);
     emit_kind(APT_KIND_KV, rs.s.kv_chunk, 0, 1);
     // absorbed-weight path: the 256-token tiles of the hidden-kind ranges in their order, 2 * item + half; then the units
     // (their first ranges), longest first
