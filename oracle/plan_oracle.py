@@ -40,6 +40,8 @@ its (j // block_size)-th block at slot j % block_size; a request of n tokens own
 ceil(n / block_size) blocks per cached vector type (K and V for the KV kind, the
 input hidden vector for the hidden kind).
 """
+import itertools
+
 KIND_KV = 0
 KIND_HIDDEN = 1
 N_QUEUES = 8
@@ -111,66 +113,69 @@ def tile_patterns(count, cap, blocks):
     return out
 
 
-def _end_of_queue(tiles, kv):
-    """When the last of a queue's 32 workgroups ends, times 32.  tiles: costs in the order of the queue, dealt in rounds, every second
-    one backwards; the KV-kind items (kv) even the workgroups out."""
-    load = [0] * 32
-    for i, cost in enumerate(tiles):
-        load[i % 32 if (i // 32) % 2 == 0 else 31 - i % 32] += cost
-    return max(32 * max(load), sum(tiles) + 32 * kv)
+def tile_ns(blocks, d_model, filled, ranges):
+    """Time of a tile of `blocks` blocks of which `filled` hold tokens of `ranges` ranges."""
+    f = max(filled, 2)
+    if blocks == 8:
+        return 10000 + d_model * (20000 + 11100 * f) // 5120 + 800 * (ranges - 1)
+    k_loop = 4300 + 2280 * f if d_model < 8192 else 11100 + 1880 * f
+    return 11000 + 800 * f + d_model * k_loop // 1024 + 1100 * (ranges - 1)
 
 
-def _tile_cost(blocks, filled):
-    return 1150000 + 200000 * max(filled, 2) if blocks == 10 else 700000 + 225000 * max(filled, 2)
+def _queue_options(n_full, full_blocks, count, heads, blocks, d_model):
+    """[(cap, end of the last of the queue's 32 workgroups, time of all tiles)] of a queue with `heads` heads.  Tiles are dealt in
+    rounds, every second one backwards.  Full ranges as long as the tile have tiles of their own; shorter ones are ranges like the
+    others, and then there is no cap 0.  Sharing costs a workgroup 2500 ns at its begin."""
+    def option(cap, tiles):
+        begin = 2500 if cap else 0
+        load = [begin] * 32
+        for i, ns in enumerate(tiles):
+            load[i % 32 if (i // 32) % 2 == 0 else 31 - i % 32] += ns
+        return cap, max(load), sum(load)
 
-
-def _cap_of_queue(n_full, full_blocks, count, heads, kv, blocks):
-    """(end, cap) of a queue with `heads` heads.  Full ranges as long as the tile have tiles of their own; shorter ones are ranges
-    like the others, and then there is no cap 0."""
     own = full_blocks == blocks
-    best = None
+    fulls = [tile_ns(blocks, d_model, blocks, 1)] * (n_full * heads if own else 0)
+    out = []
     if own:
-        tiles = [_tile_cost(blocks, blocks)] * (n_full * heads)
-        for c in range(blocks, 0, -1):
-            tiles += [_tile_cost(blocks, c)] * (count[c] * heads)
-        best = (_end_of_queue(tiles, kv), 0)
+        tiles = fulls + [tile_ns(blocks, d_model, c, 1) for c in range(blocks, 0, -1) for _ in range(count[c] * heads)]
+        out.append(option(0, tiles))
         if sum(count) < 2 or len(tiles) <= 32:
-            return best
+            return out
     for cap in range(blocks, 3 if own else full_blocks, -1):
-        tiles = [_tile_cost(blocks, blocks)] * (n_full * heads if own else 0)
         ranges = list(count)
         if not own:
             ranges[full_blocks] += n_full
+        tiles = list(fulls)
         for n, take in tile_patterns(ranges, cap, blocks):
-            tiles += [_tile_cost(blocks, sum(c * t for c, t in take.items()))] * (n * heads)
-        end = _end_of_queue(tiles, kv)
-        if best is None or end < best[0]:
-            best = (end, cap)
-    return best
+            tiles += [tile_ns(blocks, d_model, sum(c * t for c, t in take.items()), sum(take.values()))] * (n * heads)
+        out.append(option(cap, tiles))
+    return out
 
 
-def shared_tiles_word(ctx_lens, cache_kind, n_heads, hidden_chunk):
+def shared_tiles_word(ctx_lens, cache_kind, n_heads, d_model, hidden_chunk):
     """Word 31 of a plan with packed weights and hidden-kind requests: four bits per queue, the blocks a shared tile may fill (0: a
-    tile per range).  Tiles have hidden_chunk rows, or 320 rows for ranges of 256 where every queue is done sooner with them."""
+    tile per range).  Tiles have hidden_chunk rows, or 320 rows for ranges of 256 where the launch is done sooner with them.  A
+    launch is done when its last workgroup is, but not before all its work, the KV-kind items' included, is spread evenly over 256;
+    of equals, the one with less work, then the first (cap 0, then the larger caps)."""
     hid = [int(n) for n, k in zip(ctx_lens, cache_kind) if int(k) == KIND_HIDDEN]
-    kv = 74 * sum(int(n) for n, k in zip(ctx_lens, cache_kind) if int(k) == KIND_KV)
+    kv = sum(int(n) for n, k in zip(ctx_lens, cache_kind) if int(k) == KIND_KV) * d_model // 1375
     count = [0] * 11
     for n in hid:
         if n % hidden_chunk:
             count[ceil_div(n % hidden_chunk, 32)] += 1
     n_full = sum(n // hidden_chunk for n in hid)
     heads = [ceil_div(n_heads - x, N_QUEUES) for x in range(min(n_heads, N_QUEUES))]
+    sizes = sorted(set(heads), reverse=True)
 
-    def choice(blocks):
-        per = {h: _cap_of_queue(n_full, hidden_chunk // 32, count, h, kv, blocks) for h in set(heads)}
-        return max(per[h][0] for h in heads), sum(per[h][1] << 4 * x for x, h in enumerate(heads))
-
-    own = choice(hidden_chunk // 32)
-    if hidden_chunk == 256:
-        wide = choice(10)
-        if wide[0] < own[0]:
-            return wide[1]
-    return own[1]
+    best = None
+    for blocks in [hidden_chunk // 32] + ([10] if hidden_chunk == 256 else []):
+        options = [_queue_options(n_full, hidden_chunk // 32, count, h, blocks, d_model) for h in sizes]
+        for choice in itertools.product(*options):
+            total = sum(heads.count(h) * o[2] for h, o in zip(sizes, choice))
+            key = max(256 * max(o[1] for o in choice), total + 256 * kv), total
+            if best is None or key < best[0]:
+                best = key, {h: o[0] for h, o in zip(sizes, choice)}
+    return sum(best[1][h] << 4 * x for x, h in enumerate(heads))
 
 
 def plan(ctx_lens, cache_kind, n_heads, hidden_chunk, kv_chunk, hidden_item_per_head=True):

@@ -120,81 +120,109 @@ extern "C" int apt_workspace_bytes(const apt_shape* s, int max_batch, int max_ct
     return APT_OK;
 }
 
-// The cap of a head queue's shared tiles and when its last workgroup ends with it, in 32nds of a cost unit.
-struct SharedTiles { int cap; int64_t end; };
+// Shared tiles of the projection kernel (apt_pack.h): the cap of a head queue (0: a tile per range), when its last workgroup ends, and
+// the time of all its tiles, ns.
+struct QueueTiles { int cap; int64_t last, total; };
 
-// Tiles of NC blocks for a head queue of n_heads heads.  full: ranges of full_blocks blocks, the longest; count[c]: shorter ranges
-// of c blocks; kv: time of the KV-kind items, which even the workgroups out.  Up to one tile per workgroup nothing is shared: a
-// fuller tile only takes longer.  Beyond that, the cap (0: a tile per range, not where full ranges are shorter than the tile) is
-// the one with which the workgroup that is last ends first, the tiles dealt as the kernel deals them (rounds, every second one
-// backwards).  Unit of cost: 50 ps at d_model 5120, proportional to d_model; measured with all workgroups busy, tiles of 1, 2 .. blocks:
-// NC 8, d_model 5120: 59, 58, 67, 78, 91, 100, 117, 126 us; NC 10, d_model 9216: 129, 140, 159, 186, 199, 218, 225, 242, 267, 282
-// (the copies of a k-tile do not shrink with the rows that hold tokens).
+// Time of a tile of NC blocks of which `blocks` hold tokens of `ranges` ranges, ns, all workgroups busy: prologue and epilogue, then the
+// k loop, whose copies do not shrink with the rows that hold tokens.  Measured, us a tile of 2, 4, 6, 8 (and 10) blocks: NC 8, d_model 1024:
+// 18, 22, 28, 32; 3072: 35, 47, 61, 76; 5120: 53, 74, 97, 122.  NC 10, 1024: 22, 27, 33, 38, 47; 5120: 59, 81, 102, 126, 156; 9216:
+// 140, 186, 218, 242, 282 (there the weights of an XCD's heads no longer come from its L2).  A further range in a tile takes 0.5 to 1.5 us more.
+static int64_t tile_ns(int NC, int d, int blocks, int ranges) {
+    const int64_t b = std::max(blocks, 2);
+    if (NC == 8) return 10000 + d * (20000 + 11100 * b) / 5120 + 800 * (ranges - 1);
+    return 11000 + 800 * b + d * (d < APT_MFMA_LARGE_TILE_D_MODEL ? 4300 + 2280 * b : 11100 + 1880 * b) / 1024 + 1100 * (ranges - 1);
+}
+static constexpr int64_t kPatternsNs = 2500;               // what a workgroup's table of patterns takes
+
 // Tiles of a head queue, dealt to its workgroups in rounds, every second one backwards.  Runs of equal tiles are added as differences
 // between neighbouring workgroups, at most three to a run, so the time does not grow with the tiles.
 struct Deal {
     static constexpr int kWorkgroups = 32;                 // per queue, on 256 compute units
     int64_t step[kWorkgroups + 1] = {0}, all = 0, total = 0;
     int at = 0;                                            // place in the current pair of rounds
-    void add(int64_t cost, int64_t tiles) {
-        all += tiles / (2 * kWorkgroups) * 2 * cost;       // two rounds give every workgroup two tiles, wherever they begin
-        total += cost * tiles;
+    void add(int64_t ns, int64_t tiles) {
+        all += tiles / (2 * kWorkgroups) * 2 * ns;         // two rounds give every workgroup two tiles, wherever they begin
+        total += ns * tiles;
         for (int left = (int)(tiles % (2 * kWorkgroups)); left > 0;) {
             const int n = std::min(left, kWorkgroups - at % kWorkgroups);
             const int first = at < kWorkgroups ? at : 2 * kWorkgroups - at - n;
-            step[first] += cost;
-            step[first + n] -= cost;
+            step[first] += ns;
+            step[first + n] -= ns;
             at = (at + n) % (2 * kWorkgroups);
             left -= n;
         }
     }
-    int64_t ends(int64_t kv) const {
+    QueueTiles result(int cap) const {
         int64_t most = 0, load = 0;
         for (int i = 0; i < kWorkgroups; ++i) most = std::max(most, load += step[i]);
-        return std::max((all + most) * kWorkgroups, total + kv * kWorkgroups);
+        const int64_t begin = cap ? kPatternsNs : 0;
+        return {cap, begin + all + most, begin * kWorkgroups + total};
     }
 };
 
-// n_heads: heads of the queues, nq = one or two numbers; best[i] for n_heads[i].
+// The queues of a plan: one or two numbers of heads, the larger first, and how many queues have each.
+struct HeadQueues { int n; int64_t heads[2], queues[2]; };
+
+// When a launch ends, in 256ths of a ns: with the last workgroup of a queue, or with all its work shared evenly (the KV-kind items,
+// kv ns, go to whoever is free); then the work itself.
+struct LaunchTiles {
+    int64_t end = INT64_MAX, total = INT64_MAX;
+    int cap[2] = {0, 0};
+    bool operator<(const LaunchTiles& o) const { return end < o.end || (end == o.end && total < o.total); }
+};
+
+// The caps with which a launch on tiles of NC blocks ends first.  full: ranges of full_blocks blocks, the longest; count[c]: shorter
+// ranges of c blocks.  Up to one tile per workgroup of a queue nothing is shared: a fuller tile only takes longer.  Full ranges shorter
+// than the tile share tiles as the others do (no cap 0).  75 batches, 3 to 72 heads, 3 to 193 requests of up to 2048 tokens, every cap
+// timed: the choice took 0.6 % longer than the best one on average, 5 % at most; cost taken as proportional to d_model, without a
+// fixed part, 1.9 %, and up to 20 % where d_model is small (4 heads, 64 requests, attention call: a tile per range 60.9 us, its choice 73.8).
 template <int NC>
-static void shared_tiles(int64_t full, int full_blocks, const int32_t* count, const int64_t* n_heads, int nq, int64_t kv, SharedTiles* best) {
+static LaunchTiles shared_tiles(int d, int64_t full, int full_blocks, const int32_t* count, const HeadQueues& q, int64_t kv) {
     const bool whole = full_blocks == NC;                  // a full range is a tile of its own
-    auto cost = [](int blocks) -> int64_t { return NC == 10 ? 1150000 + 200000 * std::max(blocks, 2) : 700000 + 225000 * std::max(blocks, 2); };
+    QueueTiles option[2][NC];
+    int n_options[2] = {0, 0};
     bool share[2] = {true, true};
     int64_t tails = 0;
     for (int c = 1; c < APT_PACK_MAX_BLOCKS + 1; ++c) tails += count[c];
-    for (int i = 0; i < nq; ++i) {
-        best[i] = {0, INT64_MAX};
-        if (!whole) continue;
-        Deal d;
-        d.add(cost(NC), full * n_heads[i]);
-        for (int c = NC; c >= 1; --c) d.add(cost(c), count[c] * n_heads[i]);
-        best[i].end = d.ends(kv);
-        share[i] = tails >= 2 && (full + tails) * n_heads[i] > Deal::kWorkgroups;
+    for (int i = 0; i < q.n && whole; ++i) {
+        Deal deal;
+        deal.add(tile_ns(NC, d, NC, 1), full * q.heads[i]);
+        for (int c = NC; c >= 1; --c) deal.add(tile_ns(NC, d, c, 1), count[c] * q.heads[i]);
+        option[i][n_options[i]++] = deal.result(0);
+        share[i] = tails >= 2 && (full + tails) * q.heads[i] > Deal::kWorkgroups;
     }
-    if (!share[0] && (nq == 1 || !share[1])) return;
-    for (int k = NC; k >= (whole ? 4 : full_blocks + 1); --k) {
+    for (int k = NC; k >= (whole ? 4 : full_blocks + 1) && (share[0] || share[1]); --k) {
         int32_t left[NC + 1];
         std::copy(count, count + NC + 1, left);
         if (!whole) left[full_blocks] += (int32_t)full;
-        Deal d[2];
-        for (int i = 0; i < nq; ++i)
-            if (whole) d[i].add(cost(NC), full * n_heads[i]);
+        Deal deal[2];
+        for (int i = 0; i < q.n; ++i)
+            if (whole) deal[i].add(tile_ns(NC, d, NC, 1), full * q.heads[i]);
         apt_pack_patterns<NC>(left, k, [&](int32_t reps, const int32_t* take) {
-            int blocks = 0;
-            for (int c = 1; c <= NC; ++c) blocks += c * take[c];
-            for (int i = 0; i < nq; ++i) d[i].add(cost(blocks), reps * n_heads[i]);
+            int blocks = 0, ranges = 0;
+            for (int c = 1; c <= NC; ++c) { blocks += c * take[c]; ranges += take[c]; }
+            for (int i = 0; i < q.n; ++i) deal[i].add(tile_ns(NC, d, blocks, ranges), reps * q.heads[i]);
         });
-        for (int i = 0; i < nq; ++i) {
-            const int64_t t = d[i].ends(kv);
-            if (share[i] && t < best[i].end) best[i] = {k, t};
-        }
+        for (int i = 0; i < q.n; ++i)
+            if (share[i]) option[i][n_options[i]++] = deal[i].result(k);
     }
+    LaunchTiles best;
+    for (int a = 0; a < n_options[0]; ++a)
+        for (int b = 0; b < std::max(n_options[1], 1); ++b) {
+            const QueueTiles none = {0, 0, 0}, &x = option[0][a], &y = q.n == 2 ? option[1][b] : none;
+            LaunchTiles t;
+            t.total = q.queues[0] * x.total + q.queues[1] * y.total;
+            t.end = std::max(std::max(x.last, y.last) * APT_N_QUEUES * Deal::kWorkgroups, t.total + kv * APT_N_QUEUES * Deal::kWorkgroups);
+            t.cap[0] = x.cap, t.cap[1] = y.cap;
+            if (t < best) best = t;
+        }
+    return best;
 }
 
 // The word APT_PW_SHARED_TILES of a batch with packed weights.  Integers throughout, so that a batch has one plan whatever the compiler
 // makes of sums and ties.
-static uint32_t shared_tiles_word(const int32_t* ctx_lens, const uint8_t* cache_kind, int B, int H, int chunk, int64_t kv_tokens) {
+static uint32_t shared_tiles_word(const int32_t* ctx_lens, const uint8_t* cache_kind, int B, int H, int d, int chunk, int64_t kv_tokens) {
     int64_t full = 0;
     int32_t count[APT_PACK_MAX_BLOCKS + 1] = {0};
     for (int r = 0; r < B; ++r) {
@@ -202,26 +230,22 @@ static uint32_t shared_tiles_word(const int32_t* ctx_lens, const uint8_t* cache_
         full += ctx_lens[r] / chunk;
         if (ctx_lens[r] % chunk) ++count[ceil_div64(ctx_lens[r] % chunk, APT_PACK_BLOCK)];
     }
-    const int64_t kv = kv_tokens * 74;                     // 4 d bytes a token at 5.5 TB/s
-    // two numbers of heads at most, the larger first
-    const int64_t n_heads[2] = {(H + APT_N_QUEUES - 1) / APT_N_QUEUES, H / APT_N_QUEUES};
-    const int nq = n_heads[1] > 0 && n_heads[1] < n_heads[0] ? 2 : 1;
-    const bool large = chunk == APT_MFMA_HIDDEN_CHUNK;
-    SharedTiles t[2], tw[2];
-    if (large) shared_tiles<10>(full, 10, count, n_heads, nq, kv, t);
+    const int64_t kv = kv_tokens * d / 1375;               // 4 d bytes a token at 5.5 TB/s
+    const int rest = H % APT_N_QUEUES;
+    HeadQueues q = {1, {(H + APT_N_QUEUES - 1) / APT_N_QUEUES, H / APT_N_QUEUES}, {rest ? rest : APT_N_QUEUES, rest ? APT_N_QUEUES - rest : 0}};
+    if (H > APT_N_QUEUES && rest) q.n = 2;
+    LaunchTiles t;
+    if (chunk == APT_MFMA_HIDDEN_CHUNK) t = shared_tiles<10>(d, full, 10, count, q, kv);
     else {
-        shared_tiles<8>(full, 8, count, n_heads, nq, kv, t);
-        shared_tiles<10>(full, 8, count, n_heads, nq, kv, tw);
+        t = shared_tiles<8>(d, full, 8, count, q, kv);
+        // Ranges of 256 tokens in tiles of 320 rows, a full range beside a short one, where that saves a round: 40 heads, requests of
+        // 415, 513 and 619 tokens (40 tiles a queue, then 30) 193 -> 166 us a step.
+        const LaunchTiles wide = shared_tiles<10>(d, full, 8, count, q, kv);
+        if (wide < t) t = wide;
     }
-    auto word_of = [&](const SharedTiles* s) {
-        uint32_t word = 0;
-        for (int x = 0; x < APT_N_QUEUES && x < H; ++x) word |= (uint32_t)s[nq == 2 && x >= H % APT_N_QUEUES].cap << (4 * x);
-        return word;
-    };
-    auto end_of = [&](const SharedTiles* s) { return nq == 2 ? std::max(s[0].end, s[1].end) : s[0].end; };
-    // Ranges of 256 tokens in tiles of 320 rows, a full range beside a short one, where that saves a round: 40 heads, requests of
-    // 415, 513 and 619 tokens (40 tiles a queue, then 30) 193 -> 166 us a step.
-    return !large && end_of(tw) < end_of(t) ? word_of(tw) : word_of(t);
+    uint32_t word = 0;
+    for (int x = 0; x < APT_N_QUEUES && x < H; ++x) word |= (uint32_t)t.cap[q.n == 2 && x >= rest] << (4 * x);
+    return word;
 }
 
 extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8_t* cache_kind, int B,
@@ -388,7 +412,7 @@ extern "C" int apt_plan(const apt_shape* s, const int32_t* ctx_lens, const uint8
     }
     w[APT_PW_QUEUE0 + APT_N_QUEUES] = (int32_t)((it - it0) / 4);
     if (rs.s.hidden_impl == APT_HIDDEN_MFMA && n_hidden_items > 0)
-        w[APT_PW_SHARED_TILES] = (int32_t)shared_tiles_word(ctx_lens, cache_kind, B, H, rs.s.hidden_chunk, tok - htok);
+        w[APT_PW_SHARED_TILES] = (int32_t)shared_tiles_word(ctx_lens, cache_kind, B, H, rs.s.d_model, rs.s.hidden_chunk, tok - htok);
     order_tails(APT_KIND_KV, rs.s.kv_chunk);
     emit_kind(APT_KIND_KV, rs.s.kv_chunk, 0, 1);
     // absorbed-weight path: the 256-token tiles of the hidden-kind ranges in their order, 2 * item + half; then the units

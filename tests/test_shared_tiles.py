@@ -100,7 +100,7 @@ def test_planner_word_against_the_plain_rule():
         kinds = (g.random(B) < g.choice([0.1, 0.5, 0.9, 1.0])).astype(np.uint8)
         tile = int(g.choice([256, 320]))
         caps = _plan(lens, kinds, heads=heads, tile=tile)
-        word = po.shared_tiles_word(lens, kinds, heads, tile) if kinds.any() else 0
+        word = po.shared_tiles_word(lens, kinds, heads, 128 * heads, tile) if kinds.any() else 0
         assert caps == [(word >> 4 * x) & 15 for x in range(8)], (heads, tile, lens.tolist(), kinds.tolist())
         seen.update((tile, c) for c in caps)
     assert seen == {(t, c) for t in (256, 320) for c in [0, *range(4, 11)]}
