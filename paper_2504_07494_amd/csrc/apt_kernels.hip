@@ -42,7 +42,7 @@ __global__ __launch_bounds__(NW * 64) void apt_items_kernel(ItemParams p) {
     kv_item<DT, HD, NW>(p, it.x, it.y, it.z, it.w, lds);
 }
 
-// Whole contexts, one workgroup per request and head, straight to the output: no partials and no merge (see launch_whole).
+// Whole contexts, one workgroup per request and head, straight to the output: no partials and no merge (see takes_whole).
 // in_items: the plan has one item per request and head (longest first), else they are taken as they come.
 template <int DT, int HD, int NW, int ODT>
 __global__ __launch_bounds__(NW * 64) void apt_whole_kernel(ItemParams p, char* out, int in_items) {
@@ -288,22 +288,26 @@ template <int DT, int HD> int launch_items(const ItemParams& p, int n_cus, hipSt
 }
 
 // Batches of KV-kind requests that need no partials.  Every context is one range of the plan; or there are no more (request, head)
-// pairs than CUs, and the longest context alone does not take longer than ranges of it on more CUs and the merge would: a CU
-// reads 57 KB per us with 16 waves, the ranges take 7 us or the time of all their bytes at 6.3 TB/s, the merge and its launch
-// 5 us.  Step, 40 heads, fp16, ranges and merge / whole: one request of 500 tokens 17.9 / 14.7 us, of 1237 with the append
-// 22.7 / 21.5, of 2048 18.5 / 26.9 (not taken), six of 2000 to 2048 52.3 / 47.8, 200 of 10 to 500 203.0 / 196.7.
+// pairs than CUs, and the contexts alone do not take longer than ranges of them on more CUs and the merge would, by the times that
+// both took on 296 batches of 1 to 30 requests and 8 to 72 heads, equal and ragged lengths of 250 to 2048 tokens, rows of 128, 256 and
+// 512 bytes (us; the longest context in KB, all of them in MB; n_items <= n_cus: 16 waves a range, else four).  The choice took 0.4 % longer
+// than the better of the two on average; by the longest context at 57 KB/us alone it was 2.9 %, 36 % at most (attention call, fp16,
+// ranges and merge / whole: 40 heads, 3 requests of up to 1743 tokens 17.7 / 22.8; 12 heads of 64, 6 of up to 1949 10.5 / 13.8; 40
+// heads, one of 500 10.2 / 7.5, of 850 10.8 / 10.4, of 1250 11.7 / 14.5; 72 heads, 3 of 2048 41.4 / 35.2; 32 heads, 8 of 1000 24.0 / 20.9).
 bool takes_whole(const ItemParams& p, const int32_t* pw, int row_bytes, int n_cus) {
     if (p.n_hidden_items > 0) return false;
     if (pw[APT_PW_NPARTIALS] == p.B) return true;
     if ((int64_t)p.B * p.H > n_cus || p.max_blocks > 16 * APT_KV_MAX_PAGES_PER_WAVE) return false;
     const int32_t* lens = pw + APT_PW_HEADER + APT_PA_CTX_LEN * p.B;
-    int64_t longest = 0, all = 0;
+    int64_t longest = 0, tokens = 0;
     for (int r = 0; r < p.B; ++r) {
         longest = std::max<int64_t>(longest, lens[r]);
-        all += lens[r];
+        tokens += lens[r];
     }
-    const double us = std::max(7.0, (double)all * p.H * 2 * row_bytes / 6.3e6) + 5.0;
-    return (double)longest * 2 * row_bytes <= 57e3 * us;
+    const double kb = 2e-3 * row_bytes, all = 1e-3 * kb * (double)tokens * p.H;
+    const double whole = 3.0 + kb * (double)longest / 68.0 + all / 13.4;
+    const double ranges = p.n_items <= n_cus ? 6.4 + kb * (double)std::min<int64_t>(longest, p.kv_chunk) / 90.0 + all / 11.0 : 5.5 + all / 6.6;
+    return whole <= ranges;
 }
 template <int DT, int HD, int NW, int ODT> void launch_whole_nw(const ItemParams& p, char* out, int in_items, hipStream_t st) {
     hipLaunchKernelGGL((apt_whole_kernel<DT, HD, NW, ODT>), dim3(p.B * p.H), dim3(NW * 64), (KvItem<DT, HD, NW>::kLds), st, p, out, in_items);

@@ -36,3 +36,29 @@ def test_kv_batches_with_and_without_partials(oracle, dtype, out, hd, bs, lens, 
     print(f"[parity] max_abs={err.max():.3e}", flush=True)
     # the last rounding of a 16-bit output: half a unit in the last place of its 11 or 8 bits
     assert np.all(err <= 1e-4 + np.abs(want) * {"f32": 0.0, "f16": 2.0 ** -11, "bf16": 2.0 ** -8}[out])
+
+
+# 16 requests of one or two ranges: 4 and 16 heads, no more (request, head) pairs than CUs
+PAIRS = SHORT + [513, 600]
+
+
+@pytest.mark.parametrize("dtype,hd,bs,lens,n_heads,whole", [
+    ("f16", 128, 16, PAIRS, 16, True), ("bf16", 64, 8, PAIRS, 16, True), ("f32", 64, 16, PAIRS, 4, True), ("f32", 128, 16, SHORT, 19, True),
+    ("f16", 128, 16, LONG, 4, False), ("bf16", 128, 16, [1743, 1100, 854], 40, False), ("f16", 64, 16, [2048], 40, False),
+    ("f32", 128, 16, LONG, 4, False), ("f16", 128, 16, PAIRS, 17, False)])
+def test_whole_contexts_where_they_pay(oracle, dtype, hd, bs, lens, n_heads, whole):
+    """Which path ran shows in the workspace: whole contexts leave it as it was, ranges write their partials."""
+    print(f"[case] {dtype} hd={hd} bs={bs} heads={n_heads} requests={len(lens)} whole={whole}", flush=True)
+    cfg = wl.small_config(name="kvwhole", dtype=dtype, d_model=hd * n_heads, n_heads=n_heads, head_dim=hd, block_size=bs,
+                          batch=len(lens), len_lo=1, len_hi=max(lens), hidden_ratio=0.0, permute_pages=True)
+    batch = wl.make_batch(cfg, np.array(lens, dtype=np.int32), np.full(len(lens), wl.KIND_KV, dtype=np.uint8))
+    layer = wl.make_layer(batch)
+    rn = DecodeRunner(batch)
+    rn.out.fill_(float("nan"))
+    rn.workspace.fill_(255)
+    rn.run(rn.upload(layer))
+    got = rn.out_f64()
+    assert bool((rn.workspace == 255).all()) == whole
+    heads = sorted({0, n_heads // 2, n_heads - 1})
+    want = oracle_attn(oracle, batch, layer, pairs=[(r, h) for r in range(len(lens)) for h in heads])
+    assert np.max(np.abs(got[:, heads] - want.reshape(len(lens), len(heads), hd))) <= 1e-4
