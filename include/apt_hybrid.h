@@ -97,7 +97,10 @@ typedef struct apt_shape {
     int32_t kv_chunk;           /* tokens per KV-kind work item, whole blocks, at most 256
                                    of them; 0 = chosen by apt_plan for each batch: the
                                    longest of 2048 / 1024 / 512 that still gives 2048
-                                   KV-kind items (apt_plan_info.kv_chunk reports it)      */
+                                   KV-kind items (apt_plan_info.kv_chunk reports it), and
+                                   the attention call may serve whole contexts.  A value
+                                   given here also fixes the order of a KV-kind request's
+                                   sums: its output does not depend on the batch          */
     int32_t hidden_impl;        /* APT_HIDDEN_AUTO: MFMA kernel for 16-bit dtypes with
                                    head_dim 128, otherwise _VALU: raw weights, any
                                    dtype and head_dim (no packed copy needed).

@@ -280,24 +280,27 @@ __global__ __launch_bounds__(kThreads) void apt_mfma_probe_kernel(float* out, in
 // A CU holds 16 waves of these kernels.  Up to one workgroup per CU, a workgroup has all of them: the range of a lone 1237-token
 // request of 40 heads takes 8.8 us instead of 11.4 (of 1000 tokens, three such requests of 49 heads, 10.5 instead of 12.6).
 // Eight waves for up to two workgroups per CU gave nothing (320 to 448 items 16.4 us, with four 15.4).
-template <int DT, int HD> int launch_items(const ItemParams& p, int n_cus, hipStream_t st) {
+// most16: workgroups up to which they have 16 waves, the number of CUs; 0 where the caller has fixed kv_chunk, so that a request's sums
+// are the same in every batch.
+template <int DT, int HD> int launch_items(const ItemParams& p, int most16, hipStream_t st) {
     const int n = p.n_items - p.item_base;
-    if (n <= n_cus) hipLaunchKernelGGL((apt_items_kernel<DT, HD, 16>), dim3(n), dim3(1024), (KvItem<DT, HD, 16>::kLds), st, p);
+    if (n <= most16) hipLaunchKernelGGL((apt_items_kernel<DT, HD, 16>), dim3(n), dim3(1024), (KvItem<DT, HD, 16>::kLds), st, p);
     else hipLaunchKernelGGL((apt_items_kernel<DT, HD, 4>), dim3(n), dim3(kThreads), (KvItem<DT, HD, 4>::kLds), st, p);
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
 }
 
-// Batches of KV-kind requests that need no partials.  Every context is one range of the plan; or there are no more (request, head)
-// pairs than CUs, and the contexts alone do not take longer than ranges of them on more CUs and the merge would, by the times that
-// both took on 296 batches of 1 to 30 requests and 8 to 72 heads, equal and ragged lengths of 250 to 2048 tokens, rows of 128, 256 and
-// 512 bytes (us; the longest context in KB, all of them in MB; n_items <= n_cus: 16 waves a range, else four).  The choice took 0.4 % longer
-// than the better of the two on average; by the longest context at 57 KB/us alone it was 2.9 %, 36 % at most (attention call, fp16,
-// ranges and merge / whole: 40 heads, 3 requests of up to 1743 tokens 17.7 / 22.8; 12 heads of 64, 6 of up to 1949 10.5 / 13.8; 40
-// heads, one of 500 10.2 / 7.5, of 850 10.8 / 10.4, of 1250 11.7 / 14.5; 72 heads, 3 of 2048 41.4 / 35.2; 32 heads, 8 of 1000 24.0 / 20.9).
-bool takes_whole(const ItemParams& p, const int32_t* pw, int row_bytes, int n_cus) {
+// Batches of KV-kind requests that need no partials.  Every context is one range of the plan; or the ranges are the planner's own choice
+// (most16 > 0), there are no more (request, head) pairs than CUs, and the contexts alone do not take longer than ranges of them on
+// more CUs and the merge would, by the times that both took on 296 batches of 1 to 30 requests and 8 to 72 heads, equal and ragged
+// lengths of 250 to 2048 tokens, rows of 128, 256 and 512 bytes (us; the longest context in KB, all of them in MB; up to one range per
+// CU: 16 waves a range, else four).  The choice took 0.4 % longer than the better of the two on average; by the longest context at
+// 57 KB/us alone it was 2.9 %, 36 % at most (attention call, fp16, ranges and merge / whole: 40 heads, 3 requests of up to 1743 tokens
+// 17.7 / 22.8; 12 heads of 64, 6 of up to 1949 10.5 / 13.8; 40 heads, one of 500 10.2 / 7.5, of 850 10.8 / 10.4, of 1250 11.7 / 14.5;
+// 72 heads, 3 of 2048 41.4 / 35.2; 32 heads, 8 of 1000 24.0 / 20.9).
+bool takes_whole(const ItemParams& p, const int32_t* pw, int row_bytes, int most16) {
     if (p.n_hidden_items > 0) return false;
     if (pw[APT_PW_NPARTIALS] == p.B) return true;
-    if ((int64_t)p.B * p.H > n_cus || p.max_blocks > 16 * APT_KV_MAX_PAGES_PER_WAVE) return false;
+    if ((int64_t)p.B * p.H > most16 || p.max_blocks > 16 * APT_KV_MAX_PAGES_PER_WAVE) return false;
     const int32_t* lens = pw + APT_PW_HEADER + APT_PA_CTX_LEN * p.B;
     int64_t longest = 0, tokens = 0;
     for (int r = 0; r < p.B; ++r) {
@@ -306,15 +309,15 @@ bool takes_whole(const ItemParams& p, const int32_t* pw, int row_bytes, int n_cu
     }
     const double kb = 2e-3 * row_bytes, all = 1e-3 * kb * (double)tokens * p.H;
     const double whole = 3.0 + kb * (double)longest / 68.0 + all / 13.4;
-    const double ranges = p.n_items <= n_cus ? 6.4 + kb * (double)std::min<int64_t>(longest, p.kv_chunk) / 90.0 + all / 11.0 : 5.5 + all / 6.6;
+    const double ranges = p.n_items <= most16 ? 6.4 + kb * (double)std::min<int64_t>(longest, p.kv_chunk) / 90.0 + all / 11.0 : 5.5 + all / 6.6;
     return whole <= ranges;
 }
 template <int DT, int HD, int NW, int ODT> void launch_whole_nw(const ItemParams& p, char* out, int in_items, hipStream_t st) {
     hipLaunchKernelGGL((apt_whole_kernel<DT, HD, NW, ODT>), dim3(p.B * p.H), dim3(NW * 64), (KvItem<DT, HD, NW>::kLds), st, p, out, in_items);
 }
-template <int DT, int HD> int launch_whole(const ItemParams& p, const int32_t* pw, char* out, int out_dtype, int n_cus, hipStream_t st) {
+template <int DT, int HD> int launch_whole(const ItemParams& p, const int32_t* pw, char* out, int out_dtype, int most16, hipStream_t st) {
     const int in_items = pw[APT_PW_NPARTIALS] == p.B;
-    const bool few = (int64_t)p.B * p.H <= n_cus;
+    const bool few = (int64_t)p.B * p.H <= most16;
     if (DT == 0 || out_dtype == APT_F32) few ? launch_whole_nw<DT, HD, 16, 0>(p, out, in_items, st) : launch_whole_nw<DT, HD, 4, 0>(p, out, in_items, st);
     else few ? launch_whole_nw<DT, HD, 16, DT>(p, out, in_items, st) : launch_whole_nw<DT, HD, 4, DT>(p, out, in_items, st);
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
@@ -323,12 +326,12 @@ template <int DT, int HD> int launch_whole(const ItemParams& p, const int32_t* p
 #include "apt_absorbed.inc"
 
 template <int DT, int HD>
-int launch_items_impl(ItemParams& p, int himpl, int n_wg, hipStream_t st) {
-    if (p.n_hidden_items == 0) return launch_items<DT, HD>(p, n_wg, st);
+int launch_items_impl(ItemParams& p, int himpl, int n_wg, int most16, hipStream_t st) {
+    if (p.n_hidden_items == 0) return launch_items<DT, HD>(p, most16, st);
     if (himpl == APT_HIDDEN_ABSORBED) {
         if (DT == 0 && p.n_hidden_items < p.n_items) {
             p.item_base = p.n_hidden_items;      // the KV-kind items, one workgroup each (16-bit inputs: with the absorbed queries)
-            const int rc = launch_items<DT, HD>(p, n_wg, st);
+            const int rc = launch_items<DT, HD>(p, most16, st);
             if (rc) return rc;
         }
         return launch_absorbed<DT>(p, HD, n_wg, st);
@@ -602,10 +605,12 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
 
     const int dt = rs.s.dtype, hd = rs.s.head_dim, hi = rs.s.hidden_impl;
     if (ev_begin && hipEventRecord((hipEvent_t)ev_begin, st) != hipSuccess) return APT_EHIP;
-    const bool whole = takes_whole(p, pw, hd * rs.elem_bytes, ds->n_wg);
+    const int most16 = rs.kv_auto ? ds->n_wg : 0;
+    const bool whole = takes_whole(p, pw, hd * rs.elem_bytes, most16);
     auto launch = [&](auto dtype, auto head_dim) {
         constexpr int DT = decltype(dtype)::value, HD = decltype(head_dim)::value;
-        return whole ? launch_whole<DT, HD>(p, pw, (char*)out, rs.s.out_dtype, ds->n_wg, st) : launch_items_impl<DT, HD>(p, hi, ds->n_wg, st);
+        return whole ? launch_whole<DT, HD>(p, pw, (char*)out, rs.s.out_dtype, most16, st)
+                     : launch_items_impl<DT, HD>(p, hi, ds->n_wg, most16, st);
     };
     auto launch_hd = [&](auto dtype) {
         return hd == 64 ? launch(dtype, std::integral_constant<int, 64>{}) : launch(dtype, std::integral_constant<int, 128>{});

@@ -4,6 +4,7 @@ fp32 sums of at most 1037 weights and 128 products: errors of the scores and of 
 their size, 1e-4 is ten times that."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2504_07494_amd import workloads as wl
 from paper_2504_07494_amd.harness import DecodeRunner
@@ -62,3 +63,35 @@ def test_whole_contexts_where_they_pay(oracle, dtype, hd, bs, lens, n_heads, who
     heads = sorted({0, n_heads // 2, n_heads - 1})
     want = oracle_attn(oracle, batch, layer, pairs=[(r, h) for r in range(len(lens)) for h in heads])
     assert np.max(np.abs(got[:, heads] - want.reshape(len(lens), len(heads), hd))) <= 1e-4
+
+
+@pytest.mark.parametrize("dtype,hd,bs,chunk", [("f16", 128, 16, 256), ("bf16", 64, 8, 512), ("f32", 64, 16, 128), ("f32", 128, 4, 512)])
+def test_a_given_range_length_fixes_the_sums_of_a_request(dtype, hd, bs, chunk):
+    """Bit for bit: a KV-kind request by itself, in a small and in a large batch, and beside hidden-kind requests."""
+    print(f"[case] {dtype} hd={hd} bs={bs} kv_chunk={chunk}", flush=True)
+    lens = np.array(LONG + LONG, dtype=np.int32)
+    cfg = wl.small_config(name="kvfixed", dtype=dtype, d_model=hd * 12, n_heads=12, head_dim=hd, block_size=bs, batch=len(lens),
+                          len_lo=1, len_hi=max(lens), hidden_ratio=0.0, permute_pages=True)
+    batch = wl.make_batch(cfg, lens, np.full(len(lens), wl.KIND_KV, dtype=np.uint8))
+    layer = wl.make_layer(batch)
+    full = DecodeRunner(batch, kv_chunk=chunk)
+    assert full.info.n_items > 256                                    # four waves to a workgroup
+    dl = full.upload(layer)
+    full.run(dl)
+    want = full.out.clone()
+
+    def of(rows, kinds=None):
+        part = wl.make_batch(wl.replace(cfg, batch=len(rows)), lens[rows], np.zeros(len(rows), dtype=np.uint8) if kinds is None else kinds)
+        rn = DecodeRunner(part, kv_chunk=chunk)
+        rn.block_tables = full.block_tables[rows][:, :, :part.max_blocks].contiguous()      # its blocks in the same pool
+        q = dl.q
+        dl.q = q[rows].contiguous()
+        rn.run(dl)
+        dl.q = q
+        return rn.out
+    for rows in ([15], [4], [13, 12, 14], list(range(16))):
+        same = torch.equal(of(rows), want[rows])
+        assert same, rows
+    rows = [15, 3, 14, 13]                                            # request 3 read as hidden-kind: its output is another one
+    same = torch.equal(of(rows, np.array([0, 1, 0, 0], dtype=np.uint8))[[0, 2, 3]], want[[15, 14, 13]])
+    assert same
