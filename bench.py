@@ -148,8 +148,10 @@ def measure(cfg, args, steps, warmup, keep=False):
                 "frac": gbs / PEAK_HBM_GBS, "traffic": read_traffic(wkey)}
     mfma_items = rn.info.n_hidden_items > 0 and rn.info.hidden_impl == 2
     kname = "apt_items_mfma_kernel" if mfma_items else "apt_items_kernel"
+    if hidden_tokens == 0 and int(rn.info.n_partials) == batch.B:
+        kname = "apt_whole_kernel (the whole call: every context is one range)"
     if absorbed:
-        kname = "apt_absorb_{q,score,stats,pv,out,final}_kernel + apt_items_kernel (one event pair around all of them)"
+        kname = "apt_absorb_{q,score,stats,pv,out,merge}_kernel (the whole call; KV-kind items run beside q)"
     roof.update({"kernel": kname, "kernel_ms": kern_avg_ms, "kernel_ms_min": float(np.min(kern_ms)),
                  "algorithmic_flops": flops, "algorithmic_bytes": kv_bytes + hid_bytes})
     m = {

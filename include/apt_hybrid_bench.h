@@ -17,8 +17,10 @@ extern "C" {
  * The same step as apt_hybrid_decode_attn (Eq. 1-3 over both cache kinds); in addition
  * the HIP events ev_begin and ev_end (hipEvent_t handles created by the caller with
  * timing enabled; either may be NULL) are recorded on `stream` immediately before and
- * after the item kernel (with APT_HIDDEN_ABSORBED: before the first and after the last of the
- * kernels that run ahead of the merge), so that a caller can time it apart from the merge.
+ * after the item kernel, so that a caller can time it apart from the merge.  Where a call has no
+ * merge of its own the interval is the whole call: with APT_HIDDEN_ABSORBED and hidden-kind
+ * requests, whose last kernel sums the output partials and merges in one, and for KV-kind
+ * requests alone whose contexts go straight to the output.
  */
 int apt_hybrid_decode_attn_timed(const apt_shape* s, const void* plan_host, void* plan_dev,
                                  const void* q, const void* k_pages, const void* v_pages, const void* hidden_pages,

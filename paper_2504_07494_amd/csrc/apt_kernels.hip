@@ -619,13 +619,15 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     else if (dt == APT_F16) rc = launch_hd(std::integral_constant<int, 1>{});
     else rc = launch_hd(std::integral_constant<int, 2>{});
     if (rc) return rc;
-    if (ev_end && hipEventRecord((hipEvent_t)ev_end, st) != hipSuccess) return APT_EHIP;
+    // the last kernel of the absorbed-weight path sums the output partials of its requests: it belongs to the interval
+    const bool absorbed = hi == APT_HIDDEN_ABSORBED && n_hidden > 0;
+    if (ev_end && !absorbed && hipEventRecord((hipEvent_t)ev_end, st) != hipSuccess) return APT_EHIP;
 
     if (whole) return APT_OK;
 
     const unsigned blocks = (unsigned)(((int64_t)B * rs.s.n_heads * hd + kThreads - 1) / kThreads);
     auto launch_merge = [&](auto kern, const auto& params) { hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, st, params, (char*)out, hd); };
-    if (hi == APT_HIDDEN_ABSORBED && n_hidden > 0) {
+    if (absorbed) {
         if (rs.s.out_dtype == APT_F32) launch_merge(dt == APT_F32 ? apt_absorb_merge_kernel<0, 0> : dt == APT_F16 ? apt_absorb_merge_kernel<1, 0> : apt_absorb_merge_kernel<2, 0>, p);
         else if (rs.s.out_dtype == APT_F16) launch_merge(apt_absorb_merge_kernel<1, 1>, p);
         else launch_merge(apt_absorb_merge_kernel<2, 2>, p);
@@ -633,7 +635,9 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
         const MergeParams mp = {p.plan, p.kv_ticket, p.ws_acc, p.ws_ml, p.B, p.H};
         launch_merge(rs.s.out_dtype == APT_F32 ? apt_merge_kernel<0> : rs.s.out_dtype == APT_F16 ? apt_merge_kernel<1> : apt_merge_kernel<2>, mp);
     }
-    return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
+    if (hipGetLastError() != hipSuccess) return APT_EHIP;
+    if (ev_end && absorbed && hipEventRecord((hipEvent_t)ev_end, st) != hipSuccess) return APT_EHIP;
+    return APT_OK;
 }
 
 extern "C" int apt_hybrid_decode_attn_timed(const apt_shape* s, const void* plan_host, void* plan_dev,
