@@ -165,7 +165,9 @@ def test_short_ranges_beside_full_ones_in_larger_tiles(oracle, dtype, H):
         assert np.max(np.abs(rn.out_f64() - got)) < 2e-5
     # the kernel of 256-row tiles with a plan for larger ones
     rn.plan()
+    torch.cuda.synchronize()                  # the copy of the plan has read the host's words
     rn.plan_host[31] = 0
+    assert int(np.uint32(rn.plan_dev[31].item() & 0xffffffff)) & 15 == 10
     rn.run(dl)
     torch.cuda.synchronize()
     assert np.max(np.abs(rn.out_f64() - got)) < 2e-5
