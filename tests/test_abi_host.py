@@ -3,6 +3,7 @@ host planner matches the plain partition rule bit for bit, and bad arguments are
 into error codes.  No device call is made here."""
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -59,12 +60,10 @@ def test_library_is_published_only_after_its_calls_are_set_up(monkeypatch):
     assert len(published_early) > len(ab.EXPORTS) and not any(published_early)
 
 
-def _kernel_metadata():
-    """{kernel name: metadata} of the device code in the built library: its offload bundles (magic, count, then offset, size,
-    triple of each entry), the AMDGPU note of each code object (msgpack)."""
-    import msgpack
+def _code_objects():
+    """The gfx950 code objects in the built library: its offload bundles (magic, count, then offset, size, triple of each entry)."""
     import struct
-    lib, magic, kernels = open(ab.LIB_PATH, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", {}
+    lib, magic = open(ab.LIB_PATH, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__"
     at = lib.find(magic)
     while at >= 0:
         pos = at + len(magic) + 8
@@ -73,30 +72,73 @@ def _kernel_metadata():
             triple = lib[pos + 24:pos + 24 + n]
             pos += 24 + n
             elf = lib[at + off:at + off + size]
-            if b"gfx950" not in triple or not elf.startswith(b"\x7fELF"):
-                continue
-            sh_off, (sh_size, sh_n) = struct.unpack_from("<Q", elf, 40)[0], struct.unpack_from("<HH", elf, 58)
-            for i in range(sh_n):
-                kind, _, _, o, length = struct.unpack_from("<IQQQQ", elf, sh_off + i * sh_size + 4)
-                if kind != 7:                                    # SHT_NOTE
-                    continue
-                name_len, desc_len, note = struct.unpack_from("<III", elf, o)
-                if note == 32:                                   # NT_AMDGPU_METADATA
-                    desc = o + 12 + (name_len + 3) // 4 * 4
-                    for k in msgpack.unpackb(elf[desc:desc + desc_len])["amdhsa.kernels"]:
-                        kernels[k[".name"]] = k
+            if b"gfx950" in triple and elf.startswith(b"\x7fELF"):
+                yield elf
         at = lib.find(magic, at + 1)
+
+
+def _kernel_metadata():
+    """{kernel name: metadata} of the device code in the built library: the AMDGPU note of each code object (msgpack)."""
+    import msgpack
+    import struct
+    kernels = {}
+    for elf in _code_objects():
+        sh_off, (sh_size, sh_n) = struct.unpack_from("<Q", elf, 40)[0], struct.unpack_from("<HH", elf, 58)
+        for i in range(sh_n):
+            kind, _, _, o, length = struct.unpack_from("<IQQQQ", elf, sh_off + i * sh_size + 4)
+            if kind != 7:                                    # SHT_NOTE
+                continue
+            name_len, desc_len, note = struct.unpack_from("<III", elf, o)
+            if note == 32:                                   # NT_AMDGPU_METADATA
+                desc = o + 12 + (name_len + 3) // 4 * 4
+                for k in msgpack.unpackb(elf[desc:desc + desc_len])["amdhsa.kernels"]:
+                    kernels[k[".name"]] = k
     return kernels
 
 
 def test_kernels_with_counted_copies_do_not_spill():
     """The waits of these kernels count the global -> LDS copies in flight; a spilled register's reload is one more memory
-    operation among them and its wait drains the copies.  (The packed-weight kernel keeps its reloads out of its k loop.)"""
+    operation among them and its wait drains the copies.  (The packed-weight kernel: next test.)"""
     kernels = {n: k for n, k in _kernel_metadata().items() if re.search(r"apt_absorb_(score16|pv16|out16|q16)_kernel|apt_items_(raw|f32)_kernel", n)}
     assert len(kernels) >= 60
     spilled = {n: (k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for n, k in kernels.items()
                if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
     assert not spilled, spilled
+
+
+def test_k_loops_of_the_packed_weight_kernel_touch_no_scratch(tmp_path):
+    """Tile set-up and epilogue of this kernel spill; its k loops must not: a reload would wait for the copies in flight.  A loop (the
+    innermost ones with MFMAs, ending in a branch back) runs four k-tiles; one loop for each kind of wave and number of valid
+    blocks, 10 on tiles of 320 rows and 8 on tiles of 256."""
+    objdump = next((p for p in (os.path.join(os.path.dirname(os.path.realpath(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"))), d, "llvm-objdump")
+                                for d in (".", "../llvm/bin", "../lib/llvm/bin")) if os.path.exists(p)), None)
+    if objdump is None:
+        pytest.skip("no llvm-objdump beside hipcc")
+    seen = 0
+    for n, elf in enumerate(_code_objects()):
+        if b"apt_items_mfma_kernel" not in elf:
+            continue
+        obj = tmp_path / f"{n}.o"
+        obj.write_bytes(elf)
+        text = subprocess.run([objdump, "-d", str(obj)], capture_output=True, text=True, check=True).stdout
+        for name, body in re.findall(r"^[0-9a-f]+ <(\w*apt_items_mfma_kernel\w*)>:\n(.*?)(?=^$|\Z)", text, flags=re.M | re.S):
+            ins = [(int(m[2], 16), m[1].split()[0], m[1]) for m in re.finditer(r"^\s+(\S.*?)\s*// ([0-9A-F]+):", body, flags=re.M)]
+            at = {a: i for i, (a, _, _) in enumerate(ins)}
+            loops = []                                        # (first, last) instruction of a loop that holds MFMAs
+            for i, (a, op, line) in enumerate(ins):
+                if op.startswith(("s_branch", "s_cbranch")):
+                    offset = int(line.split()[1])
+                    first = at.get(a + 4 + 4 * (offset - 65536 if offset >= 32768 else offset))
+                    if first is not None and first <= i and any(o.startswith("v_mfma") for _, o, _ in ins[first:i]):
+                        loops.append((first, i))
+            loops = [x for x in loops if not any(y != x and x[0] <= y[0] and y[1] <= x[1] for y in loops)]
+            assert len(loops) == (10 if "ELi10E" in name else 8), (name, loops)
+            for first, last in loops:
+                assert sum(o.startswith("v_mfma") for _, o, _ in ins[first:last]) % 64 == 0      # four k-tiles of 16 to 80
+                bad = [x for _, o, x in ins[first:last] if "scratch" in o or "accvgpr" in o]
+                assert not bad, (name, bad[:5])
+            seen += 1
+    assert seen == 4                                          # two types, two tiles
 
 
 @pytest.mark.parametrize("himpl", [ab.APT_HIDDEN_AUTO, ab.APT_HIDDEN_VALU, ab.APT_HIDDEN_MFMA, ab.APT_HIDDEN_ABSORBED])
