@@ -54,6 +54,45 @@ def test_captured_attention_call_replays_like_the_eager_call(oracle, impl):
     assert np.max(np.abs(out_graph.float().cpu().numpy().astype(np.float64) - want)) < 2e-4
 
 
+@pytest.mark.parametrize("heads,lens,other,whole", [
+    (8, [300, 512, 17] * 5, [511, 2, 90] * 5, True), (24, [300, 512, 17] * 4, [511, 2, 90] * 4, True),   # a range each; 16 waves, 4
+    (16, [700, 513, 700, 600] * 4, [520, 1000, 600, 800] * 4, True),                                 # two ranges each
+    (12, [1500, 1100, 2000], [1200, 1480, 1990], False)])
+def test_captured_call_of_kv_requests_alone_replays_another_plan_of_the_same_counts(heads, lens, other, whole):
+    """The plan's upload is captured with the attention call, so a replay serves the plan that the host buffer then holds."""
+    from paper_2504_07494_amd.harness import DecodeRunner
+    print(f"[case] capture of KV-kind requests alone, {heads} heads {lens}", flush=True)
+    top = np.maximum(lens, other).astype(np.int32)
+    cfg = wl.small_config(name="graphkv", dtype="f16", d_model=128 * heads, n_heads=heads, head_dim=128, block_size=16,
+                          batch=len(lens), len_lo=1, len_hi=2048, hidden_ratio=0.0)
+    batch = wl.make_batch(cfg, top, np.zeros(len(lens), dtype=np.uint8))
+    rn = DecodeRunner(batch)
+    dl = rn.upload(wl.make_layer(batch))
+    a, b = (np.array(x, dtype=np.int32) for x in (lens, other))
+    eager = {}
+    for name, x in (("a", a), ("b", b)):
+        rn.plan(x)
+        rn.workspace.fill_(255)
+        eager[name] = rn.run(dl).clone()
+        assert bool((rn.workspace == 255).all()) == whole
+    torch.cuda.synchronize()
+    host = torch.empty_like(rn.plan_host).pin_memory()
+    ab.apt_plan(rn.shape, a, batch.cache_kind, host)
+    side, graph, out = torch.cuda.Stream(), torch.cuda.CUDAGraph(), torch.empty_like(rn.out)
+    rn.plan_host = host
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            ab.apt_plan_upload(host, rn.plan_dev, rn.stream())
+            rn.run(dl, out=out)
+    for x, name in ((a, "a"), (b, "b"), (a, "a"), (b, "b")):
+        ab.apt_plan(rn.shape, x, batch.cache_kind, host)
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        # (a sum may be associated by another number of waves than the eager call of that plan chose)
+        assert float((out - eager[name]).abs().max()) < 1e-5, name
+
+
 @pytest.mark.parametrize("n_requests", [1, 77, 78, 200])
 def test_plan_upload_small_blobs_are_read_at_once_and_captured_ones_at_replay(n_requests):
     """Blobs below, just below (77 requests: 3824 bytes), just above and far above the size that travels with a kernel launch."""
