@@ -196,8 +196,10 @@ int apt_plan_max_bytes(const apt_shape* s, int B, int max_ctx, size_t* bytes);
  * decreasing range length (ties by request, range, head).  With APT_HIDDEN_ABSORBED a hidden-kind
  * item covers all heads of its range: one item (request, 0, t0, t1) per range, all in queue 0, by
  * request and range.  The order only steers which workgroup takes which item (cache locality,
- * balance); every item is independent.  With packed weights, word 31 says how far the short last ranges of a queue's requests
- * share the tiles of the projection kernel (four bits per queue, 0: not at all); it changes neither items nor partials.
+ * balance); every item is independent.  With packed weights, word 31 says how far the short last
+ * ranges of a queue's requests share the tiles of the projection kernel (four bits per queue, 0: not
+ * at all); it changes neither items nor any bit of a partial, so that with packed weights the output
+ * of a hidden-kind request does not depend on the other requests.
  * Integer-only; the same inputs always give the same bytes.
  * Errors: APT_EINVAL (null, B < 1, length < 1, unknown kind), APT_ERANGE (length
  * beyond max_blocks_per_req*block_size), APT_EWORKSPACE (plan_bytes too small),
@@ -260,9 +262,15 @@ int apt_pack_weights(const apt_shape* s, const void* W_K, const void* W_V, void*
  *   workspace   device, at least info.workspace_bytes bytes; holds the per-range
  *               partial results (running maximum, sum, un-normalised output) that the
  *               merge kernel combines; contents are undefined afterwards
- * Two kernels are enqueued on `stream`: the item kernel (hidden-kind and KV-kind items in the
- * same launch) and the merge kernel; with APT_HIDDEN_ABSORBED the hidden-kind requests take six
- * kernels of their own before it.
+ * Enqueued on `stream`:
+ *   - the item kernel (hidden-kind and KV-kind items in the same launch) and the merge kernel;
+ *   - KV-kind requests alone, every context a single range, or (kv_chunk = 0 only) no more
+ *     (request, head) pairs than compute units and contexts short enough for it to pay: one kernel,
+ *     a workgroup per pair for its whole context, which writes `out` and no partials (the workspace is
+ *     asked for all the same);
+ *   - APT_HIDDEN_ABSORBED with hidden-kind requests: six kernels, of which the first also serves the
+ *     KV-kind items and the last also merges them; fp32 inputs with KV-kind requests seven, the
+ *     KV-kind items first.
  * Errors: APT_EINVAL (null pointer that is needed), APT_EWORKSPACE, APT_ESHAPE,
  * APT_EDTYPE, APT_EHIP (launch failure; nothing is written in the other cases).
  */

@@ -9,6 +9,7 @@
 //                                      attends to them from registers
 //                  every item writes one partial (m, l, acc[head_dim]) in fp32
 //   merge kernel   combines a request's partials per head and normalises
+//   whole kernel   KV-kind requests alone, where takes_whole says so: a workgroup per request and head, no partials
 //   apt_absorbed.inc, apt_absorb*.hip: the hidden-kind requests without the projection (opt-in, APT_HIDDEN_ABSORBED)
 //   cache append / cache write, weight packing, calibration kernels
 //
