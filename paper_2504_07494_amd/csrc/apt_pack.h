@@ -9,9 +9,9 @@
 // Tiles of 320 rows can also serve ranges of 256 tokens: then the full ranges share
 // tiles as well (a cap of 9 or 10 blocks).
 //
-// Attention call with a tile per range / shared tiles, us: 40 heads, fp16, 256 requests of 128 tokens 3370 / 2450, 128 pairs of
-// 160 and 96 tokens 3310 / 2455, 512 of 32 tokens 5020 / 1290; 72 heads, 256 of 160 tokens 13 850 / 10 310; whole steps, half of
-// the requests on the hidden cache: 40 heads, 64 of 128..2048 tokens 2847 / 2720; 72 heads, 256 of 64..2048 38 080 / 36 640.
+// Attention call with a tile per range / shared tiles, us, fp16, one run: 40 heads, 256 requests of 128 tokens 3461 / 2513, 512 of 32
+// tokens 5328 / 1300, three of 415, 513 and 619 tokens 176 / 157; 72 heads, 256 of 160 tokens 14 130 / 10 710; half of the requests on
+// the hidden cache: 40 heads, 64 of 128..2048 tokens 2812 / 2694; 72 heads, 256 of 64..2048 39 320 / 38 020.
 //
 // A queue's short ranges are sorted by decreasing length, hence by decreasing class (number of blocks).  A pattern
 // names how many ranges of each class a tile takes, the largest classes first, and is used as often as the ranges
