@@ -298,6 +298,8 @@ template <int DT, int HD> int launch_items(const ItemParams& p, int most16, hipS
 // 57 KB/us alone it was 2.9 %, 36 % at most (attention call, fp16, ranges and merge / whole: 40 heads, 3 requests of up to 1743 tokens
 // 17.7 / 22.8; 12 heads of 64, 6 of up to 1949 10.5 / 13.8; 40 heads, one of 500 10.2 / 7.5, of 850 10.8 / 10.4, of 1250 11.7 / 14.5;
 // 72 heads, 3 of 2048 41.4 / 35.2; 32 heads, 8 of 1000 24.0 / 20.9).
+// GPU time decides.  Where the host is the bound, ranges cost it a launch more: one request of 1237 tokens, 40 heads, attention calls back to
+// back 12.3 / 15.1 us, waited-for steps 39.5 / 43.1, but steps of one layer back to back 23.3 / 20.2 (planned, copied and launched from Python).
 bool takes_whole(const ItemParams& p, const int32_t* pw, int row_bytes, int most16) {
     if (p.n_hidden_items > 0) return false;
     if (pw[APT_PW_NPARTIALS] == p.B) return true;
