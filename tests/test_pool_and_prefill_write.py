@@ -305,3 +305,42 @@ def test_gpu_serving_loop_pool_prefill_write_append_attention(oracle, dtype, hd,
             assert err < 2e-4, (step, err)
     finally:
         ab.apt_pool_destroy(pool)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,H,hd,bs", [("f16", 1, 64, 8), ("bf16", 3, 64, 16), ("f16", 40, 128, 8), ("f32", 41, 128, 16), ("bf16", 72, 128, 32)])
+def test_gpu_write_of_rows_of_any_width_is_bit_exact(oracle, dtype, H, hd, bs):
+    # rows of 8 to 1312 16-byte units (a wave has 640 in flight), runs around the four tokens of a workgroup and
+    # the blocks, nothing new, a first position inside a block; then the next token through the append
+    import torch
+    from paper_2504_07494_amd.harness import _to_dev
+    print(f"[case] write {dtype} H={H} hd={hd} bs={bs}", flush=True)
+    d = H * hd
+    n_new = np.array([1, 3, 4, 5, 0, 2 * bs + 1, 8], dtype=np.int32)
+    lens = (n_new + np.array([0, 2, bs - 1, bs, 3, 1, 2 * bs], dtype=np.int32)).astype(np.int32)
+    for kinds in (np.array([0, 1, 0, 1, 0, 0, 1], dtype=np.uint8), np.ones(7, dtype=np.uint8)):
+        cfg = wl.small_config(name="write", dtype=dtype, d_model=d, n_heads=H, head_dim=hd, block_size=bs, batch=7,
+                              len_lo=1, len_hi=int(lens.max()) + 1, poison=False)
+        batch = wl.make_batch(cfg, lens + 1, kinds)
+        off = np.concatenate([[0], np.cumsum(n_new)]).astype(np.int32)
+        x, k, v = _rows(cfg, int(off[-1]), 7)
+        x1, k1, v1 = _rows(cfg, 7, 8)
+        osh = oracle.shape_of(d, H, hd, bs, dtype, batch.max_blocks, 1.0)
+        shape = ab.make_shape(d, H, hd, bs, dtype, batch.max_blocks, 1.0)
+        want = np.zeros((batch.n_pool_blocks, bs * d), dtype=x.dtype)
+        pool = _to_dev(want, "cuda:0")
+        hidden_only = bool(kinds.all())
+        tables, kind_dev = torch.from_numpy(batch.block_tables).cuda(), torch.from_numpy(kinds).cuda()
+        stream = torch.cuda.current_stream().cuda_stream
+        dev = [_to_dev(a, "cuda:0") for a in (x, k, v, x1, k1, v1)]
+        if hidden_only:
+            dev[1] = dev[2] = dev[4] = dev[5] = None
+        ab.apt_cache_write(shape, 7, torch.from_numpy(off).cuda(), int(n_new.max()), *dev[:3], pool, pool, pool, tables,
+                           torch.from_numpy(lens).cuda(), kind_dev, stream)
+        oracle.write(osh, off, x, k, v, want, want, want, batch.block_tables, lens, kinds)
+        torch.cuda.synchronize()
+        assert np.array_equal(pool.cpu().numpy().view(np.uint8).reshape(-1), want.view(np.uint8).reshape(-1))
+        ab.apt_cache_append(shape, 7, *dev[3:], pool, pool, pool, tables, torch.from_numpy(lens + 1).cuda(), kind_dev, stream)
+        oracle.append(osh, x1, k1, v1, want, want, want, batch.block_tables, lens + 1, kinds)
+        torch.cuda.synchronize()
+        assert np.array_equal(pool.cpu().numpy().view(np.uint8).reshape(-1), want.view(np.uint8).reshape(-1))
