@@ -249,8 +249,8 @@ int apt_pack_weights(const apt_shape* s, const void* W_K, const void* W_V, void*
 /*
  * The decode attention step for one layer (Eq. 1-3 over both cache kinds).
  *   plan_host / plan_dev   the blob from apt_plan and its device copy.  One word of the device
- *               copy (a ticket counter that hands out KV-kind items inside the launch) is
- *               written by the item kernel and reset by the merge kernel, so two calls that
+ *               copy (a ticket counter that hands out KV-kind items inside the launch, or tells
+ *               which workgroup is the last) is written by the item kernel and 0 again after the call, so two calls that
  *               share one plan_dev must be ordered on one stream (calls for successive layers
  *               are); everything else in it is read-only
  *   q, k_pages, v_pages, hidden_pages, b_K, b_V, block_tables, out   device, see layout
@@ -263,7 +263,8 @@ int apt_pack_weights(const apt_shape* s, const void* W_K, const void* W_V, void*
  *               partial results (running maximum, sum, un-normalised output) that the
  *               merge kernel combines; contents are undefined afterwards
  * Enqueued on `stream`:
- *   - the item kernel (hidden-kind and KV-kind items in the same launch) and the merge kernel;
+ *   - the item kernel (hidden-kind and KV-kind items in the same launch) and the merge kernel; small calls without packed
+ *     weights: the item kernel alone, whose last workgroup merges;
  *   - KV-kind requests alone, every context a single range, or (kv_chunk = 0 only) no more
  *     (request, head) pairs than compute units and contexts short enough for it to pay: one kernel,
  *     a workgroup per pair for its whole context, which writes `out` and no partials (the workspace is

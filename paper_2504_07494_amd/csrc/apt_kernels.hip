@@ -8,7 +8,8 @@
 //                                      weights, apt_raw16.hip and apt_raw32.hip raw ones) and
 //                                      attends to them from registers
 //                  every item writes one partial (m, l, acc[head_dim]) in fp32
-//   merge kernel   combines a request's partials per head and normalises
+//   merge kernel   combines a request's partials per head and normalises; in small calls the last workgroup of the items
+//                  kernel does (apt_merge.h)
 //   whole kernel   KV-kind requests alone, where takes_whole says so: a workgroup per request and head, no partials
 //   apt_absorbed.inc, apt_absorb*.hip: the hidden-kind requests without the projection (opt-in, APT_HIDDEN_ABSORBED)
 //   cache append / cache write, weight packing, calibration kernels
@@ -22,6 +23,7 @@
 #include "apt_device.h"
 #include "apt_hybrid_bench.h"
 #include "apt_launch.h"
+#include "apt_merge.h"
 #include "apt_absorb_tile.h"
 #include "apt_pack.h"
 
@@ -40,7 +42,8 @@ __global__ __launch_bounds__(NW * 64) void apt_items_kernel(ItemParams p) {
     const int item = blockIdx.x + p.item_base;
     if (item >= p.n_items) return;
     const int4 it = ((const int4*)(p.plan + p.items_off))[item];
-    kv_item<DT, HD, NW>(p, it.x, it.y, it.z, it.w, lds);
+    kv_item_through<DT, HD, NW>(p, it.x, it.y, it.z, it.w, lds);
+    merge_by_last<DT, HD>(p, lds);
 }
 
 // Whole contexts, one workgroup per request and head, straight to the output: no partials and no merge (see takes_whole).
@@ -58,7 +61,7 @@ __global__ __launch_bounds__(NW * 64) void apt_whole_kernel(ItemParams p, char* 
 }
 
 // ---------------------------------------------------------------------------------
-// merge kernel: out[r][h][c] = sum_s acc_s[c] 2^(m_s - M) / sum_s l_s 2^(m_s - M)
+// merge kernel
 // ---------------------------------------------------------------------------------
 // The merge's own parameters: 56 bytes of kernel arguments, not the 300 of ItemParams (step of the smallest batches 0.2-0.3 us less).
 struct MergeParams {
@@ -69,31 +72,14 @@ struct MergeParams {
     int32_t B, H;
 };
 
-template <typename Params> __device__ inline float merged(const Params& p, int r, int h, int c, int HD) {
-    const int32_t* split_count = p.plan + APT_PW_HEADER + APT_PA_SPLIT_COUNT * p.B;
-    const int32_t* ws_offset = p.plan + APT_PW_HEADER + APT_PA_WS_OFFSET * p.B;
-    const int ns = split_count[r];
-    const int64_t base = (int64_t)ws_offset[r] * p.H + h;
-    float M = kSentinel;
-    for (int s = 0; s < ns; ++s) M = fmaxf(M, p.ws_ml[base + (int64_t)s * p.H].x);
-    float L = 0.f, A = 0.f;
-    for (int s = 0; s < ns; ++s) {
-        const int64_t slot = base + (int64_t)s * p.H;
-        const float2 ml = p.ws_ml[slot];
-        const float wgt = fast_exp2(ml.x - M);
-        L = fmaf(ml.y, wgt, L);
-        A = fmaf(p.ws_acc[slot * HD + c], wgt, A);
-    }
-    return A / L;
-}
-
+// a thread per four channels
 template <int ODT>
 __global__ __launch_bounds__(kThreads) void apt_merge_kernel(MergeParams p, char* out, int HD) {
     const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (gid == 0) *p.kv_ticket = 0;         // the item kernel of this call is done: ready for the next call
-    if (gid >= (int64_t)p.B * p.H * HD) return;
-    const int64_t pair = gid / HD;
-    store_out<ODT>(out, gid, merged(p, (int)(pair / p.H), (int)(pair % p.H), (int)(gid % HD), HD));
+    if (4 * gid >= (int64_t)p.B * p.H * HD) return;
+    const int64_t pair = 4 * gid / HD;
+    store_out4<ODT>(out, 4 * gid, merged4<false>(p, (int)(pair / p.H), (int)(pair % p.H), (int)(4 * gid % HD), HD));
 }
 
 // ---------------------------------------------------------------------------------
@@ -342,6 +328,16 @@ bool takes_whole(const ItemParams& p, const int32_t* pw, int row_bytes, int most
     const double whole = 3.0 + kb * (double)longest / 68.0 + all / 13.4;
     const double ranges = p.n_items <= most16 ? 6.4 + kb * (double)std::min<int64_t>(longest, p.kv_chunk) / 90.0 + all / 11.0 : 5.5 + all / 6.6;
     return whole <= ranges;
+}
+// Whether the last workgroup of the item kernel merges the partials (merge_by_last): up to 16 of their values for each of its threads.
+// It saves a launch of 2.6 us where the host is the bound, and costs the GPU nothing up to there (attention call back to back,
+// us, a kernel of its own / by the last workgroup: 256 threads, 2.5 k values 12.0 / 9.7, 8 k 11.4 / 12.2, 17 k 22.8 / 26.3; 1024 threads,
+// 9 k 10.5 / 10.7, 10 k 11.0 / 11.0, 15 k 11.5 / 12.1, 28 k 13.0 / 18.1).  One request of 1237 tokens, 40 heads, append and attention,
+// steps of one layer 22.9 -> 20.2 us; the fp32 layer of 4 heads, 4 requests 17.4 -> 14.4.
+bool merges_by_itself(const ItemParams& p, const int32_t* pw, int hd, int himpl, int most16) {
+    if (p.n_hidden_items > 0 && himpl != APT_HIDDEN_VALU) return false;
+    const int threads = p.n_hidden_items == 0 && p.n_items <= most16 ? 1024 : kThreads;
+    return (int64_t)pw[APT_PW_NPARTIALS] * p.H * hd <= 16 * threads;
 }
 template <int DT, int HD, int NW, int ODT> void launch_whole_nw(const ItemParams& p, char* out, int in_items, hipStream_t st) {
     hipLaunchKernelGGL((apt_whole_kernel<DT, HD, NW, ODT>), dim3(p.B * p.H), dim3(NW * 64), (KvItem<DT, HD, NW>::kLds), st, p, out, in_items);
@@ -639,6 +635,9 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     if (ev_begin && hipEventRecord((hipEvent_t)ev_begin, st) != hipSuccess) return APT_EHIP;
     const int most16 = rs.kv_auto ? ds->n_wg : 0;
     const bool whole = takes_whole(p, pw, hd * rs.elem_bytes, most16);
+    // the last workgroup of the item kernel merges, or a kernel of its own
+    p.out = !whole && merges_by_itself(p, pw, hd, hi, most16) ? (char*)out : nullptr;
+    p.out_dtype = rs.s.out_dtype;
     auto launch = [&](auto dtype, auto head_dim) {
         constexpr int DT = decltype(dtype)::value, HD = decltype(head_dim)::value;
         return whole ? launch_whole<DT, HD>(p, pw, (char*)out, rs.s.out_dtype, most16, st)
@@ -655,9 +654,9 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     const bool absorbed = hi == APT_HIDDEN_ABSORBED && n_hidden > 0;
     if (ev_end && !absorbed && hipEventRecord((hipEvent_t)ev_end, st) != hipSuccess) return APT_EHIP;
 
-    if (whole) return APT_OK;
+    if (whole || p.out) return APT_OK;
 
-    const unsigned blocks = (unsigned)(((int64_t)B * rs.s.n_heads * hd + kThreads - 1) / kThreads);
+    const unsigned blocks = (unsigned)(((int64_t)B * rs.s.n_heads * hd / 4 + kThreads - 1) / kThreads);
     auto launch_merge = [&](auto kern, const auto& params) { hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, st, params, (char*)out, hd); };
     if (absorbed) {
         if (rs.s.out_dtype == APT_F32) launch_merge(dt == APT_F32 ? apt_absorb_merge_kernel<0, 0> : dt == APT_F16 ? apt_absorb_merge_kernel<1, 0> : apt_absorb_merge_kernel<2, 0>, p);

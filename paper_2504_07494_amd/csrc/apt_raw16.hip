@@ -2,6 +2,7 @@
 #include <type_traits>
 #include "apt_device.h"
 #include "apt_launch.h"
+#include "apt_merge.h"
 
 namespace {
 
@@ -216,8 +217,8 @@ __device__ __forceinline__ void hidden_item_raw(const ItemParams& p, int r, int 
         const float w0 = fast_exp2(m0 - M), w1 = fast_exp2(m1 - M);
         const int32_t* ws_offset = p.plan + APT_PW_HEADER + p.B;
         const int64_t slot = ((int64_t)ws_offset[r] + t0 / p.hidden_chunk) * p.H + h;
-        p.ws_acc[slot * HD + tid] = o_lds[tid] * w0 + o_lds[HD + tid] * w1;
-        if (tid == 0) p.ws_ml[slot] = make_float2(M, l0 * w0 + l1 * w1);
+        put_partial(p, slot, tid, HD, o_lds[tid] * w0 + o_lds[HD + tid] * w1);
+        if (tid == 0) put_partial_ml(p, slot, M, l0 * w0 + l1 * w1);
     }
 }
 
@@ -239,8 +240,9 @@ __global__ __launch_bounds__(kThreads, 2) void apt_items_raw_kernel(ItemParams p
         const int i = p.n_hidden_items + g - 8 * share;
         if (i >= p.n_items) return;
         const int4 it = items[i];
-        kv_item<DT, HD>(p, it.x, it.y, it.z, it.w, lds);
+        kv_item_through<DT, HD>(p, it.x, it.y, it.z, it.w, lds);
     }
+    merge_by_last<DT, HD>(p, lds);
 }
 
 template <int DT, int HD> int launch(const ItemParams& p, hipStream_t st) {

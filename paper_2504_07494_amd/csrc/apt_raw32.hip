@@ -2,6 +2,7 @@
 #include <type_traits>
 #include "apt_device.h"
 #include "apt_launch.h"
+#include "apt_merge.h"
 
 namespace {
 
@@ -114,7 +115,7 @@ __device__ __forceinline__ void hidden_item_f32(const ItemParams& p, int r, int 
     const float l = group_sum<64>(pw);
     const int32_t* ws_offset = p.plan + APT_PW_HEADER + p.B;
     const int64_t slot = ((int64_t)ws_offset[r] + t0 / p.hidden_chunk) * p.H + h;
-    if (tid == 0) p.ws_ml[slot] = make_float2(m, l);
+    if (tid == 0) put_partial_ml(p, slot, m, l);
     if (mat == 1) {
         p_lds[sub * 64 + lane] = pw;                           // read back by this wave only
         f32x4_t o = {0.f, 0.f, 0.f, 0.f};
@@ -140,7 +141,7 @@ __device__ __forceinline__ void hidden_item_f32(const ItemParams& p, int r, int 
     __syncthreads();
     if (tid < HD) {
         const float bv = ((const float*)p.b_V)[h * HD + tid];
-        p.ws_acc[slot * HD + tid] = fmaf(l, bv, HD == 64 ? o_lds[tid] + o_lds[64 + tid] : o_lds[tid]);
+        put_partial(p, slot, tid, HD, fmaf(l, bv, HD == 64 ? o_lds[tid] + o_lds[64 + tid] : o_lds[tid]));
     }
 }
 
@@ -162,8 +163,9 @@ __global__ __launch_bounds__(kThreads) void apt_items_f32_kernel(ItemParams p, i
         const int i = p.n_hidden_items + g - 8 * share;
         if (i >= p.n_items) return;
         const int4 it = items[i];
-        kv_item<0, HD>(p, it.x, it.y, it.z, it.w, lds);
+        kv_item_through<0, HD>(p, it.x, it.y, it.z, it.w, lds);
     }
+    merge_by_last<0, HD>(p, lds);
 }
 
 template <int HD> int launch(const ItemParams& p, hipStream_t st) {
