@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemP
     const char* asrc = (const char*)p.ab_qt + ((int64_t)hr * n_kt + kt0) * C::kABytes + lane * 16;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
     auto copy_x = [&](int xt, int i) {
-        gload_lds16(xsrc[i] + xt * C::kXRow, lds0 + (xt % SX) * C::kXBytes + (C::kXCopies * w + i) * 1024);
+        gload_lds16_stream(xsrc[i] + xt * C::kXRow, lds0 + (xt % SX) * C::kXBytes + (C::kXCopies * w + i) * 1024);
     };
     // k-tile kt: the queries S - 1 k-tiles ahead, and the X tile SX - 1 ahead (two k-tiles share a wide one's copies)
     auto issue = [&](int kt) {

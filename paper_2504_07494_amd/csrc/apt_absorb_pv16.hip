@@ -1,4 +1,5 @@
 // Absorbed-weight hidden path, 16-bit inputs: the weighted sums of the cached rows.
+#include <type_traits>
 #include "apt_device.h"
 #include "apt_launch.h"
 #include "apt_absorb_tile.h"
@@ -43,6 +44,7 @@ template <int DT, int NF, int CW> struct PvTile {
     static constexpr bool kFits = S >= 3 && 2 * NF * CF * 4 <= 192;
     static_assert((S - 2) * kCopies <= 63, "vmcnt range");
 };
+constexpr int kAhead = 2;                                 // weight operands read ahead of the products
 constexpr int kPvBlkBytes = APT_ABSORBED_MAX_GROUP * APT_ABSORBED_CHUNK / 4 * 4;      // block ids of a unit, blocks of 4 tokens at least
 
 template <int DT, int NF, int CW>
@@ -77,17 +79,21 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_pv16_kernel(ItemPara
         // columns past d_model repeat the last eight (never stored)
         col_of[i] = min(c0 + ((at >> 5) ^ wswz(row_of[i])) * 16 + ((at >> 4) & 1) * 8, p.d - 8) * 2;
     }
-    auto issue = [&](int kt) {
-        const uint32_t st = lds0 + (kt % S) * C::kStage;
+    // copy i of k-tile kt, its X rows from xsrc as row_sources left them
+    const char* xsrc[C::kXCopies];
+    auto row_sources = [&](int kt) {
 #pragma unroll
         for (int i = 0; i < C::kXCopies; ++i) {
             const int rel = min(kt * 32 + row_of[i], len - 1);     // rows past the range repeat its last token (their weights are zero)
-            const char* src = p.hidden_pages + ((int64_t)blk[rel >> p.log2_bs] * p.bs + (rel & (p.bs - 1))) * p.d * 2 + col_of[i];
-            gload_lds16(src, st + (C::kXCopies * w + i) * 1024);
+            xsrc[i] = p.hidden_pages + ((int64_t)blk[rel >> p.log2_bs] * p.bs + (rel & (p.bs - 1))) * p.d * 2 + col_of[i];
         }
-#pragma unroll
-        for (int i = 0; i < C::kPCopies; ++i) {          // some waves copy the last chunk again (same bytes)
-            const int n = min(w + kAbWaves * i, C::kPBytes / 1024 - 1);
+    };
+    auto copy = [&](int kt, int i) {
+        const uint32_t st = lds0 + (kt % S) * C::kStage;
+        if (i < C::kXCopies) {
+            gload_lds16_stream(xsrc[i], st + (C::kXCopies * w + i) * 1024);
+        } else {                                         // some waves copy the last chunk again (same bytes)
+            const int n = min(w + kAbWaves * (i - C::kXCopies), C::kPBytes / 1024 - 1);
             gload_lds16(psrc + (int64_t)kt * C::kPBytes + n * 1024, st + C::kXBytes + n * 1024);
         }
     };
@@ -106,31 +112,50 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_pv16_kernel(ItemPara
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[f][c][e] = sum[f][c][e] = 0.f;
 #pragma unroll
-    for (int s = 0; s < S - 1; ++s)
-        if (s < nkt) issue(s);
+    for (int s = 0; s < S - 1; ++s) {
+        if (s >= nkt) continue;
+        row_sources(s);
+#pragma unroll
+        for (int i = 0; i < C::kCopies; ++i) copy(s, i);
+    }
+    row_sources(S - 1);
     int stage = 0;
-    for (int kt = 0; kt < nkt; ++kt) {
-        if (kt + S - 2 < nkt) wait_vmcnt<(S - 2) * C::kCopies>();
-        else wait_vmcnt<0>();
+    // The copies of the k-tile S - 1 ahead go out one by one between the products: asked for in one go, a wave would be held until
+    // the copy path has taken all of the workgroup's.  Their row addresses are worked out an iteration ahead.
+    auto step = [&](int kt, auto refill) {
         __syncthreads();            // k-tile kt has landed for every wave; nobody still reads the stage refilled next
-        if (kt + S - 1 < nkt) issue(kt + S - 1);
         const uint32_t so = stage * C::kStage;
-        uint4 xf[CF];
+        uint4 xf[CF], pf[kAhead + 1];
 #pragma unroll
         for (int c = 0; c < CF; ++c) {
             const uint2 lo = lds_read_tr(xaddr[c] + so), hi = lds_read_tr(xaddr[c] + so + 4 * C::kRow);
             xf[c] = make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
+        constexpr int G = NS * NF;
+        auto read = [&](int g) { pf[g % (kAhead + 1)] = lds_read16(paddr + so + (g / NF * C::R + 16 * (g % NF)) * 64); };
 #pragma unroll
-        for (int s = 0; s < NS; ++s)
+        for (int g = 0; g < kAhead; ++g) read(g);
 #pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                const uint4 pf = lds_read16(paddr + so + (s * C::R + 16 * f) * 64);
+        for (int g = 0; g < G; ++g) {
+            if (g + kAhead < G) read(g + kAhead);
+            if constexpr (refill)
 #pragma unroll
-                for (int c = 0; c < CF; ++c) acc[f][c] = mfma16<DT>(xf[c], pf, acc[f][c]);
-            }
+                for (int i = g * C::kCopies / G; i < (g + 1) * C::kCopies / G; ++i) copy(kt + S - 1, i);
+#pragma unroll
+            for (int c = 0; c < CF; ++c) acc[g % NF][c] = mfma16<DT>(xf[c], pf[g % (kAhead + 1)], acc[g % NF][c]);
+        }
+        if constexpr (refill) row_sources(kt + S);
         stage = stage == S - 1 ? 0 : stage + 1;
         if ((kt + 1) % (kAbFold / 32) == 0) ab_fold<CF>(acc, sum, NF);
+    };
+    int kt = 0;
+    for (; kt + S - 1 < nkt; ++kt) {
+        wait_vmcnt<(S - 2) * C::kCopies>();
+        step(kt, std::true_type{});
+    }
+    for (; kt < nkt; ++kt) {
+        wait_vmcnt<0>();
+        step(kt, std::false_type{});
     }
     ab_fold<CF>(acc, sum, NF);
 #pragma unroll

@@ -61,6 +61,11 @@ template <> struct AbSplit<2> {
     }
 };
 
+// gload_lds16 of data that is read once (streamed past the caches)
+__device__ inline void gload_lds16_stream(const void* g, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds_addr), "v"(g) : "memory", "m0");
+}
+
 constexpr int kAbTok = APT_ABSORBED_CHUNK;                // tokens per range
 constexpr int kAbMT = 256;                                // tokens per workgroup of the score kernel
 
