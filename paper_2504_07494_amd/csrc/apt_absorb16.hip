@@ -1,5 +1,6 @@
 // Absorbed-weight hidden path, 16-bit inputs: the kernels that build the absorbed queries and the scores.
 #include <algorithm>
+#include <type_traits>
 #include "apt_device.h"
 #include "apt_launch.h"
 #include "apt_absorb_tile.h"
@@ -125,40 +126,70 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_q16_kernel(ItemParams p) 
 // 64..1024 tokens 386 / 374, 65 heads, 16 requests of 20..500 150 / 147.  A start of the k loop that differs between the groups,
 // so that they read other memory channels, changed nothing.  The version
 // with heads padded to 64, an accumulator per part and 512-wide slices took 117 us for the 40 heads, and 1193 us for the 72.
-template <int DT, int NF, int F0, int FN, typename Issue>
-__device__ __forceinline__ void score_loop(f32x4_t (*acc)[4], f32x4_t (*sum)[4], f32x4_t (*total)[4], uint32_t lds0, int tg, int nkt, Issue issue) {
+template <int DT, int NF, int F0, int FN, typename Copy, typename Issue>
+__device__ __forceinline__ void score_loop(f32x4_t (*acc)[4], f32x4_t (*sum)[4], f32x4_t (*total)[4], uint32_t lds0, int tg, int nkt, Copy copy, Issue issue) {
     using C = AbTile<DT, NF>;
     constexpr int NS = C::NS, KT = C::KT, S = C::S, XPT = C::XPT;
+    constexpr int G = KT / 32 * FN * NS;                 // operand fragments of a k-tile, each for four products
+    constexpr int kAhead = G > 2 ? 2 : 1;                // read ahead of the products
     const int lane = threadIdx.x & 63, l16 = lane & 15, qd = lane >> 4;
     int stage = 0, xstage = 0;
-    for (int kt = 0; kt < nkt; ++kt) {
+    // refill: the copies that iteration kt asks for go out one by one between the products (asked for in one go, a wave is held until
+    // the copy path has taken all of the workgroup's); else they have been asked for, or there are none.  odd: kt is
+    auto step = [&](int kt, auto odd, auto refill) {
+        const uint32_t xst = lds0 + xstage * C::kXBytes, ast = lds0 + C::SX * C::kXBytes + stage * C::kABytes;
+        uint4 x[KT / 32][4], a[kAhead + 1];
+        auto read = [&](int g) {
+            const int ks = g / (FN * NS), f = g / NS % FN, s = g % NS;
+            const uint32_t off = (((4 * ks + qd) ^ ab_swz<KT>(l16)) << 4) + l16 * C::kRow;
+            a[g % (kAhead + 1)] = lds_read16(ast + (s * C::R + 16 * (F0 + f)) * C::kRow + off);
+        };
+#pragma unroll
+        for (int ks = 0; ks < KT / 32; ++ks) {
+            const uint32_t xoff = (((4 * ks + qd + (XPT == 2 && odd ? 4 : 0)) ^ ab_swz<KT * XPT>(l16)) << 4) + l16 * C::kXRow;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) x[ks][t] = lds_read16(xst + (64 * tg + 16 * t) * C::kXRow + xoff);
+        }
+#pragma unroll
+        for (int g = 0; g < kAhead; ++g) read(g);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (g + kAhead < G) read(g + kAhead);
+            if constexpr (refill)
+#pragma unroll
+                for (int i = g * C::kCopies / G; i < (g + 1) * C::kCopies / G; ++i) copy(kt, i, odd);
+            const int ks = g / (FN * NS), f = g / NS % FN;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[f][t] = mfma16<DT>(a[g % (kAhead + 1)], x[ks][t], acc[f][t]);
+        }
+        stage = stage == S - 1 ? 0 : stage + 1;
+        if (XPT == 1 || odd) xstage = xstage == C::SX - 1 ? 0 : xstage + 1;
+        if ((kt + 1) % (kAbFold / KT) == 0) ab_fold<4>(acc, sum, FN);
+        if ((kt + 1) % (kAbFoldSums / KT) == 0) ab_fold<4>(sum, total, FN);
+    };
+    // k-tile kt has landed for every wave behind the barrier, and nobody still reads the stages refilled next
+    int kt = 0;
+    auto full = [&](auto odd) {
+        wait_vmcnt<(S - 2) * C::kCopies>();
+        __syncthreads();
+        step(kt++, odd, std::true_type{});
+    };
+    // iterations with all their copies
+    for (const int end = nkt - XPT * (C::SX - 1); kt < end;) {
+        full(std::false_type{});
+        if constexpr (XPT == 2) full(std::true_type{});
+    }
+    auto last = [&](auto odd) {
         // the copies of this k-tile were issued S - 1 of them ago; the last X tile's go out a k-tile before the last queries'
         if (kt + S - 3 + XPT < nkt) wait_vmcnt<(S - 2) * C::kCopies>();
         else wait_vmcnt<0>();
-        __syncthreads();            // k-tile kt has landed for every wave; nobody still reads the stages refilled next
+        __syncthreads();
         issue(kt);
-        const uint32_t xst = lds0 + xstage * C::kXBytes, ast = lds0 + C::SX * C::kXBytes + stage * C::kABytes;
-#pragma unroll
-        for (int ks = 0; ks < KT / 32; ++ks) {
-            const int xu = 4 * ks + qd + (XPT == 2 ? 4 * (kt & 1) : 0);
-            const uint32_t xoff = ((xu ^ ab_swz<KT * XPT>(l16)) << 4) + l16 * C::kXRow;
-            const uint32_t off = (((4 * ks + qd) ^ ab_swz<KT>(l16)) << 4) + l16 * C::kRow;
-            uint4 x[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) x[t] = lds_read16(xst + (64 * tg + 16 * t) * C::kXRow + xoff);
-#pragma unroll
-            for (int f = 0; f < FN; ++f)
-#pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    const uint4 a = lds_read16(ast + (s * C::R + 16 * (F0 + f)) * C::kRow + off);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) acc[f][t] = mfma16<DT>(a, x[t], acc[f][t]);
-                }
-        }
-        stage = stage == S - 1 ? 0 : stage + 1;
-        if ((kt + 1) % XPT == 0) xstage = xstage == C::SX - 1 ? 0 : xstage + 1;
-        if ((kt + 1) % (kAbFold / KT) == 0) ab_fold<4>(acc, sum, FN);
-        if ((kt + 1) % (kAbFoldSums / KT) == 0) ab_fold<4>(sum, total, FN);
+        step(kt++, odd, std::false_type{});
+    };
+    while (kt < nkt) {
+        last(std::false_type{});
+        if constexpr (XPT == 2) last(std::true_type{});
     }
     ab_fold<4>(acc, sum, FN);
     ab_fold<4>(sum, total, FN);
@@ -197,6 +228,10 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemP
     auto copy_x = [&](int xt, int i) {
         gload_lds16_stream(xsrc[i] + xt * C::kXRow, lds0 + (xt % SX) * C::kXBytes + (C::kXCopies * w + i) * 1024);
     };
+    auto copy_a = [&](int at, int i) {                   // some waves copy the last chunk again (same bytes)
+        const int n = min(w + kAbWaves * i, C::kABytes / 1024 - 1);
+        gload_lds16(asrc + (int64_t)at * C::kABytes + n * 1024, lds0 + SX * C::kXBytes + (at % S) * C::kABytes + n * 1024);
+    };
     // k-tile kt: the queries S - 1 k-tiles ahead, and the X tile SX - 1 ahead (two k-tiles share a wide one's copies)
     auto issue = [&](int kt) {
         const int xt = (kt + XPT * SX) / XPT - 1, at = kt + S - 1;
@@ -210,10 +245,13 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemP
         }
         if (at >= 0 && at < nkt)
 #pragma unroll
-            for (int i = 0; i < C::kACopies; ++i) {      // some waves copy the last chunk again (same bytes)
-                const int n = min(w + kAbWaves * i, C::kABytes / 1024 - 1);
-                gload_lds16(asrc + (int64_t)at * C::kABytes + n * 1024, lds0 + SX * C::kXBytes + (at % S) * C::kABytes + n * 1024);
-            }
+            for (int i = 0; i < C::kACopies; ++i) copy_a(at, i);
+    };
+    // copy i of those of iteration kt, which has them all
+    auto copy = [&](int kt, int i, auto odd) {
+        constexpr int kX = C::kXCopies / XPT;
+        if (i < kX) copy_x(kt / XPT + SX - 1, i + (XPT == 2 && odd ? kX : 0));
+        else copy_a(kt + S - 1, i - kX);
     };
     f32x4_t acc[NF0][4], sum[NF0][4], total[NF0][4];
 #pragma unroll
@@ -224,8 +262,8 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemP
             for (int e = 0; e < 4; ++e) acc[f][t][e] = sum[f][t][e] = total[f][t][e] = 0.f;
 #pragma unroll
     for (int kt = -XPT * (SX - 1); kt < 0; ++kt) issue(kt);
-    if (!second) score_loop<DT, NF, 0, NF0>(acc, sum, total, lds0, tg, nkt, issue);
-    else score_loop<DT, NF, NF0, NF - NF0>(acc, sum, total, lds0, tg, nkt, issue);
+    if (!second) score_loop<DT, NF, 0, NF0>(acc, sum, total, lds0, tg, nkt, copy, issue);
+    else score_loop<DT, NF, NF0, NF - NF0>(acc, sum, total, lds0, tg, nkt, copy, issue);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         const int token = 64 * tg + 16 * t + l16;
