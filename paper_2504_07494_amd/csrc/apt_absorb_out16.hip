@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kThreads, HD == 64 ? 2 : 1) void apt_absorb_out16_k
     };
     auto issue_y = [&](int step, int u, int stage) {
 #pragma unroll
-        for (int n = 0; n < C::kYCopies; ++n) gload_lds16(ysrc[n] + min(u, ylast[n]) * ystep + step * 128, yst + stage * C::kYBytes + n * 1024);
+        for (int n = 0; n < C::kYCopies; ++n) gload_lds16_stream(ysrc[n] + min(u, ylast[n]) * ystep + step * 128, yst + stage * C::kYBytes + n * 1024);
     };
     uint32_t waddr[CF];
 #pragma unroll

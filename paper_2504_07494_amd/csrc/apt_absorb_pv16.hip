@@ -21,7 +21,8 @@ namespace {
 // to 48), so that one workgroup's start-up and stores are covered by the other's loop, where the stages or accumulators of 512 do
 // not fit at all, and in batches that would leave CUs without a unit.
 //
-// 72 heads, bf16, 96 requests with 102 k tokens at d_model 9216 (1.9 GB of X): 480-520 us, 1200 us with heads padded to 128
+// 72 heads, bf16, 96 requests with 102 k tokens at d_model 9216 (1.9 GB of X): 450-480 us (whole call, copies of a k-tile in one go / between
+// the products / and X past the caches 1350 / 1325 / 1304; the kernel without its products 393, with X from the caches 457), 1200 us with heads padded to 128
 // in two passes over X, a 16-bit gather per operand and sums per 512-token range.  40 heads, fp16, 33.6 k tokens at
 // d_model 5120 (344 MB): 80 us with 256 columns and two workgroups per CU, 87 us with 512 and one, 86 us before.
 template <int DT, int NF, int CW> struct PvTile {
