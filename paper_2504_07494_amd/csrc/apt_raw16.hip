@@ -18,8 +18,9 @@ namespace {
 //
 // Tiles: at most 256 tokens x 128 channels (HD 64) or 128 x 256 (HD 128), 128 accumulator registers per wave, 24 KB
 // per k-tile and three stages, so that two workgroups share a CU and one's barriers and epilogue are covered by the
-// other's MFMAs.  Short ranges take the 128- or 64-token variant: less padding, and with the LDS this frees more
-// stages in flight.
+// other's MFMAs.  Short ranges take the 192-, 128- or 64-token variant: less padding, and with the LDS this frees more
+// stages in flight.  (Ranges of 129 to 192 tokens in 192 instead of 256 rows, whole step: 25 heads, 25 requests of 64..562 tokens 139.5 ->
+// 132 us, 27 heads, 27 of 145..1024 162 -> 153, 32 heads, 24 of 123..1006 beside as many KV-kind ones 248 -> 242.)
 //
 // Bound by the matrix pipes and, like every dense product on this card, by board power: 48 requests of 32..1024 tokens
 // at d_model 2048, head_dim 64 (13 k hidden-kind tokens) take 0.247 ms for the whole step, 864 TFLOP/s on 4 d^2 per
@@ -235,7 +236,10 @@ __global__ __launch_bounds__(kThreads, 2) void apt_items_raw_kernel(ItemParams p
         const int n = it.w - it.z;
         if (n <= 64) hidden_item_raw<DT, HD, 64>(p, it.x, it.y, it.z, it.w, lds);
         else if (HD == 128 || n <= 128) hidden_item_raw<DT, HD, 128>(p, it.x, it.y, it.z, it.w, lds);
-        else if constexpr (HD == 64) hidden_item_raw<DT, HD, 256>(p, it.x, it.y, it.z, it.w, lds);
+        else if constexpr (HD == 64) {
+            if (n <= 192) hidden_item_raw<DT, HD, 192>(p, it.x, it.y, it.z, it.w, lds);
+            else hidden_item_raw<DT, HD, 256>(p, it.x, it.y, it.z, it.w, lds);
+        }
     } else {
         const int i = p.n_hidden_items + g - 8 * share;
         if (i >= p.n_items) return;
