@@ -155,7 +155,9 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_pv16_kernel(ItemPara
         step(kt, std::true_type{});
     }
     for (; kt < nkt; ++kt) {
-        wait_vmcnt<0>();
+        // for this k-tile, not for all that are in flight: attention call in a graph, all / this one, 40 heads, fp16, a request of 1500
+        // tokens 65.4 -> 65.0 us, 25 heads, 82 requests of 55..181, half hidden-kind 73.3 -> 72.8
+        wait_tiles<S - 2, C::kCopies>(nkt - 1 - kt);
         step(kt, std::false_type{});
     }
     ab_fold<CF>(acc, sum, NF);

@@ -66,6 +66,14 @@ __device__ inline void gload_lds16_stream(const void* g, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds_addr), "v"(g) : "memory", "m0");
 }
 
+// waits until the copies of no more than `tiles` k-tiles are in flight, COPIES each; MOST: of no more than these
+template <int MOST, int COPIES> __device__ __forceinline__ void wait_tiles(int tiles) {
+    if constexpr (MOST > 0) {
+        if (tiles < MOST) return wait_tiles<MOST - 1, COPIES>(tiles);
+    }
+    wait_vmcnt<MOST * COPIES>();
+}
+
 constexpr int kAbTok = APT_ABSORBED_CHUNK;                // tokens per range
 constexpr int kAbMT = 256;                                // tokens per workgroup of the score kernel
 
