@@ -133,8 +133,8 @@ __global__ __launch_bounds__(kThreads) void apt_absorb_q16_kernel(ItemParams p) 
 // accumulator.  k-tiles of X rows and of QT go global -> LDS without registers, as many stages as LDS holds (one
 // workgroup per CU).
 //
-// X is read past the caches (72 heads, bf16, 96 requests, whole call 1304 -> 1290 us), a k-tile's copies between its products (the
-// kernel 620 -> 580 us; without the products 549, with X from the caches 631 before that, so that both sides counted).
+// X is read past the caches or not by apt_absorbed_past.  A k-tile's copies go out between its products (72 heads, bf16, 96 requests: the
+// kernel 620 -> 580 us, 549 without the products).
 // Bound by how memory serves the X rows, one 128-byte line per row and 64 k (rows lie 2 d_model apart): 64-wide k-tiles
 // in three stages take 87 us for 40 heads, fp16, 33.6 k tokens at d_model 5120 (344 MB of X; 0.40 GB of 128-byte line reads, 4.5
 // TB/s), 32-wide ones in seven stages, with more bytes in flight, 99 us.  Where both do not fit 64 wide, X is 64 wide in three
@@ -213,7 +213,8 @@ __device__ __forceinline__ void score_loop(f32x4_t (*acc)[4], f32x4_t (*sum)[4],
     ab_fold<4>(sum, total, FN);
 }
 
-template <int DT, int NF>
+// PAST: X is read past the caches
+template <int DT, int NF, bool PAST>
 __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemParams p) {
     using C = AbTile<DT, NF>;
     constexpr int KT = C::KT, S = C::S, SX = C::SX, XPT = C::XPT, NF0 = C::NF0;
@@ -244,7 +245,10 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_score16_kernel(ItemP
     const char* asrc = (const char*)p.ab_qt + ((int64_t)hr * n_kt + kt0) * C::kABytes + lane * 16;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
     auto copy_x = [&](int xt, int i) {
-        gload_lds16_stream(xsrc[i] + xt * C::kXRow, lds0 + (xt % SX) * C::kXBytes + (C::kXCopies * w + i) * 1024);
+        const char* src = xsrc[i] + xt * C::kXRow;
+        const uint32_t dst = lds0 + (xt % SX) * C::kXBytes + (C::kXCopies * w + i) * 1024;
+        if constexpr (PAST) gload_lds16_stream(src, dst);
+        else gload_lds16(src, dst);
     };
     auto copy_a = [&](int at, int i) {                   // some waves copy the last chunk again (same bytes)
         const int n = min(w + kAbWaves * i, C::kABytes / 1024 - 1);
@@ -305,7 +309,9 @@ template <int DT, int NF> int launch_scores(const ItemParams& p, int head_dim, h
     if (head_dim == 128) hipLaunchKernelGGL((apt_absorb_q16_kernel<DT, 128, NF>), dim3(first), dim3(kThreads), std::max(q_lds, KvItem<DT, 128, 4>::kLds), st, p);
     else hipLaunchKernelGGL((apt_absorb_q16_kernel<DT, 64, NF>), dim3(first), dim3(kThreads), std::max(q_lds, KvItem<DT, 64, 4>::kLds), st, p);
     const unsigned groups = (unsigned)((p.ab_tiles + 7) / 8 * p.ab_ks);
-    hipLaunchKernelGGL((apt_absorb_score16_kernel<DT, NF>), dim3((groups + 7) / 8 * 64), dim3(kAbWaves * 64), C::kLds, st, p);
+    const dim3 grid((groups + 7) / 8 * 64), block(kAbWaves * 64);
+    if (p.ab_past & APT_AB_PAST_SCORES) hipLaunchKernelGGL((apt_absorb_score16_kernel<DT, NF, true>), grid, block, C::kLds, st, p);
+    else hipLaunchKernelGGL((apt_absorb_score16_kernel<DT, NF, false>), grid, block, C::kLds, st, p);
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
 }
 
@@ -320,10 +326,11 @@ template <int DT> int launch_scores_nf(const ItemParams& p, int head_dim, hipStr
     }
 }
 
+template <int DT, int NF> bool setup_nf() {
+    return apt_raise_lds_limit(apt_absorb_score16_kernel<DT, NF, false>) && apt_raise_lds_limit(apt_absorb_score16_kernel<DT, NF, true>);
+}
 template <int DT> bool setup() {
-    return apt_raise_lds_limit(apt_absorb_score16_kernel<DT, 2>) && apt_raise_lds_limit(apt_absorb_score16_kernel<DT, 3>) &&
-           apt_raise_lds_limit(apt_absorb_score16_kernel<DT, 4>) && apt_raise_lds_limit(apt_absorb_score16_kernel<DT, 5>) &&
-           apt_raise_lds_limit(apt_absorb_score16_kernel<DT, 6>) && apt_raise_lds_limit(apt_absorb_score16_kernel<DT, 8>);
+    return setup_nf<DT, 2>() && setup_nf<DT, 3>() && setup_nf<DT, 4>() && setup_nf<DT, 5>() && setup_nf<DT, 6>() && setup_nf<DT, 8>();
 }
 
 }  // namespace

@@ -22,7 +22,7 @@ namespace {
 // not fit at all, and in batches that would leave CUs without a unit.
 //
 // 72 heads, bf16, 96 requests with 102 k tokens at d_model 9216 (1.9 GB of X): 450-480 us (whole call, copies of a k-tile in one go / between
-// the products / and X past the caches 1350 / 1325 / 1304; the kernel without its products 393, with X from the caches 457), 1200 us with heads padded to 128
+// the products / and X past the caches, by apt_absorbed_past, 1350 / 1325 / 1304; the kernel without its products 393, with X from the caches 457), 1200 us with heads padded to 128
 // in two passes over X, a 16-bit gather per operand and sums per 512-token range.  40 heads, fp16, 33.6 k tokens at
 // d_model 5120 (344 MB): 80 us with 256 columns and two workgroups per CU, 87 us with 512 and one, 86 us before.
 template <int DT, int NF, int CW> struct PvTile {
@@ -48,7 +48,8 @@ template <int DT, int NF, int CW> struct PvTile {
 constexpr int kAhead = 2;                                 // weight operands read ahead of the products
 constexpr int kPvBlkBytes = APT_ABSORBED_MAX_GROUP * APT_ABSORBED_CHUNK / 4 * 4;      // block ids of a unit, blocks of 4 tokens at least
 
-template <int DT, int NF, int CW>
+// PAST: X is read past the caches
+template <int DT, int NF, int CW, bool PAST>
 __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_pv16_kernel(ItemParams p, int n_cslices) {
     using C = PvTile<DT, NF, CW>;
     constexpr int NS = C::NS, S = C::S, CF = C::CF;
@@ -92,7 +93,8 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_pv16_kernel(ItemPara
     auto copy = [&](int kt, int i) {
         const uint32_t st = lds0 + (kt % S) * C::kStage;
         if (i < C::kXCopies) {
-            gload_lds16_stream(xsrc[i], st + (C::kXCopies * w + i) * 1024);
+            if constexpr (PAST) gload_lds16_stream(xsrc[i], st + (C::kXCopies * w + i) * 1024);
+            else gload_lds16(xsrc[i], st + (C::kXCopies * w + i) * 1024);
         } else {                                         // some waves copy the last chunk again (same bytes)
             const int n = min(w + kAbWaves * (i - C::kXCopies), C::kPBytes / 1024 - 1);
             gload_lds16(psrc + (int64_t)kt * C::kPBytes + n * 1024, st + C::kXBytes + n * 1024);
@@ -177,8 +179,10 @@ __global__ __launch_bounds__(kAbWaves * 64) void apt_absorb_pv16_kernel(ItemPara
 template <int DT, int NF, int CW> int launch_cw(const ItemParams& p, hipStream_t st) {
     using C = PvTile<DT, NF, CW>;
     const int n_cslices = (p.d + CW - 1) / CW;
-    hipLaunchKernelGGL((apt_absorb_pv16_kernel<DT, NF, CW>), dim3((unsigned)(p.ab_units * n_cslices)), dim3(kAbWaves * 64),
-                       C::S * C::kStage + kPvBlkBytes, st, p, n_cslices);
+    const dim3 grid((unsigned)(p.ab_units * n_cslices)), block(kAbWaves * 64);
+    constexpr int kLds = C::S * C::kStage + kPvBlkBytes;
+    if (p.ab_past & APT_AB_PAST_SUMS) hipLaunchKernelGGL((apt_absorb_pv16_kernel<DT, NF, CW, true>), grid, block, kLds, st, p, n_cslices);
+    else hipLaunchKernelGGL((apt_absorb_pv16_kernel<DT, NF, CW, false>), grid, block, kLds, st, p, n_cslices);
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
 }
 template <int DT, int NF> int launch_nf(const ItemParams& p, int n_cus, hipStream_t st) {
@@ -196,10 +200,13 @@ template <int DT> int launch(const ItemParams& p, int n_cus, hipStream_t st) {
     default: return launch_nf<DT, 8>(p, n_cus, st);
     }
 }
+template <int DT, int NF, int CW> bool setup_cw() {
+    return apt_raise_lds_limit(apt_absorb_pv16_kernel<DT, NF, CW, false>) && apt_raise_lds_limit(apt_absorb_pv16_kernel<DT, NF, CW, true>);
+}
 template <int DT, int NF> bool setup_nf() {
     if constexpr (PvTile<DT, NF, 512>::kFits && !PvTile<DT, NF, 256>::kTwo)
-        if (!apt_raise_lds_limit(apt_absorb_pv16_kernel<DT, NF, 512>)) return false;
-    return apt_raise_lds_limit(apt_absorb_pv16_kernel<DT, NF, 256>);
+        if (!setup_cw<DT, NF, 512>()) return false;
+    return setup_cw<DT, NF, 256>();
 }
 template <int DT> bool setup() {
     return setup_nf<DT, 2>() && setup_nf<DT, 3>() && setup_nf<DT, 4>() && setup_nf<DT, 5>() && setup_nf<DT, 6>() && setup_nf<DT, 8>();

@@ -43,6 +43,7 @@ struct ItemParams {
     int32_t ab_group;                 // ranges per unit
     int32_t ab_os;                    // slices of d_model in the output partials
     int32_t ab_rows;                  // 16-bit inputs: rows per part of the weights (heads padded to whole fragments)
+    int32_t ab_past;                  // 16-bit inputs: what is read past the caches (APT_AB_PAST_*)
 };
 
 namespace {

@@ -616,7 +616,7 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     p.item_base = 0;
     p.ab_ks = 0;
     p.ab_tiles_off = rs.s.hidden_impl == APT_HIDDEN_ABSORBED ? pw[APT_PW_TILES_OFF] : 0;
-    p.ab_tiles = p.ab_units = p.ab_units_off = p.ab_group = p.ab_rows = p.ab_os = 0;
+    p.ab_tiles = p.ab_units = p.ab_units_off = p.ab_group = p.ab_rows = p.ab_os = p.ab_past = 0;
     if (p.ab_tiles_off) {
         p.ab_tiles = pw[p.ab_tiles_off];
         p.ab_group = pw[p.ab_tiles_off + 1];
