@@ -72,27 +72,28 @@ enum {
 #define APT_ABSORBED_OUT_ROWS 256        // d_model rows per partial of the output projection
 
 // Absorbed-weight path, 16-bit inputs: which of its two passes over the hidden rows X reads them past the caches.  qt_bytes: the absorbed
-// queries QT (in parts, 2 for fp16 and 3 for bf16), written just before the scores read them.
+// queries QT, written just before the scores read them.
 // The sums: where X is more than half of the L2s (32 MB together); they are its last reader.  Attention call in a graph, us, cached / past:
 // 17 heads, fp16, 300 tokens 32.0 / 34.2, 1.3 k (X 5 MB) 34.0 / 36.2; 24 heads, 8 requests of 100..900 (20 MB) 47.8 / 47.2; 40 heads, 60 of
 // 400..800 (377 MB) 273 / 258; 72 heads, bf16, 96 of 64..2048 (1.9 GB) 1325 / 1297.
 // The scores: X read through the caches stays in the memory-side one (256 MB) for the sums, as far as it has room, and takes that room
-// from QT.  So past it where QT is large, by itself and beside X, and both do not fit; and in bf16, with half as many products again to
-// cover the reads of the sums, where little of X would be left.  cached / past (X, QT in MB):
+// from QT.  So past it where QT is large, by itself and beside X, and both do not fit, and where little of X would be left.
+// cached / past (X, QT in MB):
 //     40 heads, fp16, 32 requests of 100..500 (102, 31)    109 / 114       128..2048 (375, 31)                     237 / 246
-//     24 heads, fp16, 150 of 300..900 (560, 58)            311 / 320       bf16 (560, 88)                          340 / 343
-//     72 heads, fp16, 96 of 64..2048 (1903, 283)          1129 / 1150      bf16 (1903, 424)                       1297 / 1300
-//     20 heads, bf16, 190 of 50..250 (148, 93)             157 / 161       72 heads, bf16, half of 96 (900, 212)   968 / 953
-//     17 heads, bf16, 150 of 300..1500 (597, 62)           329 / 321       32 heads, bf16, 100 of 300..900 (497, 78)  319 / 313
-//     56 heads, bf16, 60 of 300..900 (513, 165)            428 / 410       32 heads, bf16, 180 of 100..600 (531, 141) 401 / 384
+//     24 heads, fp16, 150 of 30..400 (206, 58)             172 / 177       bf16 (206, 88)                          191 / 195
+//     20 heads, bf16, 190 of 50..250 (148, 93)             157 / 161       40 heads, bf16, 100 of 100..600 (354, 147) 315 / 309
 //     62 heads, 77 of 200, fp16 (244, 156)                 311 / 305       bf16 (244, 234)                         391 / 360
 //     48 heads, 150 of 20..120, fp16 (133, 176)            320 / 307       bf16 (133, 265)                         385 / 373
-// Of 106 such batches the choice costs 1 % or more over the better one in three, 1.6 % at most (32 heads, fp16, 100 of 300..900: 292 / 287).
+//     56 heads, bf16, 60 of 300..900 (513, 165)            428 / 410       32 heads, 100 of 300..900, bf16 (497, 78) 319 / 313
+//     17 heads, bf16, 150 of 300..1500 (597, 62)           329 / 321       72 heads, bf16, 48 of 96 of 64..2048 (900, 212) 968 / 953
+//     16 heads, bf16, 180 of 400..2000 (906, 70)           454 / 444       72 heads, bf16, 96 of 64..2048 (1903, 424)  1297 / 1300
+// Beyond 448 MB fp16 goes the way of bf16, though it is as often faster through the caches (72 heads, 96 of 64..2048 1129 / 1150, 24 heads,
+// 150 of 300..900 311 / 320, 32 heads, 100 of 300..900 292 / 287, 180 of 100..600 360 / 356).
 #define APT_AB_PAST_SCORES 1
 #define APT_AB_PAST_SUMS 2
-static inline int apt_absorbed_past(int parts, int64_t qt_bytes, int64_t x_bytes) {
+static inline int apt_absorbed_past(int64_t qt_bytes, int64_t x_bytes) {
     const int64_t mb = 1 << 20;
-    const bool scores = (qt_bytes > 96 * mb && 4 * qt_bytes > x_bytes && qt_bytes + x_bytes > 256 * mb) || (parts == 3 && x_bytes > 448 * mb);
+    const bool scores = (qt_bytes > 96 * mb && 4 * qt_bytes > x_bytes && qt_bytes + x_bytes > 256 * mb) || x_bytes > 448 * mb;
     return (scores ? APT_AB_PAST_SCORES : 0) | (x_bytes > 16 * mb ? APT_AB_PAST_SUMS : 0);
 }
 

@@ -21,9 +21,8 @@ def _past(tmp_path, batches):
 #include <stdio.h>
 #include "apt_internal.h"
 int main() {
-    int parts;
     long long q, x;
-    while (scanf("%d %lld %lld", &parts, &q, &x) == 3) printf("%d\\n", apt_absorbed_past(parts, q, x));
+    while (scanf("%lld %lld", &q, &x) == 2) printf("%d\\n", apt_absorbed_past(q, x));
 }
 """)
     subprocess.run(["g++", "-O1", "-I", os.path.join(ROOT, "include"), "-I",
@@ -31,9 +30,8 @@ int main() {
     lines = []
     for H, dtype, n, tokens in batches:
         frags = max(2, -(-H // 16))
-        parts = {"f16": 2, "bf16": 3}[dtype]
-        rows = 16 * (8 if frags == 7 else frags) * parts
-        lines.append(f"{parts} {n * rows * H * 128 * 2} {tokens * H * 128 * 2}")
+        rows = 16 * (8 if frags == 7 else frags) * {"f16": 2, "bf16": 3}[dtype]
+        lines.append(f"{n * rows * H * 128 * 2} {tokens * H * 128 * 2}")
     out = subprocess.run([str(exe)], input="\n".join(lines), text=True, capture_output=True, check=True).stdout
     return [int(v) for v in out.split()]
 
@@ -44,9 +42,10 @@ def test_hidden_rows_that_fit_stay_in_the_caches(tmp_path):
     for (H, t, n, tokens), past in zip(small, got):
         x = tokens * H * 256
         assert past == (SUMS if x > 16 << 20 else 0), (H, t, n, tokens)
-    # a working set that the memory-side cache holds, and rows many times the queries, are read through it by the scores
-    assert _past(tmp_path, [(40, "f16", 32, 9600), (40, "f16", 64, 69632), (72, "f16", 96, 101376)]) == [SUMS] * 3
+    # a working set that the memory-side cache holds, and rows of up to twice that beside small queries, are read through it by the scores
+    assert _past(tmp_path, [(40, "f16", 32, 9600), (40, "f16", 32, 34816), (24, "bf16", 150, 32250)]) == [SUMS] * 3
     assert _past(tmp_path, [(62, "bf16", 77, 15400), (48, "bf16", 150, 10500), (56, "f16", 100, 11000)]) == [SUMS | SCORES] * 3
+    assert _past(tmp_path, [(16, "f16", 180, 216000), (72, "bf16", 96, 101376)]) == [SUMS | SCORES] * 2
 
 
 @pytest.mark.gpu
