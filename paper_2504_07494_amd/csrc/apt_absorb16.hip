@@ -15,7 +15,7 @@ namespace {
 // together on one XCD (workgroup g runs on XCD g % 8), as their stores lie in the same lines.  The queries of all the
 // requests are put into LDS first: loads between the stores would wait for them, the two share a counter.
 // Bound by the write of QT, R * parts * 2 bytes per k and request (a fill of its size takes 62 us), and by each workgroup's
-// start, W_K and the queries behind their indexes.  (Stored past the caches or not: ab_q_streamed.)  72 heads, bf16, 96 requests at d_model 9216 (382 MB, 441 counted at
+// start, W_K and the queries behind their indexes.  72 heads, bf16, 96 requests at d_model 9216 (382 MB, 441 counted at
 // memory): 195 us with queries from memory, 187 in this order, 155 through LDS, 131 with 128 requests to a workgroup.
 //
 // 128 requests where that leaves two workgroups per CU (short contexts, 64 / 128, the whole call: 24 heads, 128 requests 113.1 /
@@ -23,17 +23,6 @@ namespace {
 __host__ __device__ inline int ab_q_reqs(const ItemParams& p) { return (p.d / 32 + 3) / 4 * p.H >= 512 ? 128 : 64; }
 __host__ __device__ inline int ab_q_z_blocks(const ItemParams& p) { return (p.n_hid_req + ab_q_reqs(p) - 1) / ab_q_reqs(p); }
 inline int ab_q_groups(const ItemParams& p) { return (p.d / 32 + 3) / 4 * ((p.H + 7) / 8) * ab_q_z_blocks(p); }
-
-// Whether QT is stored past the caches: where it is larger than the memory-side cache (256 MB), or would be pushed out by the hidden rows
-// that the scores read meanwhile, 2.4 times its size or more.  Whole call, us, cached / past the caches: 62 heads, bf16, 77 requests (QT
-// 235 MB) of 200 tokens (1.04 times) 363 / 374, 300 (1.6) 434 / 444, 420 (2.2) 486 / 487, 700 (3.6) 617 / 600; 170 requests (520 MB) of
-// 60..160 tokens 714 / 667; 40 heads, fp16, 60 requests (59 MB) of 100..200 tokens (1.6) 134 / 136, 300..500 (4.2) 197 / 192; 72 heads,
-// bf16, 96 requests of 64..2048 (4.4) 1277 / 1222.
-template <int DT, int NF> __device__ inline bool ab_q_streamed(const ItemParams& p) {
-    using C = AbTile<DT, NF>;
-    const int64_t rows = (int64_t)p.n_hid_req * C::R * C::NS;            // QT is as large as this many hidden rows
-    return rows * p.d * 2 > (int64_t)256 << 20 || 5 * p.ab_tokens > 12 * rows;
-}
 
 template <int HD> __device__ inline int ab_q_swz(int row) { return HD == 128 ? row & 15 : (row >> 1) & 7; }
 
@@ -63,7 +52,6 @@ __device__ __forceinline__ void absorb_q16(const ItemParams& p, int block, char*
     }
     __syncthreads();
     if (kb * 32 >= p.d) return;
-    const bool streamed = ab_q_streamed<DT, NF>(p);
     const int k8 = kb * 4 + qd;                          // this lane's unit of 8 k
     const int kt = k8 / (C::KT / 8), c = (k8 % (C::KT / 8)) ^ ab_swz<C::KT>(h);
     for (int row0 = 0; row0 < n; row0 += 16) {
@@ -87,11 +75,7 @@ __device__ __forceinline__ void absorb_q16(const ItemParams& p, int block, char*
         if (row < n) {
             char* base = (char*)p.ab_qt + ((int64_t)hr * (p.d / C::KT) + kt) * C::kABytes + c * 16;
 #pragma unroll
-            for (int sp = 0; sp < NS; ++sp) {
-                uint4* at = (uint4*)(base + (sp * C::R + h) * C::kRow);
-                if (streamed) __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, part[sp]), (u32x4_t*)at);
-                else *at = part[sp];
-            }
+            for (int sp = 0; sp < NS; ++sp) *(uint4*)(base + (sp * C::R + h) * C::kRow) = part[sp];
         }
         if (kb == 0) {                                   // CB = scale * log2(e) * q . b_K
             float s = 0.f;
