@@ -248,11 +248,12 @@ int apt_pack_weights(const apt_shape* s, const void* W_K, const void* W_V, void*
 
 /*
  * The decode attention step for one layer (Eq. 1-3 over both cache kinds).
- *   plan_host / plan_dev   the blob from apt_plan and its device copy.  One word of the device
- *               copy (a ticket counter that hands out KV-kind items inside the launch, or tells
- *               which workgroup is the last) is written by the item kernel and 0 again after the call, so two calls that
- *               share one plan_dev must be ordered on one stream (calls for successive layers
- *               are); everything else in it is read-only
+ *   plan_host / plan_dev   the blob from apt_plan and its device copy.  Nine words of the device
+ *               copy (ticket counters, which hand out KV-kind items inside a launch or tell which
+ *               workgroups are the last to write their partials) are written by the kernels and 0 again after the
+ *               call, so two calls that share one plan_dev must be ordered on one stream (calls for
+ *               successive layers are): of two small calls at once neither may find its last
+ *               workgroup, and `out` is then not written.  Everything else in it is read-only
  *   q, k_pages, v_pages, hidden_pages, b_K, b_V, block_tables, out   device, see layout
  *   W_K, W_V    device, raw [d_in][d_out]; not read by the MFMA hidden kernel
  *               (may be NULL when the resolved hidden_impl is MFMA or no request is
@@ -264,7 +265,7 @@ int apt_pack_weights(const apt_shape* s, const void* W_K, const void* W_V, void*
  *               merge kernel combines; contents are undefined afterwards
  * Enqueued on `stream`:
  *   - the item kernel (hidden-kind and KV-kind items in the same launch) and the merge kernel; small calls without packed
- *     weights: the item kernel alone, whose last workgroup merges;
+ *     weights: the item kernel alone, whose last workgroups merge;
  *   - KV-kind requests alone, every context a single range, or (kv_chunk = 0 only) no more
  *     (request, head) pairs than compute units and contexts short enough for it to pay: one kernel,
  *     a workgroup per pair for its whole context, which writes `out` and no partials (the workspace is

@@ -7,9 +7,9 @@
 
 struct ItemParams {
     const int32_t* plan;          // device blob
-    int32_t* kv_ticket;           // device blob word APT_PW_KV_TICKET: next KV-kind item of the persistent launch, items done of one that merges
+    int32_t* kv_ticket;           // device blob word APT_PW_KV_TICKET: next KV-kind item of the persistent launch, items done of one that merges (merge_by_last)
     char* out;                    // a launch that merges by itself (merge_by_last): the output and its element type, else NULL
-    int32_t out_dtype;
+    int32_t out_dtype, most_ranges;   // most_ranges: of a request
     const char* q;
     const char* k_pages;
     const char* v_pages;

@@ -21,8 +21,9 @@ enum {
     APT_PW_HTOK_HI = 13,
     APT_PW_HEAD_DIM = 14,
     APT_PW_WORDS = 15,      // total words of the blob
-    APT_PW_QUEUE0 = 16,     // 9 words: start of each hidden-kind queue (in items), then the end
-    APT_PW_KV_TICKET = 25,  // device copy only: next KV-kind item to hand out (0 between launches)
+    APT_PW_QUEUE0 = 16,     // 9 words: start of each hidden-kind queue (in items), then the end; KV-kind requests alone: 0, in the
+                            // device copy the first 8 count the items done of a launch that merges (0 between launches)
+    APT_PW_KV_TICKET = 25,  // device copy only: next KV-kind item to hand out, or the items done of a launch that merges (0 between launches)
     APT_PW_D_MODEL = 26,    // the shape the plan was made for
     APT_PW_BLOCK_SIZE = 27,
     APT_PW_MAX_BLOCKS = 28,
@@ -165,6 +166,29 @@ static inline apt_ws_layout apt_ws_sections(int64_t n_partials, int H, int hd, i
     }
     L.total = end;
     return L;
+}
+
+// Whether the last workgroups of the item kernel merge the partials (merge_by_last): KV-kind requests alone, a range to a workgroup of 1024
+// threads (of 256 where the caller fixes kv_chunk), or raw weights, 256 threads.  Four channels a thread, their ranges asked for at once
+// (256 threads: in two rounds), no more partials than when one workgroup merged them all, and not so many workgroups that they wait for
+// each other at a ticket, 10 ns each.  Up to there the call takes the GPU no longer than with a merge kernel, and the host a launch less.
+// Attention call in a graph, us, a kernel of its own / by the last workgroups, and in brackets steps of one layer back to back, planned,
+// copied and launched from Python:
+//     KV-kind, fp16, 1024 threads, heads of 128: 8 heads, 1100 tokens (24 ranges) 11.4 / 10.5, 24 heads, 2048 (96) 12.9 / 11.8, 40 heads, 1237
+//     (120) 12.3 / 11.7 (18.5 / 15.8), 20 heads, 2 of 900..1000 (80) 12.3 / 11.1, 10 heads, 6 of 900 (120) 12.4 / 11.8; beyond: 64 heads,
+//     1300 (192) 13.6 / 13.3, 20 heads, 3 of 2048 (240) 16.0 / 16.5, 8 heads, 2 of 2300 in five ranges each 12.7 / 12.7, 12 heads, 4096
+//     in eight 12.4 / 13.2; heads of 64: 24 heads, 2048 (96) 9.5 / 8.9, 40 heads, 2048 (160) 10.0 / 10.1; beyond: 30 heads, 2 of 2000
+//     (240) 11.1 / 11.9
+//     256 threads: fp32, 4 heads of 64, 4 of 16..128 tokens 10.2 / 9.3 (18.6 / 15.5), fp16, 16 heads of 64, 250 tokens 13.6 / 13.1; beyond,
+//     one workgroup for all: 8 heads, 6 of 60 (more than four channels a thread) 10.4 / 11.9, 8 heads, 4 of 200 (128 ranges) 10.7 / 12.0, one
+//     head, 2048 tokens in 64 ranges 14.7 / 15.6
+#define APT_MERGE_GROUPS 8               // KV-kind requests alone: parts of the heads, each merged by a workgroup
+#define APT_MERGE_RANGES_MANY 4          // ranges that a thread of 1024 asks for at once
+#define APT_MERGE_RANGES 8               // and one of 256
+static inline bool apt_items_merge(bool kv_alone, int threads, int64_t batch, int heads, int head_dim, int64_t n_items, int most_ranges) {
+    const int part = kv_alone ? (heads + APT_MERGE_GROUPS - 1) / APT_MERGE_GROUPS : heads;
+    return batch * part * head_dim <= 4 * threads && n_items <= 160 && n_items * head_dim <= 16 * threads &&
+           most_ranges <= (threads == 1024 ? APT_MERGE_RANGES_MANY : 2 * APT_MERGE_RANGES);
 }
 
 // Hidden-kind item of place g of a one-workgroup-per-item launch, -1 for none; queue = the nine APT_PW_QUEUE0 words of the

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(NW * 64) void apt_items_kernel(ItemParams p) {
     if (item >= p.n_items) return;
     const int4 it = ((const int4*)(p.plan + p.items_off))[item];
     kv_item_through<DT, HD, NW>(p, it.x, it.y, it.z, it.w, lds);
-    merge_by_last<DT, HD>(p, lds);
+    merge_by_last<DT, HD, NW == 16 ? APT_MERGE_RANGES_MANY : APT_MERGE_RANGES, true>(p, it.y, lds);
 }
 
 // Whole contexts, one workgroup per request and head, straight to the output: no partials and no merge (see takes_whole).
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(kThreads) void apt_merge_kernel(MergeParams p, char
     if (gid == 0) *p.kv_ticket = 0;         // the item kernel of this call is done: ready for the next call
     if (4 * gid >= (int64_t)p.B * p.H * HD) return;
     const int64_t pair = 4 * gid / HD;
-    store_out4<ODT>(out, 4 * gid, merged4<false>(p, (int)(pair / p.H), (int)(pair % p.H), (int)(4 * gid % HD), HD));
+    store_out4<ODT>(out, 4 * gid, merged4<false, 8, false>(p, merge_of(p, (int)pair), (int)(4 * gid % HD), HD));
 }
 
 // ---------------------------------------------------------------------------------
@@ -304,6 +304,13 @@ template <int DT, int HD> int launch_items(const ItemParams& p, int most16, hipS
     return hipGetLastError() == hipSuccess ? APT_OK : APT_EHIP;
 }
 
+// Whether the last workgroups of the item kernel merge the partials, by apt_items_merge.  Packed weights and the absorbed-weight path have a
+// launch of their own that ends the call.
+bool merges_by_itself(const ItemParams& p, int hd, int himpl, int most16) {
+    if (p.n_hidden_items > 0 && himpl != APT_HIDDEN_VALU) return false;
+    const bool alone = p.n_hidden_items == 0;
+    return apt_items_merge(alone, alone && p.n_items <= most16 ? 1024 : kThreads, p.B, p.H, hd, p.n_items, p.most_ranges);
+}
 // Batches of KV-kind requests that need no partials.  Every context is one range of the plan; or the ranges are the planner's own choice
 // (most16 > 0), there are no more (request, head) pairs than CUs, and the contexts alone do not take longer than ranges of them on
 // more CUs and the merge would, by the times that both took on 296 batches of 1 to 30 requests and 8 to 72 heads, equal and ragged
@@ -328,16 +335,6 @@ bool takes_whole(const ItemParams& p, const int32_t* pw, int row_bytes, int most
     const double whole = 3.0 + kb * (double)longest / 68.0 + all / 13.4;
     const double ranges = p.n_items <= most16 ? 6.4 + kb * (double)std::min<int64_t>(longest, p.kv_chunk) / 90.0 + all / 11.0 : 5.5 + all / 6.6;
     return whole <= ranges;
-}
-// Whether the last workgroup of the item kernel merges the partials (merge_by_last): up to 16 of their values for each of its threads.
-// It saves a launch of 2.6 us where the host is the bound, and costs the GPU nothing up to there (attention call back to back,
-// us, a kernel of its own / by the last workgroup: 256 threads, 2.5 k values 12.0 / 9.7, 8 k 11.4 / 12.2, 17 k 22.8 / 26.3; 1024 threads,
-// 9 k 10.5 / 10.7, 10 k 11.0 / 11.0, 15 k 11.5 / 12.1, 28 k 13.0 / 18.1).  One request of 1237 tokens, 40 heads, append and attention,
-// steps of one layer 22.9 -> 20.2 us; the fp32 layer of 4 heads, 4 requests 17.4 -> 14.4.
-bool merges_by_itself(const ItemParams& p, const int32_t* pw, int hd, int himpl, int most16) {
-    if (p.n_hidden_items > 0 && himpl != APT_HIDDEN_VALU) return false;
-    const int threads = p.n_hidden_items == 0 && p.n_items <= most16 ? 1024 : kThreads;
-    return (int64_t)pw[APT_PW_NPARTIALS] * p.H * hd <= 16 * threads;
 }
 template <int DT, int HD, int NW, int ODT> void launch_whole_nw(const ItemParams& p, char* out, int in_items, hipStream_t st) {
     hipLaunchKernelGGL((apt_whole_kernel<DT, HD, NW, ODT>), dim3(p.B * p.H), dim3(NW * 64), (KvItem<DT, HD, NW>::kLds), st, p, out, in_items);
@@ -634,9 +631,11 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     const int dt = rs.s.dtype, hd = rs.s.head_dim, hi = rs.s.hidden_impl;
     if (ev_begin && hipEventRecord((hipEvent_t)ev_begin, st) != hipSuccess) return APT_EHIP;
     const int most16 = rs.kv_auto ? ds->n_wg : 0;
+    const int32_t* ranges = pw + APT_PW_HEADER + APT_PA_SPLIT_COUNT * B;
+    p.most_ranges = *std::max_element(ranges, ranges + std::min(B, 256));       // more requests never merge by themselves
+    const bool merges = merges_by_itself(p, hd, hi, most16);
     const bool whole = takes_whole(p, pw, hd * rs.elem_bytes, most16);
-    // the last workgroup of the item kernel merges, or a kernel of its own
-    p.out = !whole && merges_by_itself(p, pw, hd, hi, most16) ? (char*)out : nullptr;
+    p.out = merges && !whole ? (char*)out : nullptr;
     p.out_dtype = rs.s.out_dtype;
     auto launch = [&](auto dtype, auto head_dim) {
         constexpr int DT = decltype(dtype)::value, HD = decltype(head_dim)::value;

@@ -246,7 +246,7 @@ __global__ __launch_bounds__(kThreads, 2) void apt_items_raw_kernel(ItemParams p
         const int4 it = items[i];
         kv_item_through<DT, HD>(p, it.x, it.y, it.z, it.w, lds);
     }
-    merge_by_last<DT, HD>(p, lds);
+    merge_by_last<DT, HD, APT_MERGE_RANGES, false>(p, 0, lds);
 }
 
 template <int DT, int HD> int launch(const ItemParams& p, hipStream_t st) {

@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kThreads) void apt_items_f32_kernel(ItemParams p, i
         const int4 it = items[i];
         kv_item_through<0, HD>(p, it.x, it.y, it.z, it.w, lds);
     }
-    merge_by_last<0, HD>(p, lds);
+    merge_by_last<0, HD, APT_MERGE_RANGES, false>(p, 0, lds);
 }
 
 template <int HD> int launch(const ItemParams& p, hipStream_t st) {
