@@ -313,15 +313,15 @@ bool merges_by_itself(const ItemParams& p, int hd, int himpl, int most16) {
 }
 // Batches of KV-kind requests that need no partials.  Every context is one range of the plan; or the ranges are the planner's own choice
 // (most16 > 0), there are no more (request, head) pairs than CUs, and the contexts alone do not take longer than ranges of them on
-// more CUs and the merge would, by the times that both took on 296 batches of 1 to 30 requests and 8 to 72 heads, equal and ragged
-// lengths of 250 to 2048 tokens, rows of 128, 256 and 512 bytes (us; the longest context in KB, all of them in MB; up to one range per
-// CU: 16 waves a range, else four).  The choice took 0.4 % longer than the better of the two on average; by the longest context at
-// 57 KB/us alone it was 2.9 %, 36 % at most (attention call, fp16, ranges and merge / whole: 40 heads, 3 requests of up to 1743 tokens
-// 17.7 / 22.8; 12 heads of 64, 6 of up to 1949 10.5 / 13.8; 40 heads, one of 500 10.2 / 7.5, of 850 10.8 / 10.4, of 1250 11.7 / 14.5;
-// 72 heads, 3 of 2048 41.4 / 35.2; 32 heads, 8 of 1000 24.0 / 20.9).
-// GPU time decides.  Where the host is the bound, ranges cost it a launch more: one request of 1237 tokens, 40 heads, attention calls back to
-// back 12.3 / 15.1 us, waited-for steps 39.5 / 43.1, but steps of one layer back to back 23.3 / 20.2 (planned, copied and launched from Python).
-bool takes_whole(const ItemParams& p, const int32_t* pw, int row_bytes, int most16) {
+// more CUs and the merge would.  GPU time decides, by the times that both took (us; the longest context in KB, all of them in MB):
+//   - with a merge kernel, on 296 batches of 1 to 30 requests and 8 to 72 heads, equal and ragged lengths of 250 to 2048 tokens, rows of
+//     128, 256 and 512 bytes (up to one range per CU: 16 waves a range, else four).  The choice took 0.4 % longer than the better of the
+//     two on average; by the longest context at 57 KB/us alone it was 2.9 %, 36 % at most (attention call, fp16, ranges and merge /
+//     whole: 40 heads, 3 requests of up to 1743 tokens 17.7 / 22.8; 72 heads, 3 of 2048 41.4 / 35.2; 32 heads, 8 of 1000 24.0 / 20.9);
+//   - with a merge by the last workgroups (merges), on 260 batches of 1 to 12 requests and 1 to 72 heads, in a graph: 0.2 % longer than
+//     the better one, 6 % at most; by the line above 2.6 % and 41 % (2 heads of 64, bf16, 6 requests of 739..1269 tokens 7.9 / 11.1; one
+//     head of 64, 8 of 789..1282 7.8 / 10.9; 9 heads, bf16, 843 tokens 10.4 / 12.6; 32 heads, 563 tokens 11.1 / 9.8).
+bool takes_whole(const ItemParams& p, const int32_t* pw, int row_bytes, int most16, bool merges) {
     if (p.n_hidden_items > 0) return false;
     if (pw[APT_PW_NPARTIALS] == p.B) return true;
     if ((int64_t)p.B * p.H > most16 || p.max_blocks > 16 * APT_KV_MAX_PAGES_PER_WAVE) return false;
@@ -332,9 +332,9 @@ bool takes_whole(const ItemParams& p, const int32_t* pw, int row_bytes, int most
         tokens += lens[r];
     }
     const double kb = 2e-3 * row_bytes, all = 1e-3 * kb * (double)tokens * p.H;
-    const double whole = 3.0 + kb * (double)longest / 68.0 + all / 13.4;
-    const double ranges = p.n_items <= most16 ? 6.4 + kb * (double)std::min<int64_t>(longest, p.kv_chunk) / 90.0 + all / 11.0 : 5.5 + all / 6.6;
-    return whole <= ranges;
+    const double context = kb * (double)longest, range = kb * (double)std::min<int64_t>(longest, p.kv_chunk);
+    if (merges) return 4.2 + context / 58.0 + all / 16.9 <= 5.5 + range / 63.5 + all / 12.3;
+    return 3.0 + context / 68.0 + all / 13.4 <= (p.n_items <= most16 ? 6.4 + range / 90.0 + all / 11.0 : 5.5 + all / 6.6);
 }
 template <int DT, int HD, int NW, int ODT> void launch_whole_nw(const ItemParams& p, char* out, int in_items, hipStream_t st) {
     hipLaunchKernelGGL((apt_whole_kernel<DT, HD, NW, ODT>), dim3(p.B * p.H), dim3(NW * 64), (KvItem<DT, HD, NW>::kLds), st, p, out, in_items);
@@ -634,7 +634,7 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     const int32_t* ranges = pw + APT_PW_HEADER + APT_PA_SPLIT_COUNT * B;
     p.most_ranges = *std::max_element(ranges, ranges + std::min(B, 256));       // more requests never merge by themselves
     const bool merges = merges_by_itself(p, hd, hi, most16);
-    const bool whole = takes_whole(p, pw, hd * rs.elem_bytes, most16);
+    const bool whole = takes_whole(p, pw, hd * rs.elem_bytes, most16, merges);
     p.out = merges && !whole ? (char*)out : nullptr;
     p.out_dtype = rs.s.out_dtype;
     auto launch = [&](auto dtype, auto head_dim) {

@@ -115,3 +115,24 @@ int main() {
         if merges:
             assert batch * (-(-heads // 8) if alone else heads) * hd // 4 <= threads and items <= 160
             assert items * hd <= 16 * threads and ranges <= (4 if threads == 1024 else 16)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,hd,H,lens,whole", [("bf16", 64, 2, [1269, 1017, 739, 996, 1229, 1065], False), ("bf16", 128, 9, [843], False),
+                                                   ("f16", 64, 1, [1282, 789, 868, 991], False), ("f16", 128, 32, [563], True),
+                                                   ("f32", 64, 9, [371, 586, 340, 593, 569], True)])
+def test_whole_contexts_beside_a_merge_by_the_last_workgroups(oracle, dtype, hd, H, lens, whole):
+    """Whole contexts only where they are faster than ranges whose partials the last workgroups merge (they leave the workspace as it was)."""
+    from paper_2504_07494_amd.harness import DecodeRunner
+    print(f"[case] {dtype} hd={hd} heads={H} lens={lens} whole={whole}", flush=True)
+    cfg = wl.small_config(name="mergewhole", dtype=dtype, d_model=hd * H, n_heads=H, head_dim=hd, block_size=16, batch=len(lens),
+                          len_lo=1, len_hi=max(lens), hidden_ratio=0.0, permute_pages=True)
+    batch = wl.make_batch(cfg, np.array(lens, dtype=np.int32), np.full(len(lens), KV, dtype=np.uint8))
+    layer = wl.make_layer(batch)
+    rn = DecodeRunner(batch)
+    rn.out.fill_(float("nan"))
+    rn.workspace.fill_(255)
+    rn.run(rn.upload(layer))
+    got = rn.out_f64()
+    assert bool((rn.workspace == 255).all()) == whole
+    assert np.max(np.abs(got - oracle_attn(oracle, batch, layer).reshape(got.shape))) <= 1e-4
