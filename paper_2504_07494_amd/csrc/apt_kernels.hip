@@ -190,8 +190,12 @@ __global__ __launch_bounds__(kThreads) void apt_append_kernel(CacheParams p) {
 // as much 50 us, non-temporal 47): 85 us by request, a store behind each load, cached; 80 non-temporal; 73 with ten units in
 // flight and four tokens to a workgroup instead of eight; 58 by group.  Eight tokens by group 60, cached accesses 63; runs of 4
 // tokens of one head instead of whole rows 58, of 8 tokens 64, of 16 tokens 74.
+// (Those are passes over the same buffers.)  Buffers that no pass of the last gigabytes has touched, as a prefill has them, by request with
+// a store behind each load / as it is: this shape 81 / 52, d_model 2048 35 / 22, 7168 114 / 73, 9216 148 / 95 (14 and 18 units a lane, in
+// two rounds), a KV-kind request of 500 tokens, d_model 5120 (20 MB) 32 / 5.2, 4 requests at d_model 9216 (38 MB) 48 / 11.
 constexpr int kWriteTokens = 4;
 constexpr int kWriteUnits = 10;
+constexpr int kMaxNewTokens = 524280;                // of a request and call, as the header states
 __global__ __launch_bounds__(kWriteTokens * 64) void apt_write_kernel(CacheParams p, const int32_t* new_offsets) {
     const int t = blockIdx.x * kWriteTokens + (threadIdx.x >> 6), lane = threadIdx.x & 63, mat = blockIdx.z;
     const int row_units = p.d * p.eb / 16;
@@ -496,7 +500,7 @@ extern "C" int apt_cache_write(const apt_shape* s, int B, const int32_t* new_off
     if (!aligned16(x_new) || !aligned16(k_new) || !aligned16(v_new) || !aligned16(k_pages) || !aligned16(v_pages) ||
         !aligned16(hidden_pages))
         return APT_EINVAL;
-    if ((max_new_tokens - 1) / 8 >= 65535) return APT_ERANGE;
+    if (max_new_tokens > kMaxNewTokens) return APT_ERANGE;
     int log2_bs = 0;
     while ((1 << log2_bs) < rs.s.block_size) ++log2_bs;
     const CacheParams p = {(const char*)x_new, (const char*)k_new, (const char*)v_new, (char*)k_pages, (char*)v_pages, (char*)hidden_pages,

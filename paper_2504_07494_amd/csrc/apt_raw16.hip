@@ -18,8 +18,8 @@ namespace {
 //
 // Tiles: at most 256 tokens x 128 channels (HD 64) or 128 x 256 (HD 128), 128 accumulator registers per wave, 24 KB
 // per k-tile and three stages, so that two workgroups share a CU and one's barriers and epilogue are covered by the
-// other's MFMAs.  Short ranges take the 192-, 128- or 64-token variant: less padding, and with the LDS this frees more
-// stages in flight.  (Ranges of 129 to 192 tokens in 192 instead of 256 rows, whole step: 25 heads, 25 requests of 64..562 tokens 139.5 ->
+// other's MFMAs.  Short ranges take the 192-, 128- or 64-token variant: less padding, and in the two smaller ones
+// with the LDS this frees more stages in flight.  (Ranges of 129 to 192 tokens in 192 instead of 256 rows, whole step: 25 heads, 25 requests of 64..562 tokens 139.5 ->
 // 132 us, 27 heads, 27 of 145..1024 162 -> 153, 32 heads, 24 of 123..1006 beside as many KV-kind ones 248 -> 242.)
 //
 // Bound by the matrix pipes and, like every dense product on this card, by board power: 48 requests of 32..1024 tokens
@@ -42,7 +42,7 @@ template <int HD, int T> struct RawTile {
 template <int HD> constexpr int raw_max_tile() { return 16384 / HD; }      // 256 or 128 tokens
 template <int HD> constexpr int raw_lds_bytes() {
     int m = 0;
-    if (HD == 64) m = RawTile<HD, raw_max_tile<HD>()>::kLds;
+    if constexpr (HD == 64) m = RawTile<HD, 256>::kLds > RawTile<HD, 192>::kLds ? RawTile<HD, 256>::kLds : RawTile<HD, 192>::kLds;
     m = m > RawTile<HD, 128>::kLds ? m : RawTile<HD, 128>::kLds;
     return m > RawTile<HD, 64>::kLds ? m : RawTile<HD, 64>::kLds;
 }
