@@ -19,8 +19,9 @@ extern "C" {
  * timing enabled; either may be NULL) are recorded on `stream` immediately before and
  * after the item kernel, so that a caller can time it apart from the merge.  Where a call has no
  * merge of its own the interval is the whole call: with APT_HIDDEN_ABSORBED and hidden-kind
- * requests, whose last kernel sums the output partials and merges in one, and for KV-kind
- * requests alone whose contexts go straight to the output.
+ * requests, whose last kernel sums the output partials and merges in one, for KV-kind
+ * requests alone whose contexts go straight to the output, and for small calls without packed
+ * weights, whose item kernel merges.
  */
 int apt_hybrid_decode_attn_timed(const apt_shape* s, const void* plan_host, void* plan_dev,
                                  const void* q, const void* k_pages, const void* v_pages, const void* hidden_pages,

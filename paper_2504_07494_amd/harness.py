@@ -107,7 +107,8 @@ class DecodeRunner:
 
     def run(self, dl: DeviceLayer, ev_begin=None, ev_end=None, out=None) -> torch.Tensor:
         """a2-a4: the attention call for one layer (asynchronous on the current stream).
-        ev_begin / ev_end: optional raw hipEvent_t handles recorded around the item kernel.
+        ev_begin / ev_end: optional raw hipEvent_t handles recorded around the item kernel (the whole call where there is
+        no merge kernel).
         out: optional output tensor of this layer (default: the runner's own buffer)."""
         out = self.out if out is None else out
         if ev_begin is None and ev_end is None:
