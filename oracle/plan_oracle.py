@@ -178,6 +178,32 @@ def shared_tiles_word(ctx_lens, cache_kind, n_heads, d_model, hidden_chunk):
     return sum(best[1][h] << 4 * x for x, h in enumerate(heads))
 
 
+def deals_heads(ctx_lens, cache_kind, n_heads, hidden_chunk, word, n_workgroups=256):
+    """Whether a launch with packed weights deals the heads that not every queue has to all XCDs.  word: the plan's word 31."""
+    more, per_queue = n_heads % N_QUEUES, n_workgroups // N_QUEUES
+    if more == 0 or (more > 4 and n_heads > N_QUEUES):
+        return False
+    lens = [int(n) for n, k in zip(ctx_lens, cache_kind) if int(k) == KIND_HIDDEN]
+    caps = [(word >> 4 * x) & 15 for x in range(N_QUEUES)]
+    blocks = 10 if hidden_chunk == 320 or max(caps) > 8 else 8
+    ranges, heads = sum(ceil_div(n, hidden_chunk) for n in lens), ceil_div(n_heads, N_QUEUES)
+    if ranges * heads >= 4 * per_queue:
+        return True
+    if n_heads > N_QUEUES and caps[0] != caps[more]:
+        return False
+    tiles = ranges
+    if caps[0]:
+        count, own = [0] * (blocks + 1), 0
+        for n in lens:
+            for t0 in range(0, n, hidden_chunk):
+                c = ceil_div(min(n - t0, hidden_chunk), 32)
+                own += n - t0 >= hidden_chunk == 32 * blocks
+                count[c] += not n - t0 >= hidden_chunk == 32 * blocks
+        tiles = own + sum(n for n, _ in tile_patterns(count, caps[0], blocks))
+    dealt = [tiles * (n_heads // N_QUEUES) + sum((t + q) % N_QUEUES == x for t in range(tiles) for q in range(more)) for x in range(N_QUEUES)]
+    return ceil_div(max(dealt), per_queue) < ceil_div(tiles * heads, per_queue)
+
+
 def plan(ctx_lens, cache_kind, n_heads, hidden_chunk, kv_chunk, hidden_item_per_head=True):
     """hidden_item_per_head=False: the absorbed-weight hidden path, whose items serve all heads of a
     range at once: one item (r, 0, t0, t1) per range of a hidden-kind request, by request and range,

@@ -12,7 +12,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libapt_hybrid.so")
 CALL = os.path.join(PKG, "_apt_call.so")
-SOURCES = ["apt_mfma_f16.hip", "apt_mfma_bf16.hip", "apt_kernels.hip", "apt_raw16.hip", "apt_raw32.hip", "apt_absorb16.hip", "apt_absorb_pv16.hip", "apt_absorb_out16.hip", "apt_plan.cpp", "apt_pool.cpp", "apt_sched.cpp"]
+SOURCES = ["apt_mfma_f16.hip", "apt_mfma_bf16.hip", "apt_mfma_dealt_f16.hip", "apt_mfma_dealt_bf16.hip",
+           "apt_kernels.hip", "apt_raw16.hip", "apt_raw32.hip", "apt_absorb16.hip", "apt_absorb_pv16.hip", "apt_absorb_out16.hip", "apt_plan.cpp", "apt_pool.cpp", "apt_sched.cpp"]
 
 
 def build(verbose: bool = False) -> str:

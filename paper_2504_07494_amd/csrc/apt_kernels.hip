@@ -401,7 +401,7 @@ int launch_items_impl(ItemParams& p, int himpl, int n_wg, int most16, hipStream_
         else return apt_launch_raw16(p, DT, HD, st);
     }
     if constexpr (DT != 0 && HD == 128) {
-        return apt_launch_mfma<DT>(p, n_wg, st);
+        return p.dealt ? apt_launch_mfma<DT, true>(p, n_wg, st) : apt_launch_mfma<DT, false>(p, n_wg, st);
     }
     return APT_ESHAPE;
 }
@@ -428,7 +428,7 @@ int device_setup(const DeviceState** out) {
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return APT_EHIP;
         ds.n_wg = cus >= 8 ? (cus / 8) * 8 : 8;
         // every kernel that can be launched with more than 64 KB of dynamic LDS
-        const bool ok = apt_setup_mfma<1>() && apt_setup_mfma<2>() &&
+        const bool ok = apt_setup_mfma<1, false>() && apt_setup_mfma<1, true>() && apt_setup_mfma<2, false>() && apt_setup_mfma<2, true>() &&
                         apt_setup_raw16() &&
                         apt_raise_lds_limit(apt_absorb_score_kernel<0>) && apt_raise_lds_limit(apt_absorb_pv_kernel<0>) &&
                         apt_setup_absorb_scores16() &&
@@ -657,6 +657,7 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     p.ab_tokens = hidden_tokens;
     p.n_hid_req = pw[APT_PW_NHIDREQ];
     p.wide_tiles = apt_pack_wide((uint32_t)pw[APT_PW_SHARED_TILES]);
+    p.dealt = 0;
     p.item_base = 0;
     p.ab_ks = 0;
     p.ab_tiles_off = rs.s.hidden_impl == APT_HIDDEN_ABSORBED ? pw[APT_PW_TILES_OFF] : 0;
@@ -673,6 +674,11 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     p.n_items = n_items; p.n_hidden_items = n_hidden;
     p.hidden_chunk = hidden_chunk; p.kv_chunk = kv_chunk; p.items_off = pw[APT_PW_ITEMS_OFF];
     p.scale_log2e = rs.s.softmax_scale * 1.4426950408889634f;
+    if (rs.s.hidden_impl == APT_HIDDEN_MFMA && n_hidden > 0) {
+        const int32_t *lens = pw + APT_PW_HEADER + APT_PA_CTX_LEN * B, *kinds = pw + APT_PW_HEADER + APT_PA_KIND * B;
+        const bool rows320 = hidden_chunk == APT_MFMA_HIDDEN_CHUNK || p.wide_tiles;
+        p.dealt = (rows320 ? apt_deals<10> : apt_deals<8>)(lens, kinds, B, p.H, hidden_chunk, (uint32_t)pw[APT_PW_SHARED_TILES], ds->n_wg);
+    }
     hipStream_t st = (hipStream_t)stream;
 
     const int dt = rs.s.dtype, hd = rs.s.head_dim, hi = rs.s.hidden_impl;

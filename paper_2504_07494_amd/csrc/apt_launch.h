@@ -7,13 +7,18 @@ template <typename K> static inline bool apt_raise_lds_limit(K kern) {
     return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
 }
 
-// apt_mfma.inc: hidden-kind items on packed weights (then the KV-kind items, in the same launch).  DT: 1 = fp16, 2 = bf16
-template <int DT> int apt_launch_mfma(const ItemParams& p, int n_wg, hipStream_t st);
-template <int DT> bool apt_setup_mfma();
-template <> int apt_launch_mfma<1>(const ItemParams& p, int n_wg, hipStream_t st);
-template <> int apt_launch_mfma<2>(const ItemParams& p, int n_wg, hipStream_t st);
-template <> bool apt_setup_mfma<1>();
-template <> bool apt_setup_mfma<2>();
+// apt_mfma.inc: hidden-kind items on packed weights (then the KV-kind items, in the same launch).  DT: 1 = fp16, 2 = bf16; DEAL: the
+// heads that not every queue has are dealt to all XCDs
+template <int DT, bool DEAL> int apt_launch_mfma(const ItemParams& p, int n_wg, hipStream_t st);
+template <int DT, bool DEAL> bool apt_setup_mfma();
+template <> int apt_launch_mfma<1, false>(const ItemParams& p, int n_wg, hipStream_t st);
+template <> int apt_launch_mfma<1, true>(const ItemParams& p, int n_wg, hipStream_t st);
+template <> int apt_launch_mfma<2, false>(const ItemParams& p, int n_wg, hipStream_t st);
+template <> int apt_launch_mfma<2, true>(const ItemParams& p, int n_wg, hipStream_t st);
+template <> bool apt_setup_mfma<1, false>();
+template <> bool apt_setup_mfma<1, true>();
+template <> bool apt_setup_mfma<2, false>();
+template <> bool apt_setup_mfma<2, true>();
 
 // apt_raw16.hip: 16-bit inputs, hidden-kind items on the raw weights (and the KV-kind items, in the same launch)
 int apt_launch_raw16(const ItemParams& p, int dtype, int head_dim, hipStream_t st);

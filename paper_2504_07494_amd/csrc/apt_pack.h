@@ -67,3 +67,64 @@ APT_HOST_DEVICE static inline void apt_pack_patterns(int32_t* left, int cap, Emi
         emit(reps, take);
     }
 }
+
+// Heads dealt to all XCDs.  Queue x holds the heads h with h % 8 == x and runs on XCD x; with a head count that is no multiple of eight the
+// first H % 8 queues have a head more than the others.  The tiles of these heads can be dealt to all XCDs in turn: XCD x takes its own
+// other heads as always, and tile t of the dealt head of queue q where (t + q) % 8 == x.  Dealt launches share tiles by one cap for all
+// queues, that of the queues with the nearer number of heads (the other one where that is 0); below eight heads all are dealt.
+APT_HOST_DEVICE static inline int apt_dealt_cap(uint32_t word, int H) {
+    const int more = H & 7, cap_long = word & 15, cap_short = H < 8 ? cap_long : (int)(word >> (4 * more)) & 15;
+    const int nearer = more >= 4 ? cap_long : cap_short;
+    return nearer ? nearer : cap_long > cap_short ? cap_long : cap_short;
+}
+
+// The i-th tile of XCD x: the number of the tile among its head's (returned; from the number of a head's tiles on: none, nor are the later
+// ones), the queue of the head and its place among that queue's heads.  nh = H / 8 heads of the XCD's own, more = H % 8 dealt ones.
+APT_HOST_DEVICE static inline int apt_dealt_tile(int i, int x, int nh, int more, int* queue, int* place) {
+    const int per_eight = 8 * nh + more;                      // tiles of this XCD among tiles 8 j .. 8 j + 7 of every head
+    int at = i / per_eight * 8, left = i % per_eight, q;
+    for (;;) {                                                // (ends within eight steps: q is every queue once)
+        q = (x - at) & 7;
+        const int here = nh + (q < more);
+        if (left < here) break;
+        left -= here;
+        ++at;
+    }
+    *queue = left < nh ? x : q;
+    *place = left;
+    return at;
+}
+
+// Whether a launch deals: counts with up to four such heads (below eight any), where the longer queues hold four rounds of ranges or
+// more, and in shorter launches whose queues share tiles alike (their word), where that saves a round.
+// Whole step, us, a queue's heads on its XCD / dealt: 3 heads, 64 requests of 64..1024 tokens 100.8 / 59.4; 17 heads, 247 of 32..300
+// 861 / 671; 18 heads, 60 of 100..600 391 / 309; 41 heads, 109 of 10..90 686 / 617; 60 heads, 28 of 636..1941 12.8 / 11.4 ms; 26 heads, two
+// of 1064 tokens 128 / 92.  Where the rule does not: 69 heads, 30 of 100..800 2778 / 2852 (each XCD reads the weights of all these
+// heads; five to seven such heads were timed there and at 30 heads only); a round saved by nobody: 43 heads, three of 20..200 75.2 / 77.8,
+// 36 heads, eleven of 28 69.2 / 73.6; tiles shared by another queue's cap: 51 heads, twelve of 75 190 / 266.
+// A captured launch keeps its choice when it is replayed with another plan: outputs are the same bits either way.
+template <int NC>
+static inline bool apt_deals(const int32_t* ctx_lens, const int32_t* kinds, int B, int H, int chunk, uint32_t word, int n_workgroups) {
+    const int more = H % APT_N_QUEUES, per_queue = n_workgroups / APT_N_QUEUES;
+    if (more == 0 || (more > 4 && H > APT_N_QUEUES)) return false;
+    int64_t full = 0, tails = 0;
+    int32_t count[NC + 1] = {0};
+    for (int r = 0; r < B; ++r) {
+        if (kinds[r] != APT_KIND_HIDDEN) continue;
+        full += ctx_lens[r] / chunk;
+        if (ctx_lens[r] % chunk) ++tails, ++count[(ctx_lens[r] % chunk + APT_PACK_BLOCK - 1) / APT_PACK_BLOCK];
+    }
+    const int64_t heads = (H + APT_N_QUEUES - 1) / APT_N_QUEUES;
+    if ((full + tails) * heads >= 4 * per_queue) return true;
+    const int cap = word & 15;
+    if (H > APT_N_QUEUES && cap != (int)(word >> (4 * more) & 15)) return false;
+    int64_t tiles = full + tails;
+    if (cap) {
+        const int full_blocks = chunk / APT_PACK_BLOCK;
+        tiles = full_blocks == NC ? full : 0;
+        if (full_blocks < NC) count[full_blocks] += (int32_t)full;
+        apt_pack_patterns<NC>(count, cap < NC ? cap : NC, [&](int32_t reps, const int32_t*) { tiles += reps; });
+    }
+    const int64_t most = tiles * (H / APT_N_QUEUES) + tiles / APT_N_QUEUES * more + (tiles % APT_N_QUEUES < more ? tiles % APT_N_QUEUES : more);
+    return (most + per_queue - 1) / per_queue < (tiles * heads + per_queue - 1) / per_queue;
+}

@@ -1,4 +1,5 @@
 """Test-side helpers: call the oracle on a workload, brute-force references."""
+import ctypes as C
 import math
 
 import numpy as np
@@ -49,3 +50,38 @@ def brute_force_attention(q, K, V, scale):
         for c in range(hd):
             out[c] += (e[j] / den) * float(V[j][c])
     return np.array(out)
+
+
+class _NodeParams(C.Structure):                          # hipKernelNodeParams
+    _fields_ = [("block", C.c_uint32 * 3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", C.c_uint32 * 3), ("params", C.c_void_p),
+                ("shared", C.c_uint32)]
+
+
+def launched_kernels(call):
+    """Names of the kernels that `call` launches on torch's current stream, in order.  They are captured, not run."""
+    import torch
+    with open("/proc/self/maps") as maps:
+        hip = C.CDLL(next(line.split()[-1] for line in maps if "libamdhip64.so" in line))
+    hip.hipKernelNameRefByPtr.restype = C.c_char_p
+
+    def check(status):
+        assert status == 0, status
+
+    side, graph, n = torch.cuda.Stream(), C.c_void_p(), C.c_size_t()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        check(hip.hipStreamBeginCapture(C.c_void_p(side.cuda_stream), 2))
+        try:
+            call()
+        finally:
+            check(hip.hipStreamEndCapture(C.c_void_p(side.cuda_stream), C.byref(graph)))
+    check(hip.hipGraphGetNodes(graph, None, C.byref(n)))
+    nodes = (C.c_void_p * n.value)()
+    check(hip.hipGraphGetNodes(graph, nodes, C.byref(n)))
+    names = []
+    for node in nodes:
+        p = _NodeParams()
+        check(hip.hipGraphKernelNodeGetParams(C.c_void_p(node), C.byref(p)))
+        names.append(hip.hipKernelNameRefByPtr(C.c_void_p(p.func), C.c_void_p(side.cuda_stream)).decode())
+    check(hip.hipGraphDestroy(graph))
+    return names

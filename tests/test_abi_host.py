@@ -138,7 +138,7 @@ def test_k_loops_of_the_packed_weight_kernel_touch_no_scratch(tmp_path):
                 bad = [x for _, o, x in ins[first:last] if "scratch" in o or "accvgpr" in o]
                 assert not bad, (name, bad[:5])
             seen += 1
-    assert seen == 4                                          # two types, two tiles
+    assert seen == 8                                          # two types, two tiles, heads dealt or not
 
 
 @pytest.mark.parametrize("himpl", [ab.APT_HIDDEN_AUTO, ab.APT_HIDDEN_VALU, ab.APT_HIDDEN_MFMA, ab.APT_HIDDEN_ABSORBED])
