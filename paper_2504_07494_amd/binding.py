@@ -67,7 +67,7 @@ def lib():
         for name in EXPORTS[1:] + BENCH_EXPORTS:
             getattr(loaded, name).restype = C.c_int
         loaded.apt_pool_destroy.restype = None
-        # the calls of a decode step take plain addresses
+        # the calls of a decode step, as the extension and _by_ctypes issue them
         p, i, n = C.c_void_p, C.c_int, C.c_size_t
         loaded.apt_plan.argtypes = [p, p, p, i, p, n, p]
         loaded.apt_plan_upload.argtypes = [p, p, p]
@@ -78,7 +78,7 @@ def lib():
             from . import _apt_call
         except ImportError as e:
             raise RuntimeError(f"{_HERE}/_apt_call.so cannot be loaded ({e}): build it with the library") from e
-        _apt_call.init(np.ndarray, _addr)
+        _apt_call.init(np.ndarray, C.Structure)
         loaded.steps = {}
         _lib = loaded             # published last: another thread's first call must find the argument types set
     return _lib
@@ -87,8 +87,14 @@ def lib():
 # The calls of a decode step and the kinds of their arguments (csrc/apt_call.c).  The whole call on the host, us, one small
 # request, converted by ctypes / by the extension: apt_plan 3.1 / 0.9, apt_hybrid_decode_attn 7.5 / 4.2, apt_cache_append 5.9 / 3.6; steps
 # back to back, 40 heads, one KV-kind request of 1237 tokens with its append 19.1 / 14.4, the fp32 layer of 4 heads, 4 requests 14.3 / 12.0.
-_STEP_KINDS = {"apt_plan": b"sppipis", "apt_plan_upload": b"ppp", "apt_hybrid_decode_attn": b"s" + b"p" * 14 + b"ip",
-               "apt_cache_append": b"si" + b"p" * 10, "apt_cache_write": b"sipi" + b"p" * 10}
+# What the extension does not know (numpy integers, ctypes objects, anything with _as_parameter_) is left to ctypes.
+_STEP_KINDS = {"apt_plan": b"saaiais", "apt_plan_upload": b"aap", "apt_hybrid_decode_attn": b"s" + b"a" * 14 + b"ip",
+               "apt_cache_append": b"si" + b"a" * 9 + b"p", "apt_cache_write": b"siai" + b"a" * 9 + b"p"}
+
+
+def _by_ctypes(function, kinds, *args):
+    """The call through ctypes; kinds: s a structure, a an address (see _addr), anything else as it is."""
+    return function(*[C.byref(x) if k == ord("s") else _addr(x) if k == ord("a") else x for k, x in zip(kinds, args)])
 
 
 def _step(name):
@@ -96,7 +102,8 @@ def _step(name):
     f = loaded.steps.get(name)
     if f is None:
         from ._apt_call import call
-        f = loaded.steps[name] = partial(call, C.cast(getattr(loaded, name), C.c_void_p).value, _STEP_KINDS[name])
+        function, kinds = getattr(loaded, name), _STEP_KINDS[name]
+        f = loaded.steps[name] = partial(call, C.cast(function, C.c_void_p).value, kinds, partial(_by_ctypes, function, kinds))
     return f
 
 

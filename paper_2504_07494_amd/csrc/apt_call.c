@@ -5,60 +5,53 @@
 #include <Python.h>
 #include <stdint.h>
 
-static PyObject *g_ndarray, *g_addr, *g_data_ptr;
+#if !defined(__x86_64__) || defined(_WIN32)
+#error "call() passes every argument as 64 bits, which the System V calling convention of x86-64 allows (build.py leaves the file out elsewhere)"
+#endif
 
-// call(function address, kinds, arguments...) -> int.  kinds, a byte per argument: p an address (None: NULL; anything that is no integer,
-// array or tensor goes through the address function given to init), s a ctypes structure, i an integer.
+static PyObject *g_ndarray, *g_structure, *g_data_ptr;
+
+// call(function address, kinds, other, arguments...) -> int.  kinds, a byte per argument: a an address given as an integer, None (NULL), an
+// array or a tensor; p one given as an integer or None; s a ctypes structure; i an integer.  An argument of any other type: other is
+// called with all of them and its result returned, so that what is taken and what is refused is for it to say.
 enum { kMost = 17 };
 
-static int address_of(PyObject* x, uint64_t* out) {
-    if (x == Py_None) {
+// 1: converted, 0: not a type of this kind, -1: an exception is set
+static int integer(PyObject* x, uint64_t* out) {
+    if (!PyLong_Check(x)) return 0;
+    *out = PyLong_AsUnsignedLongLongMask(x);
+    return *out == (uint64_t)-1 && PyErr_Occurred() ? -1 : 1;
+}
+
+static int buffer(PyObject* x, uint64_t* out) {
+    Py_buffer view;
+    if (PyObject_GetBuffer(x, &view, PyBUF_STRIDED_RO)) {    // (arrays of dates, for instance, have an address but no buffer)
+        PyErr_Clear();
+        return 0;
+    }
+    *out = (uint64_t)(uintptr_t)view.buf;                // the caller holds the object during the call
+    PyBuffer_Release(&view);
+    return 1;
+}
+
+static int convert(char kind, PyObject* x, uint64_t* out) {
+    if (kind == 's') return PyObject_TypeCheck(x, (PyTypeObject*)g_structure) ? buffer(x, out) : 0;
+    if (kind != 'i' && x == Py_None) {
         *out = 0;
-        return 0;
+        return 1;
     }
-    if (PyLong_Check(x)) {
-        *out = PyLong_AsUnsignedLongLongMask(x);
-        return *out == (uint64_t)-1 && PyErr_Occurred() ? -1 : 0;
-    }
-    if (PyObject_TypeCheck(x, (PyTypeObject*)g_ndarray)) {
-        Py_buffer view;
-        if (PyObject_GetBuffer(x, &view, PyBUF_STRIDED_RO)) return -1;
-        *out = (uint64_t)(uintptr_t)view.buf;            // the caller holds the array during the call
-        PyBuffer_Release(&view);
-        return 0;
-    }
+    const int rc = integer(x, out);
+    if (rc || kind != 'a') return rc;
+    if (PyObject_TypeCheck(x, (PyTypeObject*)g_ndarray)) return buffer(x, out);
     PyObject* at = PyObject_CallMethodNoArgs(x, g_data_ptr);
     if (!at) {
         if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return -1;
         PyErr_Clear();
-        at = PyObject_CallOneArg(g_addr, x);
-        if (!at) return -1;
-        if (at == Py_None) {
-            Py_DECREF(at);
-            *out = 0;
-            return 0;
-        }
+        return 0;
     }
-    *out = PyLong_AsUnsignedLongLongMask(at);
+    const int done = integer(at, out);
     Py_DECREF(at);
-    return *out == (uint64_t)-1 && PyErr_Occurred() ? -1 : 0;
-}
-
-static int convert(char kind, PyObject* x, uint64_t* out) {
-    if (kind == 'p') return address_of(x, out);
-    if (kind == 'i') {
-        if (!PyLong_Check(x)) {
-            PyErr_Format(PyExc_TypeError, "an integer is required, not %s", Py_TYPE(x)->tp_name);
-            return -1;
-        }
-        *out = PyLong_AsUnsignedLongLongMask(x);
-        return *out == (uint64_t)-1 && PyErr_Occurred() ? -1 : 0;
-    }
-    Py_buffer view;
-    if (PyObject_GetBuffer(x, &view, PyBUF_SIMPLE)) return -1;
-    *out = (uint64_t)(uintptr_t)view.buf;
-    PyBuffer_Release(&view);
-    return 0;
+    return done;
 }
 
 typedef uint64_t U;
@@ -67,18 +60,25 @@ static PyObject* call(PyObject* self, PyObject* const* args, Py_ssize_t n_args) 
     U a[kMost] = {0};
     char* kinds;
     Py_ssize_t n;
-    if (n_args < 2 || PyBytes_AsStringAndSize(args[1], &kinds, &n)) {
-        if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "a function address and argument kinds are required");
+    if (n_args < 3 || PyBytes_AsStringAndSize(args[1], &kinds, &n)) {
+        if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "a function address, argument kinds and a function are required");
         return NULL;
     }
-    if (n != n_args - 2 || n > kMost) {
-        PyErr_Format(PyExc_TypeError, "%zd arguments are required, not %zd", n, n_args - 2);
+    if (n != n_args - 3 || n > kMost) {
+        PyErr_Format(PyExc_TypeError, "%zd arguments are required, not %zd", n, n_args - 3);
         return NULL;
     }
     U f;
-    if (convert('i', args[0], &f)) return NULL;
-    for (Py_ssize_t i = 0; i < n; ++i)
-        if (convert(kinds[i], args[2 + i], &a[i])) return NULL;
+    const int known = integer(args[0], &f);
+    if (known <= 0) {
+        if (known == 0) PyErr_SetString(PyExc_TypeError, "the function address is not an integer");
+        return NULL;
+    }
+    for (Py_ssize_t i = 0; i < n; ++i) {
+        const int done = convert(kinds[i], args[3 + i], &a[i]);
+        if (done < 0) return NULL;
+        if (done == 0) return PyObject_Vectorcall(args[2], args + 3, (size_t)n, NULL);
+    }
     int rc;
     // Every argument is an integer or an address and so has a register or eight bytes of stack of its own.
     Py_BEGIN_ALLOW_THREADS
@@ -92,19 +92,19 @@ static PyObject* call(PyObject* self, PyObject* const* args, Py_ssize_t n_args) 
     return PyLong_FromLong(rc);
 }
 
-// init(array type, address function)
+// init(array type, type of ctypes structures)
 static PyObject* init(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     (void)self;
-    if (n != 2 || !PyType_Check(args[0]) || !PyCallable_Check(args[1])) {
-        PyErr_SetString(PyExc_TypeError, "an array type and a function are required");
+    if (n != 2 || !PyType_Check(args[0]) || !PyType_Check(args[1])) {
+        PyErr_SetString(PyExc_TypeError, "two types are required");
         return NULL;
     }
     Py_INCREF(args[0]);
     Py_INCREF(args[1]);
     Py_XDECREF(g_ndarray);
-    Py_XDECREF(g_addr);
+    Py_XDECREF(g_structure);
     g_ndarray = args[0];
-    g_addr = args[1];
+    g_structure = args[1];
     Py_RETURN_NONE;
 }
 
