@@ -2,6 +2,7 @@
 what is taken and refused is what ctypes takes and refuses."""
 import ctypes as C
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -146,15 +147,21 @@ def test_an_error_inside_data_ptr_is_not_taken_for_another_kind():
         _apt_call.call(address, b"a", _never, Tensor())
 
 
-def test_another_thread_runs_during_a_call():
-    entered, done = threading.Event(), threading.Event()
+def test_other_threads_run_during_a_call():
+    """The called function blocks without touching Python: another thread only gets on if the call has released the interpreter."""
+    ticks, stop = [0], threading.Event()
 
-    def wait(_):
-        entered.set()
-        return 1 if done.wait(20) else 0
+    def tick():
+        while not stop.is_set():
+            ticks[0] += 1
+            time.sleep(0.001)
 
-    f = C.CFUNCTYPE(C.c_int, C.c_uint64)(wait)
-    other = threading.Thread(target=lambda: entered.wait(20) and done.set())
+    other = threading.Thread(target=tick)
     other.start()
-    assert _apt_call.call(C.cast(f, C.c_void_p).value, b"i", _never, 0) == 1
+    usleep = C.cast(C.CDLL(None).usleep, C.c_void_p).value
+    before = ticks[0]
+    assert _apt_call.call(usleep, b"i", _never, 500000) == 0
+    after = ticks[0]
+    stop.set()
     other.join()
+    assert after - before >= 5                            # held: at most the tick that the call's own end lets through
