@@ -74,11 +74,6 @@ def lib():
         loaded.apt_hybrid_decode_attn.argtypes = [p] * 15 + [n, p]
         loaded.apt_cache_append.argtypes = [p, i] + [p] * 10
         loaded.apt_cache_write.argtypes = [p, i, p, C.c_int32] + [p] * 10
-        try:
-            from . import _apt_call
-        except ImportError as e:
-            raise RuntimeError(f"{_HERE}/_apt_call.so cannot be loaded ({e}): build it with the library") from e
-        _apt_call.init(np.ndarray, C.Structure)
         loaded.steps = {}
         _lib = loaded             # published last: another thread's first call must find the argument types set
     return _lib
@@ -101,9 +96,16 @@ def _step(name):
     loaded = lib()
     f = loaded.steps.get(name)
     if f is None:
-        from ._apt_call import call
         function, kinds = getattr(loaded, name), _STEP_KINDS[name]
-        f = loaded.steps[name] = partial(call, C.cast(function, C.c_void_p).value, kinds, partial(_by_ctypes, function, kinds))
+        f = partial(_by_ctypes, function, kinds)
+        try:
+            from . import _apt_call
+        except ImportError:                # not built for this Python: the same calls, each some us longer
+            pass
+        else:
+            _apt_call.init(np.ndarray, C.Structure)
+            f = partial(_apt_call.call, C.cast(function, C.c_void_p).value, kinds, f)
+        loaded.steps[name] = f
     return f
 
 

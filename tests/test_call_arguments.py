@@ -1,6 +1,10 @@
 """The extension that calls the library (csrc/apt_call.c): every kind of argument arrives as the address or integer it stands for, and
 what is taken and refused is what ctypes takes and refuses."""
 import ctypes as C
+import os
+import subprocess
+import sys
+import sysconfig
 import threading
 import time
 
@@ -9,9 +13,10 @@ import pytest
 import torch
 
 from paper_2504_07494_amd import binding as ab
+from paper_2504_07494_amd import build
 
-ab.lib()
-from paper_2504_07494_amd import _apt_call  # noqa: E402
+_apt_call = pytest.importorskip("paper_2504_07494_amd._apt_call", reason="built without a host compiler or Python headers")
+ab._step("apt_plan")                                      # (sets the extension up)
 
 SEEN = []
 
@@ -165,3 +170,47 @@ def test_other_threads_run_during_a_call():
     stop.set()
     other.join()
     assert after - before >= 5                            # held: at most the tick that the call's own end lets through
+
+
+def test_without_the_extension_the_calls_go_through_ctypes():
+    """In a process of its own, where the extension cannot be imported: the planner, the pool and the library's checks answer the same."""
+    script = """
+import sys
+if "without" in sys.argv:
+    sys.modules["paper_2504_07494_amd._apt_call"] = None
+import numpy as np
+from paper_2504_07494_amd import binding as ab
+shape = ab.make_shape(5120, 40, 128, 16, "f16", 64, 0.1)
+lens, kinds = np.array([700, 33, 512, 1000], dtype=np.int32), np.array([1, 0, 1, 0], dtype=np.uint8)
+blob = np.zeros(ab.apt_plan_max_bytes(shape, 4, 1024) // 4, dtype=np.int32)
+info = ab.apt_plan(shape, lens, kinds, blob)
+assert ab.apt_pool_free_blocks(ab.apt_pool_create(8, 16, 4, 2)) == 8
+try:
+    ab.apt_cache_append(shape, np.int64(4), *[None] * 9, 0)
+except ab.AptError as e:
+    assert e.status == ab.APT_EINVAL
+print(info.n_items, info.plan_bytes, hash(blob.tobytes()), ab._step("apt_plan").func is ab._by_ctypes)
+"""
+    env = dict(os.environ, PYTHONHASHSEED="0", PYTHONPATH=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    got = [subprocess.run([sys.executable, "-c", script, *words], env=env, text=True, capture_output=True, check=True).stdout.split()
+           for words in ([], ["without"])]
+    assert got[0][:3] == got[1][:3] and [g[3] for g in got] == ["False", "True"]
+
+
+def test_the_extension_is_left_out_of_a_build_that_cannot_make_it(monkeypatch, tmp_path):
+    monkeypatch.delenv("CC", raising=False)
+    assert build.CALL.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    with monkeypatch.context() as m:
+        m.setattr(build.shutil, "which", lambda name: f"/usr/bin/{name}")
+        m.setenv("CC", "ccache gcc -pipe")
+        command = build.extension_command()
+        assert command[:3] == ["ccache", "gcc", "-pipe"] and command[-1] == build.CALL
+    with monkeypatch.context() as m:
+        m.setenv("CC", str(tmp_path / "no such compiler").replace(" ", "_"))
+        assert build.extension_command() is None
+    with monkeypatch.context() as m:
+        m.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+        assert build.extension_command() is None
+    with monkeypatch.context() as m:
+        m.setattr(build.platform, "machine", lambda: "aarch64")
+        assert build.extension_command() is None
