@@ -131,25 +131,28 @@ __global__ __launch_bounds__(kThreads) void apt_plan_copy_kernel(uint64_t* dst, 
     if ((words & 1) && blockIdx.x == 0 && threadIdx.x == 0)          // the last word of an odd number
         ((int32_t*)dst)[words - 1] = __hip_atomic_load((const int32_t*)src + words - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-// Whether apt_plan_copy_kernel can take the blob: all of it lies in one page-locked allocation that the device sees at the same address, and
-// the current device, the stream's and that of plan_dev are one (the runtime's copy also serves others).
+// Whether apt_plan_copy_kernel can take the blob: all of it lies in one page-locked allocation that the device sees at the same address, its
+// destination in one allocation of the device too, and the current device, the stream's and that of plan_dev are one.  Anything
+// else, buffers that are too small among them, is for the runtime's copy to serve or to refuse.
 static bool copied_by_kernel(const void* host, const void* dev, size_t bytes, hipStream_t st) {
     hipPointerAttribute_t from = {}, to = {};
-    void* start = nullptr;
-    size_t size = 0;
     int current = -1, streams = -1;
     auto ok = [](hipError_t e) {                          // a query's error is not left for a later call to find
         if (e != hipSuccess) (void)hipGetLastError();
         return e == hipSuccess;
     };
-    if (!ok(hipPointerGetAttributes(&from, host)) || from.type != hipMemoryTypeHost || from.devicePointer != host ||
-        !ok(hipPointerGetAttributes(&to, dev)) || to.type != hipMemoryTypeDevice ||
-        !ok(hipPointerGetAttribute(&start, HIP_POINTER_ATTRIBUTE_RANGE_START_ADDR, (hipDeviceptr_t)host)) ||
-        !ok(hipPointerGetAttribute(&size, HIP_POINTER_ATTRIBUTE_RANGE_SIZE, (hipDeviceptr_t)host)) ||
-        !ok(hipGetDevice(&current)) || !ok(hipStreamGetDevice(st, &streams)))
-        return false;
-    const uintptr_t at = (uintptr_t)host - (uintptr_t)start;
-    return at <= size && bytes <= size - at && streams == current && to.device == current;
+    auto in_one_allocation = [&](const void* p) {
+        void* start = nullptr;
+        size_t size = 0;
+        if (!ok(hipPointerGetAttribute(&start, HIP_POINTER_ATTRIBUTE_RANGE_START_ADDR, (hipDeviceptr_t)p)) ||
+            !ok(hipPointerGetAttribute(&size, HIP_POINTER_ATTRIBUTE_RANGE_SIZE, (hipDeviceptr_t)p)))
+            return false;
+        const uintptr_t at = (uintptr_t)p - (uintptr_t)start;
+        return at <= size && bytes <= size - at;
+    };
+    return ok(hipPointerGetAttributes(&from, host)) && from.type == hipMemoryTypeHost && from.devicePointer == host &&
+           ok(hipPointerGetAttributes(&to, dev)) && to.type == hipMemoryTypeDevice && in_one_allocation(host) && in_one_allocation(dev) &&
+           ok(hipGetDevice(&current)) && ok(hipStreamGetDevice(st, &streams)) && streams == current && to.device == current;
 }
 
 // Where the cache calls put a new token's vector: 16-byte unit u of it (row_units in all; a unit never straddles a head, as
