@@ -211,13 +211,14 @@ int apt_plan(const apt_shape* s, const int32_t* ctx_lens_host, const uint8_t* ca
 /* Read the counts back from a plan blob made by apt_plan (host; helper of apt_plan). */
 int apt_plan_get_info(const void* plan_host, apt_plan_info* info);
 
-/* Asynchronous copy of a plan blob to device memory (plan_dev: at least
- * info.plan_bytes bytes; helper of apt_plan: the device half of the work partition).  plan_host
- * must stay unchanged until the copy is done (re-planning into the same host buffer before that
+/* Copy of a plan blob to device memory in the order of the stream, asynchronous for page-locked host memory (plan_dev: at
+ * least info.plan_bytes bytes; helper of apt_plan: the device half of the work partition).  plan_host
+ * must stay unchanged and allocated until the copy is done (re-planning into the same host buffer before that
  * tears the copy: use one host buffer per step in flight, or wait for an event recorded after
- * this call); use page-locked host memory for a truly asynchronous copy.  A blob of at most
- * APT_PLAN_INLINE_BYTES travels with a kernel launch instead and has been read when the call
- * returns, unless the stream is being captured (a captured copy reads plan_host at every replay). */
+ * this call).  How it travels: a blob of at most APT_PLAN_INLINE_BYTES with a kernel launch, and it has been read when the call
+ * returns; one of more than 16 KB in page-locked memory that the device sees at the same address (both addresses
+ * multiples of eight, everything on the current device) is read by a kernel over the bus when the stream gets there; any other by the
+ * runtime's asynchronous copy, and every one while the stream is being captured (a captured copy reads plan_host at every replay). */
 #define APT_PLAN_INLINE_BYTES 3840
 int apt_plan_upload(const void* plan_host, void* plan_dev, void* stream);
 
