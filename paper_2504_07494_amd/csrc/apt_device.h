@@ -26,7 +26,6 @@ struct ItemParams {
     int32_t n_items, n_hidden_items, hidden_chunk, kv_chunk, items_off;
     float scale_log2e;
     int32_t wide_tiles;           // packed weights, ranges of 256 tokens: tiles of 320 rows (apt_pack.h)
-    int32_t dealt;                // packed weights: the heads that not every queue has are dealt to all XCDs (apt_pack.h)
     int32_t item_base;            // one-workgroup-per-item launch: first item of the grid
     // absorbed-weight hidden path: workspace sections (fp32)
     float* ab_qt;                 // [n_hid_req][H][d], 16-bit inputs: parts in the score kernel's order
