@@ -81,7 +81,7 @@ def lib():
 
 # The calls of a decode step and the kinds of their arguments (csrc/apt_call.c).  The whole call on the host, us, one small
 # request, converted by ctypes / by the extension: apt_plan 3.1 / 0.9, apt_hybrid_decode_attn 7.5 / 4.2, apt_cache_append 5.9 / 3.6; steps
-# back to back, 40 heads, one KV-kind request of 1237 tokens with its append 19.1 / 14.4, the fp32 layer of 4 heads, 4 requests 14.3 / 12.0.
+# back to back, 40 heads, one KV-kind request of 1237 tokens with its append 19.5 / 16.2, the fp32 layer of 4 heads, 4 requests 14.5 / 11.7.
 # What the extension does not know (numpy integers, ctypes objects, anything with _as_parameter_) is left to ctypes.
 _STEP_KINDS = {"apt_plan": b"saaiais", "apt_plan_upload": b"aap", "apt_hybrid_decode_attn": b"s" + b"a" * 14 + b"ip",
                "apt_cache_append": b"si" + b"a" * 9 + b"p", "apt_cache_write": b"siai" + b"a" * 9 + b"p"}

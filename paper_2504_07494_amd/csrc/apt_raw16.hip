@@ -22,9 +22,11 @@ namespace {
 // with the LDS this frees more stages in flight.  (Ranges of 129 to 192 tokens in 192 instead of 256 rows, whole step: 25 heads, 25 requests of 64..562 tokens 139.5 ->
 // 132 us, 27 heads, 27 of 145..1024 162 -> 153, 32 heads, 24 of 123..1006 beside as many KV-kind ones 248 -> 242.)
 //
-// Bound by the matrix pipes and, like every dense product on this card, by board power: 48 requests of 32..1024 tokens
-// at d_model 2048, head_dim 64 (13 k hidden-kind tokens) take 0.223 ms for the whole step, 957 TFLOP/s on 4 d^2 per
-// token; the plain-ALU kernel that served these shapes before took 13.58 ms (16 TFLOP/s).
+// 48 requests of 32..1024 tokens at d_model 2048, head_dim 64 (13 k hidden-kind tokens) take 0.225 ms for the whole step (0.224 to 0.229
+// over boxes), 950 TFLOP/s on 4 d^2 per token; the plain-ALU kernel that served these shapes before took 13.58 ms (16 TFLOP/s).
+// No one unit is at its limit there (counters): matrix pipes 0.51 of the cycles, LDS about 0.57 by its bytes (72 KB of reads and copies per
+// k-tile and workgroup at 128 a clock), L2 0.63 of a request per clock and channel (four in five ask for half a line: 32 k of a token's row),
+// 1790 of 2048 waves resident, which wait for an instruction's turn 45 % of their time and for copies and barriers 25 %.
 template <int HD, int T> struct RawTile {
     static constexpr int kChan = 2 * HD;
     static constexpr int kWRow = kChan * 2;                    // bytes of a k-row of the W image
@@ -122,8 +124,10 @@ __device__ __forceinline__ void hidden_item_raw(const ItemParams& p, int r, int 
     // The copies of the k-tile S - 1 ahead go out one by one between the products (asked for in one go, a wave is held until the copy path
     // has taken all of the workgroup's), and a token fragment is read two ahead of its products.  Whole step, copies in one go and all operands
     // read first / so: 39 heads, 8 requests of 16..105 tokens 35.5 / 30.4 us, 22 heads, 19 of 148..762 69.9 / 62.3, 35 heads, 36 of 64..222
-    // 124.6 / 113.5, 32 heads, 48 of 32..1024 231.7 / 226.3 (there LDS is the limit either way).  In one go through the first quarter or half
-    // of the products: between the two.
+    // 124.6 / 113.5, 32 heads, 48 of 32..1024 231.7 / 226.3.  Attention call of 30 drawn batches 0.94 of the time, of 40 more whose
+    // hidden-kind items fill the chip about once beside KV-kind ones 0.93 to 0.94 (0.81 to 1.04, four of them above 1: there two runs of
+    // one side differ by as much).  Copies in one go, operands read ahead 0.97; in the first quarter of the products 0.95; all operands read
+    // first and copies spread 0.93 to 0.96.
     auto k_loop = [&](auto is_v) {
         int stage = 0;
         auto step = [&](int kt, auto refill) {
