@@ -187,21 +187,30 @@ def deals_heads(ctx_lens, cache_kind, n_heads, hidden_chunk, word, n_workgroups=
     caps = [(word >> 4 * x) & 15 for x in range(N_QUEUES)]
     blocks = 10 if hidden_chunk == 320 or max(caps) > 8 else 8
     ranges, heads = sum(ceil_div(n, hidden_chunk) for n in lens), ceil_div(n_heads, N_QUEUES)
-    if ranges * heads >= 4 * per_queue:
-        return True
-    if n_heads > N_QUEUES and caps[0] != caps[more]:
-        return False
-    tiles = ranges
-    if caps[0]:
+
+    def tiles(cap):
+        if not cap:
+            return ranges
         count, own = [0] * (blocks + 1), 0
         for n in lens:
             for t0 in range(0, n, hidden_chunk):
                 c = ceil_div(min(n - t0, hidden_chunk), 32)
                 own += n - t0 >= hidden_chunk == 32 * blocks
                 count[c] += not n - t0 >= hidden_chunk == 32 * blocks
-        tiles = own + sum(n for n, _ in tile_patterns(count, caps[0], blocks))
-    dealt = [tiles * (n_heads // N_QUEUES) + sum((t + q) % N_QUEUES == x for t in range(tiles) for q in range(more)) for x in range(N_QUEUES)]
-    return ceil_div(max(dealt), per_queue) < ceil_div(tiles * heads, per_queue)
+        return own + sum(n for n, _ in tile_patterns(count, cap, blocks))
+
+    longer, shorter = caps[0], caps[more if n_heads > N_QUEUES else 0]
+    undealt, d = tiles(longer) * heads, 128 * n_heads
+    kv = sum(int(n) for n, k in zip(ctx_lens, cache_kind) if int(k) == KIND_KV) * d // 1375
+    if 5 * kv * n_workgroups >= 4 * tiles(longer) * tile_ns(blocks, d, blocks, 1) * (heads * N_QUEUES - n_heads):
+        return False
+    if undealt >= 4 * per_queue:
+        return True
+    if longer != shorter and ranges * heads < 4 * per_queue:
+        return False
+    n = tiles((longer if more >= 4 else shorter) or max(longer, shorter))
+    dealt = [n * (n_heads // N_QUEUES) + sum((t + q) % N_QUEUES == x for t in range(n) for q in range(more)) for x in range(N_QUEUES)]
+    return ceil_div(max(dealt), per_queue) < ceil_div(undealt, per_queue)
 
 
 def plan(ctx_lens, cache_kind, n_heads, hidden_chunk, kv_chunk, hidden_item_per_head=True):

@@ -682,7 +682,8 @@ static int decode_attn(const apt_shape* s, const void* plan_host, void* plan_dev
     if (rs.s.hidden_impl == APT_HIDDEN_MFMA && n_hidden > 0) {
         const int32_t *lens = pw + APT_PW_HEADER + APT_PA_CTX_LEN * B, *kinds = pw + APT_PW_HEADER + APT_PA_KIND * B;
         const bool rows320 = hidden_chunk == APT_MFMA_HIDDEN_CHUNK || p.wide_tiles;
-        dealt = (rows320 ? apt_deals<10> : apt_deals<8>)(lens, kinds, B, p.H, hidden_chunk, (uint32_t)pw[APT_PW_SHARED_TILES], ds->n_wg);
+        const int64_t kv_tokens = (((int64_t)pw[APT_PW_TOK_HI] << 32) | (uint32_t)pw[APT_PW_TOK_LO]) - hidden_tokens;
+        dealt = (rows320 ? apt_deals<10> : apt_deals<8>)(lens, kinds, B, kv_tokens, p.H, p.d, hidden_chunk, (uint32_t)pw[APT_PW_SHARED_TILES], ds->n_wg);
     }
     hipStream_t st = (hipStream_t)stream;
 

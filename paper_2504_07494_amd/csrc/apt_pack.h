@@ -68,6 +68,19 @@ APT_HOST_DEVICE static inline void apt_pack_patterns(int32_t* left, int cap, Emi
     }
 }
 
+// Time of a tile of NC blocks of which `blocks` hold tokens of `ranges` ranges, ns, all workgroups busy: prologue and epilogue, then the
+// k loop, whose copies do not shrink with the rows that hold tokens.  Measured, us a tile of 2, 4, 6, 8 (and 10) blocks: NC 8, d_model 1024:
+// 18, 22, 28, 32; 3072: 35, 47, 61, 76; 5120: 53, 74, 97, 122.  NC 10, 1024: 22, 27, 33, 38, 47; 5120: 59, 81, 102, 126, 156; 9216:
+// 140, 186, 218, 242, 282 (there the weights of an XCD's heads no longer come from its L2).  A further range in a tile takes 0.5 to 1.5 us more.
+static inline int64_t apt_tile_ns(int NC, int d, int blocks, int ranges) {
+    const int64_t b = blocks > 2 ? blocks : 2;
+    if (NC == 8) return 10000 + d * (20000 + 11100 * b) / 5120 + 800 * (ranges - 1);
+    return 11000 + 800 * b + d * (d < APT_MFMA_LARGE_TILE_D_MODEL ? 4300 + 2280 * b : 11100 + 1880 * b) / 1024 + 1100 * (ranges - 1);
+}
+
+// Time of the KV-kind items of a launch with packed weights on the whole chip, ns: 4 d bytes a token at 5.5 TB/s.
+static inline int64_t apt_kv_ns(int64_t kv_tokens, int d) { return kv_tokens * d / 1375; }
+
 // Heads dealt to all XCDs.  Queue x holds the heads h with h % 8 == x and runs on XCD x; with a head count that is no multiple of eight the
 // first H % 8 queues have a head more than the others.  The tiles of these heads can be dealt to all XCDs in turn: XCD x takes its own
 // other heads as always, and tile t of the dealt head of queue q where (t + q) % 8 == x.  Dealt launches share tiles by one cap for all
@@ -95,36 +108,53 @@ APT_HOST_DEVICE static inline int apt_dealt_tile(int i, int x, int nh, int more,
     return at;
 }
 
-// Whether a launch deals: counts with up to four such heads (below eight any), where the longer queues hold four rounds of ranges or
-// more, and in shorter launches whose queues share tiles alike (their word), where that saves a round.
+// Whether a launch deals: counts with up to four such heads (below eight any), where the longer queues hold four rounds of tiles or
+// more, and in shorter launches where that saves a round; not in launches of less than four rounds of ranges whose queues share tiles
+// differently, nor where KV-kind items fill four fifths of what the shorter queues leave idle (they go to whoever is free).
 // Whole step, us, a queue's heads on its XCD / dealt: 3 heads, 64 requests of 64..1024 tokens 100.8 / 59.4; 17 heads, 247 of 32..300
 // 861 / 671; 18 heads, 60 of 100..600 391 / 309; 41 heads, 109 of 10..90 686 / 617; 60 heads, 28 of 636..1941 12.8 / 11.4 ms; 26 heads, two
 // of 1064 tokens 128 / 92.  Where the rule does not: 69 heads, 30 of 100..800 2778 / 2852 (each XCD reads the weights of all these
 // heads; five to seven such heads were timed there and at 30 heads only); a round saved by nobody: 43 heads, three of 20..200 75.2 / 77.8,
-// 36 heads, eleven of 28 69.2 / 73.6; tiles shared by another queue's cap: 51 heads, twelve of 75 190 / 266.
+// 36 heads, eleven of 28 69.2 / 73.6, and with four rounds of ranges in fewer of tiles 65 heads, 16 of 130..275 802 / 834, 20 heads, 91 of 29..95
+// beside as many KV-kind ones 183 / 188 (of 60 attention calls with four rounds of ranges all nine that saved no round of less than four
+// took 0.99 to 1.04 of the time dealt, the 13 that did 0.67 to 1.02); tiles shared by another queue's cap: 51 heads, twelve of 75 190 / 266; an
+// idle share that is filled: six heads, 186 of 442..1199, a quarter hidden-kind 170 / 185 (60 such attention calls: 32 with less
+// KV-kind time than that 0.61 to 0.99 of the time dealt, the other 28 0.96 to 1.09, 1.02 on average).
 // A captured launch keeps its choice when it is replayed with another plan: outputs are the same bits either way.
 template <int NC>
-static inline bool apt_deals(const int32_t* ctx_lens, const int32_t* kinds, int B, int H, int chunk, uint32_t word, int n_workgroups) {
+static inline bool apt_deals(const int32_t* ctx_lens, const int32_t* kinds, int B, int64_t kv_tokens, int H, int d, int chunk, uint32_t word,
+                             int n_workgroups) {
     const int more = H % APT_N_QUEUES, per_queue = n_workgroups / APT_N_QUEUES;
     if (more == 0 || (more > 4 && H > APT_N_QUEUES)) return false;
-    const int64_t heads = (H + APT_N_QUEUES - 1) / APT_N_QUEUES;
+    const int64_t heads = (H + APT_N_QUEUES - 1) / APT_N_QUEUES, four_rounds = 4 * (int64_t)per_queue;
+    const int64_t kv = apt_kv_ns(kv_tokens, d) * n_workgroups, idle = apt_tile_ns(NC, d, NC, 1) * (heads * APT_N_QUEUES - H);   // a tile per head
+    auto filled = [&](int64_t tiles) { return 5 * kv >= 4 * tiles * idle; };
     int64_t full = 0, tails = 0;
     int32_t count[NC + 1] = {0};
-    for (int r = 0; r < B; ++r) {                             // (host time of every call: ends early, 4096 requests 6.0 -> 0.03 us)
+    for (int r = 0; r < B; ++r) {                             // (host time of every call: ends where the fewest tiles it can be are enough)
         if (kinds[r] != APT_KIND_HIDDEN) continue;
         full += ctx_lens[r] / chunk;
         if (ctx_lens[r] % chunk) ++tails, ++count[(ctx_lens[r] % chunk + APT_PACK_BLOCK - 1) / APT_PACK_BLOCK];
-        if ((full + tails) * heads >= 4 * per_queue) return true;
+        const int64_t least = (full + tails) / apt_pack_tile<NC>::max_ranges;
+        if (least * heads >= four_rounds && !filled(least)) return true;
     }
+    const int full_blocks = chunk / APT_PACK_BLOCK;
+    auto tiles_of = [&](int cap) {                            // of a head
+        if (!cap) return full + tails;
+        int32_t left[NC + 1];
+        for (int c = 0; c <= NC; ++c) left[c] = count[c];
+        int64_t tiles = full_blocks == NC ? full : 0;
+        if (full_blocks < NC) left[full_blocks] += (int32_t)full;
+        apt_pack_patterns<NC>(left, cap < NC ? cap : NC, [&](int32_t reps, const int32_t*) { tiles += reps; });
+        return tiles;
+    };
     const int cap = word & 15;
-    if (H > APT_N_QUEUES && cap != (int)(word >> (4 * more) & 15)) return false;
-    int64_t tiles = full + tails;
-    if (cap) {
-        const int full_blocks = chunk / APT_PACK_BLOCK;
-        tiles = full_blocks == NC ? full : 0;
-        if (full_blocks < NC) count[full_blocks] += (int32_t)full;
-        apt_pack_patterns<NC>(count, cap < NC ? cap : NC, [&](int32_t reps, const int32_t*) { tiles += reps; });
-    }
+    const int64_t queues = tiles_of(cap) * heads;
+    if (filled(queues / heads)) return false;
+    if (queues >= four_rounds) return true;
+    const bool alike = H < APT_N_QUEUES || cap == (int)(word >> (4 * more) & 15);
+    if (!alike && (full + tails) * heads < four_rounds) return false;
+    const int64_t tiles = tiles_of(apt_dealt_cap(word, H));
     const int64_t most = tiles * (H / APT_N_QUEUES) + tiles / APT_N_QUEUES * more + (tiles % APT_N_QUEUES < more ? tiles % APT_N_QUEUES : more);
-    return (most + per_queue - 1) / per_queue < (tiles * heads + per_queue - 1) / per_queue;
+    return (most + per_queue - 1) / per_queue < (queues + per_queue - 1) / per_queue;
 }

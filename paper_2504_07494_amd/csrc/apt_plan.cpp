@@ -124,15 +124,6 @@ extern "C" int apt_workspace_bytes(const apt_shape* s, int max_batch, int max_ct
 // the time of all its tiles, ns.
 struct QueueTiles { int cap; int64_t last, total; };
 
-// Time of a tile of NC blocks of which `blocks` hold tokens of `ranges` ranges, ns, all workgroups busy: prologue and epilogue, then the
-// k loop, whose copies do not shrink with the rows that hold tokens.  Measured, us a tile of 2, 4, 6, 8 (and 10) blocks: NC 8, d_model 1024:
-// 18, 22, 28, 32; 3072: 35, 47, 61, 76; 5120: 53, 74, 97, 122.  NC 10, 1024: 22, 27, 33, 38, 47; 5120: 59, 81, 102, 126, 156; 9216:
-// 140, 186, 218, 242, 282 (there the weights of an XCD's heads no longer come from its L2).  A further range in a tile takes 0.5 to 1.5 us more.
-static int64_t tile_ns(int NC, int d, int blocks, int ranges) {
-    const int64_t b = std::max(blocks, 2);
-    if (NC == 8) return 10000 + d * (20000 + 11100 * b) / 5120 + 800 * (ranges - 1);
-    return 11000 + 800 * b + d * (d < APT_MFMA_LARGE_TILE_D_MODEL ? 4300 + 2280 * b : 11100 + 1880 * b) / 1024 + 1100 * (ranges - 1);
-}
 static constexpr int64_t kPatternsNs = 2500;               // what a workgroup's table of patterns takes
 
 // Tiles of a head queue, dealt to its workgroups in rounds, every second one backwards.  Runs of equal tiles are added as differences
@@ -187,8 +178,8 @@ static LaunchTiles shared_tiles(int d, int64_t full, int full_blocks, const int3
     for (int c = 1; c < APT_PACK_MAX_BLOCKS + 1; ++c) tails += count[c];
     for (int i = 0; i < q.n && whole; ++i) {
         Deal deal;
-        deal.add(tile_ns(NC, d, NC, 1), full * q.heads[i]);
-        for (int c = NC; c >= 1; --c) deal.add(tile_ns(NC, d, c, 1), count[c] * q.heads[i]);
+        deal.add(apt_tile_ns(NC, d, NC, 1), full * q.heads[i]);
+        for (int c = NC; c >= 1; --c) deal.add(apt_tile_ns(NC, d, c, 1), count[c] * q.heads[i]);
         option[i][n_options[i]++] = deal.result(0);
         share[i] = tails >= 2 && (full + tails) * q.heads[i] > Deal::kWorkgroups;
     }
@@ -198,11 +189,11 @@ static LaunchTiles shared_tiles(int d, int64_t full, int full_blocks, const int3
         if (!whole) left[full_blocks] += (int32_t)full;
         Deal deal[2];
         for (int i = 0; i < q.n; ++i)
-            if (whole) deal[i].add(tile_ns(NC, d, NC, 1), full * q.heads[i]);
+            if (whole) deal[i].add(apt_tile_ns(NC, d, NC, 1), full * q.heads[i]);
         apt_pack_patterns<NC>(left, k, [&](int32_t reps, const int32_t* take) {
             int blocks = 0, ranges = 0;
             for (int c = 1; c <= NC; ++c) { blocks += c * take[c]; ranges += take[c]; }
-            for (int i = 0; i < q.n; ++i) deal[i].add(tile_ns(NC, d, blocks, ranges), reps * q.heads[i]);
+            for (int i = 0; i < q.n; ++i) deal[i].add(apt_tile_ns(NC, d, blocks, ranges), reps * q.heads[i]);
         });
         for (int i = 0; i < q.n; ++i)
             if (share[i]) option[i][n_options[i]++] = deal[i].result(k);
@@ -230,7 +221,7 @@ static uint32_t shared_tiles_word(const int32_t* ctx_lens, const uint8_t* cache_
         full += ctx_lens[r] / chunk;
         if (ctx_lens[r] % chunk) ++count[ceil_div64(ctx_lens[r] % chunk, APT_PACK_BLOCK)];
     }
-    const int64_t kv = kv_tokens * d / 1375;               // 4 d bytes a token at 5.5 TB/s
+    const int64_t kv = apt_kv_ns(kv_tokens, d);
     const int rest = H % APT_N_QUEUES;
     HeadQueues q = {1, {(H + APT_N_QUEUES - 1) / APT_N_QUEUES, H / APT_N_QUEUES}, {rest ? rest : APT_N_QUEUES, rest ? APT_N_QUEUES - rest : 0}};
     if (H > APT_N_QUEUES && rest) q.n = 2;

@@ -73,27 +73,30 @@ def test_rule_against_the_plain_one(tmp_path):
         kinds = (g.random(B) < g.choice([0.3, 1.0])).astype(np.uint8)
         word = int(np.uint32(_plan(lens, kinds, H, tile)[31]))
         workgroups = int(g.choice([256, 256, 304, 64, 8]))
-        lines.append(" ".join(map(str, [B, H, tile, word, workgroups, *lens, *kinds])))
+        kv_tokens = int(lens[kinds == 0].sum())
+        lines.append(" ".join(map(str, [B, H, tile, word, workgroups, kv_tokens, *lens, *kinds])))
         want.append(po.deals_heads(lens, kinds, H, tile, word, workgroups))
         ranges = sum(-(-int(n) // tile) for n, k in zip(lens, kinds) if k) * -(-H // 8)
         seen.add((H < 8, ranges >= workgroups // 2, want[-1]))
     got = _run_host(tmp_path, """
-    int B, H, chunk, workgroups;
+    int B, H, chunk, workgroups, kv;
     unsigned word;
-    while (scanf("%d %d %d %u %d", &B, &H, &chunk, &word, &workgroups) == 5) {
+    while (scanf("%d %d %d %u %d %d", &B, &H, &chunk, &word, &workgroups, &kv) == 6) {
         std::vector<int32_t> lens(B), kinds(B);
         for (int& v : lens) if (scanf("%d", &v) != 1) return 1;
         for (int& v : kinds) if (scanf("%d", &v) != 1) return 1;
         const bool rows320 = chunk == 320 || apt_pack_wide(word);
-        printf("%d\\n", (rows320 ? apt_deals<10> : apt_deals<8>)(lens.data(), kinds.data(), B, H, chunk, word, workgroups));
+        printf("%d\\n", (rows320 ? apt_deals<10> : apt_deals<8>)(lens.data(), kinds.data(), B, kv, H, 128 * H, chunk, word, workgroups));
     }""", "\n".join(lines))
     assert [int(v) for v in got.split()] == [int(v) for v in want]
-    # below eight heads and beyond, both reasons to deal, and none; four rounds of ranges of fewer than eight heads are always dealt
-    assert seen == {(few, many, dealt) for few in (False, True) for many in (False, True) for dealt in (False, True)} - {(True, True, False)}
+    # below eight heads and beyond, with four rounds of ranges and with fewer, dealt and not
+    assert seen == {(few, many, dealt) for few in (False, True) for many in (False, True) for dealt in (False, True)}
 
 
 @pytest.mark.parametrize("heads,lens,tile,dealt", [
-    (3, [200] * 140, 256, True), (7, [90] * 300, 320, True), (17, [300] * 100, 256, True),              # four rounds of ranges
+    (3, [200] * 140, 256, True), (7, [90] * 400, 320, True), (17, [300] * 100, 256, True),              # four rounds of tiles
+    (7, [90] * 300, 320, True), (3, [200] * 60 + [31] * 80, 256, True), (65, [130, 180, 230, 275] * 4, 256, True),   # of ranges; a round saved
+    (7, [90, 33, 320] * 50, 320, False), (20, [31, 64, 95] * 30, 256, False), (5, [40] * 140, 256, False),           # of ranges; no round saved
     (10, [4608] * 2, 256, True), (9, [130] * 36, 256, True), (20, [512] * 18, 256, True), (5, [256] * 33, 256, True),    # a round saved
     (10, [64] * 36, 256, False), (12, [1064] * 2, 256, False), (7, [60] * 20, 320, False),               # no round saved
     (10, [100] * 36, 256, False),                                                                        # queues share tiles differently
@@ -102,6 +105,15 @@ def test_batches_of_every_branch(heads, lens, tile, dealt):
     word = int(np.uint32(_plan(lens, [1] * len(lens), heads, tile)[31]))
     assert word == po.shared_tiles_word(lens, [1] * len(lens), heads, 128 * heads, tile)
     assert po.deals_heads(lens, [1] * len(lens), heads, tile, word) == dealt
+
+
+@pytest.mark.parametrize("heads,hidden,kv,dealt", [(6, [800] * 45, 0, True), (6, [800] * 45, 50, True), (6, [800] * 45, 140, False),
+                                                   (33, [1200] * 20, 20, True), (33, [1200] * 20, 160, False), (3, [200] * 60, 400, False)])
+def test_what_kv_kind_items_fill_is_not_dealt(heads, hidden, kv, dealt):
+    lens, kinds = hidden + [800] * kv, [1] * len(hidden) + [0] * kv
+    word = int(np.uint32(_plan(lens, kinds, heads, 256)[31]))
+    assert po.deals_heads(lens, kinds, heads, 256, word) == dealt
+    assert po.deals_heads(hidden, [1] * len(hidden), heads, 256, word)
 
 
 def _deals(rn, lens, kinds):
@@ -166,7 +178,8 @@ def test_every_request_as_alone(H, tile, what):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("H,lens,tile,dealt", [
-    (3, [200] * 60 + [31] * 80, 256, True), (7, [90, 33, 320] * 50, 320, True),                        # four rounds, below eight heads
+    (3, [200] * 60 + [31] * 80, 256, True), (7, [90, 33, 320] * 90, 320, True),                        # four rounds of ranges, below eight heads
+    (7, [90, 33, 320] * 50, 320, False), (20, [31, 64, 95] * 30, 256, False),                           # in tiles less, and no round saved
     (10, [4608] * 2, 256, True), (9, [130] * 36, 256, True), (20, [512] * 18, 256, True),              # a round saved, beyond eight
     (26, [512, 512, 256, 256, 768], 256, True),
     (10, [64] * 36, 256, False), (10, [100] * 36, 256, False), (13, [200] * 100, 256, False), (16, [512] * 18, 256, False)])
