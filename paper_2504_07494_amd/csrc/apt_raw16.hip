@@ -23,7 +23,7 @@ namespace {
 // 132 us, 27 heads, 27 of 145..1024 162 -> 153, 32 heads, 24 of 123..1006 beside as many KV-kind ones 248 -> 242.)
 //
 // 48 requests of 32..1024 tokens at d_model 2048, head_dim 64 (13 k hidden-kind tokens) take 0.225 ms for the whole step (0.224 to 0.229
-// over boxes), 950 TFLOP/s on 4 d^2 per token; the plain-ALU kernel that served these shapes before took 13.58 ms (16 TFLOP/s).
+// over machines), 950 TFLOP/s on 4 d^2 per token; the plain-ALU kernel that served these shapes before took 13.58 ms (16 TFLOP/s).
 // No one unit is at its limit there (counters): matrix pipes 0.51 of the cycles, LDS about 0.57 by its bytes (72 KB of reads and copies per
 // k-tile and workgroup at 128 a clock), L2 0.63 of a request per clock and channel (four in five ask for half a line: 32 k of a token's row),
 // 1790 of 2048 waves resident, which wait for an instruction's turn 45 % of their time and for copies and barriers 25 %.
